@@ -74,12 +74,12 @@ typedef enum bnn_binx_arm {
 } bnn_binx_arm;
 
 /* Kernel-selection knobs for bnn_set_option (measurement and tuning; results never change, except that
- * BNN_OPT_REALX_F32_MFMA moves fp32 outputs within rounding, as its comment says). */
+ * BNN_OPT_REALX_F32_MFMA, BNN_OPT_REALX_I8_LOGSOFTMAX and BNN_OPT_REALW_SPLIT_LOGSOFTMAX move log-posteriors of
+ * real-input layers within rounding, as their comments say). */
 typedef enum bnn_option {
     BNN_OPT_BINX_ARM = 1,      /* arm used for BNN_ARM_AUTO: BNN_ARM_VALU_XOR, BNN_ARM_MFMA or BNN_ARM_MFMA_I8   */
-    BNN_OPT_REALX_TM = 2,      /* real-input vector-ALU kernel: 0 (default) = frames staged through LDS, 16 frames x 4
-                                  outputs per lane, where K % 4 == 0 and X is 16-byte aligned; 1, 2, 4, 8, 16 or 32 =
-                                  that many frames per wavefront on the row-broadcast kernel.  Same results.        */
+    BNN_OPT_REALX_TM = 2,        /* real-input layers, ascending-k sums: 0 (default) = fp32 matrix cores; 1, 2, 4, 8, 16 or
+                                  32 = that many frames per wavefront on the vector ALU.  Same results.             */
     BNN_OPT_BINX_VALU_TM = 3,  /* frames per wavefront of the XOR/popcount kernel: 1, 2, 4, 8, 16 (default) or 32  */
     BNN_OPT_MFMA_WM = 4,       /* 16-row accumulator fragments per wavefront of the matrix-core kernel: 2 or 4  */
     BNN_OPT_REALX_SIGN_MFMA = 5, /* bnn_forward, binary-weight layers real input -> Sign (the first layer of a
@@ -89,7 +89,7 @@ typedef enum bnn_option {
                                    than the first: for 128 frames or more a tiled product, 128 frames x 256 outputs per
                                    workgroup, followed by a kernel that sums the undecided outputs; workgroups of 16
                                    frames otherwise), 2 = the same with workgroups of 16 frames for every batch size,
-                                   0 = vector-ALU kernel; same bits in all three                                  */
+                                   0 = the ascending-k sums of BNN_OPT_REALX_TM; same bits in all three            */
     BNN_OPT_FUSED_LOGSOFTMAX = 6, /* binary-input LOGSOFTMAX layer on the matrix-core arm: 1 = product and
                                    log-Softmax in one kernel (needs K % 256 == 0 and N <= 4096),
                                    0 = product kernel followed by a row kernel (default: measured faster)        */
@@ -99,13 +99,14 @@ typedef enum bnn_option {
                                    by grid size (default)                                                        */
     BNN_OPT_MFMA32_XCD_ORDER = 11, /* 32x32x64 kernel: 1 = tiles that share rows of frames run on the same XCD (one L2),
                                    2 = tiles in dispatch order, 0 = by problem size (default)                     */
-    BNN_OPT_REALX_F32_MFMA = 10, /* real-input layers with fp32 outputs of 128 frames or more: which of them run on the fp32
-                                   matrix-core kernel (about 3x faster; sums in the matrix core's order, within 2e-6 of
-                                   the layer's output scale of the ascending-k sum) instead of the vector-ALU kernel
-                                   (ascending k, bit-identical to the reference definition): 0 = LOGSOFTMAX layers only
-                                   (default: nothing follows them), 1 = LINEAR, HARDTANH and SIGMOID layers too, 2 =
-                                   none.  A deep hard-tanh network amplifies the different rounding from layer to layer
-                                   (measured: 8e-4 of the output scale after 7 layers of 2048 units), hence the default */
+    BNN_OPT_REALX_F32_MFMA = 10, /* sums of real-input layers.  0 (default): in ascending k (fp32 matrix cores fed in natural
+                                   order: the same bits as a chain of fused multiply-adds), except in front of a
+                                   log-Softmax inside bnn_forward, where BNN_OPT_REALX_I8_LOGSOFTMAX and
+                                   BNN_OPT_REALW_SPLIT_LOGSOFTMAX choose.  2: in ascending k there too.  1: fp32 outputs of
+                                   128 frames or more from another fp32 matrix-core kernel, whose chain runs over k in a
+                                   permuted order (comparison arm; within 2e-6 of the layer's output scale.  A deep hard-tanh
+                                   network amplifies the different rounding from layer to layer: measured 8e-4 of the
+                                   output scale after 7 layers of 2048 units)                                       */
     BNN_OPT_MFMA32_PIPELINE = 9, /* operand fetch of the 32x32x64 kernel on 16-byte aligned rows with K % 512 == 0:
                                    0 or 1 = two register sets, the fetch of the next piece of K pinned ahead of
                                    the products of the current one (default), 2 = one set, order left to the
@@ -121,7 +122,7 @@ typedef enum bnn_option {
     BNN_OPT_REALX_I8_LOGSOFTMAX = 16, /* bnn_forward, LOGSOFTMAX layer with binary weights and real inputs, 128 frames or more,
                                        K <= 8192: 1 = the sum of +-x on the int8 matrix cores from four 7-bit digit planes of
                                        the frames (|sum - exact| < K 2^-27 max|x| per frame: below what the order of an fp32
-                                       summation changes; about 3x faster than the fp32 matrix cores; default, unless
+                                       summation changes; about 3x faster than the ascending-k sum; default, unless
                                        BNN_OPT_REALX_F32_MFMA = 2 asks for the ascending-k sum everywhere; a tiled product,
                                        128 frames x 256 outputs per workgroup), 2 = the same sums with workgroups of 16
                                        frames x 512 outputs (identical results), 0 = as BNN_OPT_REALX_F32_MFMA says       */
@@ -129,17 +130,13 @@ typedef enum bnn_option {
                                        1 = the products run on the bf16 matrix cores with every fp32 operand split into
                                        three bf16 pieces (v = p0 + p1 + p2 to 2^-24 |v|) and the six piece products of
                                        weight 2^-16 or more added in fp32: |sum - exact| <= 2^-22 sum_k |x_k w_k| plus
-                                       ordinary fp32 rounding, no more than the fp32 matrix cores give, in half their time
+                                       ordinary fp32 rounding, no more than the ascending-k sum has, in half its time
                                        (default, unless BNN_OPT_REALX_F32_MFMA = 2 asks for the ascending-k sum
                                        everywhere); 2 = the same with workgroups of eight waves, two per SIMD (measured
                                        2 % slower); 0 = as BNN_OPT_REALX_F32_MFMA says.  The planes of both operands
                                        (six bytes per element, K padded to 32) are part of bnn_forward_workspace_bytes */
-    BNN_OPT_REALW_VALU_LDS = 18,    /* bnn_forward, layer with real-valued weights whose outputs do not go into the
-                                       log-Softmax, 512 frames or more, K a multiple of 4, X 16-byte aligned: 1 = the
-                                       ascending-k sums on fused multiply-adds with three register operands (frames through
-                                       LDS, weights from a transposed copy made once per call: K padded to 64, times N, fp32,
-                                       part of bnn_forward_workspace_bytes); 0 = the kernel of bnn_layer_realw.  Same bits
-                                       (default 1: 130 against 192 us at 4096 x 440 x 2048)                              */
+    BNN_OPT_REALW_VALU_LDS = 18,    /* 0 or 1; accepted and without effect: layers with real-valued weights run on one kernel
+                                       inside bnn_forward and outside it                                            */
     BNN_OPT_COOPERATIVE_SPIN = 15,  /* polls of the other workgroups' flags before a workgroup of a cooperative kernel gives
                                        up (>= 1; default 2^20, about a second).  A small value makes the bounded wait run
                                        out on purpose: the kernel still ends, its rows are wrong and
@@ -247,9 +244,8 @@ int bnn_layer_binw_binx01(const void* Xp, const void* Wp, const float* scale, co
  *   act: LINEAR, HARDTANH, SIGMOID -> Y fp32 [M][N]: the sum is taken in fp32 in ascending k, one fused multiply-add
  *        per step, one accumulator per output (the order of bnn_layer_binw_realx);
  *        SIGN -> Y words [M][bnn_packed_words(N, word_bits)], bits from that same sum;
- *        LOGSOFTMAX -> Y fp32 [M][N]; for M >= 128 the sum is taken on the fp32 matrix cores in their own order
- *        (within ordinary fp32 rounding of the ascending-k sum; BNN_OPT_REALX_F32_MFMA = 2 turns this off, = 1
- *        extends it to LINEAR, HARDTANH and SIGMOID).
+ *        LOGSOFTMAX -> Y fp32 [M][N], from that sum too (up to 64 frames: K split over the lanes of a wavefront, within
+ *        ordinary fp32 rounding of it; BNN_OPT_REALX_F32_MFMA = 2 turns that off).
  *   word_bits only sets the packing of a SIGN output.
  * Errors as bnn_layer_binw_realx.
  */

@@ -3,14 +3,15 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn_hip.so")
-SOURCES = [os.path.join(CSRC, "bnn_api.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("bnn_api.hip", "f32_chain.hip")]
 
 HIPCC_FLAGS = [
-    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-fvisibility=hidden",
     "-ffp-contract=off",                                   # the fused multiply-adds are the ones written, no others
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU instructions
     "-Wall", "-Wno-unused-command-line-argument",
@@ -26,13 +27,18 @@ def sources_newer_than_lib() -> bool:
 
 
 def build(verbose: bool = False) -> str:
-    """Always compiles (seconds).  Returns the path of the shared library."""
-    cmd = ["hipcc", *HIPCC_FLAGS, "-o", LIB, *SOURCES]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    noise = "packed-fp32-ops"
-    err = "\n".join(ln for ln in res.stderr.splitlines() if noise not in ln)
-    if res.returncode != 0:
-        raise RuntimeError("hipcc failed:\n" + err)
+    """Always compiles (the translation units side by side).  Returns the path of the shared library."""
+    with tempfile.TemporaryDirectory() as tmp:
+        objects = [os.path.join(tmp, os.path.basename(src) + ".o") for src in SOURCES]
+        jobs = [subprocess.Popen(["hipcc", *HIPCC_FLAGS, "-c", "-o", o, src], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+                for src, o in zip(SOURCES, objects)]
+        done = [j.communicate() for j in jobs]
+        err = "\n".join(ln for _, e in done for ln in e.splitlines() if "packed-fp32-ops" not in ln)
+        if any(j.returncode for j in jobs):
+            raise RuntimeError("hipcc failed:\n" + err)
+        res = subprocess.run(["hipcc", *HIPCC_FLAGS, "-shared", "-o", LIB, *objects], capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError("hipcc failed to link:\n" + res.stderr)
     if verbose and err.strip():
         print(err)
     return LIB

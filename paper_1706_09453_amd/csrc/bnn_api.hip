@@ -9,6 +9,7 @@
 #include "../../include/bnn.h"
 #include "mfma32_kernels.hpp"
 #include "mfma_i8_kernels.hpp"
+#include "launch.hpp"
 #include "realx_mfma_kernels.hpp"
 #include "realw_kernels.hpp"
 #include "realw_split_kernels.hpp"
@@ -52,7 +53,6 @@ std::atomic<int> g_mfma32_xcd_order{0};
 std::atomic<int> g_stream_max_frames{64};
 std::atomic<int> g_realx_i8_lsm{1};
 std::atomic<int> g_realw_split_lsm{1};
-std::atomic<int> g_realw_valu_lds{1};
 std::atomic<int> g_cooperative{0};
 std::atomic<int> g_coop_spin{1 << 20};
 std::atomic<int> g_mfma32_splitk{0};
@@ -84,7 +84,6 @@ inline bool word_bits_ok(int wb) { return wb == 32 || wb == 64; }
 inline int64_t words_per_row(int64_t K, int wb) { return (K + wb - 1) / wb; }
 // Row length in 32-bit words (a 64-bit word is two little-endian 32-bit words).
 inline int64_t row_w32(int64_t K, int wb) { return words_per_row(K, wb) * (wb / 32); }
-inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 inline bool overlap(const void* a, size_t na, const void* b, size_t nb) {
     const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), b0 = reinterpret_cast<uintptr_t>(b);
     return na && nb && a0 < b0 + nb && b0 < a0 + na;
@@ -119,6 +118,30 @@ int check_layer_args(const void* X, const void* Wp, int64_t M, int64_t K, int64_
 
 // ---------------------------------------------------------------- launches (arguments already checked)
 
+// The comparison arm of the fp32 sums (BNN_OPT_REALX_F32_MFMA = 1), 128 frames or more, fp32 outputs.
+template <int ACT, bool WREAL>
+void launch_f32_mfma(const ChainArgs& a) {
+    const dim3 grid((unsigned)((a.M + 255) / 256), (unsigned)((a.N + 127) / 128));
+    float* Y = static_cast<float*>(a.Y);
+    if (a.K % 16 == 0 && aligned(a.X, 16) && (!WREAL || aligned(a.W, 16)))
+        realx_f32_mfma_kernel<ACT, true, WREAL><<<grid, 256, 0, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, Y);
+    else
+        realx_f32_mfma_kernel<ACT, false, WREAL><<<grid, 256, 0, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, Y);
+}
+// Sums of a real-input layer that is no small batch; arguments already checked.
+template <bool WREAL>
+void launch_f32_sums(const ChainArgs& a, int act) {
+    if (act != BNN_ACT_SIGN && a.M >= 128 && g_realx_f32_mfma.load() == 1) {
+        if (act == BNN_ACT_HARDTANH) launch_f32_mfma<ACT_HARDTANH, WREAL>(a);
+        else if (act == BNN_ACT_SIGMOID) launch_f32_mfma<ACT_SIGMOID, WREAL>(a);
+        else launch_f32_mfma<ACT_LINEAR, WREAL>(a);
+    } else if (WREAL) {
+        launch_chain_real(a, act);
+    } else {
+        launch_chain_bits(a, act);
+    }
+}
+
 template <int TM, bool BCAST>
 void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
                        int w32, int act, void* Y, int yw32, hipStream_t st) {
@@ -147,14 +170,6 @@ void launch_realx_tm(const float* X, const uint32_t* Wp, const float* scale, con
     else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st);
 }
 
-// The fp32 matrix-core kernel runs one workgroup per CU (measured: 1.06 ms with two against 0.54 ms on 432 workgroups);
-// the kernel's own occupancy attribute says so.
-template <int ACT, bool VEC, bool WREAL>
-void launch_f32_mfma(dim3 grid, dim3 block, hipStream_t st, const float* X, const void* W, const float* scale,
-                     const float* bias, int M, int K, int N, int w32, float* Y) {
-    realx_f32_mfma_kernel<ACT, VEC, WREAL><<<grid, block, 0, st>>>(X, W, scale, bias, M, K, N, w32, Y);
-}
-
 void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
     const dim3 grid(M < 65536 ? M : 65536), block(256);
     const bool al = aligned(Z, 16);
@@ -170,46 +185,11 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
     if (M == 0) return BNN_OK;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
-    const int f32_mfma = g_realx_f32_mfma.load();
-    if (act != BNN_ACT_SIGN && M >= 128 && (f32_mfma == 1 || (f32_mfma == 0 && act == BNN_ACT_LOGSOFTMAX))) {
-        // fp32 outputs of a large batch on the matrix cores (fp32 MFMA, weights as +-1.0f).  By default only where
-        // nothing but the log-Softmax follows; Sign bits never come here
-        const dim3 grid((unsigned)((M + 255) / 256), (unsigned)((N + 127) / 128)), block(256);
-        const bool vec = (K % 16 == 0) && aligned(X, 16);
-        float* Yf = static_cast<float*>(Y);
-        if (act == BNN_ACT_HARDTANH) {
-            if (vec) launch_f32_mfma<ACT_HARDTANH, true, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-            else launch_f32_mfma<ACT_HARDTANH, false, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-        } else if (act == BNN_ACT_SIGMOID) {
-            if (vec) launch_f32_mfma<ACT_SIGMOID, true, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-            else launch_f32_mfma<ACT_SIGMOID, false, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-        } else {
-            if (vec) launch_f32_mfma<ACT_LINEAR, true, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-            else launch_f32_mfma<ACT_LINEAR, false, false>(grid, block, st, X, W, scale, bias, (int)M, (int)K, (int)N, w32, Yf);
-        }
-        if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(Yf, (int)M, (int)N, st);
-        return launch_status();
-    }
     // batches of a few frames (streaming): 1 or 2 frames per workgroup spread the layer over the chip
-    int tm = M <= g_stream_max_frames.load() ? (M <= 16 ? 1 : 2) : g_realx_tm.load();
-    if (tm == 0 && ((M + 15) / 16) * ((N + 1023) / 1024) < 256) {
-        // too few frames for 16 x 1024 tiles to give every CU a workgroup: the row-broadcast kernel with the most
-        // frames per workgroup (fewest sign-building instructions per fma) that still gives 256 workgroups
-        tm = 16;
-        while (tm > 2 && ((M + tm - 1) / tm) * ((N + 255) / 256) < 256) tm >>= 1;
-    }
-    if (tm == 0 && (K & 3) == 0 && aligned(X, 16)) {
-        // large batch, aligned rows: frames through LDS, every fma on three VGPRs
-        constexpr int TM = 16, TNN = 4;
-        const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
-        const dim3 grid((unsigned)((M + TM - 1) / TM), (unsigned)((N + 256 * TNN - 1) / (256 * TNN))), block(256);
-        switch (act) {
-            case BNN_ACT_SIGN: realx_valu_lds_kernel<TM, TNN, ACT_SIGN><<<grid, block, 0, st>>>(X, W, scale, bias, Mi, Ki, Ni, w32, Y, yw32); break;
-            case BNN_ACT_HARDTANH: realx_valu_lds_kernel<TM, TNN, ACT_HARDTANH><<<grid, block, 0, st>>>(X, W, scale, bias, Mi, Ki, Ni, w32, Y, yw32); break;
-            case BNN_ACT_SIGMOID: realx_valu_lds_kernel<TM, TNN, ACT_SIGMOID><<<grid, block, 0, st>>>(X, W, scale, bias, Mi, Ki, Ni, w32, Y, yw32); break;
-            default: realx_valu_lds_kernel<TM, TNN, ACT_LINEAR><<<grid, block, 0, st>>>(X, W, scale, bias, Mi, Ki, Ni, w32, Y, yw32); break;
-        }
-        if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), Mi, Ni, st);
+    const int tm = M <= g_stream_max_frames.load() ? (M <= 16 ? 1 : 2) : g_realx_tm.load();
+    if (tm == 0) {
+        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st}, act);
+        if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
         return launch_status();
     }
     switch (tm) {
@@ -224,51 +204,30 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
     return launch_status();
 }
 
-template <int TM, int ACT, int KC>
-void launch_realw_valu_tm(const float* X, const float* W, const float* bias, int M, int K, int N, void* Y, int yw32,
-                          hipStream_t st) {
+// Batches of a few frames (streaming): 2 frames per workgroup, so that the layer is spread over ceil(M / 2) x N / 256
+// workgroups (up to 16 frames with chunks of 64 k: fewer memory round trips, but 136 KiB of LDS, one workgroup per CU;
+// measured at 64 frames: 134 us with chunks of 16 k, 151 us with 64).
+template <int ACT, int KC>
+void launch_realw_valu_kc(const float* X, const float* W, const float* bias, int M, int K, int N, void* Y, int yw32, hipStream_t st) {
+    constexpr int TM = 2;
     const dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
     if ((K & 3) == 0 && aligned(X, 16) && aligned(W, 16)) {
         constexpr unsigned lds = realw_lds_bytes(KC);
-        if (lds > 64 * 1024) {   // LDS above 64 KiB has to be allowed once per kernel and device
-            static std::atomic<uint64_t> allowed{0};
-            int dev = 0;
-            (void)hipGetDevice(&dev);
-            const uint64_t bit = 1ull << (dev & 63);
-            if (!(allowed.load() & bit)) {
-                (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&realw_valu_kernel<TM, ACT, KC>),
-                                          hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-                allowed.fetch_or(bit);
-            }
-        }
+        static std::atomic<uint64_t> allowed{0};
+        if (lds > 64 * 1024) allow_lds(&realw_valu_kernel<TM, ACT, KC>, lds, allowed);
         realw_valu_kernel<TM, ACT, KC><<<grid, block, lds, st>>>(X, W, bias, M, K, N, Y, yw32);
     } else {
         realw_valu_simple_kernel<TM, ACT><<<grid, block, 0, st>>>(X, W, bias, M, K, N, Y, yw32);
     }
 }
-
-// batches of a few frames (streaming): 2 frames per workgroup, so that the layer is spread over ceil(M / 2) x N / 256
-// workgroups (up to 16 frames with chunks of 64 k: fewer memory round trips, but 136 KiB of LDS, one workgroup per CU;
-// measured at 64 frames: 134 us with chunks of 16 k, 151 us with 64); otherwise 16 frames per workgroup
 template <int ACT>
 void launch_realw_valu(const float* X, const float* W, const float* bias, int M, int K, int N, void* Y, int yw32,
                        hipStream_t st) {
-    if (M <= g_stream_max_frames.load() && M <= 16) launch_realw_valu_tm<2, ACT, 64>(X, W, bias, M, K, N, Y, yw32, st);
-    else if (M <= g_stream_max_frames.load()) launch_realw_valu_tm<2, ACT, 16>(X, W, bias, M, K, N, Y, yw32, st);
-    else if (M >= 2048 && getenv("BNN_REALW_TM32")) launch_realw_valu_tm<32, ACT, 16>(X, W, bias, M, K, N, Y, yw32, st);
-    else launch_realw_valu_tm<16, ACT, 16>(X, W, bias, M, K, N, Y, yw32, st);
+    if (M <= 16) launch_realw_valu_kc<ACT, 64>(X, W, bias, M, K, N, Y, yw32, st);
+    else launch_realw_valu_kc<ACT, 16>(X, W, bias, M, K, N, Y, yw32, st);
 }
 
-template <int ACT>
-void launch_realw_mfma(const float* X, const float* W, const float* bias, int M, int K, int N, float* Y, hipStream_t st) {
-    const dim3 grid((unsigned)((M + 255) / 256), (unsigned)((N + 127) / 128)), block(256);
-    if ((K % 16 == 0) && aligned(X, 16) && aligned(W, 16))
-        launch_f32_mfma<ACT, true, true>(grid, block, st, X, W, nullptr, bias, M, K, N, 0, Y);
-    else
-        launch_f32_mfma<ACT, false, true>(grid, block, st, X, W, nullptr, bias, M, K, N, 0, Y);
-}
-
-// A layer with real-valued weights.  The matrix-core rule is the one of run_realx.
+// A layer with real-valued weights.
 int run_realw(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, int act, int wb,
               void* Y, hipStream_t st) {
     if (M == 0) return BNN_OK;
@@ -281,11 +240,8 @@ int run_realw(const float* X, const float* W, const float* bias, int64_t M, int6
         const unsigned nb = (unsigned)((N + 15) / 16);
         if (M <= 4) realw_gemv_kernel<4><<<dim3(nb, (unsigned)((M + 3) / 4)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
         else realw_gemv_kernel<8><<<dim3(nb, (unsigned)((M + 7) / 8)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
-    } else if (act != BNN_ACT_SIGN && M >= 128 && (f32_mfma == 1 || (f32_mfma == 0 && act == BNN_ACT_LOGSOFTMAX))) {
-        float* Yf = static_cast<float*>(Y);
-        if (act == BNN_ACT_HARDTANH) launch_realw_mfma<ACT_HARDTANH>(X, W, bias, (int)M, (int)K, (int)N, Yf, st);
-        else if (act == BNN_ACT_SIGMOID) launch_realw_mfma<ACT_SIGMOID>(X, W, bias, (int)M, (int)K, (int)N, Yf, st);
-        else launch_realw_mfma<ACT_LINEAR>(X, W, bias, (int)M, (int)K, (int)N, Yf, st);
+    } else if (M > g_stream_max_frames.load()) {
+        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st}, act);
     } else {
         switch (act) {
             case BNN_ACT_SIGN: launch_realw_valu<ACT_SIGN>(X, W, bias, (int)M, (int)K, (int)N, Y, yw32, st); break;
@@ -749,37 +705,15 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     return launch_status();
 }
 
-// Layers with real weights whose outputs are not log-Softmax inputs, 512 frames or more, inside bnn_forward: the
-// ascending-k chains of realw_valu_kernel on fmas with three register operands (realw_valu_lds_kernel), from a
-// transposed copy of the weights in the workspace (kpad x N fp32, 256-byte aligned; K padded to 64).
-bool realw_valu_lds_applies(const bnn_layer_desc& d, int64_t M) {
-    // (the limits keep the grids of both kernels and the 32-bit byte offset inside a row of the copy in range)
+// bnn_forward_workspace_bytes counts kpad x N fp32 (256-byte aligned; K padded to 64) for a layer with real weights that
+// is not in front of the log-Softmax, 512 frames or more: room for a transposed copy of its weights.  The matrix-core
+// kernel reads the weights as they are and leaves it unused; the size is part of the interface.
+bool realw_transposed_applies(const bnn_layer_desc& d, int64_t M) {
     return d.w_is_real && d.act != BNN_ACT_LOGSOFTMAX && M >= 512 && (d.K & 3) == 0 && d.K <= 65536 && d.N <= (1 << 22);
 }
-size_t realw_valu_lds_bytes(int64_t K, int64_t N) {
-    return round_up((size_t)realw_lds_kpad((int)K) * (size_t)N * 4, 256);
+size_t realw_transposed_bytes(int64_t K, int64_t N) {
+    return round_up((size_t)((K + 63) / 64 * 64) * (size_t)N * 4, 256);
 }
-template <int ACT>
-void launch_realw_valu_lds(const float* X, const float* Wt, const float* bias, int M, int K, int kpad, int N, void* Y, int yw32,
-                           hipStream_t st) {
-    const dim3 grid((unsigned)((M + kRealwLdsFrames - 1) / kRealwLdsFrames), (unsigned)((N + 255) / 256));
-    realw_valu_lds_kernel<ACT><<<grid, 256, 0, st>>>(X, Wt, bias, M, K, kpad, N, Y, yw32);
-}
-int run_realw_valu_lds(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, int act, int wb, void* Y,
-                       void* scratch_mem, hipStream_t st) {
-    const int Mi = (int)M, Ki = (int)K, Ni = (int)N, kpad = realw_lds_kpad(Ki);
-    const int yw32 = (int)row_w32(N, wb);
-    float* Wt = static_cast<float*>(scratch_mem);
-    weights_transposed_kernel<<<dim3((unsigned)((Ni + 31) / 32), (unsigned)(kpad / 32)), 256, 0, st>>>(W, Ni, Ki, kpad, Wt);
-    switch (act) {
-        case BNN_ACT_SIGN: launch_realw_valu_lds<ACT_SIGN>(X, Wt, bias, Mi, Ki, kpad, Ni, Y, yw32, st); break;
-        case BNN_ACT_HARDTANH: launch_realw_valu_lds<ACT_HARDTANH>(X, Wt, bias, Mi, Ki, kpad, Ni, Y, yw32, st); break;
-        case BNN_ACT_SIGMOID: launch_realw_valu_lds<ACT_SIGMOID>(X, Wt, bias, Mi, Ki, kpad, Ni, Y, yw32, st); break;
-        default: launch_realw_valu_lds<ACT_LINEAR>(X, Wt, bias, Mi, Ki, kpad, Ni, Y, yw32, st); break;
-    }
-    return launch_status();
-}
-
 // Real-input layers with binary weights on the int8 matrix cores as a tiled product (128 frames x 256 outputs per
 // workgroup), inside bnn_forward for batches of 128 frames or more: Sign layers (three digit planes, exact bits: the
 // outputs the filter cannot decide are listed and resolved by a second kernel) and the layer in front of the
@@ -964,8 +898,7 @@ BNN_EXPORT int bnn_set_option(int option, int value) {
             return BNN_OK;
         case BNN_OPT_REALW_VALU_LDS:
             if (value != 0 && value != 1) return BNN_EINVAL;
-            g_realw_valu_lds.store(value);
-            return BNN_OK;
+            return BNN_OK;   // one kernel, the same bits
         case BNN_OPT_COOPERATIVE_SPIN:
             if (value < 1) return BNN_EINVAL;
             g_coop_spin.store(value);
@@ -1252,7 +1185,7 @@ static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_la
             // the transposed weights of another layer with real weights
             size_t b = layers[l].x_is_binary ? round_up((size_t)M * (size_t)layers[l].K * 4, 256) : 0;
             if (roomy && realw_split_lsm_applies(layers[l], M)) b += realw_split_lsm_bytes(M, layers[l].K, layers[l].N);
-            if (roomy && realw_valu_lds_applies(layers[l], M)) b += realw_valu_lds_bytes(layers[l].K, layers[l].N);
+            if (roomy && realw_transposed_applies(layers[l], M)) b += realw_transposed_bytes(layers[l].K, layers[l].N);
             if (b > unpacked) unpacked = b;
         }
         if (realx_i8_lsm_applies(layers[l], M)) {
@@ -1377,10 +1310,6 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                     M > g_stream_max_frames.load())
                     rc = run_realw_split_lsm(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N,
                                              static_cast<float*>(o), planes, st);
-                else if (roomy && realw_valu_lds_applies(d, M) && g_realw_valu_lds.load() && M > g_stream_max_frames.load() &&
-                         !(d.act != BNN_ACT_SIGN && g_realx_f32_mfma.load() == 1) && aligned(xin, 16))
-                    rc = run_realw_valu_lds(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o,
-                                            planes, st);
                 else
                     rc = run_realw(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o, st);
             } else if (d.x_is_binary) {

@@ -1,0 +1,37 @@
+// Launchers that live in translation units of their own (compiled side by side), and what they share.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <atomic>
+#include <cstdint>
+
+namespace bnn {
+
+inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
+
+// Dynamic LDS above 64 KiB has to be allowed once per kernel and device.
+template <class Kernel>
+void allow_lds(Kernel kernel, unsigned bytes, std::atomic<uint64_t>& allowed) {
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    const uint64_t bit = 1ull << (dev & 63);
+    if (allowed.load(std::memory_order_relaxed) & bit) return;
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    allowed.fetch_or(bit);
+}
+
+// Ascending-k fp32 sums on the matrix cores (f32_chain.hip); arguments already checked.
+struct ChainArgs {
+    const float* X;
+    const void* W;   // packed bits, or fp32 with real weights
+    const float *scale, *bias;
+    int M, K, N, w32;
+    void* Y;
+    int yw32;
+    hipStream_t st;
+};
+void launch_chain_bits(const ChainArgs& a, int act);   // W packed bits
+void launch_chain_real(const ChainArgs& a, int act);   // W fp32
+
+}  // namespace bnn

@@ -1,10 +1,9 @@
 // Real input x binary weights with fp32 outputs (paper Alg. 1 forward: every product is +-x, the sum needs no
 // multiplier) on the matrix cores: V_MFMA_F32_32X32X2_F32 with the weight bits expanded to +-1.0f.
 //
-// Products +-1.0f * x are exact; the 2 x K/2 partial sums are added in fp32 in the matrix core's own order, so the
-// result differs from the sum taken in ascending k by ordinary fp32 rounding (a few units in the last place of the
-// largest partial sum) and is checked against the fp64 value of the same sum within the stated tolerance.  Layers
-// whose outputs are Sign bits never use this kernel: bits are defined from the sum in ascending k.
+// The comparison arm of f32_chain_kernels.hpp (BNN_OPT_REALX_F32_MFMA = 1): operands straight from memory to registers,
+// k in an order that suits 16-byte loads (k and k + 8 of every 16 in one MFMA), so the sum is an fp32 chain over permuted
+// k and differs from the one in ascending k by ordinary rounding.  Layers whose outputs are Sign bits never use it.
 //
 // Tiling: a workgroup of 2 x 2 waves, each wave 4 x 2 accumulator fragments of 32 x 32 (128 frames x 64 outputs).
 // K advances in chunks of 16: lane (r = lane % 32, g = lane / 32) holds, per frames fragment, the 8 values

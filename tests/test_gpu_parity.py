@@ -523,6 +523,24 @@ def test_realx_against_fp64_shadow(G, bnn, oracle):
     _close(Y.cpu().numpy(), oracle.affine_f64(acc64, scale, bias), "fp64 shadow")
 
 
+@pytest.mark.parametrize("act", ["sign", "linear"])
+@pytest.mark.parametrize("M,K,N", [(4097, 36, 2050), (4097, 33, 2050), (4096, 64, 2048),   # 256 x 128 tiles; K that is no multiple of 4
+                                   (2049, 100, 2100), (1100, 32, 1300),                    # 128 x 128, 64 x 64
+                                   (65, 4, 33), (65, 128, 65), (80, 132, 1), (129, 260, 70), (65, 516, 40)])  # 32 x 64; 1 to 5 chunks of K
+def test_ascending_sums_on_the_matrix_cores(G, bnn, oracle, M, K, N, act):
+    """Binary and real weights, real input: every workgroup tile the dispatch can pick, ragged on both sides, K ending in
+    every part of a chunk.  The fp32 matrix cores fed in natural order give the bits of the oracle's chain."""
+    X, W, scale, bias = _rand_layer(M + K * 3 + N, M, K, N)
+    Wr = (W * np.float32(np.sqrt(3.0 / K))).astype(np.float32)
+    Wp = oracle.pack_sign(W, 64)
+    a = bnn.ACT_BY_NAME[act]
+    got = [G.layer_realx(G.to_dev(X), G.to_dev(Wp), G.to_dev(scale), G.to_dev(bias), K, N, a, 64),
+           G.layer_realw(G.to_dev(X), G.to_dev(Wr), G.to_dev(bias), K, N, a, 64)]
+    want = [oracle.layer_binw_realx(X, Wp, K, scale, bias, act, 64), oracle.layer_realw(X, Wr, bias, act, 64)]
+    for g_, w_ in zip(got, want):
+        assert np.array_equal(G.words_to_host(g_, 64) if act == "sign" else g_.cpu().numpy(), w_)
+
+
 # ----------------------------------------------------------------------------- first layer on the matrix cores
 
 def _first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, use_mfma):
