@@ -530,8 +530,7 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
 
 int run_pack(const float* X, int64_t rows, int64_t K, int wb, void* out, hipStream_t st) {
     if (rows == 0) return BNN_OK;
-    const int64_t chunks = (K + 63) / 64;
-    const int64_t tasks = rows * chunks;
+    const int64_t tasks = rows * ((K + kPackElems - 1) / kPackElems);
     int64_t blocks = (tasks + 3) / 4;
     if (blocks > 65536 * 4) blocks = 65536 * 4;
     pack_sign_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(X, rows, K, row_w32(K, wb),
@@ -1004,6 +1003,8 @@ unsigned elementwise_blocks(int64_t count) {
     const int64_t b = (count + 255) / 256;
     return (unsigned)(b < 65536 ? (b > 0 ? b : 1) : 65536);
 }
+// blocks for `count` elements, four consecutive ones per thread where the arrays are 16-byte aligned
+unsigned quad_blocks(int64_t count) { return elementwise_blocks((count + 3) / 4); }
 bool dims_ok(int64_t a, int64_t b) { return a > 0 && b > 0 && a <= kMaxDim && b <= kMaxDim; }
 }  // namespace
 
@@ -1013,7 +1014,7 @@ BNN_EXPORT int bnn_pack_weights_transposed(const float* W, int64_t N, int64_t K,
     if (!aligned(W, 4) || !aligned(WpT, word_bits / 8)) return BNN_EALIGN;
     const int w32t = (int)row_w32(N, word_bits);
     if (overlap(W, (size_t)N * K * 4, WpT, (size_t)K * w32t * 4)) return BNN_EINVAL;
-    const dim3 grid((unsigned)((K + 63) / 64), (unsigned)((N + 63) / 64));
+    const dim3 grid((unsigned)((K + 255) / 256), (unsigned)((N + 63) / 64));
     pack_sign_transposed_kernel<<<grid, 256, 0, static_cast<hipStream_t>(stream)>>>(W, (int)N, (int)K, w32t,
                                                                                      static_cast<uint32_t*>(WpT));
     return launch_status();
@@ -1034,7 +1035,10 @@ BNN_EXPORT int bnn_softmax_xent_grad(const float* logp, const int32_t* labels, i
     if (M == 0) return BNN_OK;
     if (!logp || !labels || !g) return BNN_EINVAL;
     if (!aligned(logp, 4) || !aligned(labels, 4) || !aligned(g, 4)) return BNN_EALIGN;
-    softmax_xent_grad_kernel<<<elementwise_blocks(M * N), 256, 0, static_cast<hipStream_t>(stream)>>>(logp, labels, M, (int)N, g);
+    const unsigned rows = (unsigned)(M < 65536 ? M : 65536);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (N % 4 == 0 && aligned(logp, 16) && aligned(g, 16)) softmax_xent_grad_kernel<true><<<rows, 256, 0, st>>>(logp, labels, M, (int)N, g);
+    else softmax_xent_grad_kernel<false><<<rows, 256, 0, st>>>(logp, labels, M, (int)N, g);
     return launch_status();
 }
 
@@ -1044,7 +1048,9 @@ BNN_EXPORT int bnn_mask_grad(const float* g_h, const float* hhat, int64_t count,
     if (count == 0) return BNN_OK;
     if (!g_h || !hhat || !g_hhat) return BNN_EINVAL;
     if (!aligned(g_h, 4) || !aligned(hhat, 4) || !aligned(g_hhat, 4)) return BNN_EALIGN;
-    mask_grad_kernel<<<elementwise_blocks(count), 256, 0, static_cast<hipStream_t>(stream)>>>(g_h, hhat, count, k, g_hhat);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (aligned(g_h, 16) && aligned(hhat, 16) && aligned(g_hhat, 16)) mask_grad_kernel<true><<<quad_blocks(count), 256, 0, st>>>(g_h, hhat, count, k, g_hhat);
+    else mask_grad_kernel<false><<<elementwise_blocks(count), 256, 0, st>>>(g_h, hhat, count, k, g_hhat);
     return launch_status();
 }
 
@@ -1053,7 +1059,9 @@ BNN_EXPORT int bnn_sigmoid_grad(const float* g_h, const float* h, int64_t count,
     if (count == 0) return BNN_OK;
     if (!g_h || !h || !g_hhat) return BNN_EINVAL;
     if (!aligned(g_h, 4) || !aligned(h, 4) || !aligned(g_hhat, 4)) return BNN_EALIGN;
-    sigmoid_grad_kernel<<<elementwise_blocks(count), 256, 0, static_cast<hipStream_t>(stream)>>>(g_h, h, count, g_hhat);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (aligned(g_h, 16) && aligned(h, 16) && aligned(g_hhat, 16)) sigmoid_grad_kernel<true><<<quad_blocks(count), 256, 0, st>>>(g_h, h, count, g_hhat);
+    else sigmoid_grad_kernel<false><<<elementwise_blocks(count), 256, 0, st>>>(g_h, h, count, g_hhat);
     return launch_status();
 }
 
@@ -1118,7 +1126,10 @@ BNN_EXPORT int bnn_bias_grad(const float* g_hhat, int64_t M, int64_t N, float* g
     if (!g_hhat || !g_r) return BNN_EINVAL;
     if (!aligned(g_hhat, 4) || !aligned(g_r, 4)) return BNN_EALIGN;
     if (overlap(g_hhat, (size_t)M * N * 4, g_r, (size_t)N * 4)) return BNN_EINVAL;
-    colsum_kernel<<<(unsigned)((N + 63) / 64), 64, 0, static_cast<hipStream_t>(stream)>>>(g_hhat, (int)M, (int)N, g_r);
+    const unsigned blocks = (unsigned)((N + kColsumCols - 1) / kColsumCols);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (N % 4 == 0 && aligned(g_hhat, 16)) colsum_kernel<true><<<blocks, 256, 0, st>>>(g_hhat, (int)M, (int)N, g_r);
+    else colsum_kernel<false><<<blocks, 256, 0, st>>>(g_hhat, (int)M, (int)N, g_r);
     return launch_status();
 }
 
@@ -1129,7 +1140,9 @@ BNN_EXPORT int bnn_update_clip(float* w, const float* g, int64_t count, float et
     if (!w || !g) return BNN_EINVAL;
     if (!aligned(w, 4) || !aligned(g, 4)) return BNN_EALIGN;
     if (overlap(w, (size_t)count * 4, g, (size_t)count * 4)) return BNN_EINVAL;
-    update_clip_kernel<<<elementwise_blocks(count), 256, 0, static_cast<hipStream_t>(stream)>>>(w, g, count, eta, clip);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (aligned(w, 16) && aligned(g, 16)) update_clip_kernel<true><<<quad_blocks(count), 256, 0, st>>>(w, g, count, eta, clip);
+    else update_clip_kernel<false><<<elementwise_blocks(count), 256, 0, st>>>(w, g, count, eta, clip);
     return launch_status();
 }
 
@@ -1140,9 +1153,13 @@ BNN_EXPORT int bnn_grad_norm_clip(float* g, int64_t count, float alpha, void* wo
     if (!aligned(g, 4) || !aligned(workspace, 8) || !aligned(norm_out, 4)) return BNN_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     double* partial = static_cast<double*>(workspace);
-    sumsq_partial_kernel<<<kSumsqBlocks, 256, 0, st>>>(g, count, partial);
-    sumsq_final_kernel<<<1, 256, 0, st>>>(partial, norm_out);
-    if (count > 0) scale_if_above_kernel<<<elementwise_blocks(count), 256, 0, st>>>(g, count, alpha, norm_out);
+    if (aligned(g, 16)) {
+        sumsq_partial_kernel<true><<<kSumsqBlocks, kSumsqThreads, 0, st>>>(g, count, partial);
+        scale_if_above_kernel<true><<<min(quad_blocks(count), 1024u), 256, 0, st>>>(g, count, alpha, partial, norm_out);
+    } else {
+        sumsq_partial_kernel<false><<<kSumsqBlocks, kSumsqThreads, 0, st>>>(g, count, partial);
+        scale_if_above_kernel<false><<<min(elementwise_blocks(count), 1024u), 256, 0, st>>>(g, count, alpha, partial, norm_out);
+    }
     return launch_status();
 }
 

@@ -254,6 +254,36 @@ def test_backward_products_on_the_int8_matrix_cores(G, bnn, oracle, T, M, N, K):
     assert np.all(np.abs(gw - exact_w) <= M * 2.0 ** -27 * np.abs(g64).max(0)[:, None] + 2.0 ** -23 * np.abs(exact_w))
 
 
+@pytest.mark.parametrize("M,N", [(1, 1), (255, 15), (256, 16), (257, 33), (513, 68), (1030, 20)])
+def test_bias_grad_slabs(G, bnn, T, M, N):
+    """Column sums at the edges of the 256-row slabs and of the 16-column workgroups, rows 16-byte aligned or not."""
+    g = np.random.default_rng(M * N).standard_normal((M, N)).astype(np.float32)
+    out = _f32(1, N)
+    dg = G.to_dev(g)
+    bnn.bnn_bias_grad(G.ptr(dg), M, N, G.ptr(out), G.stream())
+    assert np.array_equal(out.cpu().numpy()[0], T.bias_grad(g))
+
+
+def test_elementwise_kernels_on_unaligned_arrays(G, bnn, T):
+    """Arrays at 4 bytes past a 16-byte boundary take the one-element accesses: the same values."""
+    rng = np.random.default_rng(12)
+    n = 4099
+    a, h, w = (rng.standard_normal(n).astype(np.float32) for _ in range(3))
+    da, dh, dw = (torch.cat([torch.zeros(1, device="cuda:0"), G.to_dev(v)]) for v in (a, h, w))
+    pa, ph, pw = (t.data_ptr() + 4 for t in (da, dh, dw))
+    bnn.bnn_update_clip(pw, pa, n, 0.1, 1, G.stream())
+    assert np.array_equal(dw[1:].cpu().numpy(), T.update_clip(w, a, 0.1, True))
+    bnn.bnn_sigmoid_grad(pa, ph, n, pw, G.stream())
+    assert np.array_equal(dw[1:].cpu().numpy(), T.sigmoid_grad(a, h))
+    ws, norm = torch.empty(2048, dtype=torch.uint8, device="cuda:0"), _f32(1, 1)
+    bnn.bnn_grad_norm_clip(pa, n, 1.0, G.ptr(ws), G.ptr(norm), G.stream())
+    want, want_norm = T.grad_norm_clip(a, 1.0)
+    assert abs(float(norm) - float(want_norm)) <= 1e-6 * float(want_norm)
+    assert np.max(np.abs(da[1:].cpu().numpy() - want)) <= 1e-6 * np.max(np.abs(want))
+    bnn.bnn_mask_grad(ph, pw, n, 0.2, ph, G.stream())
+    assert np.array_equal(dh[1:].cpu().numpy(), T.mask_grad(h, T.sigmoid_grad(a, h), 0.2))
+
+
 @pytest.mark.parametrize("clip", [0, 1])
 def test_update_clip(G, bnn, T, clip):
     rng = np.random.default_rng(5)
