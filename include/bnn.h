@@ -94,7 +94,8 @@ typedef enum bnn_option {
                                    log-Softmax in one kernel (needs K % 256 == 0 and N <= 4096),
                                    0 = product kernel followed by a row kernel (default: measured faster)        */
     BNN_OPT_MFMA_SHAPE = 7,      /* matrix-core arm: 16 = 16x16x128 MFMA (64 x 64 wave tiles), 32 = 32x32x64 MFMA
-                                   (128 x 64 wave tiles), 0 = by batch size (32 from 1024 frames; default)       */
+                                   (128 x 64 wave tiles), 0 = by the number of tiles (default): 16x16x128 with 16 x 64
+                                   wave tiles while those fill the chip at most once, 32x32x64 beyond            */
     BNN_OPT_MFMA32_WM = 8,       /* 32-row accumulator fragments per wavefront of the 32x32x64 kernel: 2, 4, or 0 =
                                    by grid size (default)                                                        */
     BNN_OPT_MFMA32_XCD_ORDER = 11, /* 32x32x64 kernel: 1 = tiles that share rows of frames run on the same XCD (one L2),
@@ -114,7 +115,8 @@ typedef enum bnn_option {
     BNN_OPT_STREAM_MAX_FRAMES = 12, /* batches of at most this many frames (streaming; the paper's motivation is on-device,
                                        frame-by-frame inference) run every layer on the vector-ALU kernels with 1 or 2 frames
                                        per workgroup, so that a layer is spread over the whole chip and takes one pass
-                                       over its weight rows; 0 = never.  Default 64.  Same results either way.          */
+                                       over its weight rows (binary layers that would need more workgroups than the chip
+                                       holds stay on the matrix cores); 0 = never.  Default 64.  Same results either way. */
     BNN_OPT_MFMA32_SPLITK = 14,     /* Sign layers on the 128-row 32x32x64 kernel with K % 1024 == 0: 1 = a workgroup of 8
                                        waves, the second four taking the second half of K and handing their sums over
                                        through LDS (two waves per SIMD from a grid of one workgroup per CU); 0 = no

@@ -5,6 +5,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <type_traits>
 
 #include "../../include/bnn.h"
 #include "mfma32_kernels.hpp"
@@ -286,26 +287,26 @@ void launch_binx_valu_tm(const uint32_t* Xp, const uint32_t* Wp, const float* sc
     }
 }
 
-template <int WM, bool AL>
+template <int WM, bool AL, bool X01>
 void launch_binx_mfma_wm(const uint32_t* Xp, const uint32_t* Wp, const float* scale, const float* bias, int M, int K,
                          int N, int w32, int act, void* Y, int yw32, hipStream_t st) {
     constexpr int WN = 4;
     const dim3 grid((M + 32 * WM - 1) / (32 * WM), (N + 32 * WN - 1) / (32 * WN)), block(256);
     switch (act) {
         case BNN_ACT_RAW_I32:
-            binx_mfma_kernel<WM, WN, ACT_RAW_I32, AL><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            binx_mfma_kernel<WM, WN, ACT_RAW_I32, AL, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         case BNN_ACT_SIGN:
-            binx_mfma_kernel<WM, WN, ACT_SIGN, AL><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            binx_mfma_kernel<WM, WN, ACT_SIGN, AL, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         case BNN_ACT_HARDTANH:
-            binx_mfma_kernel<WM, WN, ACT_HARDTANH, AL><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            binx_mfma_kernel<WM, WN, ACT_HARDTANH, AL, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         case BNN_ACT_SIGMOID:
-            binx_mfma_kernel<WM, WN, ACT_SIGMOID, AL><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            binx_mfma_kernel<WM, WN, ACT_SIGMOID, AL, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         default:
-            binx_mfma_kernel<WM, WN, ACT_LINEAR, AL><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            binx_mfma_kernel<WM, WN, ACT_LINEAR, AL, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
     }
 }
@@ -374,14 +375,24 @@ void launch_binx_mfma_i8(const uint32_t* Xp, const uint32_t* Wp, const float* sc
 int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N,
              int act, int wb, void* Y, int arm, hipStream_t st, bool x01 = false) {
     if (M == 0) return BNN_OK;
-    const bool stream = arm == BNN_ARM_AUTO && M <= g_stream_max_frames.load();
+    // wide layers leave the vector-ALU kernel from where its workgroups no longer fit the chip at once: 64 frames of
+    // 4096 x 4096 took 12.0 us there, 7.7 on the matrix cores (64 x 2048 x 2048, 256 workgroups: 5.1 against 5.4)
+    const bool stream = arm == BNN_ARM_AUTO && M <= g_stream_max_frames.load() &&
+                        (K < 2048 || ((M + 1) / 2) * ((N + 255) / 256) <= 256 || g_default_arm.load() != BNN_ARM_MFMA);
     if (arm == BNN_ARM_AUTO) arm = g_default_arm.load();
-    if (x01) arm = BNN_ARM_MFMA;   // large batches: the 0/1 reading of the input bits exists on the 32x32x64 kernel only
+    if (x01) arm = BNN_ARM_MFMA;   // larger batches: the 0/1 reading of the input bits exists on the fp4 matrix-core kernels only
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* A = static_cast<const uint32_t*>(Xp);
     const uint32_t* B = static_cast<const uint32_t*>(Wp);
     const bool rows16 = (w32 % 4 == 0) && aligned(Xp, 16) && aligned(Wp, 16);
     const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
+    // The 16x16x128 kernel with 16 x 64 wave tiles (32 x 128 per workgroup) while its grid fits the 256 CUs once: a layer
+    // then lasts about one memory round trip plus a short epilogue, where larger tiles leave most CUs idle.  Measured
+    // (Sign, K = N): 333 x 1024 4.4 us (64-row tiles of the same kernel 8.5, 64-row tiles of the 32x32x64 kernel 6.4),
+    // 100 x 2048 5.5 (10.7, 6.8), 1000 x 512 3.6 (6.3, 4.0); with more than 256 tiles the 32x32x64 kernel is the faster
+    // one: 600 x 2048 8.2 against 7.4, 1000 x 4096 23.2 against 12.2.
+    const int64_t tiles1 = ((M + 31) / 32) * ((N + 127) / 128);
+    const int mfma_shape = g_mfma_shape.load();
     if (stream) {
         // Batches of a few frames (streaming): the matrix-core tiles would be nearly empty and a workgroup would
         // still walk all of K for its 64 or 128 rows.  The vector-ALU kernel with 1 or 2 frames per workgroup spreads
@@ -434,7 +445,7 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         else
             binx_mfma_logsoftmax_kernel<32, 2><<<grid, block, 0, st>>>(A, B, scale, bias, Mi, Ki, Ni, w32, Yf, ab, bb);
         return launch_status();
-    } else if (x01 || g_mfma_shape.load() == 32 || (g_mfma_shape.load() == 0 && M >= 1024)) {
+    } else if (mfma_shape == 32 || (x01 && mfma_shape == 16) || (mfma_shape == 0 && tiles1 > 256)) {
         // large batch: 32x32x64 MFMA, 128 x 64 (or 64 x 64) wave tiles
         const bool al = rows16 && (K % 512 == 0);
         // Output layer: the product goes to memory as int16 (half the bytes of fp32 pre-activations), and the row
@@ -506,13 +517,18 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
     } else {
         const bool al = rows16 && (K % 512 == 0);
         const int wm = g_mfma_wm.load();
-        if (al) {
-            if (wm == 2) launch_binx_mfma_wm<2, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-            else launch_binx_mfma_wm<4, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-        } else {
-            if (wm == 2) launch_binx_mfma_wm<2, false>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-            else launch_binx_mfma_wm<4, false>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-        }
+        auto go = [&](auto wmc, auto alc, auto z1) {
+            launch_binx_mfma_wm<decltype(wmc)::value, decltype(alc)::value, decltype(z1)::value>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
+        };
+        using WM1 = std::integral_constant<int, 1>;
+        using WM2 = std::integral_constant<int, 2>;
+        using WM4 = std::integral_constant<int, 4>;
+        const std::true_type yes;
+        const std::false_type no;
+        if (x01) { if (al) go(WM1{}, yes, yes); else go(WM1{}, no, yes); }
+        else if (mfma_shape == 0) { if (al) go(WM1{}, yes, no); else go(WM1{}, no, no); }
+        else if (wm == 2) { if (al) go(WM2{}, yes, no); else go(WM2{}, no, no); }
+        else { if (al) go(WM4{}, yes, no); else go(WM4{}, no, no); }
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), Mi, Ni, st);
     if (act == ACT_DOT_I16) {
@@ -551,8 +567,19 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const int kpad = (Ki + 63) / 64 * 64;
-    int nb = (Ni + kRealxChunk - 1) / kRealxChunk * kRealxChunk;
-    if (nb > kRealxMaxNB) nb = kRealxMaxNB;
+    // Outputs per workgroup.  A workgroup costs about 11 us (frames in, digits, the undecided outputs) and 4 us per 512
+    // outputs, and a CU holds one at a time, so the outputs are split as far as that shortens the longest CU's work:
+    // measured at 440 x 2048, 333 frames 27.7 us with all outputs in one workgroup, 15.5 with 512; 1500 frames 27.5 and
+    // 19.4 (1024); 4096 frames 28.2 unsplit, 37.1 with 1024, 55.6 with 512.
+    const int chunks = min((Ni + kRealxChunk - 1) / kRealxChunk, kRealxMaxNB / kRealxChunk);
+    const int64_t mt = (M + kRealxBM - 1) / kRealxBM;
+    int nb = 0;
+    double best = 0.0;
+    for (int c = chunks; c >= 1; --c) {
+        const int64_t wgs = mt * ((Ni + c * kRealxChunk - 1) / (c * kRealxChunk));
+        const double cost = (double)((wgs + 255) / 256) * (11.0 + 4.1 * c);
+        if (nb == 0 || cost < best) best = cost, nb = c * kRealxChunk;
+    }
     const size_t lds = realx_dynamic_lds(Ki, kpad, w32, nb);
     const dim3 grid((Mi + kRealxBM - 1) / kRealxBM, (Ni + nb - 1) / nb), block(kRealxThreads);
     // More than 64 KB of LDS per workgroup has to be requested explicitly (gfx950 has 160 KB per CU).

@@ -14,7 +14,8 @@
 // expand to (+1)(+1) and are subtracted afterwards as a constant.
 //
 // Tiling: a workgroup of 4 waves (2 x 2) computes a (2*WM*16) x (2*WN*16) tile of [M][N]; each wave owns
-// WM x WN accumulator fragments of 16 x 16.  K advances in super-steps of 512 bits: lane (r = lane%16,
+// WM x WN accumulator fragments of 16 x 16 (WM = 1 by default: a layer's time is then one pass over K and a short epilogue;
+// 333 x 1024 x 1024 4.4 us, 8.5 with WM = 4).  K advances in super-steps of 512 bits: lane (r = lane%16,
 // g = lane/16) fetches 16 bytes (words 4g..4g+3 of the super-step) of row r of each fragment in one
 // global_load_dwordx4, and word j feeds MFMA step j.  The next super-step is fetched while the current
 // one is expanded and multiplied.
@@ -50,6 +51,18 @@ __device__ __forceinline__ v8i expand_pm1_fp4(uint32_t w, const ExpandConsts& c)
     return d;
 }
 
+// The 0/1 reading of the activation bits (paper Sec. 3.2) in the same element order: nibble 0b0010 = 1.0 where the bit is
+// set, 0 elsewhere (pad bits are 0 and contribute nothing).
+__device__ __forceinline__ v8i expand_01_fp4(uint32_t w, const ExpandConsts& c) {
+    v8i d;
+    d[0] = (int)((w << 1) & c.one_bits);
+    d[1] = (int)(w & c.one_bits);
+    d[2] = (int)((w >> 1) & c.one_bits);
+    d[3] = (int)((w >> 2) & c.one_bits);
+    d[4] = 0; d[5] = 0; d[6] = 0; d[7] = 0;
+    return d;
+}
+
 // Fetch words [16*S + 4*g, +4) of a packed row.  ALIGNED: rows are 16-byte aligned and whole
 // super-steps long.  Otherwise each word is bounds-checked against the row length and reads as 0.
 template <bool ALIGNED>
@@ -71,8 +84,9 @@ __device__ __forceinline__ uint32_t word_of(const uint4& v, int j) {
     return j == 0 ? v.x : (j == 1 ? v.y : (j == 2 ? v.z : v.w));
 }
 
+// X01: the activation bits are read as 0/1; the weights' flipped sign then stays in the sum and is taken out at the end.
 // Grid: x = ceil(M / (32*WM)), y = ceil(N / (32*WN)); block = 256 threads.
-template <int WM, int WN, int ACT, bool ALIGNED>
+template <int WM, int WN, int ACT, bool ALIGNED, bool X01>
 __global__ __launch_bounds__(256) void binx_mfma_kernel(const uint32_t* __restrict__ Xp, const uint32_t* __restrict__ Wp,
                                                         const float* __restrict__ scale, const float* __restrict__ bias,
                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32) {
@@ -127,7 +141,7 @@ __global__ __launch_bounds__(256) void binx_mfma_kernel(const uint32_t* __restri
             for (int f = 0; f < WN; ++f) bx[f] = expand_pm1_fp4(word_of(braw[f], j), ec);
 #pragma unroll
             for (int fm = 0; fm < WM; ++fm) {
-                const v8i ax = expand_pm1_fp4(word_of(araw[fm], j), ec);
+                const v8i ax = X01 ? expand_01_fp4(word_of(araw[fm], j), ec) : expand_pm1_fp4(word_of(araw[fm], j), ec);
 #pragma unroll
                 for (int fn = 0; fn < WN; ++fn)
                     acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(ax, bx[fn], acc[fm][fn], 4, 4, 0, 0, 0, 0);
@@ -140,8 +154,9 @@ __global__ __launch_bounds__(256) void binx_mfma_kernel(const uint32_t* __restri
     }
 
     // ---- epilogue.  Accumulator fragment (fm, fn), register q of lane (r, g) is
-    //      dot[m_base + 16 fm + 4 g + q][n_base + 16 fn + r] + pad.
+    //      dot[m_base + 16 fm + 4 g + q][n_base + 16 fn + r] + pad, or with X01 minus the dot product.
     const float pad = (float)(nS * 512 - K);
+    auto dot_of = [&](float a) { return X01 ? 0.0f - a : a - pad; };
     float sc[WN], bi[WN];
     bool nvalid[WN];
 #pragma unroll
@@ -163,7 +178,7 @@ __global__ __launch_bounds__(256) void binx_mfma_kernel(const uint32_t* __restri
                 unsigned long long b[WN];
 #pragma unroll
                 for (int fn = 0; fn < WN; ++fn) {
-                    const float h = affine(sc[fn], acc[fm][fn][q] - pad, bi[fn]);
+                    const float h = affine(sc[fn], dot_of(acc[fm][fn][q]), bi[fn]);
                     b[fn] = __ballot(nvalid[fn] && sign_bit(h));
                 }
                 // ballot bit 16*gg + rr belongs to row 4*gg + q, column 16*fn + rr.  Lane gg (< 4) assembles row 4*gg + q.
@@ -189,7 +204,7 @@ __global__ __launch_bounds__(256) void binx_mfma_kernel(const uint32_t* __restri
 #pragma unroll
                 for (int fn = 0; fn < WN; ++fn) {
                     const int n = n_base + fn * 16 + r;
-                    const float dot = acc[fm][fn][q] - pad;
+                    const float dot = dot_of(acc[fm][fn][q]);
                     if (m < M && nvalid[fn]) {
                         if constexpr (ACT == ACT_RAW_I32) {
                             ((int*)Y)[(size_t)m * N + n] = (int)dot;

@@ -1280,3 +1280,39 @@ def test_subtract_log_prior(G, bnn, oracle, M, N):
     with np.errstate(all="ignore"):
         want = oracle.subtract_log_prior(logp, log_prior)
     assert np.array_equal(d.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+# ----------------------------------------------------------------------------- tiles chosen by the number of frames
+
+@pytest.mark.parametrize("wb", [32, 64])
+@pytest.mark.parametrize("x01", [False, True])
+@pytest.mark.parametrize("act", ["sign", "raw", "logsoftmax"])
+@pytest.mark.parametrize("M,K,N", [(1, 512, 1), (31, 512, 127), (33, 1024, 129), (65, 2048, 64), (65, 700, 1001), (1000, 512, 1000),
+                                   (64, 2048, 4096), (1025, 512, 960)])
+def test_binary_layer_default_tiles(G, bnn_defaults, oracle, M, K, N, act, x01, wb):
+    """Binary layers on the default dispatch at the edges of the 32 x 128 tiles (one frame or output more or less, the last
+    size with 33 x 8 tiles: beyond the kernel's range), both readings of the bits: exact sums and bits."""
+    bnn = bnn_defaults
+    bnn.bnn_set_option(bnn.BNN_OPT_STREAM_MAX_FRAMES, 64 if M == 64 else 0)
+    aw, bw = _bin_operands(oracle, 5 * M + K + N, M, K, N, wb)
+    _, _, scale, bias = _rand_layer(M + 2 * N, 1, 1, N)
+    layer = G.layer_binx01 if x01 else G.layer_binx
+    Y = layer(G.to_dev(aw), G.to_dev(bw), G.to_dev(scale), G.to_dev(bias), K, N, bnn.ACT_BY_NAME[act], wb)
+    torch.cuda.synchronize()
+    want = (oracle.layer_binw_binx01(aw, bw, K, scale, bias, act, wb, form="and") if x01 else
+            oracle.layer_binw_binx(aw, bw, K, scale, bias, act, wb, form="xor"))
+    if act == "sign":
+        assert np.array_equal(G.words_to_host(Y, wb), want)
+    elif act == "raw":
+        assert np.array_equal(Y.cpu().numpy(), want)
+    else:
+        _close(Y.cpu().numpy(), want, act)
+
+
+@pytest.mark.parametrize("M,N", [(17, 513), (300, 1500), (1500, 2048), (700, 4000)])
+def test_first_layer_outputs_split_over_workgroups(G, bnn, oracle, M, N):
+    """The first layer's filter with its outputs in one, two or more blocks per 16 frames: bits of the ascending-k sum."""
+    X, W, scale, bias = _rand_layer(M + N, M, 440, N)
+    Wp = oracle.pack_sign(W, 32)
+    want = oracle.layer_binw_realx(X, Wp, 440, scale, bias, "sign", 32)
+    assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, 440, N, 32, True), want)
