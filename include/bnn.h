@@ -113,8 +113,9 @@ typedef enum bnn_option {
                                    the products of the current one (default), 2 = one set, order left to the
                                    compiler (kept for comparison)                                                */
     BNN_OPT_STREAM_MAX_FRAMES = 12, /* batches of at most this many frames (streaming; the paper's motivation is on-device,
-                                       frame-by-frame inference) run every layer on the vector-ALU kernels with 1 or 2 frames
-                                       per workgroup, so that a layer is spread over the whole chip and takes one pass
+                                       frame-by-frame inference) run every layer on kernels with few frames per workgroup (1 or 2
+                                       on the vector ALU; 16 on the fp32 matrix cores for real weights, and for real inputs
+                                       from 17 frames on), so that a layer is spread over the whole chip and takes one pass
                                        over its weight rows (binary layers that would need more workgroups than the chip
                                        holds stay on the matrix cores); 0 = never.  Default 64.  Same results either way. */
     BNN_OPT_MFMA32_SPLITK = 14,     /* Sign layers on the 128-row 32x32x64 kernel with K % 1024 == 0: 1 = a workgroup of 8

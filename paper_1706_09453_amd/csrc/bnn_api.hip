@@ -129,10 +129,10 @@ void launch_f32_mfma(const ChainArgs& a) {
     else
         realx_f32_mfma_kernel<ACT, false, WREAL><<<grid, 256, 0, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, Y);
 }
-// Sums of a real-input layer that is no small batch; arguments already checked.
+// Sums of a real-input layer; arguments already checked.  few: a streaming batch, which has no comparison arm.
 template <bool WREAL>
-void launch_f32_sums(const ChainArgs& a, int act) {
-    if (act != BNN_ACT_SIGN && a.M >= 128 && g_realx_f32_mfma.load() == 1) {
+void launch_f32_sums(const ChainArgs& a, int act, bool few) {
+    if (!few && act != BNN_ACT_SIGN && a.M >= 128 && g_realx_f32_mfma.load() == 1) {
         if (act == BNN_ACT_HARDTANH) launch_f32_mfma<ACT_HARDTANH, WREAL>(a);
         else if (act == BNN_ACT_SIGMOID) launch_f32_mfma<ACT_SIGMOID, WREAL>(a);
         else launch_f32_mfma<ACT_LINEAR, WREAL>(a);
@@ -186,10 +186,15 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
     if (M == 0) return BNN_OK;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
-    // batches of a few frames (streaming): 1 or 2 frames per workgroup spread the layer over the chip
-    const int tm = M <= g_stream_max_frames.load() ? (M <= 16 ? 1 : 2) : g_realx_tm.load();
+    const bool few = M <= g_stream_max_frames.load();   // batches of a few frames (streaming): always the chains
+    // Up to 16 of them on the vector ALU with one frame per workgroup: a lone wave takes 6.7 ns per k there, the chain of
+    // matrix instructions 8.2 (16 x 2048 x 2048 14.5 against 17.6 us, 16 x 440 x 2048 4.8 against 6.3); rows that are no
+    // multiple of 16 bytes cost the vector ALU a load per k (16 x 2047 x 2048 22.0 against 17.8), which short rows hide
+    // (16 x 441 x 2048 6.4 both).  From 17 frames on the workgroups share the CUs and the matrix cores win (see launch_chain_act).
+    const bool valu = M <= 16 && (K < 1024 || ((K & 3) == 0 && aligned(X, 16)));
+    const int tm = few ? (valu ? 1 : 0) : g_realx_tm.load();
     if (tm == 0) {
-        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st}, act);
+        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st}, act, few);
         if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
         return launch_status();
     }
@@ -205,29 +210,6 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
     return launch_status();
 }
 
-// Batches of a few frames (streaming): 2 frames per workgroup, so that the layer is spread over ceil(M / 2) x N / 256
-// workgroups (up to 16 frames with chunks of 64 k: fewer memory round trips, but 136 KiB of LDS, one workgroup per CU;
-// measured at 64 frames: 134 us with chunks of 16 k, 151 us with 64).
-template <int ACT, int KC>
-void launch_realw_valu_kc(const float* X, const float* W, const float* bias, int M, int K, int N, void* Y, int yw32, hipStream_t st) {
-    constexpr int TM = 2;
-    const dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
-    if ((K & 3) == 0 && aligned(X, 16) && aligned(W, 16)) {
-        constexpr unsigned lds = realw_lds_bytes(KC);
-        static std::atomic<uint64_t> allowed{0};
-        if (lds > 64 * 1024) allow_lds(&realw_valu_kernel<TM, ACT, KC>, lds, allowed);
-        realw_valu_kernel<TM, ACT, KC><<<grid, block, lds, st>>>(X, W, bias, M, K, N, Y, yw32);
-    } else {
-        realw_valu_simple_kernel<TM, ACT><<<grid, block, 0, st>>>(X, W, bias, M, K, N, Y, yw32);
-    }
-}
-template <int ACT>
-void launch_realw_valu(const float* X, const float* W, const float* bias, int M, int K, int N, void* Y, int yw32,
-                       hipStream_t st) {
-    if (M <= 16) launch_realw_valu_kc<ACT, 64>(X, W, bias, M, K, N, Y, yw32, st);
-    else launch_realw_valu_kc<ACT, 16>(X, W, bias, M, K, N, Y, yw32, st);
-}
-
 // A layer with real-valued weights.
 int run_realw(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, int act, int wb,
               void* Y, hipStream_t st) {
@@ -241,15 +223,8 @@ int run_realw(const float* X, const float* W, const float* bias, int64_t M, int6
         const unsigned nb = (unsigned)((N + 15) / 16);
         if (M <= 4) realw_gemv_kernel<4><<<dim3(nb, (unsigned)((M + 3) / 4)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
         else realw_gemv_kernel<8><<<dim3(nb, (unsigned)((M + 7) / 8)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
-    } else if (M > g_stream_max_frames.load()) {
-        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st}, act);
     } else {
-        switch (act) {
-            case BNN_ACT_SIGN: launch_realw_valu<ACT_SIGN>(X, W, bias, (int)M, (int)K, (int)N, Y, yw32, st); break;
-            case BNN_ACT_HARDTANH: launch_realw_valu<ACT_HARDTANH>(X, W, bias, (int)M, (int)K, (int)N, Y, yw32, st); break;
-            case BNN_ACT_SIGMOID: launch_realw_valu<ACT_SIGMOID>(X, W, bias, (int)M, (int)K, (int)N, Y, yw32, st); break;
-            default: launch_realw_valu<ACT_LINEAR>(X, W, bias, (int)M, (int)K, (int)N, Y, yw32, st); break;
-        }
+        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st}, act, M <= g_stream_max_frames.load());
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();

@@ -23,6 +23,15 @@ void launch_chain_act(const ChainArgs& a) {
     // 32-bit byte offsets inside a workgroup's rows: 256 rows of at most 2^22 - 1 numbers
     const bool vec = (a.K & 3) == 0 && a.K < (1 << 22) && aligned(a.X, 16) && (!WREAL || aligned(a.W, 16));
     const bool wide = a.N > 65535 * 64 - 64;   // tiles of 64 outputs would not fit the second grid dimension
+    // Up to 64 frames: tiles of 16 frames x 64 outputs, one fragment per wave.  The time is the chain itself (K / 4 dependent
+    // MFMAs), the same for 1 frame and for 64 as long as the grid fits the chip.  Measured against the vector-ALU kernels
+    // that took 1 or 2 frames per workgroup: real weights 16 x 440 x 2048 12.1 -> 5.8 us, 16 x 2048 x 2048 50 -> 14,
+    // 16 x 2047 x 2048 547 -> 16; weight bits 64 x 2048 x 2048 23.6 -> 17.7, 64 x 4096 x 4096 69 -> 33.
+    if (a.M <= 64 && !wide) {
+        if (vec) launch_chain_tile<1, 1, 1, 128, ACT, WREAL, true>(a);
+        else launch_chain_tile<1, 1, 1, 128, ACT, WREAL, false>(a);
+        return;
+    }
     if (!vec) {
         if (wide) launch_chain_tile<4, 4, 2, 32, ACT, WREAL, false>(a);
         else launch_chain_tile<2, 2, 2, 64, ACT, WREAL, false>(a);

@@ -17,7 +17,7 @@
 // t: one LDS instruction brings the operands of two steps, and with rows KC + 4 numbers apart its 64 lanes (16 rows, four
 // neighbours each) read 64 different banks.
 // Measured at 4096 x 2048 x 2048: binary weights 261 us = 132 TFLOP/s, real weights 272 us (vector-ALU kernels: 331 us,
-// and 290 with real weights); at 256 x 2048 x 2048 27 us against 72.  What is left to 153 TFLOP/s (register-only loop of
+// and 290 with real weights); at 256 x 2048 x 2048 27 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.  What is left to 153 TFLOP/s (register-only loop of
 // the same MFMA): the sign-building and LDS instructions of the staging, and the first and last chunk of a workgroup.
 // Columns past K are stored as 0 in the frames (and real weights): fma(w, 0, acc) returns acc (an accumulator that starts
 // at +0 is never -0), so the sum over k < K is unchanged.
@@ -45,6 +45,9 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
     constexpr int XPR = KC / 4, WPR = WREAL ? KC / 4 : KC / 16;   // pieces per row and chunk: 4 numbers, or 16 weight bits
     constexpr int NPX = TM * XPR / 256, NPW = TN * WPR / 256;      // pieces per thread
     constexpr int NS = KC / 16;                                   // groups of four MFMA steps per chunk
+    // Real weights, one dependent chain per wave: the staging is spread over the whole chunk (16 x 2048 x 2048 16.4 -> 13.9 us;
+    // with weight bits, an eighth of the loads, it gains nothing: 17.6 -> 17.9)
+    constexpr bool kSpread = WREAL && FM * FN == 1;
     static_assert(TM * XPR % 256 == 0 && TN * WPR % 256 == 0 && NS % 2 == 0, "whole pieces per thread");
     extern __shared__ __attribute__((aligned(16))) float chain_lds[];   // [2][TM + TN][LD]
     const int tid = (int)threadIdx.x;
@@ -83,44 +86,50 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
             return v;
         }
     };
+    auto gload_x = [&](Loads& L, int c, int j, auto tail) { L.x[j] = load4(xtile + (size_t)c * (KC * 4), xofs[j], c * KC + xcol, tail); };
+    auto gload_w = [&](Loads& L, int c, int j, auto tail) {
+        if constexpr (WREAL) {
+            L.w[j] = load4(wtile + (size_t)c * (KC * 4), wofs[j], c * KC + wcol, tail);
+        } else {
+            asm volatile("" : "+v"(wofs[j]));
+            const int back = decltype(tail)::value ? max(((c * KC + wcol) >> 5) - (w32 - 1), 0) : 0;
+            L.b[j] = *reinterpret_cast<const uint32_t*>(wtile + (size_t)c * (KC / 8) + (wofs[j] - (ofs_t)(4 * back)));
+        }
+    };
     auto gload = [&](Loads& L, int c, auto tail) {
 #pragma unroll
-        for (int j = 0; j < NPX; ++j) L.x[j] = load4(xtile + (size_t)c * (KC * 4), xofs[j], c * KC + xcol, tail);
+        for (int j = 0; j < NPX; ++j) gload_x(L, c, j, tail);
 #pragma unroll
-        for (int j = 0; j < NPW; ++j) {
-            if constexpr (WREAL) {
-                L.w[j] = load4(wtile + (size_t)c * (KC * 4), wofs[j], c * KC + wcol, tail);
-            } else {
-                asm volatile("" : "+v"(wofs[j]));
-                const int back = decltype(tail)::value ? max(((c * KC + wcol) >> 5) - (w32 - 1), 0) : 0;
-                L.b[j] = *reinterpret_cast<const uint32_t*>(wtile + (size_t)c * (KC / 8) + (wofs[j] - (ofs_t)(4 * back)));
-            }
+        for (int j = 0; j < NPW; ++j) gload_w(L, c, j, tail);
+    };
+    auto clean = [&](f32x4c v, int k, auto tail) {
+        if constexpr (decltype(tail)::value) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[i] = k + i < K ? v[i] : 0.0f;
+        }
+        return v;
+    };
+    auto lstore_x = [&](float* buf, const Loads& L, int c, int j, auto tail) {
+        *reinterpret_cast<f32x4c*>(buf + ((tid + 256 * j) / XPR) * LD + xcol) = clean(L.x[j], c * KC + xcol, tail);
+    };
+    constexpr int WST = WREAL ? 1 : 4;   // 16-byte stores of a weight piece
+    auto lstore_w = [&](float* buf, const Loads& L, int c, int j, int q, auto tail) {
+        float* row = buf + (TM + (tid + 256 * j) / WPR) * LD + wcol;
+        if constexpr (WREAL) {
+            *reinterpret_cast<f32x4c*>(row) = clean(L.w[j], c * KC + wcol, tail);
+        } else {   // (bits past K: +-1 times a frame value stored as 0)
+            const uint32_t inv = ~L.b[j] >> (wcol & 16);
+            *reinterpret_cast<f32x4c*>(row + 4 * q) = f32x4c{pm1_from_inverted_bit(inv, 4 * q), pm1_from_inverted_bit(inv, 4 * q + 1),
+                                                             pm1_from_inverted_bit(inv, 4 * q + 2), pm1_from_inverted_bit(inv, 4 * q + 3)};
         }
     };
     auto lstore = [&](float* buf, const Loads& L, int c, auto tail) {
-        auto clean = [&](f32x4c v, int k) {
-            if constexpr (decltype(tail)::value) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = k + i < K ? v[i] : 0.0f;
-            }
-            return v;
-        };
+        for (int j = 0; j < NPX; ++j) lstore_x(buf, L, c, j, tail);
 #pragma unroll
-        for (int j = 0; j < NPX; ++j)
-            *reinterpret_cast<f32x4c*>(buf + ((tid + 256 * j) / XPR) * LD + xcol) = clean(L.x[j], c * KC + xcol);
+        for (int j = 0; j < NPW; ++j)
 #pragma unroll
-        for (int j = 0; j < NPW; ++j) {
-            float* row = buf + (TM + (tid + 256 * j) / WPR) * LD + wcol;
-            if constexpr (WREAL) {
-                *reinterpret_cast<f32x4c*>(row) = clean(L.w[j], c * KC + wcol);
-            } else {   // (bits past K: +-1 times a frame value stored as 0)
-                const uint32_t inv = ~L.b[j] >> (wcol & 16);
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<f32x4c*>(row + 4 * q) = f32x4c{pm1_from_inverted_bit(inv, 4 * q), pm1_from_inverted_bit(inv, 4 * q + 1),
-                                                                     pm1_from_inverted_bit(inv, 4 * q + 2), pm1_from_inverted_bit(inv, 4 * q + 3)};
-            }
-        }
+            for (int q = 0; q < WST; ++q) lstore_w(buf, L, c, j, q, tail);
     };
     // operands of four MFMA steps: lane (r, g) takes k = 16 s + 4 t + g of its rows (two per LDS instruction)
     struct Frags { float x[FM][4]; float w[FN][4]; };
@@ -181,8 +190,28 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
             } else {
                 lread(F[(s + 1) & 1], cur, s + 1);
             }
+            // (nxt was last read before the previous barrier)
+            if constexpr (kSpread) {
+                // a share of the stores with each group of products, every piece's next load behind its last store
+                constexpr int U = NPX + WST * NPW;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (u * (NS - 1) / U != s) continue;
+                    const int j = u < NPX ? u : (u - NPX) / WST, q = u < NPX ? 0 : (u - NPX) % WST;
+                    if (u < NPX) {
+                        if constexpr (kStore) lstore_x(nxt, L, c + 1, j, st_tail);
+                        if constexpr (kLoad) gload_x(L, c + 2, j, ld_tail);
+                    } else {
+                        if constexpr (kStore) lstore_w(nxt, L, c + 1, j, q, st_tail);
+                        if constexpr (kLoad) if (q == WST - 1) gload_w(L, c + 2, j, ld_tail);
+                    }
+                }
+                products(F[s & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+                continue;
+            }
             if (s == 0) {
-                if constexpr (kStore) lstore(nxt, L, c + 1, st_tail);   // last read before the previous barrier
+                if constexpr (kStore) lstore(nxt, L, c + 1, st_tail);
                 if constexpr (kLoad) gload(L, c + 2, ld_tail);
             }
             products(F[s & 1]);

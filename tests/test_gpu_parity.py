@@ -357,7 +357,7 @@ def test_realw_layer(G, bnn, oracle, M, K, N, act, wb):
 @pytest.mark.parametrize("act", ["sign", "linear", "logsoftmax", "sigmoid"])
 @pytest.mark.parametrize("M,K,N", [(1, 440, 2048), (2, 31, 5), (5, 16, 257), (16, 452, 260), (33, 2048, 300), (64, 100, 3307)])
 def test_streaming_real_weight_layer(G, bnn, oracle, M, K, N, act):
-    """At most 64 frames: the real-weight kernels with 2 frames per workgroup; the same ascending-k chain, identical bits."""
+    """At most 64 frames: tiles of 16 frames x 64 outputs (in front of the log-Softmax K is split over the lanes); the same ascending-k chain, identical bits."""
     X, W, bias = _rand_realw(M * 13 + K + N, M, K, N)
     with _streaming(bnn):
         Y = G.layer_realw(G.to_dev(X), G.to_dev(W), G.to_dev(bias), K, N, bnn.ACT_BY_NAME[act], 32)
@@ -526,7 +526,8 @@ def test_realx_against_fp64_shadow(G, bnn, oracle):
 @pytest.mark.parametrize("act", ["sign", "linear"])
 @pytest.mark.parametrize("M,K,N", [(4097, 36, 2050), (4097, 33, 2050), (4096, 64, 2048),   # 256 x 128 tiles; K that is no multiple of 4
                                    (2049, 100, 2100), (1100, 32, 1300),                    # 128 x 128, 64 x 64
-                                   (65, 4, 33), (65, 128, 65), (80, 132, 1), (129, 260, 70), (65, 516, 40)])  # 32 x 64; 1 to 5 chunks of K
+                                   (65, 4, 33), (65, 128, 65), (80, 132, 1), (129, 260, 70), (65, 516, 40),  # 32 x 64; 1 to 5 chunks of K
+                                   (1, 4, 33), (16, 33, 2050), (17, 128, 65), (48, 260, 1), (63, 511, 70), (64, 516, 40)])  # 16 x 64
 def test_ascending_sums_on_the_matrix_cores(G, bnn, oracle, M, K, N, act):
     """Binary and real weights, real input: every workgroup tile the dispatch can pick, ragged on both sides, K ending in
     every part of a chunk.  The fp32 matrix cores fed in natural order give the bits of the oracle's chain."""
