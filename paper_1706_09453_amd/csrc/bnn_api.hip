@@ -262,6 +262,19 @@ void launch_binx_valu_tm(const uint32_t* Xp, const uint32_t* Wp, const float* sc
     }
 }
 
+template <int TM, bool X01>
+void launch_binx_split(const uint32_t* Xp, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
+                       int w32, int act, void* Y, int yw32, hipStream_t st) {
+    const dim3 grid((M + TM - 1) / TM, (N + 63) / 64), block(256);
+    switch (act) {
+        case BNN_ACT_RAW_I32: binx_split_kernel<TM, ACT_RAW_I32, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32); break;
+        case BNN_ACT_SIGN: binx_split_kernel<TM, ACT_SIGN, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32); break;
+        case BNN_ACT_HARDTANH: binx_split_kernel<TM, ACT_HARDTANH, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32); break;
+        case BNN_ACT_SIGMOID: binx_split_kernel<TM, ACT_SIGMOID, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32); break;
+        default: binx_split_kernel<TM, ACT_LINEAR, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32); break;
+    }
+}
+
 template <int WM, bool AL, bool X01>
 void launch_binx_mfma_wm(const uint32_t* Xp, const uint32_t* Wp, const float* scale, const float* bias, int M, int K,
                          int N, int w32, int act, void* Y, int yw32, hipStream_t st) {
@@ -370,22 +383,24 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
     const int mfma_shape = g_mfma_shape.load();
     if (stream) {
         // Batches of a few frames (streaming): the matrix-core tiles would be nearly empty and a workgroup would
-        // still walk all of K for its 64 or 128 rows.  The vector-ALU kernel with 1 or 2 frames per workgroup spreads
-        // the layer over ceil(M / TM) x N / 256 workgroups, each of which is done after one pass over its weight rows.
-        auto go = [&](auto tmc, auto vec, auto z1) {
-            launch_binx_valu_tm<decltype(tmc)::value, decltype(vec)::value, decltype(z1)::value>(A, B, scale, bias, Mi, Ki, Ni, w32,
-                                                                                                act, Y, yw32, st);
+        // still walk all of K for its 64 or 128 rows.  The vector-ALU kernels with 1 or 2 frames per workgroup spread
+        // the layer over the chip, and each workgroup is done after one pass over its weight rows.  K split over four lanes
+        // while its workgroups fit the chip twice (Sign: 1 x 4096 x 4096 5.9 -> 3.7 us, 16 x 2048 x 2048 4.4 -> 3.9); with
+        // more of them every lane's own row is as good or better (16 x 4096 x 4096 6.0 against 6.2, 32 x 4096 x 4096 6.1
+        // against 7.3).
+        const int tm = M <= 16 ? 1 : 2;
+        const bool split = rows16 && ((M + tm - 1) / tm) * ((N + 63) / 64) <= 512;
+        auto go = [&](auto tmc, auto z1) {
+            constexpr int TM = decltype(tmc)::value;
+            constexpr bool Z1 = decltype(z1)::value;
+            if (split) launch_binx_split<TM, Z1>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
+            else if (rows16) launch_binx_valu_tm<TM, true, Z1>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
+            else launch_binx_valu_tm<TM, false, Z1>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
         };
         using I1 = std::integral_constant<int, 1>;
         using I2 = std::integral_constant<int, 2>;
-        const bool one = M <= 16;
-        if (rows16) {
-            if (x01) { if (one) go(I1{}, std::true_type{}, std::true_type{}); else go(I2{}, std::true_type{}, std::true_type{}); }
-            else { if (one) go(I1{}, std::true_type{}, std::false_type{}); else go(I2{}, std::true_type{}, std::false_type{}); }
-        } else {
-            if (x01) { if (one) go(I1{}, std::false_type{}, std::true_type{}); else go(I2{}, std::false_type{}, std::true_type{}); }
-            else { if (one) go(I1{}, std::false_type{}, std::false_type{}); else go(I2{}, std::false_type{}, std::false_type{}); }
-        }
+        if (x01) { if (tm == 1) go(I1{}, std::true_type{}); else go(I2{}, std::true_type{}); }
+        else { if (tm == 1) go(I1{}, std::false_type{}); else go(I2{}, std::false_type{}); }
     } else if (arm == BNN_ARM_VALU_XOR) {
         const int tm = g_binx_valu_tm.load();
         if (rows16) {

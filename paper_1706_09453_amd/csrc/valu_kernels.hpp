@@ -317,4 +317,79 @@ __global__ __launch_bounds__(256) void binx_valu_kernel(const uint32_t* __restri
     epilogue_lanes_n<TM, ACT>(v, vi, scale, bias, m0, M, n0, n, N, Y, yw32);
 }
 
+// The same products for batches of a few frames, rows 16-byte aligned and a multiple of 4 words long.  Bound: latency --
+// a layer is one or two memory round trips and a short reduction, so K is split over four lanes per output: lane (o, g)
+// takes the 16-byte pieces g, g + 4, ... of output n0 + o, eight of them requested at once (K = 4096 in one round trip), and the
+// four integer counts are added by two lane exchanges (exact, whatever the order).  Four times the waves of
+// binx_valu_kernel, each with a quarter of its loads and counts.  TM frames per wave.
+// Grid: x = ceil(M / TM), y = ceil(N / 64) (4 waves x 16 outputs).
+template <int TM, int ACT, bool X01>
+__global__ __launch_bounds__(256) void binx_split_kernel(const uint32_t* __restrict__ Xp, const uint32_t* __restrict__ Wp,
+                                                         const float* __restrict__ scale, const float* __restrict__ bias,
+                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32) {
+    constexpr int PW = 8;   // pieces of a lane in flight
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lane = lane_id(), o = lane & 15, g = lane >> 4;
+    const int n0 = ((int)blockIdx.y * 4 + wave) * 16;
+    if (n0 >= (ACT == ACT_SIGN ? yw32 * 32 : N)) return;
+    const int n = n0 + o, m0 = (int)blockIdx.x * TM;
+    const int quads = w32 >> 2;
+    const uint4* wrow = reinterpret_cast<const uint4*>(Wp + (size_t)min(n, N - 1) * w32);
+    const uint4* xr[TM];
+#pragma unroll
+    for (int i = 0; i < TM; ++i) xr[i] = reinterpret_cast<const uint4*>(Xp + (size_t)min(m0 + i, M - 1) * w32);
+    const float sc = (scale && n < N) ? scale[n] : 1.0f, bi = (bias && n < N) ? bias[n] : 0.0f;
+
+    int cnt[TM];   // bits that differ; X01: 2 popcount(x AND w) - popcount(x)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) cnt[i] = 0;
+    auto one = [](uint32_t w, uint32_t x) { return X01 ? 2 * __builtin_popcount(w & x) - __builtin_popcount(x) : __builtin_popcount(w ^ x); };
+    auto count = [&](const uint4& w, const uint4& x) { return one(w.x, x.x) + one(w.y, x.y) + one(w.z, x.z) + one(w.w, x.w); };
+    // `np` pieces of this lane from piece q; those past the row read its last piece and count nothing
+    auto pieces = [&](int q, auto npc) {
+        constexpr int NP = decltype(npc)::value;
+        uint4 w[NP], x[TM][NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int at = min(q + 4 * p + g, quads - 1);
+            w[p] = wrow[at];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) x[i][p] = xr[i][at];
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                const int c = count(w[p], x[i][p]);
+                cnt[i] += q + 4 * p + g < quads ? c : 0;
+            }
+    };
+    int q = 0;
+    for (; q + 4 * (PW / 2) < quads; q += 4 * PW) pieces(q, std::integral_constant<int, PW>{});
+    if (q < quads) pieces(q, std::integral_constant<int, PW / 2>{});   // (at most half as many left: K = 2048 and below)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        cnt[i] += __shfl_xor(cnt[i], 16, kWave);
+        cnt[i] += __shfl_xor(cnt[i], 32, kWave);
+    }
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+        const int m = m0 + i, dot = X01 ? cnt[i] : K - 2 * cnt[i];
+        if (m >= M) break;
+        if constexpr (ACT == ACT_SIGN) {   // 16 outputs: half a word of the row; outputs past N: bit 0
+            const unsigned long long bits = __ballot(n < N && sign_bit(affine(sc, (float)dot, bi)));
+            if (lane == 0) reinterpret_cast<uint16_t*>(Y)[(size_t)m * 2 * yw32 + (n0 >> 4)] = (uint16_t)bits;
+        } else if (g == 0 && n < N) {
+            if constexpr (ACT == ACT_RAW_I32) {
+                static_cast<int*>(Y)[(size_t)m * N + n] = dot;
+            } else {
+                float h = affine(sc, (float)dot, bi);
+                if constexpr (ACT == ACT_HARDTANH) h = hardtanh(h);
+                if constexpr (ACT == ACT_SIGMOID) h = sigmoid(h);
+                static_cast<float*>(Y)[(size_t)m * N + n] = h;
+            }
+        }
+    }
+}
+
 }  // namespace bnn

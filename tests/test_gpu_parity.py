@@ -213,7 +213,8 @@ def test_binx01_layer(G, bnn, oracle, M, K, N, act, wb):
 @pytest.mark.parametrize("act", ["raw", "sign", "linear", "logsoftmax", "sigmoid"])
 @pytest.mark.parametrize("x01", [False, True])
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (1, 2048, 2048), (2, 31, 5), (3, 440, 3307), (16, 2048, 300), (17, 33, 65),
-                                   (33, 1024, 200), (64, 2048, 512)])
+                                   (33, 1024, 200), (64, 2048, 512),
+                                   (1, 2176, 70), (17, 4224, 33), (4, 6300, 97), (16, 4096, 2112)])   # K over 1 to 4 rounds of pieces; too many workgroups for the split
 def test_streaming_binary_layer(G, bnn, oracle, M, K, N, act, x01, wb):
     """Default arm, at most 64 frames: the vector-ALU kernel with 1 or 2 frames per workgroup; same bits as ever."""
     aw, bw = _bin_operands(oracle, 11 * M + K + N, M, K, N, wb)
