@@ -385,9 +385,9 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         // Batches of a few frames (streaming): the matrix-core tiles would be nearly empty and a workgroup would
         // still walk all of K for its 64 or 128 rows.  The vector-ALU kernels with 1 or 2 frames per workgroup spread
         // the layer over the chip, and each workgroup is done after one pass over its weight rows.  K split over four lanes
-        // while its workgroups fit the chip twice (Sign: 1 x 4096 x 4096 5.9 -> 3.7 us, 16 x 2048 x 2048 4.4 -> 3.9); with
-        // more of them every lane's own row is as good or better (16 x 4096 x 4096 6.0 against 6.2, 32 x 4096 x 4096 6.1
-        // against 7.3).
+        // while its workgroups fit the chip twice (one frame through six layers of 2048 units 33.8 -> 29.3 us a pass, 0.7 us a
+        // layer; one layer of 1 x 4096 x 4096 launched back to back 5.9 -> 3.7 to 5.7 from run to run); with more of them
+        // every lane's own row is as good or better (16 x 4096 x 4096 6.0 against 6.2, 32 x 4096 x 4096 6.1 against 7.3).
         const int tm = M <= 16 ? 1 : 2;
         const bool split = rows16 && ((M + tm - 1) / tm) * ((N + 63) / 64) <= 512;
         auto go = [&](auto tmc, auto z1) {
