@@ -402,7 +402,7 @@ int bnn_update_clip(float* w, const float* g, int64_t count, float eta, int clip
 
 /* Sec. 2.3: if ||g||_2 > alpha then g <- (alpha / ||g||_2) g; the norm is summed in fp64 in a fixed order.
  *   g in/out [count];  workspace: DEVICE scratch of at least 2048 bytes, 8-byte aligned;
- *   norm_out: DEVICE float that receives ||g||_2 (before clipping). */
+ *   norm_out: DEVICE float that receives ||g||_2 (before clipping); it may lie inside the workspace (one launch more). */
 int bnn_grad_norm_clip(float* g, int64_t count, float alpha, void* workspace, float* norm_out, void* stream);
 
 /* Sec. 2.1, optional step of Alg. 1's Update (semi-stochastic binarisation): w <- Sign(w) with probability p(|w|),

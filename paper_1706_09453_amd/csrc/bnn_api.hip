@@ -1170,13 +1170,15 @@ BNN_EXPORT int bnn_grad_norm_clip(float* g, int64_t count, float alpha, void* wo
     if (!aligned(g, 4) || !aligned(workspace, 8) || !aligned(norm_out, 4)) return BNN_EALIGN;
     hipStream_t st = static_cast<hipStream_t>(stream);
     double* partial = static_cast<double*>(workspace);
-    if (aligned(g, 16)) {
-        sumsq_partial_kernel<true><<<kSumsqBlocks, kSumsqThreads, 0, st>>>(g, count, partial);
-        scale_if_above_kernel<true><<<min(quad_blocks(count), 1024u), 256, 0, st>>>(g, count, alpha, partial, norm_out);
-    } else {
-        sumsq_partial_kernel<false><<<kSumsqBlocks, kSumsqThreads, 0, st>>>(g, count, partial);
-        scale_if_above_kernel<false><<<min(elementwise_blocks(count), 1024u), 256, 0, st>>>(g, count, alpha, partial, norm_out);
-    }
+    const bool inside = overlap(workspace, kSumsqBlocks * sizeof(double), norm_out, sizeof(float));
+    auto go = [&](auto vec, unsigned blocks) {
+        constexpr bool V = decltype(vec)::value;
+        sumsq_partial_kernel<V><<<kSumsqBlocks, kSumsqThreads, 0, st>>>(g, count, partial);
+        if (inside) sumsq_final_kernel<<<1, kWave, 0, st>>>(partial, norm_out);
+        scale_if_above_kernel<V><<<min(blocks, 1024u), 256, 0, st>>>(g, count, alpha, inside ? nullptr : partial, norm_out);
+    };
+    if (aligned(g, 16)) go(std::true_type{}, quad_blocks(count));
+    else go(std::false_type{}, elementwise_blocks(count));
     return launch_status();
 }
 

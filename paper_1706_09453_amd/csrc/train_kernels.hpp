@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void update_clip_kernel(float* __restrict__ w,
     });
 }
 
-// Sec. 2.3, gradient-norm clipping, in two launches whose order of additions is fixed (reproducible bit for bit):
+// Sec. 2.3, gradient-norm clipping, in launches whose order of additions is fixed (reproducible bit for bit):
 // 256 workgroups each sum the squares of a fixed strided subset in fp64 (four sums per thread, one per element of a
 // 16-byte piece, then a tree over LDS) ...
 constexpr int kSumsqBlocks = 256, kSumsqThreads = 1024;
@@ -270,19 +270,28 @@ __global__ __launch_bounds__(kSumsqThreads) void sumsq_partial_kernel(const floa
     }
     if (threadIdx.x == 0) partial[blockIdx.x] = part[0];
 }
-// ... then every wave of the second launch adds the 256 partial sums in one and the same order (a third of a microsecond
-// instead of a launch of its own), the first one stores ||g||_2 as fp32, and every element is multiplied by
-// alpha / ||g||_2 if the norm is above alpha.
-template <bool VEC>
-__global__ __launch_bounds__(256) void scale_if_above_kernel(float* __restrict__ g, int64_t count, float alpha,
-                                                             const double* __restrict__ partial, float* __restrict__ norm_out) {
+// ... then the 256 partial sums are added, in one and the same order wherever that is done ...
+__device__ __forceinline__ float norm_of_partials(const double* partial) {
     const int lane = lane_id();
     static_assert(kSumsqBlocks == 4 * kWave, "four partial sums per lane");
     double sum = (partial[lane] + partial[lane + 64]) + (partial[lane + 128] + partial[lane + 192]);
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, kWave);
-    const float nrm = (float)sqrt(sum);
-    if (blockIdx.x == 0 && threadIdx.x == 0) norm_out[0] = nrm;
+    return (float)sqrt(sum);
+}
+// ... by one wave in a launch of its own where norm_out lies among the partial sums (nothing may read them once it is stored) ...
+__global__ __launch_bounds__(kWave) void sumsq_final_kernel(const double* partial, float* norm_out) {
+    const float nrm = norm_of_partials(partial);
+    if (threadIdx.x == 0) norm_out[0] = nrm;
+}
+// ... otherwise by every wave of the second launch (a third of a microsecond instead of a launch), the first one storing
+// ||g||_2 as fp32; and every element is multiplied by alpha / ||g||_2 if the norm is above alpha.  partial: nullptr if
+// norm_out holds the norm already.
+template <bool VEC>
+__global__ __launch_bounds__(256) void scale_if_above_kernel(float* __restrict__ g, int64_t count, float alpha,
+                                                             const double* __restrict__ partial, float* __restrict__ norm_out) {
+    const float nrm = partial ? norm_of_partials(partial) : norm_out[0];
+    if (partial && blockIdx.x == 0 && threadIdx.x == 0) norm_out[0] = nrm;
     if (!(nrm > alpha)) return;
     const float factor = alpha / nrm;
     for_each_element<VEC>(count, [&](int64_t e, auto n) {

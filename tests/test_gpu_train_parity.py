@@ -316,6 +316,18 @@ def test_grad_norm_clip(G, bnn, T, count, alpha):
         assert abs(np.linalg.norm(got.astype(np.float64)) - alpha) <= 1e-4 * alpha
 
 
+@pytest.mark.parametrize("count", [3, 1024 * 1024 * 4 + 5])
+@pytest.mark.parametrize("at", [0, 4, 1024, 2044])
+def test_grad_norm_clip_with_the_norm_inside_the_workspace(G, bnn, count, at):
+    """norm_out among the 2048 bytes of partial sums: the same bits as with a float of its own."""
+    g = G.to_dev((np.random.default_rng(count).standard_normal(count) * 20.0).astype(np.float32))
+    want, norm, ws = g.clone(), _f32(1, 1), torch.empty(2048, dtype=torch.uint8, device="cuda:0")
+    bnn.bnn_grad_norm_clip(G.ptr(want), count, 15.0, G.ptr(ws), G.ptr(norm), G.stream())
+    bnn.bnn_grad_norm_clip(G.ptr(g), count, 15.0, G.ptr(ws), G.ptr(ws) + at, G.stream())
+    assert torch.equal(ws[at:at + 4].view(torch.float32), norm.view(-1)) and float(norm) > 15.0
+    assert torch.equal(g, want)
+
+
 def test_semi_stochastic_binarize(G, bnn, T):
     rng = np.random.default_rng(9)
     w = rng.uniform(-1, 1, 500003).astype(np.float32)
