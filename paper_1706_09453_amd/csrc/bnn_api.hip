@@ -572,19 +572,11 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     }
     const size_t lds = realx_dynamic_lds(Ki, kpad, w32, nb);
     const dim3 grid((Mi + kRealxBM - 1) / kRealxBM, (Ni + nb - 1) / nb), block(kRealxThreads);
-    // More than 64 KB of LDS per workgroup has to be requested explicitly (gfx950 has 160 KB per CU).
-    static std::atomic<size_t> granted_vec{48 * 1024}, granted_scalar{48 * 1024};
+    // (the LDS of a launch depends on nb, and so on the batch; what is allowed covers every K and nb)
+    static std::atomic<uint64_t> allowed[2];
+    constexpr unsigned most = (unsigned)realx_dynamic_lds(kRealxMfmaMaxK, (kRealxMfmaMaxK + 63) / 64 * 64, (kRealxMfmaMaxK + 63) / 64 * 2, kRealxMaxNB);
     const bool vec16 = aligned(Wp, 16);   // chunks start at multiples of 512 rows: 16-byte aligned whenever the matrix is
-    std::atomic<size_t>& granted = vec16 ? granted_vec : granted_scalar;
-    if (lds > granted.load()) {
-        const void* fn = vec16 ? reinterpret_cast<const void*>(realx_sign_fused_kernel<true>)
-                               : reinterpret_cast<const void*>(realx_sign_fused_kernel<false>);
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-            (void)hipGetLastError();
-            return BNN_EDEVICE;
-        }
-        granted.store(lds);
-    }
+    if (!allow_lds(vec16 ? &realx_sign_fused_kernel<true> : &realx_sign_fused_kernel<false>, most, allowed[vec16])) return BNN_EDEVICE;
     if (vec16)
         realx_sign_fused_kernel<true><<<grid, block, lds, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, kpad,
                                                                Ni, nb, w32, static_cast<uint32_t*>(Y), yw32);
@@ -616,16 +608,8 @@ int run_realx_sign_slab(const float* X, const void* Wp, const float* scale, cons
         realx_quantize_kernel<false><<<dim3((Mi + 3) / 4), dim3(256), 0, st>>>(X, Mi, Ki, kpad, slab_quant_bits(Ki), planes, meta);
     const size_t lds = slab_dynamic_lds();
     const bool vec16 = aligned(Wp, 16) && (w32 % 4 == 0);
-    static std::atomic<int> granted[2] = {{0}, {0}};   // more than 64 KB of LDS per workgroup has to be requested explicitly
-    if (!granted[vec16].load()) {
-        const void* fn = vec16 ? reinterpret_cast<const void*>(realx_sign_slab_kernel<true>)
-                               : reinterpret_cast<const void*>(realx_sign_slab_kernel<false>);
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-            (void)hipGetLastError();
-            return BNN_EDEVICE;
-        }
-        granted[vec16].store(1);
-    }
+    static std::atomic<uint64_t> allowed[2];
+    if (!allow_lds(vec16 ? &realx_sign_slab_kernel<true> : &realx_sign_slab_kernel<false>, (unsigned)lds, allowed[vec16])) return BNN_EDEVICE;
     const dim3 grid((Mi + kRealxBM - 1) / kRealxBM, (Ni + kSlabNB - 1) / kSlabNB), block(kSlabThreads);
     if (vec16)
         realx_sign_slab_kernel<true><<<grid, block, lds, st>>>(X, planes, meta, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki,
@@ -655,16 +639,8 @@ int run_realx_i8_lsm(const float* X, const void* Wp, const float* scale, const f
     realx_quantize4_kernel<<<dim3((Mi + 3) / 4), dim3(256), 0, st>>>(X, Mi, Ki, kpad, planes, meta);
     const size_t lds = slab4_dynamic_lds();
     const bool vec16 = aligned(Wp, 16) && (w32 % 4 == 0);
-    static std::atomic<int> granted[2] = {{0}, {0}};
-    if (!granted[vec16].load()) {
-        const void* fn = vec16 ? reinterpret_cast<const void*>(realx_i8_linear_kernel<true>)
-                               : reinterpret_cast<const void*>(realx_i8_linear_kernel<false>);
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-            (void)hipGetLastError();
-            return BNN_EDEVICE;
-        }
-        granted[vec16].store(1);
-    }
+    static std::atomic<uint64_t> allowed[2];
+    if (!allow_lds(vec16 ? &realx_i8_linear_kernel<true> : &realx_i8_linear_kernel<false>, (unsigned)lds, allowed[vec16])) return BNN_EDEVICE;
     const dim3 grid((Mi + kRealxBM - 1) / kRealxBM, (Ni + kSlabNB - 1) / kSlabNB), block(kSlabThreads);
     if (vec16)
         realx_i8_linear_kernel<true><<<grid, block, lds, st>>>(X, planes, meta, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki,
@@ -704,16 +680,8 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     launch_split(W, N, Ki, kpad, ws, st);
     const unsigned lds = split_dynamic_lds();
     const int eight = g_realw_split_lsm.load() == 2;   // 4 x 2 waves of 64 x 64 (two per SIMD) instead of 2 x 2 waves of 128 x 64
-    static std::atomic<int> granted[2] = {{0}, {0}};   // more than 64 KB of LDS per workgroup has to be requested explicitly
-    if (!granted[eight].load()) {
-        const void* fn = eight ? reinterpret_cast<const void*>(realw_bf16x3_kernel<ACT_LINEAR, 8>)
-                               : reinterpret_cast<const void*>(realw_bf16x3_kernel<ACT_LINEAR, 4>);
-        if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-            (void)hipGetLastError();
-            return BNN_EDEVICE;
-        }
-        granted[eight].store(1);
-    }
+    static std::atomic<uint64_t> allowed[2];
+    if (!allow_lds(eight ? &realw_bf16x3_kernel<ACT_LINEAR, 8> : &realw_bf16x3_kernel<ACT_LINEAR, 4>, lds, allowed[eight])) return BNN_EDEVICE;
     const dim3 grid((unsigned)((Mi + kSplitTileM - 1) / kSplitTileM), (unsigned)((Ni + kSplitTileN - 1) / kSplitTileN));
     if (eight) realw_bf16x3_kernel<ACT_LINEAR, 8><<<grid, 512, lds, st>>>(xs, ws, bias, Mi, kpad, Ni, Y);
     else realw_bf16x3_kernel<ACT_LINEAR, 4><<<grid, 256, lds, st>>>(xs, ws, bias, Mi, kpad, Ni, Y);
@@ -771,15 +739,8 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
         realx_quantize_nat_kernel<D, false><<<dim3((Mi + 3) / 4), dim3(256), 0, st>>>(X, Mi, Ki, kpad, qbits, planes, meta);
     const int64_t eb = ((int64_t)Ni * (kpad / 16) + 255) / 256;
     bits_to_bytes_kernel<<<(unsigned)(eb < 16384 ? eb : 16384), 256, 0, st>>>(static_cast<const uint32_t*>(Wp), Ni, Ki, w32, kpad, bytes);
-    static std::atomic<int> granted{0};   // more than 64 KB of LDS per workgroup has to be requested explicitly
-    if (!granted.load()) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(realx_i8_gemm_kernel<D>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)i8_gemm_lds(D)) != hipSuccess) {
-            (void)hipGetLastError();
-            return BNN_EDEVICE;
-        }
-        granted.store(1);
-    }
+    static std::atomic<uint64_t> allowed;
+    if (!allow_lds(&realx_i8_gemm_kernel<D>, (unsigned)i8_gemm_lds(D), allowed)) return BNN_EDEVICE;
     const dim3 grid((unsigned)((Mi + kI8TileM - 1) / kI8TileM), (unsigned)((Ni + kI8TileN - 1) / kI8TileN));
     realx_i8_gemm_kernel<D><<<grid, kI8Threads, i8_gemm_lds(D), st>>>(planes, bytes, meta, X, static_cast<const uint32_t*>(Wp), scale, bias,
                                                                       Mi, Ki, kpad, Ni, w32, Y, yw32, D == 3 ? undecided : nullptr);

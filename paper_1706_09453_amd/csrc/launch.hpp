@@ -10,15 +10,20 @@ namespace bnn {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 
-// Dynamic LDS above 64 KiB has to be allowed once per kernel and device.
+// Dynamic LDS above 64 KiB has to be allowed once per kernel and device.  `bytes` is the most the kernel ever asks for and
+// the same in every call, so threads that get here together all set the same value.  false: refused.
 template <class Kernel>
-void allow_lds(Kernel kernel, unsigned bytes, std::atomic<uint64_t>& allowed) {
+bool allow_lds(Kernel kernel, unsigned bytes, std::atomic<uint64_t>& allowed) {
     int dev = 0;
     (void)hipGetDevice(&dev);
-    const uint64_t bit = 1ull << (dev & 63);
-    if (allowed.load(std::memory_order_relaxed) & bit) return;
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    const uint64_t bit = dev >= 0 && dev < 64 ? 1ull << dev : 0;   // (devices past 64: asked for every time)
+    if (allowed.load(std::memory_order_relaxed) & bit) return true;
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
     allowed.fetch_or(bit);
+    return true;
 }
 
 // Ascending-k fp32 sums on the matrix cores (f32_chain.hip); arguments already checked.

@@ -58,3 +58,55 @@ for norm in (B, B + 4, B + 2044, B + 2048, C):
         assert len(kernels) == 3 and "sumsq_partial" in kernels[0] and "sumsq_final" in kernels[1] and "scale_if_above" in kernels[2], kernels
     for kernels in got[3:]:
         assert len(kernels) == 2 and "sumsq_partial" in kernels[0] and "scale_if_above" in kernels[1], kernels
+
+
+FORWARD = """
+def forward(M, dims=(440, 2048), acts=(bnn.BNN_ACT_SIGN,), real=(), out=D):
+    d, binary = [], 0
+    for l, a in enumerate(acts):
+        d.append(dict(K=dims[l], N=dims[l + 1], act=a, word_bits=32, x_is_binary=binary, w_is_real=l in real, Wp=B + l * 0x10000000,
+                      scale=0 if l in real else C, bias=C))
+        binary = int(a == bnn.BNN_ACT_SIGN)
+    arr = bnn.make_layer_array(d)
+    bnn.bnn_forward(arr, len(d), A, M, out, E, bnn.bnn_forward_workspace_bytes(arr, len(d), M), 0)
+"""
+
+
+def test_lds_is_allowed_on_every_device(host):
+    """Dynamic LDS above 64 KiB is allowed per device: a second device is asked too, whichever kernel it is."""
+    got = host(FORWARD + """
+Z, H, S, G = bnn.BNN_ACT_LOGSOFTMAX, bnn.BNN_ACT_HARDTANH, bnn.BNN_ACT_SIGN, bnn.BNN_ACT_SIGMOID
+for dev in (0, 1, 70, 6):
+    stub.stub_set_device(dev)
+    for M in (100, 333, 4096):
+        forward(M)                                                   # first layer, Sign
+        forward(M, (440, 2048, 2048, 3400), (G, S, Z))               # real inputs further on, real outputs
+        forward(M, (440, 2048, 3400), (H, Z))
+        forward(M, (440, 2048, 3400), (G, Z), real=(0, 1))           # real weights
+    for opt, v in ((bnn.BNN_OPT_REALX_SIGN_MFMA, 2), (bnn.BNN_OPT_REALX_I8_LOGSOFTMAX, 2), (bnn.BNN_OPT_REALW_SPLIT_LOGSOFTMAX, 2)):
+        bnn.bnn_set_option(opt, v)
+        forward(333, (440, 2048, 2048, 3400), (G, S, Z))
+        forward(333, (440, 2048, 3400), (H, Z))
+        forward(333, (440, 2048, 3400), (G, Z), real=(0, 1))
+        bnn.bnn_set_option(opt, 1)
+result = launches()
+""")
+    assert {l["device"] for l in got if l["lds"] > 65536} == {0, 1, 70, 6}
+    assert not [l for l in got if l["wrong"]]
+
+
+def test_lds_of_two_batch_sizes_at_once(host):
+    """The first layer's LDS depends on the batch: two threads that ask for it at the same time both get what they need."""
+    got = host(FORWARD + """
+first = threading.Thread(target=forward, args=(4096,))    # all 2048 outputs in one workgroup: the most LDS
+stub.stub_hold_next_grant()
+first.start()
+import time
+time.sleep(0.2)
+forward(333, out=D + 0x10000000)
+first.join()
+forward(4096)
+result = launches()
+""")
+    assert len(got) == 3 and len({l["lds"] for l in got}) == 2 and min(l["lds"] for l in got) > 65536
+    assert not [l for l in got if l["wrong"]]
