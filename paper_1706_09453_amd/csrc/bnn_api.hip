@@ -1104,8 +1104,15 @@ BNN_EXPORT int bnn_bias_grad(const float* g_hhat, int64_t M, int64_t N, float* g
     if (!g_hhat || !g_r) return BNN_EINVAL;
     if (!aligned(g_hhat, 4) || !aligned(g_r, 4)) return BNN_EALIGN;
     if (overlap(g_hhat, (size_t)M * N * 4, g_r, (size_t)N * 4)) return BNN_EINVAL;
-    const unsigned blocks = (unsigned)((N + kColsumCols - 1) / kColsumCols);
     hipStream_t st = static_cast<hipStream_t>(stream);
+    // Slabs through LDS up to three workgroups of 16 columns per CU; beyond that one wave per 64 columns, which also keeps the
+    // grid of 2^30 columns in range.  Measured, slabs against waves: 4096 x 8192 40 and 56 us, 1000 x 12000 16.4 and 18.9,
+    // 300 x 12000 6.0 and 5.7, 300 x 16384 8.9 and 5.5, 4096 x 16384 81 and 61, 16 x 20000 4.6 and 3.5.
+    if (N > kColsumMaxCols) {
+        colsum_wave_kernel<<<(unsigned)((N + kWave - 1) / kWave), kWave, 0, st>>>(g_hhat, (int)M, (int)N, g_r);
+        return launch_status();
+    }
+    const unsigned blocks = (unsigned)((N + kColsumCols - 1) / kColsumCols);
     if (N % 4 == 0 && aligned(g_hhat, 16)) colsum_kernel<true><<<blocks, 256, 0, st>>>(g_hhat, (int)M, (int)N, g_r);
     else colsum_kernel<false><<<blocks, 256, 0, st>>>(g_hhat, (int)M, (int)N, g_r);
     return launch_status();

@@ -145,6 +145,7 @@ __global__ __launch_bounds__(256) void sigmoid_grad_kernel(const float* g_h, con
 // In LDS a column's rows lie side by side, so the adding lanes read four rows at a time, 32 rows ahead of the additions
 // (a lone wave issues one vector instruction per 2.6 ns, and the chain should be all it issues).
 constexpr int kColsumRows = 256, kColsumCols = 16, kColsumLd = kColsumRows + 4;
+constexpr int64_t kColsumMaxCols = 3 * 256 * kColsumCols;   // wider matrices: colsum_wave_kernel
 template <bool VEC>
 __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ g, int M, int N, float* __restrict__ out) {
     __shared__ __attribute__((aligned(16))) float slab[2][kColsumCols][kColsumLd];
@@ -214,6 +215,25 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ g
         __syncthreads();
     }
     if (tid < kColsumCols && n0 + tid < N) out[n0 + tid] = sum;
+}
+
+// The same sums, one wave per 64 columns (lanes <-> n: every row is read coalesced, 32 rows requested at a time, the
+// additions in order).  Where the columns alone fill the chip the slabs' way through LDS only costs: the
+// rule is in bnn_bias_grad.  Grid: ceil(N / 64), one wave per workgroup.
+__global__ __launch_bounds__(kWave) void colsum_wave_kernel(const float* __restrict__ g, int M, int N, float* __restrict__ out) {
+    const int n = (int)blockIdx.x * kWave + (int)threadIdx.x;
+    if (n >= N) return;
+    float s = 0.0f;
+    int m = 0;
+    for (; m + 32 <= M; m += 32) {
+        float v[32];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) v[i] = g[(size_t)(m + i) * N + n];
+#pragma unroll
+        for (int i = 0; i < 32; ++i) s = s + v[i];
+    }
+    for (; m < M; ++m) s = s + g[(size_t)m * N + n];
+    out[n] = s;
 }
 
 // Alg. 1 Update: w <- Clip(w - eta g) with Clip to [-1, +1] (Sec. 2.1); clip == 0: the plain update.  One fma.

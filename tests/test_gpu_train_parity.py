@@ -254,9 +254,11 @@ def test_backward_products_on_the_int8_matrix_cores(G, bnn, oracle, T, M, N, K):
     assert np.all(np.abs(gw - exact_w) <= M * 2.0 ** -27 * np.abs(g64).max(0)[:, None] + 2.0 ** -23 * np.abs(exact_w))
 
 
-@pytest.mark.parametrize("M,N", [(1, 1), (255, 15), (256, 16), (257, 33), (513, 68), (1030, 20)])
+@pytest.mark.parametrize("M,N", [(1, 1), (255, 15), (256, 16), (257, 33), (513, 68), (1030, 20), (300, 12288), (1, 12289), (33, 12289),
+                                 (70, 20000)])
 def test_bias_grad_slabs(G, bnn, T, M, N):
-    """Column sums at the edges of the 256-row slabs and of the 16-column workgroups, rows 16-byte aligned or not."""
+    """Column sums at the edges of the 256-row slabs and of the 16-column workgroups, rows 16-byte aligned or not; with more
+    than 12288 columns at the edges of the 32 rows that one wave per 64 columns requests at a time."""
     g = np.random.default_rng(M * N).standard_normal((M, N)).astype(np.float32)
     out = _f32(1, N)
     dg = G.to_dev(g)

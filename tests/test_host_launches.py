@@ -110,3 +110,18 @@ result = launches()
 """)
     assert len(got) == 3 and len({l["lds"] for l in got}) == 2 and min(l["lds"] for l in got) > 65536
     assert not [l for l in got if l["wrong"]]
+
+
+def test_bias_grad_grids(host):
+    """The sums of a wide matrix take one wave per 64 columns, and every width up to 2^30 columns has a grid that the
+    runtime accepts."""
+    got = host("""
+bnn.bnn_bias_grad(A, 4096, 12288, D)
+for M, N in ((1, 12289), (64, 20000), (1, 1 << 28), (1, (1 << 30) - 1), (1, 1 << 30)):
+    bnn.bnn_bias_grad(A, M, N, D)
+result = launches()
+""")
+    assert "colsum_kernel" in got[0]["kernel"] and got[0]["grid"][0] == 768
+    for l in got[1:]:
+        assert "colsum_wave_kernel" in l["kernel"] and l["block"] == 64 and not l["wrong"]
+    assert [l["grid"][0] for l in got[1:3]] == [193, 313]
