@@ -87,11 +87,18 @@ __device__ __forceinline__ void store_few(float* p, const Few<N>& r) {
 }
 
 // Alg. 1/2: gradient of the summed cross entropy through the Softmax layer, g[m][n] = exp(logp[m][n]) - (n == label[m]),
-// evaluated in fp64 from the fp32 log-posteriors and rounded once.  A workgroup takes whole frames.  VEC: N % 4 == 0,
-// arrays 16-byte aligned.  g may be logp itself.
+// evaluated in fp64 from the fp32 log-posteriors and rounded once.  g may be logp itself.  VEC: N % 4 == 0, arrays 16-byte
+// aligned.
+__device__ __forceinline__ float softmax_xent_grad_of(float logp, bool is_label) {
+    const float z = logp < -1000.0f ? -1000.0f : (logp > 1000.0f ? 1000.0f : logp);   // exp is 0 / inf beyond
+    const double p = exp_f64((double)z);
+    return (float)(is_label ? p - 1.0 : p);
+}
+
+// Many frames of many classes: a workgroup takes whole frames.
 template <bool VEC>
-__global__ __launch_bounds__(256) void softmax_xent_grad_kernel(const float* logp, const int32_t* __restrict__ labels,
-                                                                int64_t M, int N, float* g) {
+__global__ __launch_bounds__(256) void softmax_xent_grad_rows_kernel(const float* logp, const int32_t* __restrict__ labels,
+                                                                     int64_t M, int N, float* g) {
     const std::integral_constant<int, VEC ? 4 : 1> few;
     for (int64_t m = blockIdx.x; m < M; m += gridDim.x) {
         const int label = labels[m];
@@ -99,14 +106,26 @@ __global__ __launch_bounds__(256) void softmax_xent_grad_kernel(const float* log
         for (int n = (int)threadIdx.x * few.value; n < N; n += 256 * few.value) {
             Few<few.value> r = load_few(logp + m * N + n, few);
 #pragma unroll
-            for (int i = 0; i < few.value; ++i) {
-                const float z = r.v[i] < -1000.0f ? -1000.0f : (r.v[i] > 1000.0f ? 1000.0f : r.v[i]);   // exp is 0 / inf beyond
-                const double p = exp_f64((double)z);
-                r.v[i] = (float)(n + i == label ? p - 1.0 : p);
-            }
+            for (int i = 0; i < few.value; ++i) r.v[i] = softmax_xent_grad_of(r.v[i], n + i == label);
             store_few(g + m * N + n, r);
         }
     }
+}
+
+// Any other shape: threads take elements (VEC: four consecutive ones, all of one frame) of the whole matrix and find the
+// frame by a division.  With a workgroup per frame, few classes leave its threads and few frames the chip idle.
+// I: type that holds M N.
+template <bool VEC, class I>
+__global__ __launch_bounds__(256) void softmax_xent_grad_kernel(const float* logp, const int32_t* __restrict__ labels,
+                                                                int64_t M, int N, float* g) {
+    for_each_element<VEC>(M * N, [&](int64_t e, auto few) {
+        const I m = (I)e / (I)N;
+        const int n = (int)((I)e - m * (I)N), label = labels[m];
+        auto r = load_few(logp + e, few);
+#pragma unroll
+        for (int i = 0; i < few.value; ++i) r.v[i] = softmax_xent_grad_of(r.v[i], n + i == label);
+        store_few(g + e, r);
+    });
 }
 
 // Sec. 2.2: g_{h^} = g_h (.) Mask(h^, k); Mask = 0 where |h^| > k, 1 otherwise.  out may be g_h itself.

@@ -55,7 +55,8 @@ def test_transpose(G, bnn, R, C):
     assert np.array_equal(out.cpu().numpy(), A.T)
 
 
-@pytest.mark.parametrize("M,N", [(1, 1), (7, 10), (64, 3307), (300, 1000)])
+@pytest.mark.parametrize("M,N", [(1, 1), (7, 10), (64, 3307), (300, 1000), (5, 4), (3001, 3), (70000, 1), (1, 70004), (2, 70001),
+                                 (1023, 512), (1024, 511), (1024, 512), (1030, 701)])
 def test_softmax_xent_grad(G, bnn, T, M, N):
     rng = np.random.default_rng(M + N)
     z = rng.standard_normal((M, N)) * 3

@@ -125,3 +125,13 @@ result = launches()
     for l in got[1:]:
         assert "colsum_wave_kernel" in l["kernel"] and l["block"] == 64 and not l["wrong"]
     assert [l["grid"][0] for l in got[1:3]] == [193, 313]
+
+
+def test_softmax_gradient_spreads_elements_over_the_chip(host):
+    """Few classes or few frames: as many threads as there are elements (or groups of four), not a workgroup per frame."""
+    got = host("""
+for M, N, off in ((50000, 4, 0), (1, 100000, 0), (16, 3400, 0), (50000, 10, 0), (1, 100000, 4), (4096, 3400, 0)):
+    bnn.bnn_softmax_xent_grad(A + off, B, M, N, C)
+result = launches()
+""")
+    assert [l["grid"][0] for l in got] == [196, 98, 54, 1954, 391, 4096] and all(l["block"] == 256 for l in got)
