@@ -536,11 +536,18 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
 
 int run_pack(const float* X, int64_t rows, int64_t K, int wb, void* out, hipStream_t st) {
     if (rows == 0) return BNN_OK;
-    const int64_t tasks = rows * ((K + kPackElems - 1) / kPackElems);
-    int64_t blocks = (tasks + 3) / 4;
-    if (blocks > 65536 * 4) blocks = 65536 * 4;
-    pack_sign_kernel<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(X, rows, K, row_w32(K, wb),
-                                                                    static_cast<uint32_t*>(out));
+    uint32_t* words = static_cast<uint32_t*>(out);
+    auto go = [&](auto ballots) {
+        constexpr int B = decltype(ballots)::value;
+        const int64_t tasks = rows * ((K + 64 * B - 1) / (64 * B));
+        int64_t blocks = (tasks + 3) / 4;
+        if (blocks > 65536 * 4) blocks = 65536 * 4;
+        pack_sign_kernel<B><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(X, rows, K, row_w32(K, wb), words);
+    };
+    if (K <= 64) go(std::integral_constant<int, 1>{});
+    else if (K <= 128) go(std::integral_constant<int, 2>{});
+    else if (K <= 256) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 8>{});
     return launch_status();
 }
 

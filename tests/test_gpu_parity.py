@@ -96,7 +96,7 @@ def _rand_layer(seed, M, K, N):
 
 @pytest.mark.parametrize("wb", [32, 64])
 @pytest.mark.parametrize("rows,K", [(1, 1), (3, 31), (5, 32), (7, 33), (4, 63), (4, 64), (9, 65), (64, 440),
-                                    (33, 2048), (2, 3307), (130, 1000)])
+                                    (33, 2048), (2, 3307), (130, 1000), (5, 128), (6, 129), (7, 256), (8, 257), (20000, 40)])
 def test_pack_activations_bit_exact(G, oracle, rows, K, wb):
     rng = np.random.default_rng(rows * 1000 + K)
     X = rng.standard_normal((rows, K)).astype(np.float32)

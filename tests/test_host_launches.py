@@ -135,3 +135,15 @@ for M, N, off in ((50000, 4, 0), (1, 100000, 0), (16, 3400, 0), (50000, 10, 0), 
 result = launches()
 """)
     assert [l["grid"][0] for l in got] == [196, 98, 54, 1954, 391, 4096] and all(l["block"] == 256 for l in got)
+
+
+def test_packing_takes_no_more_per_wave_than_a_row_holds(host):
+    """64, 128, 256 or 512 numbers of a row per wave: short rows do not load theirs several times over."""
+    got = host("""
+for K in (1, 64, 65, 128, 129, 256, 257, 2048):
+    bnn.bnn_pack_activations(A, 4096, K, 32, D)
+result = launches()
+""")
+    ballots = [int(l["kernel"].split("pack_sign_kernelILi")[1].split("E")[0]) for l in got]
+    assert ballots == [1, 1, 2, 2, 4, 4, 8, 8]
+    assert [l["grid"][0] for l in got] == [1024] * 7 + [4096]
