@@ -8,7 +8,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libbnn_hip.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("bnn_api.hip", "f32_chain.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("bnn_api.hip", "f32_chain_bits.hip", "f32_chain_real.hip")]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-fvisibility=hidden",

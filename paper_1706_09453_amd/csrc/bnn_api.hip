@@ -188,11 +188,20 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
     const bool few = M <= g_stream_max_frames.load();   // batches of a few frames (streaming): always the chains
     // Up to 16 of them on the vector ALU with one frame per workgroup: a lone wave takes 6.7 ns per k there, the chain of
-    // matrix instructions 8.2 (16 x 2048 x 2048 14.5 against 17.6 us, 16 x 440 x 2048 4.8 against 6.3); rows that are no
-    // multiple of 16 bytes cost the vector ALU a load per k (16 x 2047 x 2048 22.0 against 17.8), which short rows hide
-    // (16 x 441 x 2048 6.4 both).  From 17 frames on the workgroups share the CUs and the matrix cores win (see launch_chain_act).
-    const bool valu = M <= 16 && (K < 1024 || ((K & 3) == 0 && aligned(X, 16)));
-    const int tm = few ? (valu ? 1 : 0) : g_realx_tm.load();
+    // matrix instructions 7.4 (16 x 2048 x 2048 14.5 against 15.1 us, 16 x 440 x 2048 4.8 against 5.2); rows that are no
+    // multiple of 16 bytes cost the vector ALU a load per k, which only short rows hide (16 x 143 x 1000 3.7 against 3.9 us,
+    // 16 x 429 x 1000 5.8 against 5.2, 16 x 2047 x 1000 20.7 against 15.0).  From 17 frames on the workgroups share the CUs and the matrix cores win (see
+    // launch_chain_act).
+    const bool rows_vec = (K & 3) == 0 && aligned(X, 16);
+    const bool valu = M <= 16 && (K < 256 || rows_vec);
+    int tm = few ? (valu ? 1 : 0) : g_realx_tm.load();
+    // Rows of a few numbers that are no multiple of 16 bytes, in more tiles of 16 x 64 than the chip holds: the vector ALU with 4
+    // frames per workgroup, 8 in large batches, while the bits of a row end in its first eight or little behind its first word
+    // (4096 x 5 x 4096 26.7 us, 43 on the matrix cores; 4096 x 33 x 4096 30 and 45, x 39 40 and 47; but x 17 55 and 47, x 43 48
+    // and 49; 1000 x 37 x 1000 5.2 us with 4 frames, 6.5 with 8, 5.8 on the matrix cores).
+    if (!few && tm == 0 && !rows_vec && (K <= 8 || (K > 32 && K <= 40)) && N > 128 && ((M + 15) / 16) * ((N + 63) / 64) > 256 &&
+        g_realx_f32_mfma.load() != 1)
+        tm = ((M + 7) / 8) * ((N + 255) / 256) >= 2048 ? 8 : 4;
     if (tm == 0) {
         launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st}, act, few);
         if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);

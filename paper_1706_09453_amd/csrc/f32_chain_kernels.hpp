@@ -17,8 +17,9 @@
 // t: one LDS instruction brings the operands of two steps, and with rows KC + 4 numbers apart its 64 lanes (16 rows, four
 // neighbours each) read 64 different banks.
 // Measured at 4096 x 2048 x 2048: binary weights 261 us = 132 TFLOP/s, real weights 272 us (vector-ALU kernels: 331 us,
-// and 290 with real weights); at 256 x 2048 x 2048 27 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.  What is left to 153 TFLOP/s (register-only loop of
-// the same MFMA): the sign-building and LDS instructions of the staging, and the first and last chunk of a workgroup.
+// and 290 with real weights); at 256 x 2048 x 2048 27 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.
+// What is left to 153 TFLOP/s (register-only loop of the same MFMA): the sign-building and LDS instructions of the staging,
+// and the first and last chunk of a workgroup.
 // Columns past K are stored as 0 in the frames (and real weights): fma(w, 0, acc) returns acc (an accumulator that starts
 // at +0 is never -0), so the sum over k < K is unchanged.
 #pragma once
@@ -33,11 +34,13 @@ typedef float f32x4c __attribute__((ext_vector_type(4)));
 
 // VEC: K % 4 == 0, X (and real weights) 16-byte aligned; otherwise element loads.  WREAL: Wv is fp32 [N][K]; otherwise
 // packed bits [N][w32].  ACT: ACT_LINEAR, ACT_HARDTANH, ACT_SIGMOID or ACT_SIGN.
+// SKIP: the last chunk ends behind the last group of 16 columns that K reaches; otherwise it is multiplied to its end, without
+// a branch between its groups (3 % faster at 2500 x 440 x 2048, where there is nothing to leave out).
 // Grid: x = tiles of TM = 16 FM WR frames, y = tiles of TN = 64 FN / WR outputs (Sign: enough for yw32 words);
 // block = 256 threads; dynamic LDS = f32_chain_lds(TM, TN, KC).
 constexpr unsigned f32_chain_lds(int TM, int TN, int KC) { return 2u * (unsigned)(TM + TN) * (unsigned)(KC + 4) * 4u; }
 
-template <int FM, int FN, int WR, int KC, int ACT, bool WREAL, bool VEC>
+template <int FM, int FN, int WR, int KC, int ACT, bool WREAL, bool VEC, bool SKIP>
 __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict__ X, const void* __restrict__ Wv,
                                                         const float* __restrict__ scale, const float* __restrict__ bias, int M, int K,
                                                         int N, int w32, void* __restrict__ Y, int yw32) {
@@ -178,6 +181,7 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
         constexpr int kMfma = 4 * FM * FN;
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
+            if (SKIP && !kStore && s > 0 && c * KC + 16 * s >= K) break;
             const bool turn = s == NS - 1;      // the next operands come from the next chunk
             if (turn) {
                 if (!kStore) {                  // last chunk: nothing follows

@@ -26,7 +26,7 @@ bool allow_lds(Kernel kernel, unsigned bytes, std::atomic<uint64_t>& allowed) {
     return true;
 }
 
-// Ascending-k fp32 sums on the matrix cores (f32_chain.hip); arguments already checked.
+// Ascending-k fp32 sums on the matrix cores (f32_chain_launch.hpp); arguments already checked.
 struct ChainArgs {
     const float* X;
     const void* W;   // packed bits, or fp32 with real weights

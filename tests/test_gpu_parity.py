@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import workloads
+from chain_sizes import CHAIN_TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -525,13 +526,12 @@ def test_realx_against_fp64_shadow(G, bnn, oracle):
 
 
 @pytest.mark.parametrize("act", ["sign", "linear"])
-@pytest.mark.parametrize("M,K,N", [(4097, 36, 2050), (4097, 33, 2050), (4096, 64, 2048),   # 256 x 128 tiles; K that is no multiple of 4
-                                   (2049, 100, 2100), (1100, 32, 1300),                    # 128 x 128, 64 x 64
-                                   (65, 4, 33), (65, 128, 65), (80, 132, 1), (129, 260, 70), (65, 516, 40),  # 32 x 64; 1 to 5 chunks of K
-                                   (1, 4, 33), (16, 33, 2050), (17, 128, 65), (48, 260, 1), (63, 511, 70), (64, 516, 40)])  # 16 x 64
-def test_ascending_sums_on_the_matrix_cores(G, bnn, oracle, M, K, N, act):
-    """Binary and real weights, real input: every workgroup tile the dispatch can pick, ragged on both sides, K ending in
-    every part of a chunk.  The fp32 matrix cores fed in natural order give the bits of the oracle's chain."""
+@pytest.mark.parametrize("M,K,N", [s for s, _, _ in CHAIN_TILES])
+def test_ascending_sums_on_the_matrix_cores(G, bnn_defaults, oracle, M, K, N, act):
+    """Binary and real weights, real input: every workgroup tile the dispatch can pick (which size takes which tile is held
+    in chain_sizes.py and checked against the dispatch by test_host_launches.py).  The fp32 matrix cores fed in natural order
+    give the bits of the oracle's chain."""
+    bnn = bnn_defaults
     X, W, scale, bias = _rand_layer(M + K * 3 + N, M, K, N)
     Wr = (W * np.float32(np.sqrt(3.0 / K))).astype(np.float32)
     Wp = oracle.pack_sign(W, 64)

@@ -147,3 +147,48 @@ result = launches()
     ballots = [int(l["kernel"].split("pack_sign_kernelILi")[1].split("E")[0]) for l in got]
     assert ballots == [1, 1, 2, 2, 4, 4, 8, 8]
     assert [l["grid"][0] for l in got] == [1024] * 7 + [4096]
+
+
+def _chain_tile(kernel):
+    """256x128x32 and so on from the kernel's template arguments (FM, FN, WR, KC, ACT, WREAL, VEC, SKIP)."""
+    if "f32_chain_kernel" not in kernel:
+        return "valu" if "valu" in kernel else kernel
+    args = kernel.split("f32_chain_kernelI")[1].split("E")
+    fm, fn, wr, kc = (int(a[2:]) for a in args[:4])
+    real, vec, skip = (a[2:] == "1" for a in args[5:8])
+    return f"{16 * fm * wr}x{64 * fn // wr}x{kc}" + ("+" if skip else "") + ("" if vec else ":1")
+
+
+def test_every_tile_of_the_ascending_sums_is_among_the_tested_sizes(host):
+    """The sizes the GPU tests run take the tiles they are listed for, and no tile the dispatch picks anywhere in its range is
+    missing among them."""
+    from chain_sizes import CHAIN_TILES
+    got = host("""
+sizes = %r
+result = []
+for M, K, N in sizes:
+    for real in (0, 1):
+        if real:
+            bnn.bnn_layer_realw(A, B, C, M, K, N, bnn.BNN_ACT_LINEAR, 32, D)
+        else:
+            bnn.bnn_layer_binw_realx(A, B, C, C, M, K, N, bnn.BNN_ACT_LINEAR, 32, D)
+        result.append(launches())
+seen = set()
+for M in (1, 16, 17, 64, 65, 100, 200, 333, 512, 777, 1000, 1500, 2048, 3000, 4096, 16384):
+    for K in (1, 4, 8, 16, 24, 31, 32, 33, 36, 48, 60, 64, 68, 100, 143, 429, 440, 1024, 2047, 2048):
+        for N in (1, 64, 100, 512, 1000, 1024, 2048, 3400, 4096, 30000):
+            bnn.bnn_layer_realw(A, B, C, M, K, N, bnn.BNN_ACT_LINEAR, 32, D)
+            bnn.bnn_layer_binw_realx(A, B, C, C, M, K, N, bnn.BNN_ACT_LINEAR, 32, D)
+for l in launches():
+    assert not l["wrong"], l
+    seen.add(l["kernel"])
+result = [result, sorted(seen)]
+""" % [s for s, _, _ in CHAIN_TILES])
+    per_size, seen = got
+    tested = set()
+    for i, (size, bits, real) in enumerate(CHAIN_TILES):
+        for launched, want in ((per_size[2 * i], bits), (per_size[2 * i + 1], real)):
+            assert len(launched) == 1 and _chain_tile(launched[0]["kernel"]) == want, (size, launched)
+            tested.add(launched[0]["kernel"])
+    chains = [k for k in seen if "f32_chain_kernel" in k]
+    assert len(chains) >= 16 and not set(chains) - tested
