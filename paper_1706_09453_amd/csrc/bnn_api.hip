@@ -390,6 +390,18 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
     // one: 600 x 2048 8.2 against 7.4, 1000 x 4096 23.2 against 12.2.
     const int64_t tiles1 = ((M + 31) / 32) * ((N + 127) / 128);
     const int mfma_shape = g_mfma_shape.load();
+    // Output layer on the 32x32x64 kernel: the product goes to memory as int16 (half the bytes of fp32 pre-activations), and
+    // the row kernel forms fma(scale, dot, bias) itself before the log-Softmax.
+    const bool i16 = act == BNN_ACT_LOGSOFTMAX && K < 32768 && N % 4 == 0 && N <= 8192 && aligned(Y, 16) &&
+                     (!scale || aligned(scale, 16)) && (!bias || aligned(bias, 16));
+    // Exceptions to the line at 256 tiles.  An output layer whose product is short gains more from the int16 hand-over than from
+    // the smaller tiles (K = 512: 1024 x 1000 outputs 8.8 us against 9.8, 1024 x 64 6.9 and 7.3; K = 1024: 1000 x 1000 9.9 and
+    // 10.6, but 512 x 512 8.1 and 7.8, 200 x 4096 10.8 and 9.9; K = 2048: 1000 x 512 9.7 and 8.9).  Integer dot products of
+    // fewer than 1024 frames whose rows are read word by word leave the 32x32x64 kernel more slowly than 64-row tiles of the
+    // 16x16x128 kernel (1000 x 64 x 3400 8.5 us and 7.5, x 700 11.1 and 10.3).
+    const bool al512 = rows16 && K % 512 == 0;
+    const bool short_lsm = i16 && al512 && M >= 512 && (K <= 512 || (K <= 1024 && tiles1 > 128));
+    const bool few_raw = act == BNN_ACT_RAW_I32 && !x01 && !al512 && M < 1024 && K < 1024 && tiles1 > 256;
     if (stream) {
         // Batches of a few frames (streaming): the matrix-core tiles would be nearly empty and a workgroup would
         // still walk all of K for its 64 or 128 rows.  The vector-ALU kernels with 1 or 2 frames per workgroup spread
@@ -444,13 +456,9 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         else
             binx_mfma_logsoftmax_kernel<32, 2><<<grid, block, 0, st>>>(A, B, scale, bias, Mi, Ki, Ni, w32, Yf, ab, bb);
         return launch_status();
-    } else if (mfma_shape == 32 || (x01 && mfma_shape == 16) || (mfma_shape == 0 && tiles1 > 256)) {
+    } else if (mfma_shape == 32 || (x01 && mfma_shape == 16) || (mfma_shape == 0 && (tiles1 > 256 || short_lsm) && !few_raw)) {
         // large batch: 32x32x64 MFMA, 128 x 64 (or 64 x 64) wave tiles
         const bool al = rows16 && (K % 512 == 0);
-        // Output layer: the product goes to memory as int16 (half the bytes of fp32 pre-activations), and the row
-        // kernel forms fma(scale, dot, bias) itself before the log-Softmax.
-        const bool i16 = act == BNN_ACT_LOGSOFTMAX && K < 32768 && N % 4 == 0 && N <= 8192 && aligned(Y, 16) &&
-                         (!scale || aligned(scale, 16)) && (!bias || aligned(bias, 16));
         if (i16) act = ACT_DOT_I16;
         const int64_t tiles_n4 = (N + 127) / 128, tiles4 = ((M + 255) / 256) * tiles_n4;
         // 128-row wave tiles expand fewer operand words per MAC; 64-row ones give twice the workgroups, which
@@ -514,7 +522,7 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
             else launch_binx_mfma32<4, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
         }
     } else {
-        const bool al = rows16 && (K % 512 == 0);
+        const bool al = rows16 && w32 % 16 == 0;   // whole super-steps of 512 bits, the pad bits among them
         const int wm = g_mfma_wm.load();
         auto go = [&](auto wmc, auto alc, auto z1) {
             launch_binx_mfma_wm<decltype(wmc)::value, decltype(alc)::value, decltype(z1)::value>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
@@ -525,8 +533,8 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         const std::true_type yes;
         const std::false_type no;
         if (x01) { if (al) go(WM1{}, yes, yes); else go(WM1{}, no, yes); }
-        else if (mfma_shape == 0) { if (al) go(WM1{}, yes, no); else go(WM1{}, no, no); }
-        else if (wm == 2) { if (al) go(WM2{}, yes, no); else go(WM2{}, no, no); }
+        else if (mfma_shape == 0 && !few_raw) { if (al) go(WM1{}, yes, no); else go(WM1{}, no, no); }
+        else if (mfma_shape != 0 && wm == 2) { if (al) go(WM2{}, yes, no); else go(WM2{}, no, no); }
         else { if (al) go(WM4{}, yes, no); else go(WM4{}, no, no); }
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), Mi, Ni, st);

@@ -1290,7 +1290,10 @@ def test_subtract_log_prior(G, bnn, oracle, M, N):
 @pytest.mark.parametrize("x01", [False, True])
 @pytest.mark.parametrize("act", ["sign", "raw", "logsoftmax"])
 @pytest.mark.parametrize("M,K,N", [(1, 512, 1), (31, 512, 127), (33, 1024, 129), (65, 2048, 64), (65, 700, 1001), (1000, 512, 1000),
-                                   (64, 2048, 4096), (1025, 512, 960)])
+                                   (64, 2048, 4096), (1025, 512, 960),
+                                   (512, 512, 36), (511, 512, 300), (1000, 1024, 520), (600, 512, 33),   # log-Softmax: int16 hand-over or not
+                                   (1000, 100, 1100), (1023, 700, 1030), (1000, 1024, 1030),             # int32 of up to 1000 frames in more than 256 tiles
+                                   (33, 1000, 129), (65, 500, 70), (40, 2040, 100), (17, 992, 65)])       # pad bits inside whole super-steps of 512, or not
 def test_binary_layer_default_tiles(G, bnn_defaults, oracle, M, K, N, act, x01, wb):
     """Binary layers on the default dispatch at the edges of the 32 x 128 tiles (one frame or output more or less, the last
     size with 33 x 8 tiles: beyond the kernel's range), both readings of the bits: exact sums and bits."""

@@ -192,3 +192,21 @@ result = [result, sorted(seen)]
             tested.add(launched[0]["kernel"])
     chains = [k for k in seen if "f32_chain_kernel" in k]
     assert len(chains) >= 16 and not set(chains) - tested
+
+
+def test_binary_layers_take_the_kernel_their_size_wants(host):
+    """Exceptions to the line at 256 tiles of 32 x 128: short output layers hand int16 over, integer outputs of few frames
+    stay on 64-row tiles; and rows whose pad bits complete their 512-bit pieces are read 16 bytes at a time."""
+    got = host("""
+Z, R, S = bnn.BNN_ACT_LOGSOFTMAX, bnn.BNN_ACT_RAW_I32, bnn.BNN_ACT_SIGN
+result = []
+for M, K, N, act in ((1024, 512, 1000, Z), (512, 512, 64, Z), (511, 512, 64, Z), (1000, 1024, 1000, Z), (512, 1024, 512, Z), (1000, 2048, 512, Z),
+                     (1000, 64, 3400, R), (1000, 512, 3400, R), (1024, 64, 3400, R), (1000, 64, 3400, S),
+                     (100, 1000, 512, S), (100, 960, 512, S), (100, 993, 512, S)):
+    bnn.bnn_layer_binw_binx(A, B, C, C, M, K, N, act, 32, D)
+    result.append(launches()[0]["kernel"])
+""")
+    small, large = "binx_mfma_kernel", "binx_mfma32_kernel"
+    assert [large if large in k else small for k in got] == [large, large, small, large, small, small, small, large, large, large, small, small, small]
+    assert "Li4ELi4ELi0E" in got[6]                                   # 64-row tiles
+    assert ["Lb1ELb0E" in k for k in got[10:]] == [True, False, True]  # ALIGNED
