@@ -275,8 +275,8 @@ int bnn_layer_binw_binx_arm(const void* Xp, const void* Wp, const float* scale, 
  * 512 inputs), or for the digit planes of a binary-weight LOGSOFTMAX layer with real inputs (4 bytes per input and
  * frame, 16 per frame, from 128 frames on), whichever is larger; with 128 frames or more these two also hold a byte per
  * weight (K padded to 64) and, for Sign units, a record of 32 bytes per frame and 256 outputs; a real-weight layer adds
- * the bf16 pieces of both operands (LOGSOFTMAX, 128 frames or more: 6 bytes per element, K padded to 32) or a
- * transposed copy of its weights (other activations, 512 frames or more: 4 bytes per weight, K padded to 64).
+ * the bf16 pieces of both operands (LOGSOFTMAX, 128 frames or more: 6 bytes per element, K padded to 32) or reserves
+ * 4 bytes per weight that no kernel uses (other activations, 512 frames or more, K a multiple of 4 and padded to 64).
  * 0 on invalid arguments, and for a one-layer network without such a layer.
  * HOST helper; layers is a HOST array.
  */
@@ -306,7 +306,8 @@ int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64
  * serving loops, harnesses that forbid hipMalloc): the same forward pass with the ping-pong buffers in a fixed
  * BNN_FORWARD_STATIC_MAX_BYTES array inside the library's device image.  Calls no hipMalloc / hipFree or any other
  * allocating routine.  Arguments, results and errors as bnn_forward, except:
- *   - BNN_EWORKSPACE if bnn_forward_workspace_bytes(layers, n_layers, M) exceeds BNN_FORWARD_STATIC_MAX_BYTES
+ *   - BNN_EWORKSPACE if what bnn_forward_workspace_bytes(layers, n_layers, M) counts, without the bytes it only
+ *     reserves and without the extra scratch named below, exceeds BNN_FORWARD_STATIC_MAX_BYTES
  *     (16 MiB: Config-3-sized networks up to 32768 frames, 4096-unit ones up to 16384; a network with a real-input
  *     Sign layer that is not its first layer, or has more than 512 inputs, also keeps 3 bytes per input and frame of
  *     that layer there: 2048 inputs fit up to about 2600 frames).  The extra scratch of the tiled matrix-core products

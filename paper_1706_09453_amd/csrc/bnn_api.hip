@@ -713,13 +713,14 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     return launch_status();
 }
 
-// bnn_forward_workspace_bytes counts kpad x N fp32 (256-byte aligned; K padded to 64) for a layer with real weights that
-// is not in front of the log-Softmax, 512 frames or more: room for a transposed copy of its weights.  The matrix-core
-// kernel reads the weights as they are and leaves it unused; the size is part of the interface.
-bool realw_transposed_applies(const bnn_layer_desc& d, int64_t M) {
+// kpad x N fp32 (256-byte aligned; K padded to 64) for a layer with real weights that is not in front of the log-Softmax, 512
+// frames or more.  No kernel uses it: it is what bnn_forward asks of the caller's workspace beyond what it needs, as it always
+// has, so that the sizes programs were built with stay what bnn_forward_workspace_bytes says.  The fixed array of
+// bnn_forward_static is not charged for it.
+bool realw_reserved_applies(const bnn_layer_desc& d, int64_t M) {
     return d.w_is_real && d.act != BNN_ACT_LOGSOFTMAX && M >= 512 && (d.K & 3) == 0 && d.K <= 65536 && d.N <= (1 << 22);
 }
-size_t realw_transposed_bytes(int64_t K, int64_t N) {
+size_t realw_reserved_bytes(int64_t K, int64_t N) {
     return round_up((size_t)((K + 63) / 64 * 64) * (size_t)N * 4, 256);
 }
 // Real-input layers with binary weights on the int8 matrix cores as a tiled product (128 frames x 256 outputs per
@@ -1209,7 +1210,8 @@ struct ForwardWorkspace {
 };
 // `roomy`: with the scratch of the tiled matrix-core products (the weight bytes and the list of realx_i8_gemm, the bf16
 // planes of a Softmax layer with real weights); without it those layers run on the kernels that need less or none
-static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_layers, int64_t M, bool roomy = true) {
+// `callers`: a workspace of the caller's, with what is only reserved (realw_reserved_bytes)
+static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_layers, int64_t M, bool callers, bool roomy = true) {
     size_t biggest = 0, unpacked = 0;
     for (int l = 0; l < n_layers; ++l) {
         if (l + 1 < n_layers) {
@@ -1217,11 +1219,10 @@ static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_la
             if (b > biggest) biggest = b;
         }
         if (layers[l].w_is_real) {
-            // unpacked binary input first, then the bf16 planes of both operands of a Softmax layer with real weights, or
-            // the transposed weights of another layer with real weights
+            // unpacked binary input first, then the bf16 planes of both operands of a Softmax layer with real weights
             size_t b = layers[l].x_is_binary ? round_up((size_t)M * (size_t)layers[l].K * 4, 256) : 0;
             if (roomy && realw_split_lsm_applies(layers[l], M)) b += realw_split_lsm_bytes(M, layers[l].K, layers[l].N);
-            if (roomy && realw_transposed_applies(layers[l], M)) b += realw_transposed_bytes(layers[l].K, layers[l].N);
+            if (callers && realw_reserved_applies(layers[l], M)) b += realw_reserved_bytes(layers[l].K, layers[l].N);
             if (b > unpacked) unpacked = b;
         }
         if (realx_i8_lsm_applies(layers[l], M)) {
@@ -1243,7 +1244,7 @@ static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_la
 
 BNN_EXPORT size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, int64_t M) {
     if (check_chain(layers, n_layers, M) != BNN_OK) return 0;
-    const ForwardWorkspace ws = forward_workspace(layers, n_layers, M);
+    const ForwardWorkspace ws = forward_workspace(layers, n_layers, M, true);
     return 2 * ws.half + ws.unpacked;
 }
 
@@ -1276,7 +1277,7 @@ void* static_scratch() {
 }  // namespace
 
 static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out, void* workspace,
-                       size_t workspace_bytes, void* stream, bool roomy);
+                       size_t workspace_bytes, void* stream, bool callers, bool roomy);
 
 BNN_EXPORT int bnn_forward_static(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,
                                   void* stream) {
@@ -1287,10 +1288,10 @@ BNN_EXPORT int bnn_forward_static(const bnn_layer_desc* layers, int n_layers, co
     // Softmax layer with real weights) is left out when it does not fit the array: those layers then run on the kernels
     // bnn_forward uses with these products switched off.
     bool roomy = true;
-    ForwardWorkspace ws = forward_workspace(layers, n_layers, M, true);
+    ForwardWorkspace ws = forward_workspace(layers, n_layers, M, false);
     if (2 * ws.half + ws.unpacked > kStaticScratchBytes) {
         roomy = false;
-        ws = forward_workspace(layers, n_layers, M, false);
+        ws = forward_workspace(layers, n_layers, M, false, false);
     }
     const size_t need = 2 * ws.half + ws.unpacked;
     if (need > kStaticScratchBytes) return BNN_EWORKSPACE;
@@ -1299,21 +1300,21 @@ BNN_EXPORT int bnn_forward_static(const bnn_layer_desc* layers, int n_layers, co
         mem = static_scratch();
         if (!mem) return BNN_EDEVICE;
     }
-    return forward_run(layers, n_layers, X, M, out, mem, need, stream, roomy);
+    return forward_run(layers, n_layers, X, M, out, mem, need, stream, false, roomy);
 }
 
 BNN_EXPORT int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,
                            void* workspace, size_t workspace_bytes, void* stream) {
-    return forward_run(layers, n_layers, X, M, out, workspace, workspace_bytes, stream, true);
+    return forward_run(layers, n_layers, X, M, out, workspace, workspace_bytes, stream, true, true);
 }
 
 static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out, void* workspace,
-                       size_t workspace_bytes, void* stream, bool roomy) {
+                       size_t workspace_bytes, void* stream, bool callers, bool roomy) {
     int rc = check_chain(layers, n_layers, M);
     if (rc != BNN_OK) return rc;
     if (M == 0) return BNN_OK;
     if (!X || !out) return BNN_EINVAL;
-    const ForwardWorkspace ws = forward_workspace(layers, n_layers, M, roomy);
+    const ForwardWorkspace ws = forward_workspace(layers, n_layers, M, callers, roomy);
     const size_t need = 2 * ws.half + ws.unpacked;
     if (need && (!workspace || workspace_bytes < need)) return BNN_EWORKSPACE;
     if (need && !aligned(workspace, 256)) return BNN_EALIGN;

@@ -210,3 +210,21 @@ for M, K, N, act in ((1024, 512, 1000, Z), (512, 512, 64, Z), (511, 512, 64, Z),
     assert [large if large in k else small for k in got] == [large, large, small, large, small, small, small, large, large, large, small, small, small]
     assert "Li4ELi4ELi0E" in got[6]                                   # 64-row tiles
     assert ["Lb1ELb0E" in k for k in got[10:]] == [True, False, True]  # ALIGNED
+
+
+def test_static_forward_is_not_charged_for_memory_no_kernel_uses(host):
+    """A hidden layer with real weights: what bnn_forward only reserves for it does not keep the tiled products out of the
+    fixed array.  The size a caller provides stays what it was."""
+    got = host(FORWARD + """
+H, Z = bnn.BNN_ACT_HARDTANH, bnn.BNN_ACT_LOGSOFTMAX
+dims, acts = (300, 2048, 2048, 1000), (H, H, Z)
+forward(512, dims, acts, real=(1,))
+want = [l["kernel"] for l in launches()]
+d = [dict(K=dims[l], N=dims[l + 1], act=acts[l], word_bits=32, x_is_binary=0, w_is_real=l == 1, Wp=B + l * 0x10000000,
+          scale=0 if l == 1 else C, bias=C) for l in range(3)]
+arr = bnn.make_layer_array(d)
+bnn.bnn_forward_static(arr, 3, A, 512, D, 0)
+result = [want, [l["kernel"] for l in launches()], bnn.bnn_forward_workspace_bytes(arr, 3, 512)]
+""")
+    assert got[0] == got[1] and any("realx_i8_gemm" in k for k in got[0])
+    assert got[2] == 2 * 512 * 2048 * 4 + 2048 * 2048 * 4

@@ -54,3 +54,24 @@ def test_forward_static_matches_forward_on_two_calls_in_a_row():
     with pytest.raises(bnn.BnnError) as e:
         bnn.bnn_forward_static(model.layers, model.n_layers, 0x10000, M, 0x20000, G.stream())
     assert e.value.status == bnn.BNN_EWORKSPACE
+
+
+def test_forward_static_is_not_charged_for_memory_no_kernel_uses():
+    """A hidden layer with real weights, 512 frames: bnn_forward asks for more than the fixed array holds, but what is used
+    fits, so both run the same kernels (the output layer's tiled int8 product among them) and every bit agrees."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import harness as G
+    import paper_1706_09453_amd as bnn
+
+    rng = np.random.default_rng(3)
+    dims, M = (300, 2048, 2048, 1000), 512
+    Ws = [(rng.uniform(-1, 1, (n, k)) * np.sqrt(3.0 / k)).astype(np.float32) for k, n in zip(dims, dims[1:])]
+    bs = [(rng.standard_normal(n) * 0.1).astype(np.float32) for n in dims[1:]]
+    model = G.GpuModel(Ws, bs, "hardtanh", 32, real_weight_layers=(1,))
+    assert bnn.bnn_forward_workspace_bytes(model.layers, model.n_layers, M) > bnn.BNN_FORWARD_STATIC_MAX_BYTES
+    X = G.to_dev(rng.standard_normal((M, dims[0])).astype(np.float32))
+    want, got = model.forward(X), torch.full((M, dims[-1]), float("nan"), dtype=torch.float32, device=G.DEV)
+    bnn.bnn_forward_static(model.layers, model.n_layers, G.ptr(X), M, G.ptr(got), G.stream())
+    torch.cuda.synchronize()
+    assert torch.isfinite(got).all() and torch.equal(got.view(torch.int32), want.view(torch.int32))
