@@ -20,8 +20,9 @@
 // and 290 with real weights); at 256 x 2048 x 2048 27 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.
 // What is left to 153 TFLOP/s (register-only loop of the same MFMA): the sign-building and LDS instructions of the staging,
 // and the first and last chunk of a workgroup.
-// Columns past K are stored as 0 in the frames (and real weights): fma(w, 0, acc) returns acc (an accumulator that starts
-// at +0 is never -0), so the sum over k < K is unchanged.
+// Columns past K are stored as +0 in the frames and as -0 in real weights: fma(-0, 0, acc) adds -0, which returns every acc,
+// either zero included (a sum of real products that underflow below zero is -0).  Weight bits past K stand for +-1, and
+// fma(+-1, 0, acc) returns acc too: sums of +-x start at +0, cannot underflow and so are never -0.
 #pragma once
 
 #include <type_traits>
@@ -75,7 +76,7 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
     const char* xtile = reinterpret_cast<const char*>(X + (size_t)m_tile * K);
     const char* wtile = static_cast<const char*>(Wv) + (size_t)n_tile * (WREAL ? K : w32) * 4;
     struct Loads { f32x4c x[NPX]; f32x4c w[WREAL ? NPW : 1]; uint32_t b[WREAL ? 1 : NPW]; };
-    // TAIL: chunk nC - 1, which may end past K: what lies there is read from inside the row and replaced by 0
+    // TAIL: chunk nC - 1, which may end past K: what lies there is read from inside the row and replaced
     auto load4 = [&](const char* base, ofs_t& ofs, int k, auto tail) -> f32x4c {
         asm volatile("" : "+v"(ofs));   // keeps the offset next to its load: scalar base + lane offset, no address arithmetic
         if constexpr (VEC) {
@@ -105,21 +106,21 @@ __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict_
 #pragma unroll
         for (int j = 0; j < NPW; ++j) gload_w(L, c, j, tail);
     };
-    auto clean = [&](f32x4c v, int k, auto tail) {
+    auto clean = [&](f32x4c v, int k, float pad, auto tail) {
         if constexpr (decltype(tail)::value) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = k + i < K ? v[i] : 0.0f;
+            for (int i = 0; i < 4; ++i) v[i] = k + i < K ? v[i] : pad;
         }
         return v;
     };
     auto lstore_x = [&](float* buf, const Loads& L, int c, int j, auto tail) {
-        *reinterpret_cast<f32x4c*>(buf + ((tid + 256 * j) / XPR) * LD + xcol) = clean(L.x[j], c * KC + xcol, tail);
+        *reinterpret_cast<f32x4c*>(buf + ((tid + 256 * j) / XPR) * LD + xcol) = clean(L.x[j], c * KC + xcol, 0.0f, tail);
     };
     constexpr int WST = WREAL ? 1 : 4;   // 16-byte stores of a weight piece
     auto lstore_w = [&](float* buf, const Loads& L, int c, int j, int q, auto tail) {
         float* row = buf + (TM + (tid + 256 * j) / WPR) * LD + wcol;
         if constexpr (WREAL) {
-            *reinterpret_cast<f32x4c*>(row) = clean(L.w[j], c * KC + wcol, tail);
+            *reinterpret_cast<f32x4c*>(row) = clean(L.w[j], c * KC + wcol, -0.0f, tail);
         } else {   // (bits past K: +-1 times a frame value stored as 0)
             const uint32_t inv = ~L.b[j] >> (wcol & 16);
             *reinterpret_cast<f32x4c*>(row + 4 * q) = f32x4c{pm1_from_inverted_bit(inv, 4 * q), pm1_from_inverted_bit(inv, 4 * q + 1),

@@ -543,6 +543,20 @@ def test_ascending_sums_on_the_matrix_cores(G, bnn_defaults, oracle, M, K, N, ac
         assert np.array_equal(G.words_to_host(g_, 64) if act == "sign" else g_.cpu().numpy(), w_)
 
 
+@pytest.mark.parametrize("M,K,N", [(5, 5, 70), (64, 100, 33), (250, 132, 2000), (1100, 4, 1300), (1100, 21, 1299), (1100, 68, 1300), (2047, 68, 2046)])
+def test_sums_that_underflow_keep_their_sign(G, bnn_defaults, oracle, M, K, N):
+    """Real weights whose products all underflow below zero: the chain stays at -0, also through the columns that complete the
+    last chunk, and with a bias of -0 the outputs are -0 as the oracle has them."""
+    bnn = bnn_defaults
+    X, W = np.full((M, K), -1e-30, np.float32), np.full((N, K), 1e-30, np.float32)
+    X[1::2] *= -1
+    bias = np.where(np.arange(N) % 3 == 0, np.float32(0.0), np.float32(-0.0)).astype(np.float32)
+    got = G.layer_realw(G.to_dev(X), G.to_dev(W), G.to_dev(bias), K, N, bnn.BNN_ACT_LINEAR, 32).cpu().numpy()
+    want = oracle.layer_realw(X, W, bias, "linear", 32)
+    assert (want.view(np.uint32) == 0x80000000).any()
+    assert np.array_equal(got.view(np.uint32), want.view(np.uint32))
+
+
 # ----------------------------------------------------------------------------- first layer on the matrix cores
 
 def _first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, use_mfma):
