@@ -339,8 +339,8 @@ def _rand_realw(seed, M, K, N):
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (3, 31, 5), (70, 33, 65), (64, 440, 512), (130, 440, 200), (17, 16, 257),
                                    (37, 2048, 300), (50, 100, 3307), (33, 12, 70), (300, 452, 260)])
 def test_realw_layer(G, bnn, oracle, M, K, N, act, wb):
-    """Real-valued weights on the vector ALU: the same ascending-k chain of fused multiply-adds as the oracle's, so fp32
-    outputs are identical bits (K a multiple of 4 takes the LDS-staged kernel, any other K the element-load one)."""
+    """Real-valued weights on the fp32 matrix cores: the same ascending-k chain of fused multiply-adds as the oracle's, so fp32
+    outputs are identical bits (K a multiple of 4 loads 16 bytes at a time, any other K number by number)."""
     bnn.bnn_set_option(bnn.BNN_OPT_REALX_F32_MFMA, 2)
     try:
         X, W, bias = _rand_realw(M * 7 + K + N, M, K, N)
@@ -373,8 +373,8 @@ def test_streaming_real_weight_layer(G, bnn, oracle, M, K, N, act):
         assert np.array_equal(Y.cpu().numpy(), want)
 
 
-def _one_layer_realw_forward(G, bnn, X, W, bias, K, N, act, arm, wb=32):
-    """A one-layer network with real weights through bnn_forward; `arm` = BNN_OPT_REALW_VALU_LDS."""
+def _one_layer_realw_forward(G, bnn, X, W, bias, K, N, act, wb=32):
+    """A one-layer network with real weights through bnn_forward."""
     keep = [G.to_dev(W), G.to_dev(bias)]
     d = [dict(K=K, N=N, act=act, word_bits=wb, x_is_binary=False, w_is_real=True, Wp=G.ptr(keep[0]), scale=0, bias=G.ptr(keep[1]))]
     arr = bnn.make_layer_array(d)
@@ -384,63 +384,93 @@ def _one_layer_realw_forward(G, bnn, X, W, bias, K, N, act, arm, wb=32):
     ws = torch.zeros(max(nbytes, 256), dtype=torch.uint8, device=G.DEV)
     out = (G.word_tensor(M, N, wb) if act == bnn.BNN_ACT_SIGN
            else torch.full((M, N), float("nan"), dtype=torch.float32, device=G.DEV))
-    bnn.bnn_set_option(bnn.BNN_OPT_REALW_VALU_LDS, arm)
-    try:
-        assert bnn.bnn_forward(arr, 1, G.ptr(dX), M, G.ptr(out), G.ptr(ws), nbytes, G.stream()) == bnn.BNN_OK
-        torch.cuda.synchronize()
-    finally:
-        bnn.bnn_set_option(bnn.BNN_OPT_REALW_VALU_LDS, 1)
+    assert bnn.bnn_forward(arr, 1, G.ptr(dX), M, G.ptr(out), G.ptr(ws), nbytes, G.stream()) == bnn.BNN_OK
+    torch.cuda.synchronize()
     return G.words_to_host(out, wb) if act == bnn.BNN_ACT_SIGN else out.cpu().numpy()
 
 
 @pytest.mark.parametrize("act", ["sign", "linear", "hardtanh", "sigmoid"])
 @pytest.mark.parametrize("M,K,N", [(512, 4, 1), (513, 12, 70), (600, 440, 300), (1030, 200, 513), (577, 64, 256),
                                    (2048, 452, 1025), (640, 2048, 257)])
-def test_real_weight_layer_in_forward_register_fmas(G, bnn, oracle, M, K, N, act):
-    """512 frames or more inside bnn_forward: the ascending-k chains of the real-weight layer (paper Sec. 3.1) from the
-    kernel whose fmas take three register operands (frames through LDS, weights from a transposed copy): the oracle's
-    chain, so identical bits, and identical to the other kernel's."""
+def test_real_weight_layer_in_forward(G, bnn, oracle, M, K, N, act):
+    """512 frames or more inside bnn_forward: the real-weight layer (paper Sec. 3.1) gives the oracle's ascending-k chain, so
+    identical bits."""
     X, W, bias = _rand_realw(M * 5 + K + N, M, K, N)
-    a = bnn.ACT_BY_NAME[act]
-    got = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, a, 1)
-    old = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, a, 0)
+    got = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, bnn.ACT_BY_NAME[act])
     want = oracle.layer_realw(X, W, bias, act, 32)
-    assert np.array_equal(got.view(np.uint32), old.view(np.uint32))
     if act == "sigmoid":
         _close(got, want, act)
     else:
         assert np.array_equal(got, want)
 
 
-def test_real_weight_layer_in_forward_register_fmas_special_values(G, bnn, oracle):
-    """NaN, infinities, signed zeros, denormals and huge values in frames and weights: the same bits from both kernels
-    (NaN payloads included), and rows without them as the oracle has them."""
-    M, K, N = 700, 100, 330
+@pytest.mark.parametrize("M,K", [(700, 100), (700, 33), (60, 100)])
+@pytest.mark.parametrize("real", [True, False])
+def test_special_values_in_sums_of_real_inputs(G, bnn_defaults, oracle, M, K, real):
+    """NaN, infinities, signed zeros, denormals and huge values in frames and real weights: NaN where the oracle has NaN, the
+    same bits everywhere else; the Sigmoid within its tolerance there."""
+    bnn, N = bnn_defaults, 330
     X, W, bias = _rand_realw(77, M, K, N)
     X[3, 17] = np.inf
-    X[4, 50] = np.nan
+    X[4, 20] = np.nan
     X[5] = 0.0
     X[6] = -0.0
     X[7] *= np.float32(1e-41)
-    X[8, 99] = np.float32(3e38)
+    X[8, 29] = np.float32(3e38)
     X[9, 0] = -np.inf
-    W[10, 3] = np.nan
-    W[11] = -0.0
-    W[12] *= np.float32(1e-40)
-    W[13, 99] = np.float32(3e38)
-    for act in ("linear", "sign", "sigmoid"):
+    X[10, :2] = np.inf, -np.inf
+    scale = None if real else np.full(N, 0.75, np.float32)
+    if real:
+        W[10, 3] = np.nan
+        W[11] = -0.0
+        W[12] *= np.float32(1e-40)
+        W[13, 29] = np.float32(3e38)
+    for act in ("linear", "hardtanh", "sign", "sigmoid"):
         a = bnn.ACT_BY_NAME[act]
-        got = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, a, 1)
-        old = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, a, 0)
-        assert np.array_equal(got.view(np.uint32), old.view(np.uint32)), act
         with np.errstate(all="ignore"):
-            want = oracle.layer_realw(X, W, bias, act, 32)
-        if act == "linear":
-            assert np.array_equal(np.isnan(got), np.isnan(want))
-            fin = ~np.isnan(want)
-            assert np.array_equal(got[fin], want[fin])
-        elif act == "sign":
+            if real:
+                got = _one_layer_realw_forward(G, bnn, X, W, bias, K, N, a)
+                want = oracle.layer_realw(X, W, bias, act, 32)
+            else:
+                Wp = oracle.pack_sign(W, 32)
+                Y = G.layer_realx(G.to_dev(X), G.to_dev(Wp), G.to_dev(scale), G.to_dev(bias), K, N, a, 32)
+                got = G.words_to_host(Y, 32) if act == "sign" else Y.cpu().numpy()
+                want = oracle.layer_binw_realx(X, Wp, K, scale, bias, act, 32)
+        if act == "sign":
             assert np.array_equal(got, want)
+            continue
+        assert np.isnan(want).any() and np.array_equal(np.isnan(got), np.isnan(want)), act
+        fin = ~np.isnan(want)
+        if act == "sigmoid":
+            _close(got[fin], want[fin], act)
+        else:
+            assert np.array_equal(got[fin], want[fin]), act
+
+
+@pytest.mark.parametrize("real", [True, False])
+def test_sigmoid_bits(G, bnn_defaults, oracle, real):
+    """The Sigmoid alone (one input, weight +1): fp32 values as the fp64 definition rounds them, bit for bit, since Sign layers
+    behind it read them.  Both sides are within 1.5 units in the last place of fp64, so a value differs with a probability of
+    about 2^-28, all 200000 of them with less than 1e-3.  Infinities, the ends of the clamped range, fp32 underflow, zeros, NaN."""
+    bnn = bnn_defaults
+    rng = np.random.default_rng(21)
+    edges = [0.0, -0.0, np.inf, -np.inf, np.nan, 700.0, -700.0, 709.8, -709.8, 1000.0, -1000.0, 3e38, -3e38, 1e-45, -1e-45, 2e-38, 16.5, 17.4, 36.8,
+             -87.3, -87.4, -88.0, -88.7, -88.8, -102.0, -103.0, -103.2, -103.28, -103.97, -104.0, -105.0]
+    x = np.concatenate([np.array(edges, np.float32), np.linspace(-110, 110, 120001, dtype=np.float32),
+                        (rng.standard_normal(60000) * 4).astype(np.float32),
+                        (rng.choice([-1, 1], 20000) * 2.0 ** rng.uniform(-40, 4, 20000)).astype(np.float32)]).astype(np.float32)
+    X, one, zero = x[:, None].copy(), np.ones((1, 1), np.float32), np.zeros(1, np.float32)
+    for rows in (slice(None), slice(0, 64)):      # a large batch and a few frames
+        dX = G.to_dev(X[rows])
+        if real:
+            Y = G.layer_realw(dX, G.to_dev(one), G.to_dev(zero), 1, 1, bnn.BNN_ACT_SIGMOID, 32)
+        else:
+            Y = G.layer_realx(dX, G.to_dev(oracle.pack_sign(one, 32)), G.to_dev(one[0]), G.to_dev(zero), 1, 1, bnn.BNN_ACT_SIGMOID, 32)
+        got = Y.cpu().numpy()[:, 0]
+        with np.errstate(all="ignore"):
+            want = oracle.layer_realw(X[rows], one, zero, "sigmoid", 32)[:, 0]
+        nan = np.isnan(x[rows])
+        assert np.isnan(got[nan]).all() and np.array_equal(got[~nan].view(np.uint32), want[~nan].view(np.uint32))
 
 
 def test_realw_layer_with_pm1_weights_equals_binary_weight_layer(G, bnn, oracle):
