@@ -81,7 +81,8 @@ typedef enum bnn_option {
     BNN_OPT_REALX_TM = 2,        /* real-input layers, ascending-k sums: 0 (default) = fp32 matrix cores; 1, 2, 4, 8, 16 or
                                   32 = that many frames per wavefront on the vector ALU.  Same results.             */
     BNN_OPT_BINX_VALU_TM = 3,  /* frames per wavefront of the XOR/popcount kernel: 1, 2, 4, 8, 16 (default) or 32  */
-    BNN_OPT_MFMA_WM = 4,       /* 16-row accumulator fragments per wavefront of the matrix-core kernel: 2 or 4  */
+    BNN_OPT_MFMA_WM = 4,       /* 16-row accumulator fragments per wavefront of the 16x16x128 matrix-core kernel: 2 or 4; acts with
+                                  BNN_OPT_MFMA_SHAPE = 16 (by default the library picks the tile)               */
     BNN_OPT_REALX_SIGN_MFMA = 5, /* bnn_forward, binary-weight layers real input -> Sign (the first layer of a
                                    binary-activation network; the layer behind a Sigmoid layer in the paper's Table 2
                                    topology): 1 = matrix-core filter with exact sums for the outputs it cannot decide

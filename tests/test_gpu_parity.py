@@ -268,7 +268,7 @@ def test_streaming_forward_equals_large_batch_forward(G, bnn, oracle):
 @pytest.mark.parametrize("M,K,N", [(1, 1, 1), (3, 31, 5), (70, 33, 65), (64, 440, 512), (130, 440, 200),
                                    (37, 2048, 300), (50, 100, 3307)])
 def test_realx_layer(G, bnn, oracle, M, K, N, act, wb, tm):
-    """The vector-ALU kernel adds in ascending k, as the oracle's fp32 sum does: fp32 outputs are identical bits."""
+    """Real-input sums run in ascending k, as the oracle's fp32 sum does: fp32 outputs are identical bits."""
     bnn.bnn_set_option(bnn.BNN_OPT_REALX_TM, tm)
     bnn.bnn_set_option(bnn.BNN_OPT_REALX_F32_MFMA, 2)
     try:
