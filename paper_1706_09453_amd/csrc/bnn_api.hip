@@ -584,7 +584,9 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     // Outputs per workgroup.  A workgroup costs about 11 us (frames in, digits, the undecided outputs) and 4 us per 512
     // outputs, and a CU holds one at a time, so the outputs are split as far as that shortens the longest CU's work:
     // measured at 440 x 2048, 333 frames 27.7 us with all outputs in one workgroup, 15.5 with 512; 1500 frames 27.5 and
-    // 19.4 (1024); 4096 frames 28.2 unsplit, 37.1 with 1024, 55.6 with 512.
+    // 19.4 (1024); 4096 frames 28.2 unsplit, 37.1 with 1024, 55.6 with 512.  (Rows of up to about 300 numbers leave LDS for
+    // two or three workgroups per CU, which the rule does not count; of K = 16 to 520, 64 to 4096 outputs and 65 to 16384
+    // frames no size measured slower than with all outputs in one workgroup.)
     const int chunks = min((Ni + kRealxChunk - 1) / kRealxChunk, kRealxMaxNB / kRealxChunk);
     const int64_t mt = (M + kRealxBM - 1) / kRealxBM;
     int nb = 0;
