@@ -110,19 +110,17 @@ typedef enum bnn_option {
                                    network amplifies the different rounding from layer to layer: measured 8e-4 of the
                                    output scale after 7 layers of 2048 units)                                       */
     BNN_OPT_MFMA32_PIPELINE = 9, /* operand fetch of the 32x32x64 kernel on 16-byte aligned rows with K % 512 == 0:
-                                   0 or 1 = two register sets, the fetch of the next piece of K pinned ahead of
-                                   the products of the current one (default), 2 = one set, order left to the
-                                   compiler (kept for comparison)                                                */
+                                   0 or 1 = through LDS, three stages in rotation, 0/1 operands, instruction order pinned
+                                   (default), 2 = from memory to registers, -1/+1 operands, order left to the compiler
+                                   (kept for comparison and for operands of 2 GiB or more).  Same bits.            */
     BNN_OPT_STREAM_MAX_FRAMES = 12, /* batches of at most this many frames (streaming; the paper's motivation is on-device,
                                        frame-by-frame inference) run every layer on kernels with few frames per workgroup (1 or 2
                                        on the vector ALU; 16 on the fp32 matrix cores for real weights, and for real inputs
                                        from 17 frames on), so that a layer is spread over the whole chip and takes one pass
                                        over its weight rows (binary layers that would need more workgroups than the chip
                                        holds stay on the matrix cores); 0 = never.  Default 64.  Same results either way. */
-    BNN_OPT_MFMA32_SPLITK = 14,     /* Sign layers on the 128-row 32x32x64 kernel with K % 1024 == 0: 1 = a workgroup of 8
-                                       waves, the second four taking the second half of K and handing their sums over
-                                       through LDS (two waves per SIMD from a grid of one workgroup per CU); 0 = no
-                                       (default: measured 12.4 against 9.9 us at 4096 x 2048 x 2048).  Same bits.       */
+    BNN_OPT_MFMA32_SPLITK = 14,     /* 0 or 1, without effect: Sign layers once had a variant with K split between the halves of
+                                       a workgroup of 8 waves.  Same bits.                                               */
     BNN_OPT_REALX_I8_LOGSOFTMAX = 16, /* bnn_forward, LOGSOFTMAX layer with binary weights and real inputs, 128 frames or more,
                                        K <= 8192: 1 = the sum of +-x on the int8 matrix cores from four 7-bit digit planes of
                                        the frames (|sum - exact| < K 2^-27 max|x| per frame: below what the order of an fp32

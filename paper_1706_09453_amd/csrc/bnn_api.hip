@@ -56,7 +56,6 @@ std::atomic<int> g_realx_i8_lsm{1};
 std::atomic<int> g_realw_split_lsm{1};
 std::atomic<int> g_cooperative{0};
 std::atomic<int> g_coop_spin{1 << 20};
-std::atomic<int> g_mfma32_splitk{0};
 
 std::atomic<unsigned long long> g_coop_launches{0};
 constexpr int kCoopMaxDevices = 64;
@@ -320,29 +319,25 @@ void launch_binx_mfma32(const uint32_t* Xp, const uint32_t* Wp, const float* sca
                                               (N >= 4096 && (size_t)M * N / 8 >= ((size_t)32 << 20))));
     const unsigned int ab = (unsigned int)((size_t)M * w32 * 4), bb = (unsigned int)((size_t)N * w32 * 4);   // used by the PP variants only
     const dim3 grid((M + 64 * WM - 1) / (64 * WM), (N + 64 * WN - 1) / (64 * WN)), block(256);
+    auto go = [&](auto actc) {
+        constexpr int ACT = decltype(actc)::value;
+        constexpr unsigned lds = m32_lds(WM, WN, ACT, PP);
+        if constexpr (lds > 65536) {
+            static std::atomic<uint64_t> allowed{0};
+            (void)allow_lds(&binx_mfma32_kernel<WM, WN, ACT, AL, PP, X01>, lds, allowed);   // (refused: the launch fails)
+        }
+        binx_mfma32_kernel<WM, WN, ACT, AL, PP, X01><<<grid, block, lds, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
+    };
     switch (act) {
         case ACT_LSM_COOP:
-            if constexpr (WM == 4 && AL && PP)
-                binx_mfma32_kernel<WM, WN, ACT_LSM_COOP, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
+            if constexpr (WM == 4 && AL && PP) go(std::integral_constant<int, ACT_LSM_COOP>{});
             break;
-        case ACT_DOT_I16:
-            binx_mfma32_kernel<WM, WN, ACT_DOT_I16, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
-        case BNN_ACT_RAW_I32:
-            binx_mfma32_kernel<WM, WN, ACT_RAW_I32, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
-        case BNN_ACT_SIGN:
-            binx_mfma32_kernel<WM, WN, ACT_SIGN, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
-        case BNN_ACT_HARDTANH:
-            binx_mfma32_kernel<WM, WN, ACT_HARDTANH, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
-        case BNN_ACT_SIGMOID:
-            binx_mfma32_kernel<WM, WN, ACT_SIGMOID, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
-        default:
-            binx_mfma32_kernel<WM, WN, ACT_LINEAR, AL, PP, X01><<<grid, block, 0, st>>>(Xp, Wp, scale, bias, M, K, N, w32, Y, yw32, ab, bb, xo, coop);
-            break;
+        case ACT_DOT_I16: go(std::integral_constant<int, ACT_DOT_I16>{}); break;
+        case BNN_ACT_RAW_I32: go(std::integral_constant<int, ACT_RAW_I32>{}); break;
+        case BNN_ACT_SIGN: go(std::integral_constant<int, ACT_SIGN>{}); break;
+        case BNN_ACT_HARDTANH: go(std::integral_constant<int, ACT_HARDTANH>{}); break;
+        case BNN_ACT_SIGMOID: go(std::integral_constant<int, ACT_SIGMOID>{}); break;
+        default: go(std::integral_constant<int, ACT_LINEAR>{}); break;
     }
 }
 
@@ -467,8 +462,10 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         const int64_t blocks4 = ((M + 255) / 256) * ((N + 127) / 128);
         const int wm32 = g_mfma32_wm.load();
         const bool wm2 = wm32 == 2 || (wm32 == 0 && blocks4 < 200);
-        // fetch pinned ahead of the products: faster on every shape measured; buffer addressing needs operands below 2 GiB
-        const bool pinned = g_mfma32_pipeline.load() != 2 && (size_t)M * w32 * 4 < 0x7fffffffu && (size_t)N * w32 * 4 < 0x7fffffffu;
+        // fetch through LDS, order pinned: 16384 x 4096 x 4096 95 us against 124 from memory to registers, 4096 x 2048 x 2048 9.3
+        // and 10.5, 600 x 2048 x 2048 6.5 and 9.2.  Buffer addressing needs operands below 2 GiB, exact sums of 0/1 products and
+        // counts in fp32 K < 2^22
+        const bool pinned = g_mfma32_pipeline.load() != 2 && K < (1 << 22) && (size_t)M * w32 * 4 < 0x7fffffffu && (size_t)N * w32 * 4 < 0x7fffffffu;
         // Cooperative log-Softmax (opt-in): the product kernel finishes the rows itself.  Its workgroups wait for each
         // other, so all of them have to be resident at once.
         CoopLsm coop{};
@@ -479,8 +476,8 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
             int cap = base ? g_coop_capacity[dev][x01 ? 1 : 0].load() : 0;
             if (base && cap == 0) {
                 int per_cu = 0, cus = 0;
-                const hipError_t e1 = x01 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, binx_mfma32_kernel<4, 2, ACT_LSM_COOP, true, true, true>, 256, 0)
-                                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, binx_mfma32_kernel<4, 2, ACT_LSM_COOP, true, true, false>, 256, 0);
+                const hipError_t e1 = x01 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, binx_mfma32_kernel<4, 2, ACT_LSM_COOP, true, true, true>, 256, m32_lds(4, 2, ACT_LSM_COOP, true))
+                                          : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, binx_mfma32_kernel<4, 2, ACT_LSM_COOP, true, true, false>, 256, m32_lds(4, 2, ACT_LSM_COOP, true));
                 const hipError_t e2 = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
                 if (e1 != hipSuccess || e2 != hipSuccess) (void)hipGetLastError();
                 cap = (e1 == hipSuccess && e2 == hipSuccess && per_cu > 0 && cus > 0) ? per_cu * cus : -1;
@@ -499,7 +496,7 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         }
         if (x01) {
             if (!al) launch_binx_mfma32<2, false, false, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-            else if (!pinned) launch_binx_mfma32<2, true, false, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);   // operands of 2 GiB or more: pointer addressing
+            else if (!pinned) launch_binx_mfma32<2, true, false, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);   // operands of 2 GiB or more
             else if (wm2) launch_binx_mfma32<2, true, true, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
             else launch_binx_mfma32<4, true, true, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st, coop);
         } else if (!al) {
@@ -508,15 +505,6 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         } else if (wm2) {
             if (pinned) launch_binx_mfma32<2, true, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
             else launch_binx_mfma32<2, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
-        } else if (act == BNN_ACT_SIGN && pinned && K % 1024 == 0 && g_mfma32_splitk.load() == 1) {
-            // two waves per SIMD from a grid of one workgroup per CU, by splitting K inside the workgroup (comparison
-            // arm: measured slower at Config 3's size, see the option)
-            const int xsel = g_mfma32_xcd_order.load();
-            const int xo = xsel == 1 || (xsel == 0 && ((size_t)M * w32 * 4 > ((size_t)32 << 20) ||
-                                                      (N >= 4096 && (size_t)M * N / 8 >= ((size_t)32 << 20))));
-            const dim3 grid((Mi + 255) / 256, (Ni + 127) / 128), block(512);
-            binx_mfma32_kernel<4, 2, ACT_SIGN, true, true, false, true><<<grid, block, 0, st>>>(
-                A, B, scale, bias, Mi, Ki, Ni, w32, Y, yw32, (unsigned int)((size_t)M * w32 * 4), (unsigned int)((size_t)N * w32 * 4), xo, CoopLsm{});
         } else {
             if (pinned) launch_binx_mfma32<4, true, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st, coop);
             else launch_binx_mfma32<4, true>(A, B, scale, bias, Mi, Ki, Ni, w32, act, Y, yw32, st);
@@ -909,8 +897,7 @@ BNN_EXPORT int bnn_set_option(int option, int value) {
             return BNN_OK;
         case BNN_OPT_MFMA32_SPLITK:
             if (value != 0 && value != 1) return BNN_EINVAL;
-            g_mfma32_splitk.store(value);
-            return BNN_OK;
+            return BNN_OK;   // one kernel, the same bits
         default: return BNN_EINVAL;
     }
 }

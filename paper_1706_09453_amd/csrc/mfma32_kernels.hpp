@@ -8,10 +8,8 @@
 // [M][N] as 4 x 2 accumulator fragments of 32 x 32 expands 6 words for 8 MFMAs of 65536 MACs each, about
 // half the expansion work per MAC of the 16 x 16 x 128 kernel with 64 x 64 wave tiles.
 //
-// K advances in super-steps of 512 bits: lane (r = lane%32, g = lane/32) fetches 32 contiguous bytes (words
-// 8g..8g+7 of the super-step) of row r of every fragment in two 16-byte loads; word j feeds MFMA step j.
-// Inside a fragment the order of k is therefore permuted, identically for both operands.  The next
-// piece of K is fetched while the current one is expanded and multiplied.
+// K advances in super-steps of 512 bits: lane (r = lane%32, g = lane/32) takes eight words of row r of every fragment;
+// word j feeds MFMA step j.  Inside a fragment the order of k is therefore permuted, identically for both operands.
 // A workgroup is 2 x 2 waves: a (64 WM) x (64 WN) tile; at M = 4096, N = 2048 with WM = 4, WN = 2 that is
 // 256 workgroups, one wave per SIMD of the chip.
 #pragma once
@@ -21,6 +19,24 @@
 namespace bnn {
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+
+// 0/1 operands (pinned variants).  With h and w the bits of a frame and of a weight row read as 0 and 1,
+//     sum_k (+-1)(+-1) = 4 sum_k h w - 2 popcount(h) - 2 popcount(w) + K,        sum_k h (+-1) = 2 sum_k h w - popcount(h),
+// and a nibble of the 4-bit float format with a single bit set is a power of two (bit 0: 0.5, bit 1: 1, bit 2: 2), so most of
+// an operand's dwords are one AND of the packed word with a mask, with the other operand's shifted to the reciprocal:
+//     bit of the word's nibble      0            1            2            3
+//     frames                   w & 1..: 0.5   w & 2..: 1   w & 4..: 2   (w >> 2) & 2..: 1
+//     weights             (w << 2) & 4..: 2   w & 2..: 1   (w >> 2) & 1..: 0.5   (w >> 2) & 2..: 1
+// Five and six instructions per word, and one for its popcount, where +-1 takes seven; and three quarters of the products are
+// 0.  What bounds a large product here is the energy of an MFMA and of what stands around it: with +-1 operands the clock falls
+// to 1.5 GHz in the pinned loop, at 32.4 clocks per MFMA (16384 x 4096 x 4096; register to register, with five vector
+// instructions per MFMA: +-1 18.3 ns per MFMA at 1.96 GHz, 0/1 16.1 ns at 2.2).
+struct ExpandMasks { uint32_t b0, b1, b2; };
+__device__ __forceinline__ ExpandMasks expand_masks() {
+    ExpandMasks m{0x11111111u, 0x22222222u, 0x44444444u};
+    asm volatile("" : "+s"(m.b0), "+s"(m.b1), "+s"(m.b2));
+    return m;
+}
 
 struct Raw8 {
     uint4 lo, hi;   // words 0..3 and 4..7 of a lane's share of a super-step
@@ -48,15 +64,57 @@ __device__ __forceinline__ Raw8 load_raw8(const uint32_t* __restrict__ row, int 
     return v;
 }
 
-// words[lane_lo] = lo, words[lane_hi] = hi (wave-uniform values; the lanes must be compile-time constants after
-// unrolling).
-// On this core a vector instruction that reads an SGPR needs two wait states after the vector instruction (here
-// the compare behind a ballot) that wrote it.  The compiler inserts them for its own instructions but does not
-// look inside inline assembly, so the two wait states are part of the statement.
-__device__ __forceinline__ void write_lane_pair(int& words, uint32_t lo, uint32_t hi, int lane_lo, int lane_hi) {
-    asm volatile("s_nop 1\n\tv_writelane_b32 %0, %1, %3\n\tv_writelane_b32 %0, %2, %4"
-                 : "+v"(words) : "s"(lo), "s"(hi), "n"(lane_lo), "n"(lane_hi));
+// Sign(fma(scale, unit * a, bias)), with unit * a an integer below 2^24, as the sign bit of fma(neg_scale, a, neg_bias).  The two
+// fused multiply-adds are each other's negative, up to a power of two that is taken from the side that stays in range, so the
+// sign bit is set exactly where the first is above zero, if the second is never -0 and never a NaN.  neg_bias is never -0, and
+// the exact result is a multiple of 2^-149 that does not underflow, so a zero comes out as +0.  NaNs are avoided by what the
+// column is replaced with: a NaN anywhere gives bit 0 for every a; an infinite scale gives 1 where scale * a is +inf and bias is
+// not -inf (at a = 0, or against a bias of -inf, the sum is a NaN or -inf).
+struct SignColumn { float neg_scale, neg_bias; };
+__device__ __forceinline__ SignColumn sign_column(float scale, float bias, float unit) {
+    const float inf = __builtin_inff();
+    const bool big = __builtin_fabsf(scale) == inf;
+    const bool never = scale != scale || bias != bias || (big && bias == -inf);
+    scale = never ? 0.0f : (big ? __builtin_copysignf(1.0f, scale) : scale);
+    bias = never || big ? 0.0f : bias;
+    // (a scale of 2^100 and more: beside any a but 0 a bias below 1 does not count, and at a = 0 only its sign does)
+    const bool wide = __builtin_fabsf(scale) >= 0x1p100f;
+    return {wide ? -scale : -scale * unit, 0.0f - (wide && __builtin_fabsf(bias) >= 1.0f ? bias / unit : bias)};
 }
+
+// 32 x 32 bits across the 32 lanes of a half wave: afterwards bit j of lane i is what bit i of lane j was.  Five exchanges with
+// the lane whose number differs in one bit; a lane keeps the half of its bits that stays and takes the other one rotated.
+struct TransposeBits {
+    uint32_t keep[5], rot[5];
+    __device__ __forceinline__ explicit TransposeBits(int lane) {
+        constexpr uint32_t kLow[5] = {0x0000FFFFu, 0x00FF00FFu, 0x0F0F0F0Fu, 0x33333333u, 0x55555555u};
+#pragma unroll
+        for (int t = 0; t < 5; ++t) {
+            const int s = 16 >> t;
+            keep[t] = (lane & s) ? ~kLow[t] : kLow[t];
+            rot[t] = (lane & s) ? (uint32_t)s : (uint32_t)(32 - s);   // to the right
+        }
+    }
+    template <int S>
+    static __device__ __forceinline__ uint32_t partner(uint32_t v) {
+        return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x1F | (S << 10));
+    }
+    template <int T, int N>
+    __device__ __forceinline__ void step(uint32_t (&w)[N]) const {
+        uint32_t p[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) p[i] = partner<(16 >> T)>(w[i]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const uint32_t o = __builtin_amdgcn_alignbit(p[i], p[i], rot[T]);
+            w[i] = (w[i] & keep[T]) | (o & ~keep[T]);
+        }
+    }
+    template <int N>
+    __device__ __forceinline__ void run(uint32_t (&w)[N]) const {
+        step<0>(w); step<1>(w); step<2>(w); step<3>(w); step<4>(w);
+    }
+};
 
 // Called inside the product loop, after the first products: the loads that produced sc/bi then stay in front of
 // the loop, where they were written, instead of moving next to their use in the epilogue, and by the time this
@@ -67,42 +125,63 @@ __device__ __forceinline__ void pin_loaded(float (&sc)[WN], float (&bi)[WN]) {
     for (int f = 0; f < WN; ++f) asm volatile("" : "+v"(sc[f]), "+v"(bi[f]));
 }
 
-// 16 bytes at byte offset voff (per lane) + soff (wave-uniform) of a buffer.
-__device__ __forceinline__ uint4 load16(__amdgpu_buffer_rsrc_t rs, int voff, int soff) {
-    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, soff, 0);
-    return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
 __device__ __forceinline__ uint32_t word_of(const Raw8& v, int j) {
     return j < 4 ? word_of(v.lo, j) : word_of(v.hi, j - 4);
 }
 
-// PINGPONG (aligned rows only): the operand fetch runs ahead of the products in separate register sets, with the
-// issue order pinned by scheduling barriers: two whole super-steps for 64-row wave tiles (WM = 2), three half
-// super-steps in rotation for 128-row tiles (WM = 4), whose half-steps are also written out instruction slot by
-// slot.  Without it (current = next, order left to the compiler) the two sets get merged and every super-step
-// waits for its own loads; kept for ragged rows and for comparison.
+// Operand fetch of the pinned variants (PINGPONG): both operands of the workgroup's tile go to LDS as they are in memory, one
+// bit per element, by loads that write LDS directly (no registers, no LDS store instructions), in stages of 512 bits of every
+// row, three stages in rotation; a lane reads 16 bytes of its fragment rows per half-stage.  Fetched straight into registers, a
+// fragment load touches 32 rows, 64 different pieces of 16 bytes, and the texture path takes those one after the other: at
+// 16384 x 4096 x 4096 a wave then issued an MFMA every 29 ns, where the matrix core needs 13.6 and the expansion fits
+// beside it (V independent vector instructions per MFMA, one or two waves per SIMD: V = 5 14.9 ns, V = 6 15.6 to 16.8).
+// Measured, with the 0/1 operands below: Sign layers 16384 x 4096 x 4096 124 -> 95 us (of which the stages alone 100, with
+// +-1 operands), 65536 x 4096 x 4096 465 -> 328, 4096 x 8192 x 2048 29.1 -> 23.8, 4096 x 2048 x 2048 10.5 -> 9.3; a wave of the
+// last takes 1.3 us to its first operands, 6.3 for its 256 MFMAs and 1.4 behind them.
+// In LDS a row of a stage is 64 bytes, its four 16-byte slots at slot ^ (row / 4 % 4), so that the 16 lanes that are served
+// together read 16 different slots of the 64 banks.
+constexpr int kM32Stages = 3;
+constexpr int kM32RowBytes = 64;
+constexpr int kM32Ldw = 68;   // words per row of the transposing epilogue's slices: 64 columns and a pad
+__host__ __device__ constexpr int m32_stage(int WM, int WN) { return (64 * WM + 64 * WN) * kM32RowBytes; }
+__host__ __device__ constexpr unsigned m32_lds(int WM, int WN, int ACT, bool PINGPONG) {
+    const unsigned loop = PINGPONG ? (unsigned)(kM32Stages * m32_stage(WM, WN) + 2 * 64 * WN * 4) : 0u;   // stages; scale and bias
+    unsigned epi = ACT == ACT_SIGN ? 0u : 4u * 32u * kM32Ldw * 4u;
+    if (ACT == ACT_LSM_COOP) epi += 4u * 32u * (unsigned)WM * 8u + 64u * (unsigned)WM * 4u;
+    return loop > epi ? loop : epi;
+}
+typedef int i32x4m __attribute__((ext_vector_type(4)));
+// 16 bytes per lane from byte `voff` (per lane) + `soff` (wave-uniform) of a buffer to LDS: lane i's go to lds + 16 i.  The
+// request is counted by vmcnt only: whoever reads the LDS waits for it and then crosses a barrier.  (Written out because the
+// compiler, not knowing which stage a later LDS read belongs to, makes every read wait for every such load.)
+__device__ __forceinline__ void load_lds16(i32x4m rsrc, int voff, int soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+// the same with 4 bytes per lane: lane i's go to lds + 4 i
+__device__ __forceinline__ void load_lds4(i32x4m rsrc, int voff, int soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ i32x4m raw_buffer(const void* p, unsigned int bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return i32x4m{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
+}
+
+// PINGPONG (aligned rows only): the fetch described above, with the issue order pinned by scheduling barriers and, for 128-row
+// wave tiles (WM = 4), written out instruction slot by slot.  Without it the operands go from memory to registers in an order
+// left to the compiler; kept for ragged rows and for operands of 2 GiB and more.
 // X01: the activation bits are read as 0/1 instead of -1/+1 (paper Sec. 3.2).  With a the -1/+1 reading of the same
 // bits, h = (a + 1) / 2 and h.w = (a.w + sum_k w_k) / 2: the product runs unchanged, every lane counts the 1 bits of
-// the weight words it fetches anyway (the two lanes that share a row add theirs up), and the epilogue forms
+// the weight words it reads anyway (the two lanes that share a row add theirs up), and the epilogue forms
 // 0.5 (a.w) + (popcount(w) - K/2), exact in fp32.
-// SPLITK (128-row pinned variant only, K a multiple of 1024): the workgroup has 8 waves; waves 4..7 own the same four
-// wave tiles as waves 0..3 and take the second half of K, so that a grid of one workgroup per CU still puts TWO waves
-// on every SIMD (a single wave per SIMD cannot cover its own operand latencies: measured 28 ns per MFMA against 17-19
-// with two).  Their partial sums (small integers, exact in fp32 in any order) go to waves 0..3 through LDS, 64
-// accumulator registers at a time; waves 0..3 run the epilogue.
-// Grid: x = ceil(M / (64*WM)), y = ceil(N / (64*WN)); block = 256 threads (512 with SPLITK).
-template <int WM, int WN, int ACT, bool ALIGNED, bool PINGPONG = false, bool X01 = false, bool SPLITK = false>
-__global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma32_kernel(const uint32_t* __restrict__ Xp, const uint32_t* __restrict__ Wp,
+// Grid: x = ceil(M / (64*WM)), y = ceil(N / (64*WN)); block = 256 threads; dynamic LDS m32_lds(WM, WN, ACT, PINGPONG).
+template <int WM, int WN, int ACT, bool ALIGNED, bool PINGPONG = false, bool X01 = false>
+__global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __restrict__ Xp, const uint32_t* __restrict__ Wp,
                                                           const float* __restrict__ scale, const float* __restrict__ bias,
                                                           int M, int K, int N, int w32, void* __restrict__ Y, int yw32,
                                                           unsigned int a_bytes, unsigned int b_bytes, int xcd_order,
                                                           const CoopLsm coop) {
-    static_assert(!SPLITK || (WM == 4 && PINGPONG && !X01 && ACT != ACT_LSM_COOP), "split K: 128-row pinned variant, -1/+1 inputs");
-    const int wave_all = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wave = SPLITK ? (wave_all & 3) : wave_all;   // which wave tile of the workgroup
-    const int khalf = SPLITK ? (wave_all >> 2) : 0;        // which half of K
+    extern __shared__ __attribute__((aligned(16))) unsigned char m32_mem[];
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     const int r = lane & 31;   // row of the operand fragment / column of the accumulator fragment
     const int g = lane >> 5;   // k-group of the operand fragment / row-group of the accumulator fragment
@@ -120,140 +199,170 @@ __global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma3
     }
     const int m_base = (tile_m * 2 + (wave >> 1)) * (WM * 32);
     const int n_base = (tile_n * 2 + (wave & 1)) * (WN * 32);
-    // (the cooperative epilogue has workgroup barriers: there a wave without rows or columns of its own runs along on
-    // clamped rows and contributes nothing)
-    if constexpr (ACT != ACT_LSM_COOP) {
+    // (the pinned variants and the cooperative epilogue have workgroup barriers: there a wave without rows or columns of its
+    // own runs along on clamped rows and contributes nothing)
+    if constexpr (ACT != ACT_LSM_COOP && !PINGPONG) {
         if (m_base >= M || n_base >= N) return;   // wave-uniform
     }
 
-    const uint32_t* arow[WM];
-    const uint32_t* brow[WN];
-#pragma unroll
-    for (int f = 0; f < WM; ++f) {
-        const int m = m_base + f * 32 + r;
-        arow[f] = Xp + (size_t)(m < M ? m : M - 1) * w32;
-    }
-#pragma unroll
-    for (int f = 0; f < WN; ++f) {
-        const int n = n_base + f * 32 + r;
-        brow[f] = Wp + (size_t)(n < N ? n : N - 1) * w32;
-    }
-
     // Scale and bias of this lane's columns, requested before the product so that the epilogue does not wait for
-    // them.  Columns past N get scale = bias = 0: their pre-activation is 0, their Sign bit 0 (pad bits stay 0).
+    // them (the pinned variants take them through LDS, in front of the first stage).  Columns past N get scale = bias = 0:
+    // their pre-activation is 0, their Sign bit 0 (pad bits stay 0).
     float sc[WN], bi[WN];
+    if constexpr (!PINGPONG) {
 #pragma unroll
-    for (int f = 0; f < WN; ++f) {
-        const int n = n_base + f * 32 + r;
-        sc[f] = n < N ? (scale ? scale[n] : 1.0f) : 0.0f;
-        bi[f] = n < N ? (bias ? bias[n] : 0.0f) : 0.0f;
+        for (int f = 0; f < WN; ++f) {
+            const int n = n_base + f * 32 + r;
+            sc[f] = n < N ? (scale ? scale[n] : 1.0f) : 0.0f;
+            bi[f] = n < N ? (bias ? bias[n] : 0.0f) : 0.0f;
+        }
     }
 
     int ones[WN];   // X01: 1 bits of this lane's share of the weight rows
 #pragma unroll
     for (int f = 0; f < WN; ++f) ones[f] = 0;
     auto count4 = [&](const uint4 (&b)[WN]) {
-        if constexpr (X01) {
+        if constexpr (X01 && !PINGPONG) {
 #pragma unroll
             for (int f = 0; f < WN; ++f)
                 ones[f] += __builtin_popcount(b[f].x) + __builtin_popcount(b[f].y) + __builtin_popcount(b[f].z) + __builtin_popcount(b[f].w);
         }
     };
 
+    const float acc0 = PINGPONG && !X01 ? 0.25f * (float)K : 0.0f;
     v16f acc[WM][WN];
-    if constexpr (!PINGPONG || WM >= 4) {   // (the 64-row pinned variant starts its accumulators with a zero addend instead)
+#pragma unroll
+    for (int i = 0; i < WM; ++i)
+#pragma unroll
+        for (int j = 0; j < WN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = acc0;
+
+    const int nS = (K + 511) >> 9;
+    static_assert(ALIGNED || !PINGPONG, "the pinned pipelines fetch whole 16-byte pieces of whole super-steps");
+    if constexpr (PINGPONG) {
+        // ---- the wave's share of a stage's loads: 16 rows of the tile each (4 lanes a row), frames rows first.
+        constexpr int kStage = m32_stage(WM, WN), AI = WM, BI = WN;   // load instructions per wave: 64 WM (WN) rows / 16 / 4 waves
+        const i32x4m ars = raw_buffer(Xp, a_bytes), brs = raw_buffer(Wp, b_bytes);
+        const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)m32_mem;
+        const int lrow = lane >> 2, lslot = lane & 3;   // row of the instruction's 16, place in the row
+        const int lsrc = (lslot ^ ((lrow >> 2) & 3)) * 16;
+        int aofs[AI], bofs[BI];
+#pragma unroll
+        for (int i = 0; i < AI; ++i) {
+            const int m = tile_m * (64 * WM) + (wave * AI + i) * 16 + lrow;
+            aofs[i] = (m < M ? m : M - 1) * w32 * 4 + lsrc;
+        }
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+            const int n = tile_n * (64 * WN) + (wave * BI + i) * 16 + lrow;
+            bofs[i] = (n < N ? n : N - 1) * w32 * 4 + lsrc;
+        }
+        auto request = [&](int S, int slot) {   // stage S of K to LDS stage `slot`
+            const uint32_t base = lds0 + (uint32_t)(slot * kStage);
+#pragma unroll
+            for (int i = 0; i < AI; ++i) load_lds16(ars, aofs[i], S * 64, base + (uint32_t)((wave * AI + i) * 16 * kM32RowBytes));
+#pragma unroll
+            for (int i = 0; i < BI; ++i) load_lds16(brs, bofs[i], S * 64, base + (uint32_t)((64 * WM + (wave * BI + i) * 16) * kM32RowBytes));
+        };
+        // ---- the lane's operand words of half-stage h: 16 bytes per fragment row, half 0 from slots 0 and 1, half 1 from 2 and 3
+        const int arow = ((wave >> 1) * (WM * 32) + r) * kM32RowBytes, brow = (64 * WM + (wave & 1) * (WN * 32) + r) * kM32RowBytes;
+        const int so0 = ((0 + g) ^ ((r >> 2) & 3)) * 16, so1 = ((2 + g) ^ ((r >> 2) & 3)) * 16;
+        auto fetch = [&](uint4 (&a)[WM], uint4 (&b)[WN], int slot, int so) {
+            const unsigned char* base = m32_mem + slot * kStage + so;
+#pragma unroll
+            for (int f = 0; f < WN; ++f) b[f] = *reinterpret_cast<const uint4*>(base + brow + f * (32 * kM32RowBytes));
+#pragma unroll
+            for (int f = 0; f < WM; ++f) a[f] = *reinterpret_cast<const uint4*>(base + arow + f * (32 * kM32RowBytes));
+        };
+        // One barrier per stage, in its middle: behind it stage S + 1 is complete in LDS and stage S has been read by every
+        // wave, so its place takes stage S + 3.
+        auto turn = [&](int S) {
+            if (S + 2 < nS) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AI + BI) : "memory");   // stage S + 2 may be on its way
+            else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const uint32_t affine_lds = lds0 + (uint32_t)(kM32Stages * kStage);   // [2][64 WN]: scale, bias
+        {
+            static_assert(WN == 2, "two waves bring the tile's 128 scales, two its biases");
+            const float* src = (wave >> 1) ? bias : scale;
+            const int n = tile_n * (64 * WN) + (wave & 1) * 64 + lane;
+            if (src) load_lds4(raw_buffer(src, (unsigned int)N * 4u), (n < N ? n : N - 1) * 4, 0, affine_lds + (uint32_t)wave * 256u);
+        }
+        auto next_slot = [](int s) { return s == kM32Stages - 1 ? 0 : s + 1; };
+        request(0, 0);
+        if (nS > 1) request(1, 1);
+        if (nS > 2) request(2, 2);
 #pragma unroll
         for (int i = 0; i < WM; ++i)
 #pragma unroll
-            for (int j = 0; j < WN; ++j)
+            for (int j = 0; j < WN; ++j) asm volatile("" : "+v"(acc[i][j]));   // the accumulators are set while the first stage is on its way
+        const ExpandMasks em = expand_masks();
+        int ones_a[WM], ones_b[WN];   // 1 bits of this lane's share of its fragment rows
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    }
-
-    const ExpandConsts ec = expand_consts();
-    const int nS = (K + 511) >> 9;
-    static_assert(ALIGNED || !PINGPONG, "the pinned pipelines fetch whole 16-byte pieces of whole super-steps");
-    const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if constexpr (PINGPONG) {
-        // Buffer addressing: one byte offset per fragment row in a VGPR, the position along K in an SGPR, so the loop
-        // carries no 64-bit address arithmetic.  (The host selects these variants only for operands below 2 GiB.)
-        const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(Xp), 0, (int)a_bytes, 0x00020000);
-        const __amdgpu_buffer_rsrc_t brs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(Wp), 0, (int)b_bytes, 0x00020000);
-        int aoff[WM], boff[WN];
+        for (int f = 0; f < WM; ++f) ones_a[f] = 0;
 #pragma unroll
-        for (int f = 0; f < WM; ++f) {
-            const int m = m_base + f * 32 + r;
-            aoff[f] = ((m < M ? m : M - 1) * w32 + g * 8) * 4;
-        }
-#pragma unroll
-        for (int f = 0; f < WN; ++f) {
-            const int n = n_base + f * 32 + r;
-            boff[f] = ((n < N ? n : N - 1) * w32 + g * 8) * 4;
-        }
-        // the first product into each accumulator takes a zero addend instead of a cleared register
-        auto products = [&](const uint4 (&a)[WM], const uint4 (&b)[WN], bool first) {
-            count4(b);
+        for (int f = 0; f < WN; ++f) ones_b[f] = 0;
+        auto count = [](int& n, uint32_t w) { asm volatile("v_bcnt_u32_b32 %0, %1, %0" : "+v"(n) : "v"(w)); };   // (stays where it is written)
+        auto clear_hi = [&](v8i& d) { d[4] = 0; d[5] = 0; d[6] = 0; d[7] = 0; };   // unused by the 4-bit format
+        // the dwords of a frames word and of a weights word, by class
+        auto frames_piece = [&](v8i& d, uint32_t w, int part) {
+            if (part == 0) d[0] = (int)(w & em.b0);           // 0.5
+            else if (part == 1) d[1] = (int)(w & em.b1);      // 1
+            else if (part == 2) d[2] = (int)(w & em.b2);      // 2
+            else d[3] = (int)((w >> 2) & em.b1);              // 1 (two instructions)
+        };
+        auto weights_piece = [&](v8i& d, uint32_t w, int part) {
+            if (part == 0) d[0] = (int)((w << 2) & em.b2);    // 2 (two instructions)
+            else if (part == 1) d[1] = (int)(w & em.b1);      // 1
+            else if (part == 2) d[2] = (int)((w >> 2) & em.b0);   // 0.5 (the shift serves part 3 too)
+            else d[3] = (int)((w >> 2) & em.b1);              // 1
+        };
+        auto products = [&](const uint4 (&a)[WM], const uint4 (&b)[WN]) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 v8i bx[WN];
 #pragma unroll
-                for (int f = 0; f < WN; ++f) bx[f] = expand_pm1_fp4(word_of(b[f], j), ec);
+                for (int f = 0; f < WN; ++f) {
+                    clear_hi(bx[f]);
+#pragma unroll
+                    for (int part = 0; part < 4; ++part) weights_piece(bx[f], word_of(b[f], j), part);
+                    if constexpr (!X01) count(ones_b[f], word_of(b[f], j));
+                }
 #pragma unroll
                 for (int fm = 0; fm < WM; ++fm) {
-                    const v8i ax = expand_pm1_fp4(word_of(a[fm], j), ec);
+                    v8i ax;
+                    clear_hi(ax);
+#pragma unroll
+                    for (int part = 0; part < 4; ++part) frames_piece(ax, word_of(a[fm], j), part);
+                    count(ones_a[fm], word_of(a[fm], j));
 #pragma unroll
                     for (int fn = 0; fn < WN; ++fn)
-                        acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ax, bx[fn], (first && j == 0) ? zero16 : acc[fm][fn],
-                                                                                    4, 4, 0, 0, 0, 0);
+                        acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ax, bx[fn], acc[fm][fn], 4, 4, 0, 0, 0, 0);
                 }
             }
         };
+        if (nS > 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (AI + BI)) : "memory");
+        else if (nS > 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AI + BI) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        uint4 a0[WM], b0[WN], a1[WM], b1[WN];
+        fetch(a0, b0, 0, so0);
         if constexpr (WM >= 4) {
-            // 128-row wave tiles leave no room for two whole operand sets beside the 128 accumulator registers: the
-            // two sets are the two halves of a super-step (words 0..3 and 4..7 of every lane's share) instead.
-            // Three sets in rotation, fetched two half-steps ahead: with one wave per SIMD (4096 x 2048 outputs fill the
-            // chip exactly once) nothing else covers the memory latency, and one half-step of products is shorter.
-            uint4 a0[WM], b0[WN], a1[WM], b1[WN], a2[WM], b2[WN];
-            const int H = SPLITK ? nS : 2 * nS;   // half-steps of this wave (split K: nS is even, each half has nS / 2 super-steps)
-            if constexpr (SPLITK) {
-#pragma unroll
-                for (int f = 0; f < WM; ++f) arow[f] += khalf * (nS >> 1) * 16;
-#pragma unroll
-                for (int f = 0; f < WN; ++f) brow[f] += khalf * (nS >> 1) * 16;
-            }
-            // (plain pointer loads here: buffer addressing saves the address arithmetic but measured 3 % slower on
-            //  this variant, as did a peeled first round with zero addends: more code to fetch for four rounds)
-            auto fetch = [&](uint4 (&a)[WM], uint4 (&b)[WN], int h) {
-                const int hc = h < H ? h : H - 1;   // past the end: re-read the last half-step (in bounds, unused)
-                const int base = (hc >> 1) * 16 + g * 8 + (hc & 1) * 4;
-#pragma unroll
-                for (int f = 0; f < WM; ++f) a[f] = *reinterpret_cast<const uint4*>(arow[f] + base);
-#pragma unroll
-                for (int f = 0; f < WN; ++f) b[f] = *reinterpret_cast<const uint4*>(brow[f] + base);
-            };
-            // Every fetch is unconditional: a fetch whose only use sits behind a branch gets moved behind that
-            // branch by the compiler, next to its use, and then nothing overlaps.
-            // Issue order inside a half-step, written out and pinned slot by slot.  A wave issues in order, and an
-            // MFMA that finds the pipe busy (32 clocks per 32x32x64) blocks whatever follows it: left to the
-            // compiler's order (expansions in clumps, MFMAs back to back) one wave per SIMD ran at 70 clocks per
-            // MFMA.  Here every MFMA is followed by the 5-6 expansion instructions of an operand needed two to
-            // eight MFMAs later, which issue in its shadow: the frames fragment fm+1 of this step while fm is
-            // multiplied, and the two weights fragments and frames fragment 0 of the NEXT step (taken from the next
-            // register set after the last step of a half-step) spread over the eight slots.
+            // Issue order inside a half-step, written out and pinned slot by slot.  A wave issues in order, and an MFMA that
+            // finds the pipe busy (32 clocks per 32x32x64) blocks whatever follows it.  Here every MFMA is followed by four or
+            // five expansion instructions of operands needed two to eight MFMAs later, which issue in its shadow: the frames
+            // fragment fm+1 of this step while fm is multiplied, and the two weights fragments and frames fragment 0 of the
+            // NEXT step (taken from the next half-stage's words after the last step of a half-stage) spread over the slots.
             static_assert(WM == 4 && WN == 2, "the slot plan below is written for 4 x 2 fragments");
             v8i bx[2][WN];   // expanded weights: [parity of the step][fragment]
             v8i ax[2];       // expanded frames: fragment fm lives in ax[fm & 1]
-            auto piece = [&](v8i& dst, uint32_t w, int part) {   // part 0..2: shifted dwords (2 instructions), 3: unshifted (1)
-                dst[part] = (int)((((part < 3) ? (w << (3 - part)) : w) & ec.sign_mask) | ec.one_bits);
-            };
-            auto clear_hi = [&](v8i& d) { d[4] = 0; d[5] = 0; d[6] = 0; d[7] = 0; };   // unused by the 4-bit format
             clear_hi(ax[0]); clear_hi(ax[1]);
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int f = 0; f < WN; ++f) clear_hi(bx[t][f]);
             auto half_step = [&](const uint4 (&a)[WM], const uint4 (&b)[WN], const uint4 (&an)[WM], const uint4 (&bn)[WN]) {
-                count4(b);
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int pc = j & 1, pn = pc ^ 1;
@@ -262,85 +371,121 @@ __global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma3
                     const uint32_t wb1 = j < 3 ? word_of(b[1], j + 1) : word_of(bn[1], 0);
                     const uint32_t wa0 = j < 3 ? word_of(a[0], j + 1) : word_of(an[0], 0);
                     const uint32_t wa1 = word_of(a[1], j), wa2 = word_of(a[2], j), wa3 = word_of(a[3], j);
+                    auto count_a = [&](int f) { count(ones_a[f], word_of(a[f], j)); };
+                    auto count_b = [&](int f) { if constexpr (!X01) count(ones_b[f], word_of(b[f], j)); };
+                    auto fp = [&](int f, uint32_t w, int p) { frames_piece(ax[f & 1], w, p); };
+                    auto wp = [&](int f, uint32_t w, int p) { weights_piece(bx[pn][f], w, p); };
 #define BNN_MFMA(fm, fn) acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ax[(fm) & 1], bx[pc][fn], acc[fm][fn], 4, 4, 0, 0, 0, 0)
 #define BNN_SLOT_END __builtin_amdgcn_sched_barrier(0)
-                    BNN_MFMA(0, 0); piece(ax[1], wa1, 0); piece(ax[1], wa1, 1); piece(ax[1], wa1, 3); BNN_SLOT_END;
-                    BNN_MFMA(0, 1); piece(ax[1], wa1, 2); piece(bx[pn][0], wb0, 0); piece(bx[pn][0], wb0, 3); BNN_SLOT_END;
-                    BNN_MFMA(1, 0); piece(ax[0], wa2, 0); piece(ax[0], wa2, 1); piece(ax[0], wa2, 3); BNN_SLOT_END;
-                    BNN_MFMA(1, 1); piece(ax[0], wa2, 2); piece(bx[pn][0], wb0, 1); piece(bx[pn][0], wb0, 2); BNN_SLOT_END;
-                    BNN_MFMA(2, 0); piece(ax[1], wa3, 0); piece(ax[1], wa3, 1); piece(ax[1], wa3, 3); BNN_SLOT_END;
-                    BNN_MFMA(2, 1); piece(ax[1], wa3, 2); piece(bx[pn][1], wb1, 0); piece(bx[pn][1], wb1, 3); BNN_SLOT_END;
-                    BNN_MFMA(3, 0); piece(bx[pn][1], wb1, 1); piece(bx[pn][1], wb1, 2); BNN_SLOT_END;
-                    BNN_MFMA(3, 1); BNN_SLOT_END;
+                    BNN_MFMA(0, 0); fp(1, wa1, 0); fp(1, wa1, 1); fp(1, wa1, 2); count_a(0); BNN_SLOT_END;
+                    BNN_MFMA(0, 1); fp(1, wa1, 3); wp(0, wb0, 0); wp(0, wb0, 1); BNN_SLOT_END;
+                    BNN_MFMA(1, 0); fp(2, wa2, 0); fp(2, wa2, 1); fp(2, wa2, 2); count_a(1); BNN_SLOT_END;
+                    BNN_MFMA(1, 1); fp(2, wa2, 3); wp(0, wb0, 2); wp(0, wb0, 3); BNN_SLOT_END;
+                    BNN_MFMA(2, 0); fp(3, wa3, 0); fp(3, wa3, 1); fp(3, wa3, 2); count_a(2); count_b(0); BNN_SLOT_END;
+                    BNN_MFMA(2, 1); fp(3, wa3, 3); wp(1, wb1, 0); wp(1, wb1, 1); BNN_SLOT_END;
                     // frames fragment 0 of the next step overwrites ax[0], which MFMA (2, *) has finished reading
-                    piece(ax[0], wa0, 0); piece(ax[0], wa0, 1); piece(ax[0], wa0, 2); piece(ax[0], wa0, 3); BNN_SLOT_END;
+                    BNN_MFMA(3, 0); fp(0, wa0, 0); fp(0, wa0, 1); fp(0, wa0, 2); count_a(3); count_b(1); BNN_SLOT_END;
+                    BNN_MFMA(3, 1); fp(0, wa0, 3); wp(1, wb1, 2); wp(1, wb1, 3); BNN_SLOT_END;
 #undef BNN_MFMA
 #undef BNN_SLOT_END
                 }
             };
-            // Every fetch is unconditional: a fetch whose only use sits behind a branch gets moved behind that
-            // branch by the compiler, next to its use, and then nothing overlaps.
-            fetch(a0, b0, 0);
-            fetch(a1, b1, 1);
             {   // operands of the very first step
-                const uint32_t wb0 = word_of(b0[0], 0), wb1 = word_of(b0[1], 0), wa0 = word_of(a0[0], 0);
 #pragma unroll
-                for (int part = 0; part < 4; ++part) { piece(bx[0][0], wb0, part); piece(bx[0][1], wb1, part); piece(ax[0], wa0, part); }
+                for (int part = 0; part < 4; ++part) {
+                    weights_piece(bx[0][0], word_of(b0[0], 0), part);
+                    weights_piece(bx[0][1], word_of(b0[1], 0), part);
+                    frames_piece(ax[0], word_of(a0[0], 0), part);
+                }
             }
-            int h = 0;
-            for (; h + 2 < H; h += 3) {
-                fetch(a2, b2, h + 2);
+            int slot = 0, S = 0;
+            do {   // (K > 0: at least one stage)
+                const int nslot = next_slot(slot);
+                fetch(a1, b1, slot, so1);
                 __builtin_amdgcn_sched_barrier(0);
                 half_step(a0, b0, a1, b1);
-                pin_loaded(sc, bi);
                 __builtin_amdgcn_sched_barrier(0);
-                fetch(a0, b0, h + 3);
+                turn(S);
+                fetch(a0, b0, S + 1 < nS ? nslot : slot, so0);   // (behind the last stage: read again, unused)
+                if (S + 3 < nS) request(S + 3, slot);
                 __builtin_amdgcn_sched_barrier(0);
-                half_step(a1, b1, a2, b2);
+                half_step(a1, b1, a0, b0);
                 __builtin_amdgcn_sched_barrier(0);
-                fetch(a1, b1, h + 4);
-                __builtin_amdgcn_sched_barrier(0);
-                half_step(a2, b2, a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            if (h < H) half_step(a0, b0, a1, b1);       // one or two half-steps left, already fetched
-            if (h + 1 < H) half_step(a1, b1, a2, b2);
+                slot = nslot;
+            } while (++S < nS);
         } else {
-            // two whole super-steps in registers; set 0 holds the even ones at first, then the sets alternate
-            uint4 a0l[WM], a0h[WM], b0l[WN], b0h[WN], a1l[WM], a1h[WM], b1l[WN], b1h[WN];
-            auto fetch = [&](uint4 (&al)[WM], uint4 (&ah)[WM], uint4 (&bl)[WN], uint4 (&bh)[WN], int S) {
-                const int so = (S < nS ? S : nS - 1) * 64;
-#pragma unroll
-                for (int f = 0; f < WM; ++f) { al[f] = load16(ars, aoff[f], so); ah[f] = load16(ars, aoff[f], so + 16); }
-#pragma unroll
-                for (int f = 0; f < WN; ++f) { bl[f] = load16(brs, boff[f], so); bh[f] = load16(brs, boff[f], so + 16); }
+            int slot = 0, S = 0;
+            do {   // (K > 0: at least one stage)
+                const int nslot = next_slot(slot);
+                fetch(a1, b1, slot, so1);
+                __builtin_amdgcn_sched_barrier(0);
+                products(a0, b0);
+                __builtin_amdgcn_sched_barrier(0);
+                turn(S);
+                fetch(a0, b0, S + 1 < nS ? nslot : slot, so0);
+                if (S + 3 < nS) request(S + 3, slot);
+                __builtin_amdgcn_sched_barrier(0);
+                products(a1, b1);
+                __builtin_amdgcn_sched_barrier(0);
+                slot = nslot;
+            } while (++S < nS);
+        }
+        // The counts join the sum (see "0/1 operands" above) as one more product per fragment, in bfloat16, eight bits of a count
+        // per element of k: acc - popcount(frame) / 2 [- popcount(weights) / 2].
+        {
+            typedef __bf16 bf16x8m __attribute__((ext_vector_type(8)));
+            typedef uint32_t u32x4m __attribute__((ext_vector_type(4)));
+            auto hi = [](float v) { return __float_as_uint(v) >> 16; };   // (eight significant bits: exact)
+            const uint32_t h0 = hi(-0.5f), h1 = hi(-128.0f), h2 = hi(-32768.0f);
+            auto share = [&](int ones, uint32_t (&q)[3]) {
+                const uint32_t c = (uint32_t)(ones + __shfl_xor(ones, 32, kWave));
+                q[0] = hi((float)(c & 255u));
+                q[1] = hi((float)((c >> 8) & 255u));
+                q[2] = hi((float)(c >> 16));
             };
-            fetch(a0l, a0h, b0l, b0h, 0);
-            fetch(a1l, a1h, b1l, b1h, 1);
-            __builtin_amdgcn_sched_barrier(0);
-            products(a0l, b0l, true);
-            products(a0h, b0h, false);
-            __builtin_amdgcn_sched_barrier(0);
-            int S = 1;   // set 1 holds super-step S, set 0 is free
-            for (; S + 1 < nS; S += 2) {
-                fetch(a0l, a0h, b0l, b0h, S + 1);
-                __builtin_amdgcn_sched_barrier(0);
-                products(a1l, b1l, false);
-                products(a1h, b1h, false);
-                pin_loaded(sc, bi);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch(a1l, a1h, b1l, b1h, S + 2);
-                __builtin_amdgcn_sched_barrier(0);
-                products(a0l, b0l, false);
-                products(a0h, b0h, false);
-                __builtin_amdgcn_sched_barrier(0);
+            bf16x8m cb[WN];
+#pragma unroll
+            for (int f = 0; f < WN; ++f) {
+                uint32_t q[3] = {0u, 0u, 0u};
+                if constexpr (!X01) share(ones_b[f], q);
+                cb[f] = __builtin_bit_cast(bf16x8m, g == 0 ? u32x4m{h0 | (h1 << 16), h2 | (q[0] << 16), q[1] | (q[2] << 16), 0u} : u32x4m{0u, 0u, 0u, 0u});
             }
-            if (S < nS) {   // one super-step left, already in set 1
-                products(a1l, b1l, false);
-                products(a1h, b1h, false);
+#pragma unroll
+            for (int f = 0; f < WM; ++f) {
+                uint32_t q[3];
+                share(ones_a[f], q);
+                const bf16x8m ca = __builtin_bit_cast(bf16x8m, g == 0 ? (X01 ? u32x4m{q[0] | (q[1] << 16), q[2], 0u, 0u}
+                                                                            : u32x4m{q[0] | (q[1] << 16), q[2] | (h0 << 16), h1 | (h2 << 16), 0u})
+                                                                     : u32x4m{0u, 0u, 0u, 0u});
+#pragma unroll
+                for (int fn = 0; fn < WN; ++fn) acc[f][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca, cb[fn], acc[f][fn], 0, 0, 0);
             }
         }
+        if constexpr (ACT != ACT_SIGN) __syncthreads();   // the epilogue takes the stages' place
+        if constexpr (ACT != ACT_LSM_COOP) {
+            if (m_base >= M || n_base >= N) return;   // wave-uniform
+        }
+        const float* affine_s = reinterpret_cast<const float*>(m32_mem + kM32Stages * kStage) + (wave & 1) * (32 * WN) + r;
+#pragma unroll
+        for (int f = 0; f < WN; ++f) {
+            const bool in = n_base + f * 32 + r < N;
+            sc[f] = in ? (scale ? affine_s[f * 32] : 1.0f) : 0.0f;
+            bi[f] = in ? (bias ? affine_s[64 * WN + f * 32] : 0.0f) : 0.0f;
+        }
     } else {
+        const ExpandConsts ec = expand_consts();
+        const uint32_t* arow[WM];
+        const uint32_t* brow[WN];
+#pragma unroll
+        for (int f = 0; f < WM; ++f) {
+            const int m = m_base + f * 32 + r;
+            arow[f] = Xp + (size_t)(m < M ? m : M - 1) * w32;
+        }
+#pragma unroll
+        for (int f = 0; f < WN; ++f) {
+            const int n = n_base + f * 32 + r;
+            brow[f] = Wp + (size_t)(n < N ? n : N - 1) * w32;
+        }
         Raw8 araw[WM], braw[WN];
 #pragma unroll
         for (int f = 0; f < WM; ++f) araw[f] = load_raw8<ALIGNED>(arow[f], 0, g, w32);
@@ -383,75 +528,61 @@ __global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma3
         }
     }
 
-    if constexpr (SPLITK) {
-        // the second half of K joins the first: 64 accumulator registers per round through 64 KiB of LDS
-        typedef float f32x4 __attribute__((ext_vector_type(4)));
-        __shared__ f32x4 xch[4][16][kWave];   // [wave tile][four registers][lane]
-#pragma unroll
-        for (int round = 0; round < 2; ++round) {
-            if (khalf == 1) {
-#pragma unroll
-                for (int fmh = 0; fmh < 2; ++fmh)
-#pragma unroll
-                    for (int fn = 0; fn < WN; ++fn)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const v16f& c = acc[2 * round + fmh][fn];
-                            xch[wave][(fmh * 2 + fn) * 4 + q][lane] = f32x4{c[4 * q], c[4 * q + 1], c[4 * q + 2], c[4 * q + 3]};
-                        }
-            }
-            __syncthreads();
-            if (khalf == 0) {
-#pragma unroll
-                for (int fmh = 0; fmh < 2; ++fmh)
-#pragma unroll
-                    for (int fn = 0; fn < WN; ++fn)
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const f32x4 p = xch[wave][(fmh * 2 + fn) * 4 + q][lane];
-                            v16f& c = acc[2 * round + fmh][fn];
-                            c[4 * q] += p[0]; c[4 * q + 1] += p[1]; c[4 * q + 2] += p[2]; c[4 * q + 3] += p[3];
-                        }
-            }
-            if (round == 0) __syncthreads();   // everything read before the second round overwrites it
-        }
-        if (khalf == 1) return;   // wave-uniform; no barrier follows
-    }
-
     // ---- epilogue.  Accumulator fragment (fm, fn), register v of lane (r, g) is
     //      dot[m_base + 32 fm + 8 (v/4) + 4 g + v%4][n_base + 32 fn + r] + pad.
     const float pad = (float)(nS * 512 - K);
+    constexpr float kUnit = PINGPONG ? (X01 ? 2.0f : 4.0f) : 1.0f;   // what the accumulators are in units of
     float half_wsum[WN];   // X01: popcount(w) - K/2 = (sum_k w_k) / 2 of this lane's columns
 #pragma unroll
     for (int f = 0; f < WN; ++f) {
         half_wsum[f] = 0.0f;
-        if constexpr (X01) half_wsum[f] = (float)(ones[f] + __shfl_xor(ones[f], 32, kWave)) - 0.5f * (float)K;
+        if constexpr (X01 && !PINGPONG) half_wsum[f] = (float)(ones[f] + __shfl_xor(ones[f], 32, kWave)) - 0.5f * (float)K;
     }
     auto dot_of = [&](float a, int fn) -> float {
         const float d = ALIGNED ? a : a - pad;   // whole super-steps: no pad
-        if constexpr (X01) return __builtin_fmaf(d, 0.5f, half_wsum[fn]);
+        if constexpr (PINGPONG) return a * kUnit;
+        else if constexpr (X01) return __builtin_fmaf(d, 0.5f, half_wsum[fn]);
         else return d;
     };
     if constexpr (ACT == ACT_SIGN) {
+        // A lane gathers the bits of its column over the 32 frames of two fragments, two instructions a bit: the fused multiply-
+        // add of the negated layer, whose sign bit is the output, and a funnel shift that takes it in.  The 32 x 32 bits of
+        // a half wave are then transposed (TransposeBits) and leave as one word, two where the row allows it, per lane: a third
+        // of the instructions of a compare, two v_writelane and their wait states per bit, and two stores instead of eight.
+        float nsc[WN], nbi[WN];
+#pragma unroll
+        for (int f = 0; f < WN; ++f) {
+            const SignColumn c = sign_column(sc[f], bi[f], kUnit);
+            nsc[f] = c.neg_scale;
+            nbi[f] = c.neg_bias;
+        }
+        const TransposeBits tr(lane);
         uint32_t* Yw = (uint32_t*)Y;
+        const int wcol = n_base >> 5;
+        const bool pairs = (yw32 & 1) == 0 && (reinterpret_cast<uintptr_t>(Y) & 7) == 0;
 #pragma unroll
-        for (int fn = 0; fn < WN; ++fn) {
-            const int wcol = (n_base >> 5) + fn;
+        for (int p = 0; p < WM / 2; ++p) {
+            uint32_t w[WN];
 #pragma unroll
-            for (int fm = 0; fm < WM; ++fm) {
-                // One ballot is two output words: lanes 0..31 are the 32 outputs of frame row 8(v/4)+v%4,
-                // lanes 32..63 the same outputs of the frame 4 rows below.  Word v is parked in lane v
-                // (and 32+v) of one register, so the whole fragment leaves with a single store.
-                int words = 0;
+            for (int fn = 0; fn < WN; ++fn) {
+                w[fn] = 0u;
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float dot = dot_of(acc[fm][fn][v], fn);
-                    const unsigned long long b = __builtin_amdgcn_ballot_w64(sign_bit(affine(sc[fn], dot, bi[fn])));
-                    write_lane_pair(words, (uint32_t)b, (uint32_t)(b >> 32), v, 32 + v);
+                for (int i = 31; i >= 0; --i) {   // bit i: frame row 8(v/4)+4g+v%4 of fragment 2p + i/16, v = i%16
+                    const float a = acc[2 * p + (i >> 4)][fn][i & 15];
+                    w[fn] = __builtin_amdgcn_alignbit(w[fn], __float_as_uint(affine(nsc[fn], PINGPONG ? a : dot_of(a, fn), nbi[fn])), 31);
                 }
-                if (r < 16) {
-                    const int m = m_base + fm * 32 + 8 * (r >> 2) + 4 * g + (r & 3);
-                    if (m < M && wcol < yw32) Yw[(size_t)m * yw32 + wcol] = (uint32_t)words;
+            }
+            tr.run(w);
+            const int v = r & 15, m = m_base + (2 * p + (r >> 4)) * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
+            if (m < M) {
+                uint32_t* y = Yw + (size_t)m * yw32 + wcol;
+                static_assert(WN == 2, "two words per lane");
+                if (pairs && wcol + 1 < yw32) {
+                    *reinterpret_cast<uint2*>(y) = make_uint2(w[0], w[1]);
+                } else {
+#pragma unroll
+                    for (int fn = 0; fn < WN; ++fn)
+                        if (wcol + fn < yw32) y[fn] = w[fn];
                 }
             }
         }
@@ -465,12 +596,11 @@ __global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma3
         // cache of this launch can hold an older copy of a pair, because nothing reads a pair before its flag is up
         // and what earlier launches left in the caches is dropped at the kernel boundary.  The wait is bounded.
         static_assert(WN == 2, "the transposing epilogue is written for 64-column wave tiles");
-        constexpr int LDW = 32 * WN + 4;
+        constexpr int LDW = kM32Ldw;
         constexpr int ROWS = 32 * WM;                          // rows of a wave; the workgroup has 2 ROWS
-        __shared__ __attribute__((aligned(16))) uint32_t stage[4][32 * LDW];
-        __shared__ float2 wave_part[4][ROWS];
-        __shared__ float lse_s[2 * ROWS];
-        uint32_t* st = stage[wave];
+        uint32_t* st = reinterpret_cast<uint32_t*>(m32_mem) + wave * (32 * LDW);
+        float2(*wave_part)[ROWS] = reinterpret_cast<float2(*)[ROWS]>(m32_mem + 4 * 32 * LDW * 4);   // [4][ROWS]
+        float* lse_s = reinterpret_cast<float*>(m32_mem + 4 * 32 * LDW * 4 + 4 * ROWS * 8);          // [2 ROWS]
         const int c4 = (lane & 15) * 4;
         const int T = (int)gridDim.y;
         const float ninf = -__builtin_inff();
@@ -610,9 +740,8 @@ __global__ __launch_bounds__(SPLITK ? 512 : 256, SPLITK ? 1 : 2) void binx_mfma3
         // store 128-byte pieces.  Each wave turns 32 rows x (32 WN) columns at a time through its own slice
         // of LDS so that 16 lanes write 256 contiguous bytes of a row (16 bytes per lane).
         static_assert(WN == 2, "the transposing epilogue is written for 64-column wave tiles");
-        constexpr int LDW = 32 * WN + 4;                       // padded row length in words
-        __shared__ __attribute__((aligned(16))) uint32_t stage[4][32 * LDW];
-        uint32_t* st = stage[wave];
+        constexpr int LDW = kM32Ldw;
+        uint32_t* st = reinterpret_cast<uint32_t*>(m32_mem) + wave * (32 * LDW);
         const bool rows_vec = ((N & 3) == 0) && ((reinterpret_cast<uintptr_t>(Y) & 15) == 0);
         const int c4 = (lane & 15) * 4;                        // this lane's 4 columns of the 64
 #pragma unroll

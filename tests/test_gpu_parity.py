@@ -982,6 +982,42 @@ def test_binx_sign_split_k(G, bnn, oracle, M, K, N, wb):
     assert np.array_equal(G.words_to_host(Y_off, wb), want)
 
 
+@pytest.mark.parametrize("x01", [False, True])
+@pytest.mark.parametrize("wm", [2, 4])
+@pytest.mark.parametrize("M,K,N", [(1, 512, 1), (257, 1024, 129), (255, 1536, 127), (300, 2048, 260), (129, 2560, 97), (513, 3584, 33)])
+def test_binary_layer_stages_and_special_scales(G, bnn, oracle, M, K, N, wm, x01):
+    """The 32x32x64 kernel's fetch through LDS with one to seven stages of 512 bits, on tiles ragged on both sides, and the Sign
+    outputs of columns whose scale or bias is NaN, infinite, zero of either sign, denormal or next to the largest float; rows of
+    all ones and all zeros give the largest and smallest counts."""
+    aw, bw = _bin_operands(oracle, M + K + N, M, K, N, 32)
+    aw[0] = 0xFFFFFFFF
+    aw[M // 2] = 0
+    bw[N - 1] = 0xFFFFFFFF
+    _, _, scale, bias = _rand_layer(M + 3 * N, 1, 1, N)
+    special = np.array([np.nan, np.inf, -np.inf, 0.0, -0.0, 1e-45, -1e-45, 3.4e38, -3.4e38, 1.5e30, 1.0, 2e38], np.float32)
+    pairs = [(a, b) for a in special for b in special]
+    for i, (a, b) in enumerate(pairs[(M + wm) % 7:][:max(0, N - 2)]):
+        scale[1 + i], bias[1 + i] = a, b
+    fn = bnn.bnn_layer_binw_binx01 if x01 else bnn.bnn_layer_binw_binx
+    form = oracle.layer_binw_binx01 if x01 else oracle.layer_binw_binx
+    dev = [G.to_dev(v) for v in (aw, bw, scale, bias)]
+    bnn.bnn_set_option(bnn.BNN_OPT_MFMA_SHAPE, 32)
+    bnn.bnn_set_option(bnn.BNN_OPT_MFMA32_WM, wm)
+    try:
+        out = torch.full((M, (N + 31) // 32), -1, dtype=torch.int32, device="cuda")
+        raw = torch.empty((M, N), dtype=torch.int32, device="cuda")
+        st = torch.cuda.current_stream().cuda_stream
+        fn(dev[0].data_ptr(), dev[1].data_ptr(), dev[2].data_ptr(), dev[3].data_ptr(), M, K, N, bnn.BNN_ACT_SIGN, 32, out.data_ptr(), st)
+        fn(dev[0].data_ptr(), dev[1].data_ptr(), 0, 0, M, K, N, bnn.BNN_ACT_RAW_I32, 32, raw.data_ptr(), st)
+        torch.cuda.synchronize()
+    finally:
+        bnn.bnn_set_option(bnn.BNN_OPT_MFMA_SHAPE, 0)
+        bnn.bnn_set_option(bnn.BNN_OPT_MFMA32_WM, 0)
+    with np.errstate(all="ignore"):
+        assert np.array_equal(raw.cpu().numpy(), form(aw, bw, K, None, None, "raw", 32))
+        assert np.array_equal(G.words_to_host(out, 32), form(aw, bw, K, scale, bias, "sign", 32))
+
+
 class _cooperative:
     """BNN_OPT_COOPERATIVE for the duration of a test (the test process runs one stream at a time, as the option asks)."""
 
