@@ -739,6 +739,20 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
     s.total = s.undecided + (act == BNN_ACT_SIGN ? round_up((size_t)M * tiles * kUndecidedRecord, 256) : 0);
     return s;
 }
+// Frames of up to 4096 elements in 16-byte pieces are held in registers, in as many groups of 256 as they need (a power of
+// two: what a frame does not fill costs loads of its first elements again).  Longer ones would take more registers than
+// leave two waves per SIMD, ragged ones a load per element.
+template <int D>
+void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* planes, void* meta, hipStream_t st) {
+    const dim3 grid((unsigned)((M + 3) / 4));
+    const bool vec = (K & 3) == 0 && aligned(X, 16);
+    if (!vec) realx_quantize_nat_kernel<D, false, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else if (kpad <= 512) realx_quantize_nat_kernel<D, true, 2><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else if (kpad <= 1024) realx_quantize_nat_kernel<D, true, 4><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else if (kpad <= 2048) realx_quantize_nat_kernel<D, true, 8><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else if (kpad <= 4096) realx_quantize_nat_kernel<D, true, 16><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else realx_quantize_nat_kernel<D, true, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+}
 template <int D>
 int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int Mi, int Ki, int Ni, int w32,
                          void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st) {
@@ -748,10 +762,7 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     void* meta = mem + sc.meta;
     unsigned char* undecided = reinterpret_cast<unsigned char*>(mem + sc.undecided);
     const int qbits = D == 3 ? slab_quant_bits(Ki) : kQuantBits4;
-    if ((Ki & 3) == 0 && aligned(X, 16))
-        realx_quantize_nat_kernel<D, true><<<dim3((Mi + 3) / 4), dim3(256), 0, st>>>(X, Mi, Ki, kpad, qbits, planes, meta);
-    else
-        realx_quantize_nat_kernel<D, false><<<dim3((Mi + 3) / 4), dim3(256), 0, st>>>(X, Mi, Ki, kpad, qbits, planes, meta);
+    launch_quantize<D>(X, Mi, Ki, kpad, qbits, planes, meta, st);
     const int64_t eb = ((int64_t)Ni * (kpad / 16) + 255) / 256;
     bits_to_bytes_kernel<<<(unsigned)(eb < 16384 ? eb : 16384), 256, 0, st>>>(static_cast<const uint32_t*>(Wp), Ni, Ki, w32, kpad, bytes);
     static std::atomic<uint64_t> allowed;

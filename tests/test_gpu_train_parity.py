@@ -201,6 +201,21 @@ def test_layer_binw_realx_on_the_int8_matrix_cores(G, bnn, oracle, M, K, N, wb):
     assert np.all(np.abs(got.astype(np.float64) - want) <= tol)
 
 
+@pytest.mark.parametrize("K", [4, 508, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 513])
+@pytest.mark.parametrize("M", [1, 5])
+def test_layer_binw_realx_int8_row_lengths(G, bnn, oracle, M, K):
+    """Both sides of every length at which the quantisation takes another number of registers, and a ragged length: the
+    same bound.  The largest element is the frame's last one, so a tail left out shows in every digit."""
+    N = 33
+    rng = np.random.default_rng(M + K)
+    X = rng.standard_normal((M, K)).astype(np.float32)
+    X[:, -1] = 7.5
+    Wp = oracle.pack_sign(rng.uniform(-1, 1, (N, K)).astype(np.float32), 32)
+    _, acc64 = oracle.realx_acc(X, oracle.unpack_pm1(Wp, K, 32))
+    got = _realx_i8(G, bnn, G.to_dev(X), G.to_dev(Wp), M, K, N, 32)
+    assert np.all(np.abs(got.astype(np.float64) - acc64) <= K * 2.0 ** -27 * 7.5 + 2.0 ** -23 * np.abs(acc64))
+
+
 def test_layer_binw_realx_int8_rows_that_cannot_be_quantised(G, bnn, oracle):
     """Frames with NaN, Inf or values beyond 2^90 take the fp32 sum in ascending k: the bits of bnn_layer_binw_realx."""
     M, K, N, wb = 140, 700, 300, 32
