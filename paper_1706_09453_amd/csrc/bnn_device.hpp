@@ -32,6 +32,22 @@ struct CoopLsm {
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
+typedef int i32x4m __attribute__((ext_vector_type(4)));
+// 16 bytes per lane from byte `voff` (per lane) + `soff` (wave-uniform) of a buffer to LDS: lane i's go to lds + 16 i.  The
+// request is counted by vmcnt only: whoever reads the LDS waits for it and then crosses a barrier.  (Written out because the
+// compiler, not knowing which stage a later LDS read belongs to, makes every read wait for every such load.)
+__device__ __forceinline__ void load_lds16(i32x4m rsrc, int voff, int soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+// the same with 4 bytes per lane: lane i's go to lds + 4 i
+__device__ __forceinline__ void load_lds4(i32x4m rsrc, int voff, int soff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+}
+__device__ __forceinline__ i32x4m raw_buffer(const void* p, unsigned int bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return i32x4m{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
+}
+
 // Eq. 3 of the paper: +1 exactly when v > 0 (0, -0 and NaN give -1, i.e. bit 0).
 __device__ __forceinline__ bool sign_bit(float v) { return v > 0.0f; }
 

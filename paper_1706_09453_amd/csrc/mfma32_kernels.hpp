@@ -150,21 +150,6 @@ __host__ __device__ constexpr unsigned m32_lds(int WM, int WN, int ACT, bool PIN
     if (ACT == ACT_LSM_COOP) epi += 4u * 32u * (unsigned)WM * 8u + 64u * (unsigned)WM * 4u;
     return loop > epi ? loop : epi;
 }
-typedef int i32x4m __attribute__((ext_vector_type(4)));
-// 16 bytes per lane from byte `voff` (per lane) + `soff` (wave-uniform) of a buffer to LDS: lane i's go to lds + 16 i.  The
-// request is counted by vmcnt only: whoever reads the LDS waits for it and then crosses a barrier.  (Written out because the
-// compiler, not knowing which stage a later LDS read belongs to, makes every read wait for every such load.)
-__device__ __forceinline__ void load_lds16(i32x4m rsrc, int voff, int soff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
-// the same with 4 bytes per lane: lane i's go to lds + 4 i
-__device__ __forceinline__ void load_lds4(i32x4m rsrc, int voff, int soff, uint32_t lds) {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
-}
-__device__ __forceinline__ i32x4m raw_buffer(const void* p, unsigned int bytes) {
-    const uint64_t a = reinterpret_cast<uint64_t>(p);
-    return i32x4m{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
-}
 
 // PINGPONG (aligned rows only): the fetch described above, with the issue order pinned by scheduling barriers and, for 128-row
 // wave tiles (WM = 4), written out instruction slot by slot.  Without it the operands go from memory to registers in an order

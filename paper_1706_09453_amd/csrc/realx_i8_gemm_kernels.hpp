@@ -16,11 +16,13 @@
 // all exact in int32 (K <= 8192: below 2^27 each).  A fragment of b is read once from LDS and shifted in registers.
 //
 // Layout.  Planes [digit][frame][kpad] and weight bytes [output][kpad] (0 or 1), both in natural k order, kpad = K
-// rounded up to 64, zeros past K.  The product kernel is the pipeline of realw_split_kernels.hpp (steps of 64 k = 64
-// bytes of a row, two LDS buffers, loads of step j + 2 in flight, one barrier per step, memory instructions between
-// MFMAs): 2 x 2 waves of 64 frames x 128 outputs each, 2 x 4 accumulator fragments of 32 x 32, twice.
+// rounded up to 64, zeros past K.  The product kernel takes steps of 64 k = 64 bytes of a row: three LDS stages filled by loads that write LDS
+// directly, two steps in flight, one barrier per step, one memory instruction between two MFMAs.  (Loads to registers and LDS
+// stores, two stages: 4096 x 2048 x 2048 70 -> 62 us, 2048 outputs x 2048 x 4096 104 -> 91.)  2 x 2 waves of 64 frames x
+// 128 outputs each, 2 x 4 accumulator fragments of 32 x 32, twice.
 #pragma once
 
+#include <type_traits>
 #include <utility>
 
 #include "realx_slab_kernels.hpp"
@@ -39,7 +41,8 @@ constexpr int kI8Threads = 256;
 constexpr int kI8StageB = kI8TileN * kI8RowBytes;  // 16384
 __host__ __device__ constexpr int i8_stage_a(int digits) { return digits * kI8TileM * kI8RowBytes; }
 __host__ __device__ constexpr int i8_stage(int digits) { return i8_stage_a(digits) + kI8StageB; }             // 40960 / 49152
-__host__ __device__ constexpr unsigned i8_gemm_lds(int digits) { return 2u * (unsigned)i8_stage(digits); }    // 81920 / 98304
+constexpr int kI8Stages = 3;
+__host__ __device__ constexpr unsigned i8_gemm_lds(int digits) { return (unsigned)(kI8Stages * i8_stage(digits)); }   // 122880 / 147456
 __host__ __device__ inline int i8_kpad(int K) { return (K + kI8KStep - 1) / kI8KStep * kI8KStep; }
 
 // The outputs the filter could not decide, per frame and tile of 256 outputs: a record of 32 bytes, byte 0 = how many
@@ -202,9 +205,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
     static_assert(D == 3 || D == 4, "three digits for Sign layers, four in front of the log-Softmax");
     extern __shared__ __attribute__((aligned(16))) unsigned char i8_lds[];
     constexpr int WM = 2, WN = 4;
-    constexpr int LR = kI8Threads / 4;                       // rows one load instruction of the workgroup covers: 64
-    constexpr int AL = kI8TileM / LR, BL = kI8TileN / LR;     // 2, 4
-    constexpr int NL = D * AL + BL;                           // loads per thread and step: 10 / 12
+    constexpr int NL = 2 * D + 4;                             // loads per wave and step, of 16 rows each: 10 / 12
     constexpr int NR = D * WM + WN;                           // fragment reads per wave and block: 10 / 12
     constexpr int NM = D * WM * WN;                           // MFMAs per wave and block: 24 / 32
     constexpr int kStageA = i8_stage_a(D), kStage = i8_stage(D);
@@ -216,34 +217,28 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);
 
-    // ---- the thread's share of a step's loads: row (tid / 4) + 64 j, slot tid % 4
-    const int lrow = tid >> 2, lslot = tid & 3;
-    const int8_t* srcA[AL];
-    const int8_t* srcB[BL];
+    // ---- the wave's share of a step's loads, 16 rows each (four lanes a row): load i < 2 D is digit i / 2, frames
+    //      32 wave + 16 (i % 2) .. of the tile; load 2 D + j its weight rows 64 wave + 16 j ...  One buffer per digit plane
+    //      and one for the weights, over the rows of the tile (rows past the end: the last one again).
+    const int lrow = lane >> 2, lsrc = ((lane & 3) ^ ((lrow >> 2) & 3)) * 16;
+    const int rows_a = min(M - m_tile, kI8TileM), rows_b = min(N - n_tile, kI8TileN);
+    i32x4m ars[D];
 #pragma unroll
-    for (int j = 0; j < AL; ++j) {
-        const int m = m_tile + lrow + LR * j;
-        srcA[j] = planes + (size_t)(m < M ? m : M - 1) * kpad + lslot * 16;
-    }
+    for (int d = 0; d < D; ++d) ars[d] = raw_buffer(planes + ((size_t)d * M + m_tile) * kpad, (unsigned int)(rows_a * kpad));
+    const i32x4m brs = raw_buffer(Bb + (size_t)n_tile * kpad, (unsigned int)(rows_b * kpad));
+    int aofs[2], bofs[4];
 #pragma unroll
-    for (int j = 0; j < BL; ++j) {
-        const int n = n_tile + lrow + LR * j;
-        srcB[j] = Bb + (size_t)(n < N ? n : N - 1) * kpad + lslot * 16;
-    }
-    const size_t planeA = (size_t)M * kpad;
-    const int st_off = lrow * kI8RowBytes + ((lslot ^ ((lrow >> 2) & 3)) << 4);
-    // load i: digit i / AL, frames row block i % AL for i < D AL; then weights row block i - D AL
-    struct Loads { u32x4 v[NL]; };
-    auto gload_one = [&](Loads& L, int step, int i) {
-        const int off = step * kI8KStep;
-        if (i < D * AL) L.v[i] = *reinterpret_cast<const u32x4*>(srcA[i < D * AL ? i % AL : 0] + (i / AL) * planeA + off);
-        else L.v[i] = *reinterpret_cast<const u32x4*>(srcB[i < D * AL ? 0 : i - D * AL] + off);
-    };
-    auto lstore_one = [&](unsigned char* stage, const Loads& L, int i) {
-        if (i < D * AL)
-            *reinterpret_cast<u32x4*>(stage + (i / AL) * (kI8TileM * kI8RowBytes) + (i % AL) * (LR * kI8RowBytes) + st_off) = L.v[i];
+    for (int i = 0; i < 2; ++i) aofs[i] = min(32 * wave + 16 * i + lrow, rows_a - 1) * kpad + lsrc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bofs[i] = min(64 * wave + 16 * i + lrow, rows_b - 1) * kpad + lsrc;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)i8_lds;
+    auto request_one = [&](int step, uint32_t stage, int i) {
+        if (i < 2 * D)
+            load_lds16(ars[i < 2 * D ? i / 2 : 0], aofs[i % 2], step * kI8KStep,
+                       stage + (uint32_t)((i / 2) * (kI8TileM * kI8RowBytes) + (32 * wave + 16 * (i % 2)) * kI8RowBytes));
         else
-            *reinterpret_cast<u32x4*>(stage + kStageA + (i - D * AL) * (LR * kI8RowBytes) + st_off) = L.v[i];
+            load_lds16(brs, bofs[i < 2 * D ? 0 : i - 2 * D], step * kI8KStep,
+                       stage + (uint32_t)(kStageA + (64 * wave + 16 * (i - 2 * D)) * kI8RowBytes));
     };
 
     // ---- the wave's operand fragments of block h (0 or 1) of a stage: digit fragments, then weight fragments
@@ -270,82 +265,54 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0;
 
-    auto products = [&](const Frags& F) {
+    // One block of 32 k, written out MFMA by MFMA and pinned: behind each of the first ones a fragment read of the next
+    // block, behind the last ones (REQ) a load of step `step` to `stage`.
+    auto block = [&](const Frags& now, Frags& next, const unsigned char* rd, int rd_h, auto req, int step, uint32_t stage) {
+        constexpr bool REQ = decltype(req)::value;
         v4i32g bneg[WN];   // -128 b: the byte 1 becomes 0x80
 #pragma unroll
-        for (int fn = 0; fn < WN; ++fn) bneg[fn] = F.b[fn] << 7;
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-#pragma unroll
-            for (int fm = 0; fm < WM; ++fm)
-#pragma unroll
-                for (int fn = 0; fn < WN; ++fn)
-                    acc[d >> 1][fm][fn] =
-                        __builtin_amdgcn_mfma_i32_32x32x32_i8(F.a[d][fm], (d & 1) ? bneg[fn] : F.b[fn], acc[d >> 1][fm][fn], 0, 0, 0);
+        for (int i = 0; i < NM; ++i) {
+            const int d = i / (WM * WN), fm = (i / WN) % WM, fn = i % WN;
+            acc[d >> 1][fm][fn] =
+                __builtin_amdgcn_mfma_i32_32x32x32_i8(now.a[d][fm], (d & 1) ? bneg[fn] : now.b[fn], acc[d >> 1][fm][fn], 0, 0, 0);
+            if (i < NR) lread_one(next, rd, rd_h, i);
+            if (i < WN) bneg[i < WN ? i : 0] = now.b[i < WN ? i : 0] << 7;
+            if (REQ && i >= NM - NL) request_one(step, stage, i - (NM - NL));
+            __builtin_amdgcn_sched_barrier(0);
+        }
     };
+    static_assert(NR + NL <= NM && WN <= WM * WN, "a read or a load per MFMA");
 
-    // One half of a step (the pipeline and the issue pattern of realw_bf16x3_kernel): after every fragment read one load
-    // or one LDS write, alternately, while there are any, then one MFMA; the rest of the MFMAs at the end.
-    constexpr int G1 = (NL + 1) / 2, G2 = NL - G1;
-    static_assert(NL <= NR, "one load or write per fragment read");
-    auto half = [&](int hf, const Frags& now, Frags& next, const unsigned char* rd, int rd_h, unsigned char* wr, Loads& L, int sl) {
-        const int g0 = hf ? G1 : 0, ng = hf ? G2 : G1, w0 = hf ? 0 : G1, nw = hf ? G1 : G2;
-        const int mn = ng < nw ? ng : nw;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            lread_one(next, rd, rd_h, i);
-            const int e = i - 2 * mn;
-            if (i < 2 * mn) {
-                if ((i & 1) == 0) gload_one(L, sl, g0 + i / 2);
-                else lstore_one(wr, L, w0 + i / 2);
-            } else {
-                if (ng > nw && e < ng - mn) gload_one(L, sl, g0 + mn + e);
-                if (nw > ng && e < nw - mn) lstore_one(wr, L, w0 + mn + e);
-            }
-        }
-        products(now);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
-            const int e = i - 2 * mn;
-            if (i < 2 * mn) {
-                if ((i & 1) == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // load from memory
-                else __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);              // LDS write
-            } else {
-                if (ng > nw && e < ng - mn) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                if (nw > ng && e < nw - mn) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NM - NR, 0);
+    // Three stages in rotation and one barrier per step, between its blocks: behind it step j + 1 is complete in LDS, and every
+    // wave has read step j, so its place takes step j + 3.
+    const int nS = kpad / kI8KStep;
+    auto turn = [&](int j) {
+        if (j + 2 < nS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL) : "memory");   // step j + 2 may be on its way
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
-
-    const int nS = kpad / kI8KStep;
-    unsigned char* buf0 = i8_lds;
-    unsigned char* buf1 = i8_lds + kStage;
-    Loads L;
     Frags F0, F1;
 #pragma unroll
-    for (int i = 0; i < NL; ++i) gload_one(L, 0, i);
+    for (int st = 0; st < kI8Stages; ++st)
+        if (st < nS)
 #pragma unroll
-    for (int i = 0; i < NL; ++i) lstore_one(buf0, L, i);
+            for (int i = 0; i < NL; ++i) request_one(st, lds0 + (uint32_t)(st * kStage), i);
+    if (nS > 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NL) : "memory");
+    else if (nS > 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
 #pragma unroll
-    for (int i = 0; i < NL; ++i) gload_one(L, nS > 1 ? 1 : 0, i);
-#pragma unroll
-    for (int i = 0; i < G1; ++i) lstore_one(buf1, L, i);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NR; ++i) lread_one(F0, buf0, 0, i);
-    for (int j = 0; j < nS; ++j) {
-        unsigned char* cur = (j & 1) ? buf1 : buf0;
-        unsigned char* nxt = (j & 1) ? buf0 : buf1;
-        const int sl = j + 2 < nS ? j + 2 : nS - 1;   // past the end: the last step again (in bounds, never used)
-        half(0, F0, F1, cur, 1, nxt, L, sl);
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        half(1, F1, F0, nxt, 0, cur, L, sl);
-    }
+    for (int i = 0; i < NR; ++i) lread_one(F0, i8_lds, 0, i);
+    int slot = 0, j = 0;
+    auto step = [&](auto req) {
+        const int nslot = slot == kI8Stages - 1 ? 0 : slot + 1;
+        block(F0, F1, i8_lds + slot * kStage, 1, std::false_type{}, 0, 0u);
+        turn(j);
+        // (behind the last step: its first block read again, unused)
+        block(F1, F0, i8_lds + (j + 1 < nS ? nslot : slot) * kStage, 0, req, j + 3, lds0 + (uint32_t)(slot * kStage));
+        slot = nslot;
+    };
+    for (; j + 3 < nS; ++j) step(std::true_type{});
+    for (; j < nS; ++j) step(std::false_type{});
     __syncthreads();   // the buffers are free: the epilogue reuses them
 
     // ---- epilogue.  Accumulator fragment (fm, fn), register v of lane (r, g) belongs to frame
