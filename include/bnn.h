@@ -126,7 +126,7 @@ typedef enum bnn_option {
                                        the frames (|sum - exact| < K 2^-27 max|x| per frame: below what the order of an fp32
                                        summation changes; about 3x faster than the ascending-k sum; default, unless
                                        BNN_OPT_REALX_F32_MFMA = 2 asks for the ascending-k sum everywhere; a tiled product,
-                                       128 frames x 256 outputs per workgroup), 2 = the same sums with workgroups of 16
+                                       128 frames x 256 or 64 x 128 outputs per workgroup), 2 = the same sums with workgroups of 16
                                        frames x 512 outputs (identical results), 0 = as BNN_OPT_REALX_F32_MFMA says       */
     BNN_OPT_REALW_SPLIT_LOGSOFTMAX = 17, /* bnn_forward, LOGSOFTMAX layer with real-valued weights, 128 frames or more:
                                        1 = the products run on the bf16 matrix cores with every fp32 operand split into

@@ -733,10 +733,11 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
     s.bytes = round_up((size_t)digits * (size_t)M * kpad, 256);
     s.meta = s.bytes + round_up((size_t)N * kpad, 256);
     s.undecided = s.meta + round_up((size_t)M * 16, 256);
-    // Sign layers: a record per frame and tile of 256 outputs, room for 31 of them (the filter leaves about one output
-    // in 250 undecided at K = 2048); what does not fit is summed by the lane that finds it
-    const size_t tiles = (size_t)((N + kI8TileN - 1) / kI8TileN);
-    s.total = s.undecided + (act == BNN_ACT_SIGN ? round_up((size_t)M * tiles * kUndecidedRecord, 256) : 0);
+    // Sign layers: a record per frame and 128 outputs, room for 15 of them (the filter leaves about one output in 250
+    // undecided at K = 2048); what does not fit is summed by the lane that finds it.  Charged as pairs of records, as it
+    // always was.
+    const size_t pairs = (size_t)((N + 2 * kUndecidedOutputs - 1) / (2 * kUndecidedOutputs));
+    s.total = s.undecided + (act == BNN_ACT_SIGN ? round_up((size_t)M * pairs * 2 * kUndecidedRecord, 256) : 0);
     return s;
 }
 // Frames of up to 4096 elements in 16-byte pieces are held in registers, in as many groups of 256 as they need (a power of
@@ -753,6 +754,27 @@ void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* 
     else if (kpad <= 4096) realx_quantize_nat_kernel<D, true, 16><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
     else realx_quantize_nat_kernel<D, true, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
 }
+// Tiles of 128 frames x 256 outputs (one workgroup per CU) or of 64 x 128 (two per CU)?  A round of the small ones, 512
+// workgroups, is half the outputs of a round of 256 large ones and takes 0.55 to 0.67 of its time (a weight byte in LDS serves
+// half as many frames); what decides is how many rounds there are, and at most 512 small workgroups always win.  Whole calls,
+// large -> small, K = 2048: 600 frames x 2048 outputs 66 -> 32 us, 2048 x 2048 69 -> 51, 600 x 3400 66 -> 44; two rounds of small
+// tiles against one of large ones 74 -> 80 (2600 x 2048) and 78 -> 91 (3400 x 2048), three against two 139 -> 146 (6000 x 2048).
+// Sign layers with what resolves their undecided outputs: 600 x 2048 81 -> 59, 2048 x 2048 83 -> 71, 4096 x 2048 89 -> 97.
+bool i8_small_tiles(int M, int N) {
+    const int64_t large = (int64_t)((M + 127) / 128) * ((N + 255) / 256), small = (int64_t)((M + 63) / 64) * ((N + 127) / 128);
+    return 2 * ((small + 511) / 512) < 3 * ((large + 255) / 256);
+}
+template <int D, int WM, int WN>
+int launch_i8_product(const int8_t* planes, const int8_t* bytes, const void* meta, const float* X, const void* Wp, const float* scale,
+                      const float* bias, int M, int K, int kpad, int N, int w32, void* Y, int yw32, unsigned char* undecided, hipStream_t st) {
+    constexpr unsigned lds = i8_gemm_lds(D, WM, WN);
+    static std::atomic<uint64_t> allowed;
+    if (!allow_lds(&realx_i8_gemm_kernel<D, WM, WN>, lds, allowed)) return BNN_EDEVICE;
+    const dim3 grid((unsigned)((M + 64 * WM - 1) / (64 * WM)), (unsigned)((N + 64 * WN - 1) / (64 * WN)));
+    realx_i8_gemm_kernel<D, WM, WN><<<grid, kI8Threads, lds, st>>>(planes, bytes, meta, X, static_cast<const uint32_t*>(Wp), scale, bias, M, K,
+                                                                   kpad, N, w32, Y, yw32, D == 3 ? undecided : nullptr);
+    return BNN_OK;
+}
 template <int D>
 int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int Mi, int Ki, int Ni, int w32,
                          void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st) {
@@ -765,19 +787,19 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     launch_quantize<D>(X, Mi, Ki, kpad, qbits, planes, meta, st);
     const int64_t eb = ((int64_t)Ni * (kpad / 16) + 255) / 256;
     bits_to_bytes_kernel<<<(unsigned)(eb < 16384 ? eb : 16384), 256, 0, st>>>(static_cast<const uint32_t*>(Wp), Ni, Ki, w32, kpad, bytes);
-    static std::atomic<uint64_t> allowed;
-    if (!allow_lds(&realx_i8_gemm_kernel<D>, (unsigned)i8_gemm_lds(D), allowed)) return BNN_EDEVICE;
-    const dim3 grid((unsigned)((Mi + kI8TileM - 1) / kI8TileM), (unsigned)((Ni + kI8TileN - 1) / kI8TileN));
-    realx_i8_gemm_kernel<D><<<grid, kI8Threads, i8_gemm_lds(D), st>>>(planes, bytes, meta, X, static_cast<const uint32_t*>(Wp), scale, bias,
-                                                                      Mi, Ki, kpad, Ni, w32, Y, yw32, D == 3 ? undecided : nullptr);
+    const int rc = i8_small_tiles(Mi, Ni)
+        ? launch_i8_product<D, 1, 2>(planes, bytes, meta, X, Wp, scale, bias, Mi, Ki, kpad, Ni, w32, Y, yw32, undecided, st)
+        : launch_i8_product<D, 2, 4>(planes, bytes, meta, X, Wp, scale, bias, Mi, Ki, kpad, Ni, w32, Y, yw32, undecided, st);
+    if (rc != BNN_OK) return rc;
+    const int recs = (Ni + kUndecidedOutputs - 1) / kUndecidedOutputs;
     if (D == 3) {
         const unsigned int rg = (unsigned int)((Mi + kResolveFrames - 1) / kResolveFrames);
         if ((Ki & 3) == 0 && aligned(X, 16))
             realx_resolve_rows_kernel<true><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
-                                                                          undecided, (int)grid.y, static_cast<uint32_t*>(Y), yw32);
+                                                                          undecided, recs, static_cast<uint32_t*>(Y), yw32);
         else
             realx_resolve_rows_kernel<false><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
-                                                                           undecided, (int)grid.y, static_cast<uint32_t*>(Y), yw32);
+                                                                           undecided, recs, static_cast<uint32_t*>(Y), yw32);
     }
     return BNN_OK;
 }

@@ -1,6 +1,6 @@
 // Real input x binary weights on the int8 matrix cores for batches of 128 frames or more (paper Alg. 1 forward; Alg. 2:
 // Sign at a hidden layer, Softmax at l = L): the digit-plane product of realx_slab_kernels.hpp as a tiled matrix
-// product with V_MFMA_I32_32X32X32_I8, workgroups of 128 frames x 256 outputs instead of 16 x 512, so that a weight
+// product with V_MFMA_I32_32X32X32_I8, workgroups of up to 128 frames x 256 outputs instead of 16 x 512, so that a weight
 // byte fetched into LDS serves 128 frames.
 //
 // What is computed is the filter described in realx_fused_kernel.hpp and realx_slab_kernels.hpp: every frame is scaled by
@@ -19,7 +19,7 @@
 // rounded up to 64, zeros past K.  The product kernel takes steps of 64 k = 64 bytes of a row: three LDS stages filled by loads that write LDS
 // directly, two steps in flight, one barrier per step, one memory instruction between two MFMAs.  (Loads to registers and LDS
 // stores, two stages: 4096 x 2048 x 2048 70 -> 62 us, 2048 outputs x 2048 x 4096 104 -> 91.)  2 x 2 waves of 64 frames x
-// 128 outputs each, 2 x 4 accumulator fragments of 32 x 32, twice.
+// 128 outputs each, 2 x 4 accumulator fragments of 32 x 32, twice; smaller tiles where these leave part of the chip idle.
 #pragma once
 
 #include <type_traits>
@@ -35,20 +35,20 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4g __attribute__((ext_vector_type(4)));
 
 constexpr int kI8KStep = 64;                       // k per pipeline step
-constexpr int kI8TileM = 128, kI8TileN = 256;      // workgroup tile
 constexpr int kI8RowBytes = 64;
 constexpr int kI8Threads = 256;
-constexpr int kI8StageB = kI8TileN * kI8RowBytes;  // 16384
-__host__ __device__ constexpr int i8_stage_a(int digits) { return digits * kI8TileM * kI8RowBytes; }
-__host__ __device__ constexpr int i8_stage(int digits) { return i8_stage_a(digits) + kI8StageB; }             // 40960 / 49152
 constexpr int kI8Stages = 3;
-__host__ __device__ constexpr unsigned i8_gemm_lds(int digits) { return (unsigned)(kI8Stages * i8_stage(digits)); }   // 122880 / 147456
+// A workgroup of 2 x 2 waves of 32 WM frames x 32 WN outputs each.
+__host__ __device__ constexpr int i8_stage_a(int digits, int wm) { return digits * 64 * wm * kI8RowBytes; }
+__host__ __device__ constexpr int i8_stage(int digits, int wm, int wn) { return i8_stage_a(digits, wm) + 64 * wn * kI8RowBytes; }
+__host__ __device__ constexpr unsigned i8_gemm_lds(int digits, int wm, int wn) { return (unsigned)(kI8Stages * i8_stage(digits, wm, wn)); }
 __host__ __device__ inline int i8_kpad(int K) { return (K + kI8KStep - 1) / kI8KStep * kI8KStep; }
 
-// The outputs the filter could not decide, per frame and tile of 256 outputs: a record of 32 bytes, byte 0 = how many
-// (at most 31), then the outputs' positions in the tile.  Records: [frame][tile], written whole by the one workgroup
-// that owns frame and tile (no atomics in global memory, nothing to clear beforehand).
-constexpr int kUndecidedRecord = 32;
+// The outputs the filter could not decide, per frame and 128 outputs: a record of 16 bytes, byte 0 = how many (at most 15),
+// then the outputs' positions among the 128.  Records: [frame][ceil(N / 128)], written whole by the one workgroup that owns
+// frame and outputs (no atomics in global memory, nothing to clear beforehand).
+constexpr int kUndecidedOutputs = 128;
+constexpr int kUndecidedRecord = 16;
 constexpr int kUndecidedMax = kUndecidedRecord - 1;
 
 // B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k.  Grid: any number of blocks of 256.
@@ -191,54 +191,55 @@ __global__ __launch_bounds__(256) void realx_quantize_nat_kernel(const float* __
 }
 
 // The product kernel.  D = 3: Sign bits into Yv (uint32 words [M][yw32]; bits of listed outputs are left 0) and the
-// records of undecided outputs into `undecided` ([M][gridDim.y] records); D = 4: z = fma(scale, a 2^-s, bias) into Yv
+// records of undecided outputs into `undecided` ([M][ceil(N / 128)] records); D = 4: z = fma(scale, a 2^-s, bias) into Yv
 // (fp32 [M][N]), `undecided` unused.
 // planes [D][M][kpad], Bb [N][kpad], both 16-byte aligned, kpad % 64 == 0; meta: RowMeta (D = 3) or RowMeta4 (D = 4) [M].
 // X, Wp: the layer's own operands, for the fp32 sum in ascending k of outputs that do not fit a record (D = 3) or of
-// frames that could not be quantised (D = 4).  Grid: x = ceil(M / 128), y = ceil(N / 256); block = 256 threads;
-// dynamic LDS i8_gemm_lds(D).
-template <int D>
-__global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1))) void realx_i8_gemm_kernel(
+// frames that could not be quantised (D = 4).  Grid: x = ceil(M / (64 WM)), y = ceil(N / (64 WN)); block = 256 threads;
+// dynamic LDS i8_gemm_lds(D, WM, WN).
+template <int D, int WM, int WN>
+__global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, WM * WN > 2 ? 1 : 2))) void realx_i8_gemm_kernel(
     const int8_t* __restrict__ planes, const int8_t* __restrict__ Bb, const void* __restrict__ meta_in, const float* __restrict__ X,
     const uint32_t* __restrict__ Wp, const float* __restrict__ scale, const float* __restrict__ bias, int M, int K, int kpad, int N,
     int w32, void* __restrict__ Yv, int yw32, unsigned char* __restrict__ undecided) {
     static_assert(D == 3 || D == 4, "three digits for Sign layers, four in front of the log-Softmax");
     extern __shared__ __attribute__((aligned(16))) unsigned char i8_lds[];
-    constexpr int WM = 2, WN = 4;
-    constexpr int NL = 2 * D + 4;                             // loads per wave and step, of 16 rows each: 10 / 12
-    constexpr int NR = D * WM + WN;                           // fragment reads per wave and block: 10 / 12
-    constexpr int NM = D * WM * WN;                           // MFMAs per wave and block: 24 / 32
-    constexpr int kStageA = i8_stage_a(D), kStage = i8_stage(D);
+    static_assert((64 * WN) % kUndecidedOutputs == 0, "Sign layers: a record of undecided outputs belongs to one workgroup");
+    constexpr int kTileM = 64 * WM, kTileN = 64 * WN;
+    constexpr int NL = D * WM + WN;                           // loads per wave and step, of 16 rows each
+    constexpr int NR = D * WM + WN;                           // fragment reads per wave and block
+    constexpr int NM = D * WM * WN;                           // MFMAs per wave and block
+    constexpr int kStageA = i8_stage_a(D, WM), kStage = i8_stage(D, WM, WN);
     const int tid = (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = lane_id();
     const int r = lane & 31, g = lane >> 5;
-    const int m_tile = (int)blockIdx.x * kI8TileM, n_tile = (int)blockIdx.y * kI8TileN;
+    const int m_tile = (int)blockIdx.x * kTileM, n_tile = (int)blockIdx.y * kTileN;
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);
 
-    // ---- the wave's share of a step's loads, 16 rows each (four lanes a row): load i < 2 D is digit i / 2, frames
-    //      32 wave + 16 (i % 2) .. of the tile; load 2 D + j its weight rows 64 wave + 16 j ...  One buffer per digit plane
-    //      and one for the weights, over the rows of the tile (rows past the end: the last one again).
+    // ---- the wave's share of a step's loads, 16 rows each (four lanes a row): load i < D WM is digit i / WM, frames
+    //      16 (WM wave + i % WM) .. of the tile; load D WM + j its weight rows 16 (WN wave + j) ...  One buffer per digit
+    //      plane and one for the weights, over the rows of the tile (rows past the end: the last one again).
     const int lrow = lane >> 2, lsrc = ((lane & 3) ^ ((lrow >> 2) & 3)) * 16;
-    const int rows_a = min(M - m_tile, kI8TileM), rows_b = min(N - n_tile, kI8TileN);
+    const int rows_a = min(M - m_tile, kTileM), rows_b = min(N - n_tile, kTileN);
     i32x4m ars[D];
 #pragma unroll
     for (int d = 0; d < D; ++d) ars[d] = raw_buffer(planes + ((size_t)d * M + m_tile) * kpad, (unsigned int)(rows_a * kpad));
     const i32x4m brs = raw_buffer(Bb + (size_t)n_tile * kpad, (unsigned int)(rows_b * kpad));
-    int aofs[2], bofs[4];
+    int aofs[WM], bofs[WN];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) aofs[i] = min(32 * wave + 16 * i + lrow, rows_a - 1) * kpad + lsrc;
+    for (int i = 0; i < WM; ++i) aofs[i] = min(16 * (WM * wave + i) + lrow, rows_a - 1) * kpad + lsrc;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) bofs[i] = min(64 * wave + 16 * i + lrow, rows_b - 1) * kpad + lsrc;
+    for (int i = 0; i < WN; ++i) bofs[i] = min(16 * (WN * wave + i) + lrow, rows_b - 1) * kpad + lsrc;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)i8_lds;
     auto request_one = [&](int step, uint32_t stage, int i) {
-        if (i < 2 * D)
-            load_lds16(ars[i < 2 * D ? i / 2 : 0], aofs[i % 2], step * kI8KStep,
-                       stage + (uint32_t)((i / 2) * (kI8TileM * kI8RowBytes) + (32 * wave + 16 * (i % 2)) * kI8RowBytes));
+        if (i < D * WM)
+            load_lds16(ars[i < D * WM ? i / WM : 0], aofs[i % WM], step * kI8KStep,
+                       stage + (uint32_t)(((i / WM) * kTileM + 16 * (WM * wave + i % WM)) * kI8RowBytes));
         else
-            load_lds16(brs, bofs[i < 2 * D ? 0 : i - 2 * D], step * kI8KStep,
-                       stage + (uint32_t)(kStageA + (64 * wave + 16 * (i - 2 * D)) * kI8RowBytes));
+            load_lds16(brs, bofs[i < D * WM ? 0 : i - D * WM], step * kI8KStep,
+                       stage + (uint32_t)(kStageA + 16 * (WN * wave + i - D * WM) * kI8RowBytes));
     };
 
     // ---- the wave's operand fragments of block h (0 or 1) of a stage: digit fragments, then weight fragments
@@ -250,7 +251,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
         const int so = ((2 * h + g) ^ swz) << 4;
         if (i < D * WM)
             F.a[i < D * WM ? i / WM : 0][i % WM] =
-                *reinterpret_cast<const v4i32g*>(stage + (i / WM) * (kI8TileM * kI8RowBytes) + a_off + (i % WM) * (32 * kI8RowBytes) + so);
+                *reinterpret_cast<const v4i32g*>(stage + (i / WM) * (kTileM * kI8RowBytes) + a_off + (i % WM) * (32 * kI8RowBytes) + so);
         else
             F.b[i < D * WM ? 0 : i - D * WM] = *reinterpret_cast<const v4i32g*>(stage + b_off + (i - D * WM) * (32 * kI8RowBytes) + so);
     };
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
                 for (int v = 0; v < 16; ++v) acc[p][i][j][v] = 0;
 
     // One block of 32 k, written out MFMA by MFMA and pinned: behind each of the first ones a fragment read of the next
-    // block, behind the last ones (REQ) a load of step `step` to `stage`.
+    // block, behind each of the last ones (REQ) a load of step `step` to `stage`.
     auto block = [&](const Frags& now, Frags& next, const unsigned char* rd, int rd_h, auto req, int step, uint32_t stage) {
         constexpr bool REQ = decltype(req)::value;
         v4i32g bneg[WN];   // -128 b: the byte 1 becomes 0x80
@@ -281,7 +282,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    static_assert(NR + NL <= NM && WN <= WM * WN, "a read or a load per MFMA");
+    static_assert(NR <= NM && NL <= NM && WN <= WM * WN, "room for the reads, the loads and the shifted weights");
 
     // Three stages in rotation and one barrier per step, between its blocks: behind it step j + 1 is complete in LDS, and every
     // wave has read step j, so its place takes step j + 3.
@@ -323,21 +324,22 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
         // A lane decides its 16 frames of a fragment on its own and keeps the answers as bit masks (bit v: frame v of
         // the fragment): no ballots, no scalar logic, no branch per sum.  The masks of all lanes go to LDS,
         // colmask[frame block of 32][g][output of the tile], and are turned into output words afterwards.
-        // LDS: column masks 4 x 2 x 256 x 2 bytes | the frames' quantisation records | per frame: how many undecided
-        // outputs | per frame: their records (about one output per frame is expected at K = 2048).
+        // LDS: column masks 2 WM x 2 x 64 WN x 2 bytes | the frames' quantisation records | per frame and 128 outputs: how many are
+        // undecided | their records (about one output in 250 is expected at K = 2048).
         uint16_t* colmask = reinterpret_cast<uint16_t*>(i8_lds);
-        constexpr int kMaskBytes = 4 * 2 * kI8TileN * 2;
+        constexpr int kMaskBytes = 2 * WM * 2 * kTileN * 2, kRecs = kTileN / kUndecidedOutputs, kAllRecs = kTileM * kRecs;
         RowMeta* meta_s = reinterpret_cast<RowMeta*>(i8_lds + kMaskBytes);
-        unsigned int* und_count = reinterpret_cast<unsigned int*>(i8_lds + kMaskBytes + kI8TileM * sizeof(RowMeta));
-        unsigned char* und = reinterpret_cast<unsigned char*>(und_count + kI8TileM);   // [frame][kUndecidedRecord]
-        static_assert((kMaskBytes + kI8TileM * sizeof(RowMeta)) % 16 == 0 &&
-                          kMaskBytes + kI8TileM * (sizeof(RowMeta) + 4 + kUndecidedRecord) <= i8_gemm_lds(3),
+        unsigned int* und_count = reinterpret_cast<unsigned int*>(i8_lds + kMaskBytes + kTileM * sizeof(RowMeta));
+        unsigned char* und = reinterpret_cast<unsigned char*>(und_count + kAllRecs);   // [frame][kRecs][kUndecidedRecord]
+        static_assert((kMaskBytes + kTileM * sizeof(RowMeta)) % 16 == 0 &&
+                          kMaskBytes + kTileM * sizeof(RowMeta) + kAllRecs * (4 + kUndecidedRecord) <= i8_gemm_lds(3, WM, WN) &&
+                          kAllRecs <= kI8Threads && kAllRecs % 4 == 0,
                       "epilogue LDS");
-        if (tid < kI8TileM) {
+        if (tid < kTileM) {
             const int m = m_tile + tid;
             meta_s[tid] = meta[m < M ? m : M - 1];
-            und_count[tid] = 0u;
         }
+        if (tid < kAllRecs) und_count[tid] = 0u;
         __syncthreads();
         float sc[WN], bi[WN], asc[WN];
         bool nvalid[WN];
@@ -384,24 +386,25 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
                     const int v = __builtin_ctz(ub);
                     ub &= ub - 1u;
                     const int ml = fb * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                    const unsigned int slot = atomicAdd(&und_count[ml], 1u);
+                    const int rec = ml * kRecs + nl / kUndecidedOutputs;
+                    const unsigned int slot = atomicAdd(&und_count[rec], 1u);
                     if (slot < (unsigned int)kUndecidedMax) {
-                        und[ml * kUndecidedRecord + 1 + (int)slot] = (unsigned char)nl;
+                        und[rec * kUndecidedRecord + 1 + (int)slot] = (unsigned char)(nl % kUndecidedOutputs);
                     } else {   // more than the frame's record holds: summed here
                         const int m = m_tile + ml, n = n_tile + nl;
                         if (sign_bit(affine(sc[fn], canonical_acc_global(X + (size_t)m * K, Wp + (size_t)n * w32, K), bi[fn]))) bt |= 1u << v;
                     }
                 }
-                colmask[(fb * 2 + g) * kI8TileN + nl] = (uint16_t)bt;
+                colmask[(fb * 2 + g) * kTileN + nl] = (uint16_t)bt;
             }
         }
         __syncthreads();
-        // Output words: thread (frame f = tid / 2, half = tid % 2) builds words 4 half .. + 3 of its frame; bit j of word c
-        // is bit v(f) of the mask of output 32 c + j, where f = 32 fb + 8 (v / 4) + 4 g + v % 4.
-        {
-            const int f = tid >> 1, wq = (tid & 1) * 4;
+        // Output words: a thread builds four words of a frame f (the 128 outputs of a record); bit j of word c is bit v(f) of the
+        // mask of output 32 c + j, where f = 32 fb + 8 (v / 4) + 4 g + v % 4.
+        if (tid < kAllRecs) {
+            const int f = tid / kRecs, wq = (tid % kRecs) * 4;
             const int fb = f >> 5, fg = (f >> 2) & 1, fv = ((f >> 3) & 3) * 4 + (f & 3);
-            const uint32_t* cm = reinterpret_cast<const uint32_t*>(colmask + (fb * 2 + fg) * kI8TileN);   // two masks per dword
+            const uint32_t* cm = reinterpret_cast<const uint32_t*>(colmask + (fb * 2 + fg) * kTileN);   // two masks per dword
             const int m = m_tile + f;
             const int w_first = (n_tile >> 5) + wq;
             uint32_t words[4];
@@ -423,23 +426,22 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
                     if (w_first + c < yw32) y[c] = words[c];
             }
         }
-        // the frames' records, 16 bytes per thread (the barrier above also ordered the entries written to them)
-        {
-            const int f = tid >> 1, h = tid & 1;
-            const int m = m_tile + f;
-            u32x4 rec = *reinterpret_cast<const u32x4*>(und + f * kUndecidedRecord + 16 * h);
-            const unsigned int cnt = und_count[f] < (unsigned int)kUndecidedMax ? und_count[f] : (unsigned int)kUndecidedMax;
-            if (h == 0) rec.x = (rec.x & ~0xFFu) | cnt;
-            if (m < M)
-                *reinterpret_cast<u32x4*>(undecided + ((size_t)m * gridDim.y + blockIdx.y) * kUndecidedRecord + 16 * h) = rec;
+        // the frames' records, one per thread (the barrier above also ordered the entries written to them)
+        if (tid < kAllRecs) {
+            const int m = m_tile + tid / kRecs, q = n_tile / kUndecidedOutputs + tid % kRecs;
+            const int recs = (N + kUndecidedOutputs - 1) / kUndecidedOutputs;
+            u32x4 rec = *reinterpret_cast<const u32x4*>(und + tid * kUndecidedRecord);
+            const unsigned int cnt = und_count[tid] < (unsigned int)kUndecidedMax ? und_count[tid] : (unsigned int)kUndecidedMax;
+            rec.x = (rec.x & ~0xFFu) | cnt;
+            if (m < M && q < recs) *reinterpret_cast<u32x4*>(undecided + ((size_t)m * recs + q) * kUndecidedRecord) = rec;
         }
     } else {
         const RowMeta4* meta = static_cast<const RowMeta4*>(meta_in);
         float* Z = static_cast<float*>(Yv);
         if (m_base >= M || n_base >= N) return;   // wave-uniform, after the last barrier
-        // per wave 32 rows x 128 columns of outputs on their way to memory (a row is 512 contiguous bytes)
+        // per wave 32 rows x 32 WN columns of outputs on their way to memory (a row is 128 WN contiguous bytes)
         constexpr int LDW = 32 * WN + 4;
-        static_assert(4 * 32 * LDW * 4 <= (int)i8_gemm_lds(4), "epilogue LDS");
+        static_assert(4 * 32 * LDW * 4 <= (int)i8_gemm_lds(4, WM, WN), "epilogue LDS");
         float* stg = reinterpret_cast<float*>(i8_lds) + wave * (32 * LDW);
         float sc[WN], bi[WN];
 #pragma unroll
@@ -449,7 +451,8 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
             bi[fn] = (n < N && bias) ? bias[n] : 0.0f;
         }
         const bool rows_vec = ((N & 3) == 0) && ((reinterpret_cast<uintptr_t>(Z) & 15) == 0);
-        const int c4 = (lane & 31) * 4;
+        constexpr int kLanes = 8 * WN, kRows = kWave / kLanes;   // lanes that store a row, rows per pass
+        const int c4 = (lane % kLanes) * 4;
 #pragma unroll
         for (int fm = 0; fm < WM; ++fm) {
 #pragma unroll
@@ -473,10 +476,9 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, 1
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // this wave's LDS writes are done before it reads them back
-            // two rows per pass: 32 lanes x 16 bytes each
 #pragma unroll 4
-            for (int it = 0; it < 16; ++it) {
-                const int rowl = it * 2 + (lane >> 5);
+            for (int it = 0; it < 32 / kRows; ++it) {
+                const int rowl = it * kRows + lane / kLanes;
                 const int m = m_base + fm * 32 + rowl;
                 const int n = n_base + c4;
                 const float4 qv = *reinterpret_cast<const float4*>(stg + rowl * LDW + c4);
@@ -555,7 +557,7 @@ template <bool VEC>
 __global__ __launch_bounds__(kResolveThreads) void realx_resolve_rows_kernel(const float* __restrict__ X, const uint32_t* __restrict__ Wp,
                                                                            const float* __restrict__ scale, const float* __restrict__ bias,
                                                                            int M, int K, int w32, const unsigned char* __restrict__ undecided,
-                                                                           int tiles, uint32_t* __restrict__ Y, int yw32) {
+                                                                           int recs, uint32_t* __restrict__ Y, int yw32) {
     __shared__ __attribute__((aligned(16))) float xs[2][kResolveFrames][kResolveLd];
     __shared__ u32x4 ws[2][kResolveThreads][2];   // a lane's eight weight words of a slab
     __shared__ unsigned int ent[kResolveCap];   // (frame of the workgroup) << 28 | output
@@ -599,21 +601,18 @@ __global__ __launch_bounds__(kResolveThreads) void realx_resolve_rows_kernel(con
     request(P, 0);   // the frames' first slab is on its way while the records are read
     if (tid == 0) total_s = 0u;
     __syncthreads();
-    for (int t = tid; t < kResolveFrames * tiles; t += kResolveThreads) {
-        const int r = t / tiles, tile = t - r * tiles;
+    for (int t = tid; t < kResolveFrames * recs; t += kResolveThreads) {
+        const int r = t / recs, q = t - r * recs;
         const int m = m0 + r;
         if (m >= M) continue;
-        const u32x4* rec = reinterpret_cast<const u32x4*>(undecided + ((size_t)m * tiles + tile) * kUndecidedRecord);
-        const u32x4 lo = rec[0];
-        const int cnt = min((int)(lo.x & 0xFFu), kUndecidedMax);
+        const u32x4 rec = *reinterpret_cast<const u32x4*>(undecided + ((size_t)m * recs + q) * kUndecidedRecord);
+        const int cnt = min((int)(rec.x & 0xFFu), kUndecidedMax);
         if (cnt == 0) continue;
-        const u32x4 hi = rec[1];
         const unsigned int base = atomicAdd(&total_s, (unsigned int)cnt);
         for (int i = 0; i < cnt; ++i) {
             const int b = i + 1;   // byte of the record
-            const unsigned int word = b < 16 ? (b < 8 ? (b < 4 ? lo.x : lo.y) : (b < 12 ? lo.z : lo.w))
-                                             : (b < 24 ? (b < 20 ? hi.x : hi.y) : (b < 28 ? hi.z : hi.w));
-            const int n = tile * kI8TileN + (int)((word >> (8 * (b & 3))) & 0xFFu);
+            const unsigned int word = b < 8 ? (b < 4 ? rec.x : rec.y) : (b < 12 ? rec.z : rec.w);
+            const int n = q * kUndecidedOutputs + (int)((word >> (8 * (b & 3))) & 0xFFu);
             if (base + i < (unsigned int)kResolveCap) {
                 ent[base + i] = ((unsigned int)r << 28) | (unsigned int)n;
             } else {

@@ -625,6 +625,22 @@ def test_first_layer_mfma_filter_bit_exact(G, bnn, oracle, M, K, N, wb):
         assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, arm), want), arm
 
 
+@pytest.mark.parametrize("M,N", [(65, 129), (2049, 2049)])   # 64 x 128 tiles; 128 x 256 tiles; ragged on both sides
+@pytest.mark.parametrize("K", [576, 640, 641])
+def test_int8_product_tiles_sign_layers(G, bnn, oracle, M, N, K):
+    """Both tiles of the int8 product at their edges, undecided outputs among them (biases at the sums of frame 0): the bits
+    of the ascending-k sum."""
+    X, W, scale, bias = _rand_layer(M + K, M, K, N)
+    X[1::3] = X[0]
+    if M < 128:
+        X = np.concatenate([X, X])   # the tiled product starts at 128 frames
+    Wp = oracle.pack_sign(W, 32)
+    acc32, _ = oracle.realx_acc(X[:1], oracle.unpack_pm1(Wp, K, 32))
+    bias[::3] = (-scale[::3] * acc32[0, ::3]).astype(np.float32)
+    want = oracle.layer_binw_realx(X, Wp, K, scale, bias, "sign", 32)
+    assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, 32, 1), want)
+
+
 def test_first_layer_mfma_filter_all_outputs_near_tie(G, bnn, oracle):
     """Every pre-activation within rounding of 0: all outputs go through the exact fix-up (queue and its overflow)."""
     M, K, N, wb = 300, 440, 200, 32
@@ -664,9 +680,9 @@ def test_slab_filter_sigmoid_inputs_and_near_ties(G, bnn, oracle):
     want = oracle.layer_binw_realx(X, Wp, K, scale, bias, "sign", wb)
     frac = np.unpackbits(want.view(np.uint8), bitorder="little").mean()
     assert 0.05 < frac < 0.95
-    # the tiled product records what it cannot decide per frame and tile of 256 outputs (here about 110, far more than the
-    # 31 a record holds, and 1240 for 16 frames where the second kernel takes 1024: the rest is summed by the lane that
-    # finds it, in either kernel); the 16-frame kernel keeps its list in LDS
+    # the tiled product records what it cannot decide per frame and 128 outputs (here about 55, far more than the 15 a record
+    # holds, and more than 1024 for 16 frames where the second kernel takes 1024: the rest is summed by the lane that finds
+    # it, in either kernel); the 16-frame kernel keeps its list in LDS
     for arm in (1, 2):
         assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, arm), want), arm
 

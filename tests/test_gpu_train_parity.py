@@ -216,6 +216,19 @@ def test_layer_binw_realx_int8_row_lengths(G, bnn, oracle, M, K):
     assert np.all(np.abs(got.astype(np.float64) - acc64) <= K * 2.0 ** -27 * 7.5 + 2.0 ** -23 * np.abs(acc64))
 
 
+@pytest.mark.parametrize("M,N", [(1, 1), (65, 129), (2049, 2049)])   # 64 x 128 tiles, 128 x 256 tiles, ragged
+@pytest.mark.parametrize("K", [3, 64, 65, 129, 193, 257, 320])       # one to five steps of 64 k, three of them in LDS
+def test_layer_binw_realx_int8_tiles(G, bnn, oracle, M, N, K):
+    """Integers of at most 2^14 as inputs: quantised without rounding, and the sums are below 2^24, so the result is exact."""
+    rng = np.random.default_rng(M + K)
+    X = rng.integers(-(1 << 14), 1 << 14, (M, K)).astype(np.float32)
+    W = rng.uniform(-1, 1, (N, K)).astype(np.float32)
+    Wp = oracle.pack_sign(W, 32)
+    got = _realx_i8(G, bnn, G.to_dev(X), G.to_dev(Wp), M, K, N, 32)
+    want = X.astype(np.float64) @ oracle.unpack_pm1(Wp, K, 32).T.astype(np.float64)   # |sum| <= 320 2^14 < 2^24
+    assert np.array_equal(got.astype(np.float64), want)
+
+
 def test_layer_binw_realx_int8_rows_that_cannot_be_quantised(G, bnn, oracle):
     """Frames with NaN, Inf or values beyond 2^90 take the fp32 sum in ascending k: the bits of bnn_layer_binw_realx."""
     M, K, N, wb = 140, 700, 300, 32

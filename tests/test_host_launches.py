@@ -228,3 +228,21 @@ result = [want, [l["kernel"] for l in launches()], bnn.bnn_forward_workspace_byt
 """)
     assert got[0] == got[1] and any("realx_i8_gemm" in k for k in got[0])
     assert got[2] == 2 * 512 * 2048 * 4 + 2048 * 2048 * 4
+
+
+def test_int8_product_tiles_by_rounds_of_workgroups(host):
+    """64 x 128 tiles (two workgroups per CU) where their rounds cost less than those of 128 x 256 tiles."""
+    got = host("""
+result = []
+def call(M, N, K):
+    n = bnn.bnn_layer_binw_realx_i8_workspace_bytes(M, K, N)
+    bnn.bnn_layer_binw_realx_i8(A, B, 0, 0, M, K, N, 32, 0x800000000000, 0x700000000000, n, 0)
+    l = [l for l in launches() if "realx_i8_gemm_kernel" in l["kernel"]][0]
+    result.append([l["kernel"], l["grid"], l["wrong"]])
+for M, N in ((1, 1), (600, 3400), (2048, 2048), (2600, 2048), (4096, 2048), (2049, 2049), (4096, 3400), (1 << 25, 1)):
+    call(M, N, 64)
+""")
+    small = ["Li1ELi2E" in k for k, _, _ in got]
+    assert small == [True, True, True, False, False, False, False, True]
+    assert got[1][1][:2] == [10, 27] and got[4][1][:2] == [32, 8]
+    assert not [w for _, _, w in got if w]
