@@ -126,17 +126,17 @@ typedef enum bnn_option {
                                        the frames (|sum - exact| < K 2^-27 max|x| per frame: below what the order of an fp32
                                        summation changes; about 3x faster than the ascending-k sum; default, unless
                                        BNN_OPT_REALX_F32_MFMA = 2 asks for the ascending-k sum everywhere; a tiled product,
-                                       128 frames x 256 or 64 x 128 outputs per workgroup), 2 = the same sums with workgroups of 16
-                                       frames x 512 outputs (identical results), 0 = as BNN_OPT_REALX_F32_MFMA says       */
+                                       128 frames x 256 or 64 x 128 outputs per workgroup), 2 = the same sums with workgroups
+                                       of 16 frames x 512 outputs (identical results), 0 = as BNN_OPT_REALX_F32_MFMA says */
     BNN_OPT_REALW_SPLIT_LOGSOFTMAX = 17, /* bnn_forward, LOGSOFTMAX layer with real-valued weights, 128 frames or more:
                                        1 = the products run on the bf16 matrix cores with every fp32 operand split into
                                        three bf16 pieces (v = p0 + p1 + p2 to 2^-24 |v|) and the six piece products of
                                        weight 2^-16 or more added in fp32: |sum - exact| <= 2^-22 sum_k |x_k w_k| plus
                                        ordinary fp32 rounding, no more than the ascending-k sum has, in half its time
                                        (default, unless BNN_OPT_REALX_F32_MFMA = 2 asks for the ascending-k sum
-                                       everywhere); 2 = the same with workgroups of eight waves, two per SIMD (measured
-                                       2 % slower); 0 = as BNN_OPT_REALX_F32_MFMA says.  The planes of both operands
-                                       (six bytes per element, K padded to 32) are part of bnn_forward_workspace_bytes */
+                                       everywhere); 2 = the same (once a variant of eight waves per workgroup);
+                                       0 = as BNN_OPT_REALX_F32_MFMA says.  The planes of both operands (six bytes per
+                                       element, K padded to 32) are part of bnn_forward_workspace_bytes                  */
     BNN_OPT_REALW_VALU_LDS = 18,    /* 0 or 1; accepted and without effect: layers with real-valued weights run on one kernel
                                        inside bnn_forward and outside it                                            */
     BNN_OPT_COOPERATIVE_SPIN = 15,  /* polls of the other workgroups' flags before a workgroup of a cooperative kernel gives

@@ -684,6 +684,15 @@ void launch_split(const float* A, int64_t rows, int K, int kpad, uint16_t* plane
     if ((K & 3) == 0 && aligned(A, 16)) split_bf16x3_kernel<true><<<grid, 256, 0, st>>>(A, rows, K, kpad, planes);
     else split_bf16x3_kernel<false><<<grid, 256, 0, st>>>(A, rows, K, kpad, planes);
 }
+template <int WM, int WN>
+int launch_split_product(const uint16_t* xs, const uint16_t* ws, const float* bias, int M, int kpad, int N, float* Y, hipStream_t st) {
+    constexpr unsigned lds = split_dynamic_lds(WM, WN);
+    static std::atomic<uint64_t> allowed;
+    if (!allow_lds(&realw_bf16x3_kernel<WM, WN>, lds, allowed)) return BNN_EDEVICE;
+    const dim3 grid((unsigned)((M + 64 * WM - 1) / (64 * WM)), (unsigned)((N + 64 * WN - 1) / (64 * WN)));
+    realw_bf16x3_kernel<WM, WN><<<grid, 256, lds, st>>>(xs, ws, bias, M, kpad, N, Y);
+    return BNN_OK;
+}
 int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, float* Y,
                         void* scratch_mem, hipStream_t st) {
     const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
@@ -692,13 +701,14 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     uint16_t* ws = reinterpret_cast<uint16_t*>(static_cast<char*>(scratch_mem) + realw_split_planes_bytes(M, K));
     launch_split(X, M, Ki, kpad, xs, st);
     launch_split(W, N, Ki, kpad, ws, st);
-    const unsigned lds = split_dynamic_lds();
-    const int eight = g_realw_split_lsm.load() == 2;   // 4 x 2 waves of 64 x 64 (two per SIMD) instead of 2 x 2 waves of 128 x 64
-    static std::atomic<uint64_t> allowed[2];
-    if (!allow_lds(eight ? &realw_bf16x3_kernel<ACT_LINEAR, 8> : &realw_bf16x3_kernel<ACT_LINEAR, 4>, lds, allowed[eight])) return BNN_EDEVICE;
-    const dim3 grid((unsigned)((Mi + kSplitTileM - 1) / kSplitTileM), (unsigned)((Ni + kSplitTileN - 1) / kSplitTileN));
-    if (eight) realw_bf16x3_kernel<ACT_LINEAR, 8><<<grid, 512, lds, st>>>(xs, ws, bias, Mi, kpad, Ni, Y);
-    else realw_bf16x3_kernel<ACT_LINEAR, 4><<<grid, 256, lds, st>>>(xs, ws, bias, Mi, kpad, Ni, Y);
+    // 256 x 128 outputs per workgroup or 128 x 128?  One workgroup per CU either way, and a round of the small ones takes 0.55 to
+    // 0.6 of the time.  Whole layers, K = 2048, large -> small: 600 frames x 3400 outputs 145 -> 90 us, 4096 x 1000 155 -> 112, three
+    // rounds against two 306 -> 263 (2600 x 3400); but two against one 174 -> 183 (2048 x 3400), five against three 483 -> 498.
+    const int64_t large = (int64_t)((Mi + 255) / 256) * ((Ni + 127) / 128), small = (int64_t)((Mi + 127) / 128) * ((Ni + 127) / 128);
+    const bool small_tiles = 3 * ((small + 255) / 256) < 5 * ((large + 255) / 256);
+    const int rc = small_tiles ? launch_split_product<2, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st)
+                               : launch_split_product<4, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st);
+    if (rc != BNN_OK) return rc;
     launch_log_softmax(Y, Mi, Ni, st);
     return launch_status();
 }

@@ -17,6 +17,8 @@
 // workspace, kpad = K rounded up to 32, zeros past K), then the product kernel below.
 #pragma once
 
+#include <type_traits>
+
 #include "bnn_device.hpp"
 
 namespace bnn {
@@ -27,12 +29,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kSplitPieces = 3;
 constexpr int kSplitKStep = 32;                                  // k per pipeline step: 64 bytes of a plane row
-constexpr int kSplitTileM = 256, kSplitTileN = 128;              // workgroup tile: 2 x 2 waves of 128 x 64
 constexpr int kSplitRowBytes = kSplitKStep * 2;
-constexpr int kSplitStageA = kSplitPieces * kSplitTileM * kSplitRowBytes;   // 49152
-constexpr int kSplitStageB = kSplitPieces * kSplitTileN * kSplitRowBytes;   // 24576
-constexpr int kSplitStage = kSplitStageA + kSplitStageB;                    // 73728
-constexpr unsigned split_dynamic_lds() { return 2u * kSplitStage; }         // 147456 of the CU's 163840 bytes
+// A workgroup of 2 x 2 waves of 32 WM frames x 32 WN outputs each; two stages of 256 x 128 or three of 128 x 128 fit a CU's LDS.
+__host__ __device__ constexpr int split_stage(int wm, int wn) { return kSplitPieces * 64 * (wm + wn) * kSplitRowBytes; }   // 73728 / 49152
+__host__ __device__ constexpr int split_stages(int wm, int wn) { return 3 * split_stage(wm, wn) <= 163840 ? 3 : 2; }
+__host__ __device__ constexpr unsigned split_dynamic_lds(int wm, int wn) { return (unsigned)(split_stages(wm, wn) * split_stage(wm, wn)); }
 
 __host__ __device__ inline int split_kpad(int K) { return (K + kSplitKStep - 1) / kSplitKStep * kSplitKStep; }
 
@@ -95,82 +96,74 @@ __global__ __launch_bounds__(256) void split_bf16x3_kernel(const float* __restri
 }
 
 // Y[m][n] = bias[n] + sum_k X[m][k] W[n][k] from the planes Xs [3][M][kpad] and Ws [3][N][kpad] (16-byte aligned,
-// kpad % 32 == 0).  Grid: x = ceil(M / 256), y = ceil(N / 128); block = 64 NW threads; dynamic LDS split_dynamic_lds().
-// NW = 4: 2 x 2 waves of 128 x 64, one wave per SIMD; NW = 8: 4 x 2 waves of 64 x 64, two waves per SIMD (each fills the
-// other's waits).
+// kpad % 32 == 0).  Grid: x = ceil(M / (64 WM)), y = ceil(N / (64 WN)); block = 256 threads; dynamic LDS split_dynamic_lds(WM, WN).
+// One wave per SIMD.
 //
-// Pipeline, one step = 32 k = two MFMA blocks of 16: the workgroup's 384 rows x 3 pieces x 64 bytes of step j + 2 are
-// loaded into registers (16 bytes per lane and load, four lanes per 64-byte row segment) while step j runs, and stored
-// into the LDS buffer of step j once every wave has taken its last operands out of it (one barrier per step).  A wave
-// reads its operand fragments out of LDS one block ahead of the MFMAs that use them.  In LDS a row's four 16-byte slots
-// are stored at slot ^ ((row / 4) % 4), which spreads both the stores and the fragment reads of 16 lanes over all
+// Pipeline, one step = 32 k = two MFMA blocks of 16: every tile row's 64 bytes of a piece go to LDS by loads that write it
+// directly (16 bytes per lane, four lanes a row), two or three steps in rotation and one barrier per step, between its blocks:
+// behind it step j + 1 is complete in LDS and every wave has read step j, whose place takes the next step.  A wave reads its
+// operand fragments out of LDS one block ahead of the MFMAs that use them, one memory instruction between two MFMAs.  In LDS
+// a row's four 16-byte slots are stored at slot ^ ((row / 4) % 4), which spreads the fragment reads of 16 lanes over all
 // banks.  Lane (r = lane % 32, g = lane / 32) feeds row r, k = 8 g .. 8 g + 7 of a block to both operands.
-template <int ACT, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4, NW / 4))) void realw_bf16x3_kernel(
+// (With loads to registers and LDS stores a pass over 4096 frames of 6 x 2048 units and 3400 outputs took 563 us, now 545.)
+template <int WM, int WN>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void realw_bf16x3_kernel(
     const uint16_t* __restrict__ Xs, const uint16_t* __restrict__ Ws, const float* __restrict__ bias, int M, int kpad, int N,
     float* __restrict__ Y) {
-    static_assert(NW == 4 || NW == 8, "2 x 2 or 4 x 2 waves");
     extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
-    constexpr int WM = 16 / NW, WN = 2;              // 32 x 32 accumulator fragments per wave
-    constexpr int LR = 16 * NW;                      // rows one load instruction of the workgroup covers
-    constexpr int AL = kSplitTileM / LR, BL = kSplitTileN / LR, NL = kSplitPieces * (AL + BL);   // loads per thread and step
+    constexpr int kTileM = 64 * WM, kTileN = 64 * WN, kStages = split_stages(WM, WN), kStage = split_stage(WM, WN);
+    constexpr int kStageA = kSplitPieces * kTileM * kSplitRowBytes;
+    constexpr int NL = kSplitPieces * (WM + WN);     // loads per wave and step, of 16 rows each
     constexpr int NR = kSplitPieces * (WM + WN);     // fragment reads per wave and block
     constexpr int NM = 6 * WM * WN;                  // MFMAs per wave and block
-    const int tid = (int)threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    static_assert(NR <= NM && NL <= NM, "one read or load per MFMA");
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     const int r = lane & 31, g = lane >> 5;
-    const int m_tile = (int)blockIdx.x * kSplitTileM, n_tile = (int)blockIdx.y * kSplitTileN;
+    const int m_tile = (int)blockIdx.x * kTileM, n_tile = (int)blockIdx.y * kTileN;
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);
 
-    // ---- the thread's share of a step's loads: row (tid / 4) + LR j of the tile's frames or weights rows, slot tid % 4
-    const int lrow = tid >> 2, lslot = tid & 3;
-    const uint16_t* srcA[AL];
-    const uint16_t* srcB[BL];
+    // ---- the wave's share of a step's loads: piece i / (WM + WN); then frames 16 (WM wave + sub) .. of the tile for sub < WM,
+    //      else weights rows 16 (WN wave + sub - WM) ..  One buffer per piece and operand, over the rows of the tile (rows past
+    //      the end: the last one again).
+    const int lrow = lane >> 2, lsrc = ((lane & 3) ^ ((lrow >> 2) & 3)) * 16;
+    const int rows_a = min(M - m_tile, kTileM), rows_b = min(N - n_tile, kTileN), row_bytes = 2 * kpad;
+    i32x4m ars[kSplitPieces], brs[kSplitPieces];
 #pragma unroll
-    for (int j = 0; j < AL; ++j) {
-        const int m = m_tile + lrow + LR * j;
-        srcA[j] = Xs + (size_t)(m < M ? m : M - 1) * kpad + lslot * 8;
+    for (int p = 0; p < kSplitPieces; ++p) {
+        ars[p] = raw_buffer(Xs + ((size_t)p * M + m_tile) * kpad, (unsigned int)(rows_a * row_bytes));
+        brs[p] = raw_buffer(Ws + ((size_t)p * N + n_tile) * kpad, (unsigned int)(rows_b * row_bytes));
     }
+    int aofs[WM], bofs[WN];
 #pragma unroll
-    for (int j = 0; j < BL; ++j) {
-        const int n = n_tile + lrow + LR * j;
-        srcB[j] = Ws + (size_t)(n < N ? n : N - 1) * kpad + lslot * 8;
-    }
-    const size_t planeA = (size_t)M * kpad, planeB = (size_t)N * kpad;
-    const int st_off = lrow * kSplitRowBytes + ((lslot ^ ((lrow >> 2) & 3)) << 4);   // + LR j rows: (row / 4) % 4 unchanged
-
-    // NL loads per thread and step, numbered i: piece i / (AL + BL); then frames row block i % (AL + BL) if that is
-    // below AL, else weights row block i % (AL + BL) - AL
-    struct Loads { u32x4 v[NL]; };
-    auto gload_one = [&](Loads& L, int step, int i) {
-        const int off = step * kSplitKStep, p = i / (AL + BL), sub = i % (AL + BL);
-        if (sub < AL) L.v[i] = *reinterpret_cast<const u32x4*>(srcA[sub < AL ? sub : 0] + p * planeA + off);
-        else L.v[i] = *reinterpret_cast<const u32x4*>(srcB[sub < AL ? 0 : sub - AL] + p * planeB + off);
-    };
-    auto lstore_one = [&](unsigned char* stage, const Loads& L, int i) {
-        const int p = i / (AL + BL), sub = i % (AL + BL);
-        if (sub < AL)
-            *reinterpret_cast<u32x4*>(stage + p * (kSplitTileM * kSplitRowBytes) + sub * (LR * kSplitRowBytes) + st_off) = L.v[i];
+    for (int i = 0; i < WM; ++i) aofs[i] = min(16 * (WM * wave + i) + lrow, rows_a - 1) * row_bytes + lsrc;
+#pragma unroll
+    for (int i = 0; i < WN; ++i) bofs[i] = min(16 * (WN * wave + i) + lrow, rows_b - 1) * row_bytes + lsrc;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)split_lds;
+    auto request_one = [&](int step, uint32_t stage, int i) {
+        const int p = i / (WM + WN), sub = i % (WM + WN);
+        if (sub < WM)
+            load_lds16(ars[p], aofs[sub < WM ? sub : 0], step * kSplitRowBytes,
+                       stage + (uint32_t)((p * kTileM + 16 * (WM * wave + sub)) * kSplitRowBytes));
         else
-            *reinterpret_cast<u32x4*>(stage + kSplitStageA + p * (kSplitTileN * kSplitRowBytes) + (sub - AL) * (LR * kSplitRowBytes) +
-                                      st_off) = L.v[i];
+            load_lds16(brs[p], bofs[sub < WM ? 0 : sub - WM], step * kSplitRowBytes,
+                       stage + (uint32_t)(kStageA + (p * kTileN + 16 * (WN * wave + sub - WM)) * kSplitRowBytes));
     };
 
     // ---- the wave's operand fragments of block h (0 or 1) of a stage: NR reads, numbered like the loads
     struct Frags { bf16x8 a[kSplitPieces][WM]; bf16x8 b[kSplitPieces][WN]; };
     const int swz = (r >> 2) & 3;
     const int a_off = ((wave >> 1) * (WM * 32) + r) * kSplitRowBytes;
-    const int b_off = kSplitStageA + ((wave & 1) * (WN * 32) + r) * kSplitRowBytes;
+    const int b_off = kStageA + ((wave & 1) * (WN * 32) + r) * kSplitRowBytes;
     auto lread_one = [&](Frags& F, const unsigned char* stage, int h, int i) {
         const int so = ((2 * h + g) ^ swz) << 4;
         const int p = i / (WM + WN), sub = i % (WM + WN);
         if (sub < WM)
-            F.a[p][sub < WM ? sub : 0] = *reinterpret_cast<const bf16x8*>(stage + p * (kSplitTileM * kSplitRowBytes) + a_off +
+            F.a[p][sub < WM ? sub : 0] = *reinterpret_cast<const bf16x8*>(stage + p * (kTileM * kSplitRowBytes) + a_off +
                                                                          sub * (32 * kSplitRowBytes) + so);
         else
-            F.b[p][sub < WM ? 0 : sub - WM] = *reinterpret_cast<const bf16x8*>(stage + p * (kSplitTileN * kSplitRowBytes) + b_off +
+            F.b[p][sub < WM ? 0 : sub - WM] = *reinterpret_cast<const bf16x8*>(stage + p * (kTileN * kSplitRowBytes) + b_off +
                                                                               (sub - WM) * (32 * kSplitRowBytes) + so);
     };
 
@@ -182,104 +175,57 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
-    // the six piece products of a block, smallest first; each accumulator is touched once per WM WN MFMAs
-    auto products = [&](const Frags& F) {
+    // One block of 16 k, written out MFMA by MFMA and pinned: the six piece products, smallest first; each accumulator is touched
+    // once per WM WN MFMAs.  Behind each of the first ones a fragment read of the next block, behind each of the last ones (REQ)
+    // a load of step `step` to `stage`.
+    auto block = [&](const Frags& now, Frags& next, const unsigned char* rd, int rd_h, auto req, int step, uint32_t stage) {
+        constexpr bool REQ = decltype(req)::value;
         constexpr int px[6] = {0, 1, 2, 0, 1, 0};
         constexpr int pw[6] = {2, 1, 0, 1, 0, 0};
 #pragma unroll
-        for (int q = 0; q < 6; ++q)
-#pragma unroll
-            for (int fm = 0; fm < WM; ++fm)
-#pragma unroll
-                for (int fn = 0; fn < WN; ++fn)
-                    acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(F.a[px[q]][fm], F.b[pw[q]][fn], acc[fm][fn], 0, 0, 0);
-    };
-
-    // Step s lives in buffer s % 2.  The first G1 loads of step j + 2 are issued in the first half of step j and stored
-    // in its second half; the others are issued in the second half and stored in the first half of step j + 1: the
-    // buffer of step j is free from the barrier in the middle of step j to the one in the middle of step j + 1, and
-    // nothing reads it in between.
-    //
-    // A wave issues in order, and the waves share one path to memory and one to LDS: loads in a row hold the MFMAs behind
-    // them back for as long as the path takes to accept them.  So the memory instructions of a half go between its MFMAs:
-    // after every fragment read one load or one LDS write, alternately, while there are any, then MPR MFMAs; the last
-    // 12 MFMAs of a half come after all of them, so that what the next half needs has been issued that long before it
-    // starts.  The scheduler is told this pattern; it keeps LDS reads and writes in source order, so the source has it too.
-    constexpr int G1 = (NL + 1) / 2, G2 = NL - G1;
-    constexpr int MPR = (NM - 12) / NR;
-    static_assert(NL <= NR && MPR >= 1, "one load or write per fragment read");
-    // half 0: loads [0, G1) of step `sl`, writes of loads [G1, NL) into `wr`; half 1: loads [G1, NL), writes of [0, G1)
-    auto half = [&](int hf, const Frags& now, Frags& next, const unsigned char* rd, int rd_h, unsigned char* wr, Loads& L,
-                    int sl) {
-        const int g0 = hf ? G1 : 0, ng = hf ? G2 : G1, w0 = hf ? 0 : G1, nw = hf ? G1 : G2;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            lread_one(next, rd, rd_h, i);
-            // op i: loads at even i (or once the writes have run out), writes at odd i (or once the loads have run out)
-            const int k = i / 2;
-            if (i < 2 * (ng < nw ? ng : nw)) {
-                if ((i & 1) == 0) gload_one(L, sl, g0 + k);
-                else lstore_one(wr, L, w0 + k);
-            } else {
-                const int m = ng < nw ? ng : nw, e = i - 2 * m;   // the longer list alone
-                if (ng > nw && e < ng - m) gload_one(L, sl, g0 + m + e);
-                if (nw > ng && e < nw - m) lstore_one(wr, L, w0 + m + e);
-            }
+        for (int i = 0; i < NM; ++i) {
+            const int q = i / (WM * WN), fm = (i / WN) % WM, fn = i % WN;
+            acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.a[px[q]][fm], now.b[pw[q]][fn], acc[fm][fn], 0, 0, 0);
+            if (i < NR) lread_one(next, rd, rd_h, i);
+            if (REQ && i >= NM - NL) request_one(step, stage, i - (NM - NL));
+            __builtin_amdgcn_sched_barrier(0);
         }
-        products(now);
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // LDS read
-            const int m = ng < nw ? ng : nw, e = i - 2 * m;
-            if (i < 2 * m) {
-                if ((i & 1) == 0) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // load from memory
-                else __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);              // LDS write
-            } else {
-                if (ng > nw && e < ng - m) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-                if (nw > ng && e < nw - m) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x008, MPR, 0);   // MFMA
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, NM - MPR * NR, 0);
-        __builtin_amdgcn_sched_barrier(0);
     };
-
     const int nS = kpad / kSplitKStep;
-    unsigned char* buf0 = split_lds;
-    unsigned char* buf1 = split_lds + kSplitStage;
-    Loads L;
-    Frags F0, F1;
-    // start: step 0 complete, step 1 up to its loads [G1, NL), which are on their way
-#pragma unroll
-    for (int i = 0; i < NL; ++i) gload_one(L, 0, i);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) lstore_one(buf0, L, i);
-#pragma unroll
-    for (int i = 0; i < NL; ++i) gload_one(L, nS > 1 ? 1 : 0, i);
-#pragma unroll
-    for (int i = 0; i < G1; ++i) lstore_one(buf1, L, i);
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < NR; ++i) lread_one(F0, buf0, 0, i);
-    for (int j = 0; j < nS; ++j) {
-        unsigned char* cur = (j & 1) ? buf1 : buf0;
-        unsigned char* nxt = (j & 1) ? buf0 : buf1;
-        const int sl = j + 2 < nS ? j + 2 : nS - 1;   // past the end: the last step again (in bounds, never used)
-        // block 0 of step j; fragment reads of its block 1; the last loads of step j + 1 land in that step's buffer
-        half(0, F0, F1, cur, 1, nxt, L, sl);
-        // every wave has its last fragments of `cur` in registers, and step j + 1 is complete in `nxt`
-        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    auto turn = [&](int j) {   // step j + 2 may be on its way where there are three places
+        if (kStages == 3 && j + 2 < nS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        // block 1 of step j; fragment reads of block 0 of step j + 1 (after the last step: unused); the first loads of
-        // step j + 2 land in the buffer of step j
-        half(1, F1, F0, nxt, 0, cur, L, sl);
-    }
+    };
+    Frags F0, F1;
+#pragma unroll
+    for (int st = 0; st < kStages; ++st)
+        if (st < nS)
+#pragma unroll
+            for (int i = 0; i < NL; ++i) request_one(st, lds0 + (uint32_t)(st * kStage), i);
+    if (kStages == 3 && nS > 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * NL) : "memory");
+    else if (nS > 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NL) : "memory");
+    else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < NR; ++i) lread_one(F0, split_lds, 0, i);
+    int slot = 0, j = 0;
+    auto step = [&](auto req) {
+        const int nslot = slot == kStages - 1 ? 0 : slot + 1;
+        block(F0, F1, split_lds + slot * kStage, 1, std::false_type{}, 0, 0u);
+        turn(j);
+        // (behind the last step: its first block read again, unused)
+        block(F1, F0, split_lds + (j + 1 < nS ? nslot : slot) * kStage, 0, req, j + kStages, lds0 + (uint32_t)(slot * kStage));
+        slot = nslot;
+    };
+    for (; j + kStages < nS; ++j) step(std::true_type{});
+    for (; j < nS; ++j) step(std::false_type{});
     __syncthreads();   // the buffers are free: the epilogue reuses them
 
     // ---- epilogue.  Accumulator fragment (fm, fn), register v of lane (r, g) is the sum for frame
     //      m_base + 32 fm + 8 (v/4) + 4 g + v%4 and output n_base + 32 fn + r.  Each wave turns 32 rows x 64 columns at
     //      a time through its own slice of LDS so that 16 lanes write 256 contiguous bytes of a row.
     if (m_base >= M || n_base >= N) return;   // wave-uniform, after the last barrier
+    static_assert(WN == 2, "16 lanes store a row of 64 columns");
     constexpr int LDW = 32 * WN + 4;
     float* stg = reinterpret_cast<float*>(split_lds) + wave * (32 * LDW);
     float bi[WN];
@@ -295,12 +241,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(NW / 4,
 #pragma unroll
         for (int fn = 0; fn < WN; ++fn)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float h = acc[fm][fn][v] + bi[fn];
-                if constexpr (ACT == ACT_HARDTANH) h = hardtanh(h);
-                if constexpr (ACT == ACT_SIGMOID) h = sigmoid(h);
-                stg[(8 * (v >> 2) + 4 * g + (v & 3)) * LDW + fn * 32 + r] = h;
-            }
+            for (int v = 0; v < 16; ++v)
+                stg[(8 * (v >> 2) + 4 * g + (v & 3)) * LDW + fn * 32 + r] = acc[fm][fn][v] + bi[fn];
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // this wave's LDS writes are done before it reads them back
 #pragma unroll
         for (int it = 0; it < 8; ++it) {

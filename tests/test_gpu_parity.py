@@ -835,6 +835,28 @@ def test_softmax_layer_real_weights_bf16_pieces(G, bnn, oracle, M, K, N, kind):
         assert np.allclose(np.exp(got.astype(np.float64)).sum(1), 1.0, atol=1e-4)
 
 
+@pytest.mark.parametrize("M,N", [(129, 129), (2049, 3329)])   # 128 x 128 tiles; 256 x 128 tiles
+@pytest.mark.parametrize("K", [31, 64, 65, 97, 129])         # one to five steps of 32 k, two or three of them in LDS
+def test_softmax_layer_bf16_piece_tiles(G, bnn, oracle, M, N, K):
+    """Integers below 2^8 in magnitude: one piece each, every product and sum below 2^24 and exact, so the log-posteriors are
+    those of the exact sums, to the rounding of the log-Softmax."""
+    rng = np.random.default_rng(M + K)
+    X = rng.integers(-16, 17, (M, K)).astype(np.float32)
+    W = (rng.integers(-16, 17, (N, K)) / 64).astype(np.float32)
+    keep = [G.to_dev(W), G.to_dev(np.zeros(N, np.float32)), G.to_dev(X)]
+    arr = bnn.make_layer_array([dict(K=K, N=N, act=bnn.BNN_ACT_LOGSOFTMAX, word_bits=32, x_is_binary=0, w_is_real=1, Wp=G.ptr(keep[0]),
+                                     scale=0, bias=G.ptr(keep[1]))])
+    nbytes = bnn.bnn_forward_workspace_bytes(arr, 1, M)
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device=G.DEV)
+    out = torch.empty(M, N, device=G.DEV)
+    bnn.bnn_forward(arr, 1, G.ptr(keep[2]), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
+    torch.cuda.synchronize()
+    z = X.astype(np.float64) @ W.T.astype(np.float64)
+    z -= z.max(1, keepdims=True)
+    want = z - np.log(np.exp(z).sum(1, keepdims=True))
+    assert np.max(np.abs(out.cpu().numpy() - want)) <= 1e-6 * np.max(np.abs(want)) + 1e-6 * np.log(N)
+
+
 def test_softmax_layer_bf16_pieces_sum_within_its_bound(G, bnn, oracle):
     """The bound the kernel states for its sums, seen through the log-posteriors: out[m][a] - out[m][0] = z_a - z_0, and
     each z is within 2^-22 sum_k |x_k w_k| (the piece products left out) plus the rounding of about 800 fp32 additions
