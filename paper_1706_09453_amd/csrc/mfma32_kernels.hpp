@@ -261,10 +261,11 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
             for (int f = 0; f < WM; ++f) a[f] = *reinterpret_cast<const uint4*>(base + arow + f * (32 * kM32RowBytes));
         };
         // One barrier per stage, in its middle: behind it stage S + 1 is complete in LDS and stage S has been read by every
-        // wave, so its place takes stage S + 3.
+        // wave, so its place takes stage S + 3.  (lgkmcnt: the wave's own reads of stage S, requested in front of the products of
+        // its first half; the compiler places no wait for them, their first use comes behind the barrier.)
         auto turn = [&](int S) {
-            if (S + 2 < nS) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AI + BI) : "memory");   // stage S + 2 may be on its way
-            else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+            if (S + 2 < nS) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(AI + BI) : "memory");   // stage S + 2 may be on its way
+            else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
             __builtin_amdgcn_sched_barrier(0);
         };
         const uint32_t affine_lds = lds0 + (uint32_t)(kM32Stages * kStage);   // [2][64 WN]: scale, bias

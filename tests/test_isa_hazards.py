@@ -1,8 +1,11 @@
-"""The inline-assembly DPP fmac of the real-input VALU kernel gets no automatic wait states.
+"""What the assembler does not do for inline assembly, checked in the device code compiled to assembly.
 
-A DPP instruction must not read a VGPR that a VALU instruction wrote in the two instructions before it, and must
-not follow a write of EXEC within five.  The assembler inserts those waits for compiler-generated code only, so
-this test compiles the device code to assembly and checks every `v_fmac_f32_dpp` in it.
+* A DPP instruction (`v_fmac_f32_dpp` of the real-input VALU kernel) must not read a VGPR that a VALU instruction wrote in
+  the two instructions before it, and must not follow a write of EXEC within five.
+* Kernels whose operands come to LDS by loads that write it (`buffer_load_dword* ... lds`, `global_load_lds_*`) cross their
+  barriers in inline assembly, where the compiler places no waits: a wave must not cross one with LDS reads of its own
+  under way, since behind it another wave's load may overwrite the place they read.
+* Such a load reads its SGPRs and M0 at once: an SGPR written by a VALU instruction needs five wait states first.
 """
 import os
 import re
@@ -23,15 +26,109 @@ def _written_vgprs(ins: str):
     return {int(m.group(3))}
 
 
-@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
-def test_dpp_fmac_sources_are_not_fresh_valu_results(tmp_path):
-    out = tmp_path / "api.s"
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """The device code of bnn_api.hip as a list of instructions, with the labels of functions and blocks."""
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not found")
+    out = tmp_path_factory.mktemp("isa") / "api.s"
     cmd = ["hipcc", "-O3", "--offload-arch=gfx950", "-std=c++17", "-ffp-contract=off", "-Xclang", "-target-feature",
            "-Xclang", "-packed-fp32-ops", "-S", "--cuda-device-only", "-I", os.path.join(ROOT, "include"), "-o", str(out),
            os.path.join(ROOT, "paper_1706_09453_amd", "csrc", "bnn_api.hip")]
     subprocess.run(cmd, check=True, capture_output=True)
-    code = [l.strip() for l in out.read_text().splitlines()]
-    code = [l for l in code if l and not l.startswith((";", ".", "//")) and not l.endswith(":")]
+    lines = [l.split(";")[0].strip() for l in out.read_text().splitlines()]
+    return [l for l in lines if l and not l.startswith("//") and (l.endswith(":") or not l.startswith("."))]
+
+
+def _kernels(code):
+    """(name, instructions) of every function."""
+    name, body = None, []
+    for l in code:
+        if re.match(r"_Z\w+:$", l):
+            if name:
+                yield name, body
+            name, body = l[:-1], []
+        elif name:
+            body.append(l)
+    if name:
+        yield name, body
+
+
+def _loads_lds(ins: str):
+    return bool(re.match(r"buffer_load_dword\w* .*\blds$", ins)) or ins.startswith("global_load_lds_")
+
+
+def _needs_wait_for_lds(ins: str):
+    return bool(re.match(r"ds_(read|swizzle|bpermute|permute)", ins)) or bool(re.match(r"ds_\w+_rtn", ins))
+
+
+def _reads_pending(body):
+    """For every instruction: can an LDS read of the wave still be under way in front of it, on any path?"""
+    at = {l[:-1]: i for i, l in enumerate(body) if l.endswith(":")}
+    pending, work = [None] * len(body), [(0, False)]
+    while work:
+        i, p = work.pop()
+        while i < len(body) and not (pending[i] or pending[i] == p):
+            pending[i] = p
+            ins = body[i]
+            if re.match(r"s_waitcnt .*lgkmcnt\(0\)", ins):
+                p = False
+            elif _needs_wait_for_lds(ins):
+                p = True
+            if ins.startswith(("s_endpgm", "s_setpc")):
+                break
+            m = re.match(r"s_c?branch\w*\s+(\S+)", ins)
+            if m:
+                work.append((at[m.group(1)], p))
+                if ins.startswith("s_branch"):
+                    break
+            i += 1
+    return pending
+
+
+def test_no_lds_read_is_under_way_at_a_barrier_of_the_loads_that_write_lds(code):
+    n, bad = 0, set()
+    for name, body in _kernels(code):
+        if not any(_loads_lds(l) for l in body):
+            continue
+        for ins, p in zip(body, _reads_pending(body)):
+            if ins.startswith("s_barrier"):
+                n += 1
+                if p:
+                    bad.add(name)
+    assert n > 0 and not bad, (n, len(bad), sorted(bad)[:4])
+
+
+def test_loads_that_write_lds_do_not_read_fresh_sgprs(code):
+    n, bad = 0, []
+    for name, body in _kernels(code):
+        for i, ins in enumerate(body):
+            if not _loads_lds(ins):
+                continue
+            n += 1
+            regs = set()
+            for a, b in re.findall(r"\bs\[(\d+):(\d+)\]", ins):
+                regs |= set(range(int(a), int(b) + 1))
+            regs |= {int(a) for a in re.findall(r"\bs(\d+)\b", ins)}
+            states, back = 0, i - 1
+            while states < 5 and back >= 0:
+                prev = body[back]
+                back -= 1
+                if prev.endswith(":"):
+                    continue
+                dst = prev.split(None, 1)[1].split(",")[0] if " " in prev else ""
+                m = re.match(r"s(\d+)$", dst)
+                m2 = re.match(r"s\[(\d+):(\d+)\]$", dst)
+                hit = {int(m.group(1))} if m else set(range(int(m2.group(1)), int(m2.group(2)) + 1)) if m2 else set()
+                if prev.startswith("v_") and hit & regs:
+                    bad.append((name, prev, ins))
+                k = re.match(r"s_nop\s+(\d+)", prev)
+                states += int(k.group(1)) + 1 if k else 1
+    assert n > 0 and not bad, bad[:4]
+
+
+def test_dpp_fmac_sources_are_not_fresh_valu_results(code):
+    code = [l for l in code if not l.endswith(":")]
     n_dpp, bad = 0, []
     for i, ins in enumerate(code):
         if not ins.startswith("v_fmac_f32_dpp"):
