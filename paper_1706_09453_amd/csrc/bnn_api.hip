@@ -743,9 +743,8 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
     s.bytes = round_up((size_t)digits * (size_t)M * kpad, 256);
     s.meta = s.bytes + round_up((size_t)N * kpad, 256);
     s.undecided = s.meta + round_up((size_t)M * 16, 256);
-    // Sign layers: a record per frame and 128 outputs, room for 15 of them (the filter leaves about one output in 250
-    // undecided at K = 2048); what does not fit is summed by the lane that finds it.  Charged as pairs of records, as it
-    // always was.
+    // Sign layers: a record per frame and 128 outputs, one bit each (the filter leaves about one output in 250 undecided at
+    // K = 2048).  Charged as pairs of records, as it always was.
     const size_t pairs = (size_t)((N + 2 * kUndecidedOutputs - 1) / (2 * kUndecidedOutputs));
     s.total = s.undecided + (act == BNN_ACT_SIGN ? round_up((size_t)M * pairs * 2 * kUndecidedRecord, 256) : 0);
     return s;

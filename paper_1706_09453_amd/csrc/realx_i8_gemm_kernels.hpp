@@ -44,12 +44,12 @@ __host__ __device__ constexpr int i8_stage(int digits, int wm, int wn) { return 
 __host__ __device__ constexpr unsigned i8_gemm_lds(int digits, int wm, int wn) { return (unsigned)(kI8Stages * i8_stage(digits, wm, wn)); }
 __host__ __device__ inline int i8_kpad(int K) { return (K + kI8KStep - 1) / kI8KStep * kI8KStep; }
 
-// The outputs the filter could not decide, per frame and 128 outputs: a record of 16 bytes, byte 0 = how many (at most 15),
-// then the outputs' positions among the 128.  Records: [frame][ceil(N / 128)], written whole by the one workgroup that owns
-// frame and outputs (no atomics in global memory, nothing to clear beforehand).
+// The outputs the filter could not decide, per frame and 128 outputs: a record of 16 bytes, one bit per output, so that it
+// holds any number of them.  Records: [frame][ceil(N / 128)], written whole by the one workgroup that owns frame and outputs
+// (no atomics in global memory, nothing to clear beforehand).  (As a list of at most 15 positions, the rest summed by the lane
+// that found it, a single full record cost a chain of K dependent additions from global memory: 5464 x 7808 x 1024 1760 us, now 487.)
 constexpr int kUndecidedOutputs = 128;
-constexpr int kUndecidedRecord = 16;
-constexpr int kUndecidedMax = kUndecidedRecord - 1;
+constexpr int kUndecidedRecord = kUndecidedOutputs / 8;
 
 // B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k.  Grid: any number of blocks of 256.
 __global__ __launch_bounds__(256) void bits_to_bytes_kernel(const uint32_t* __restrict__ Wp, int64_t N, int K, int w32, int kpad,
@@ -194,8 +194,7 @@ __global__ __launch_bounds__(256) void realx_quantize_nat_kernel(const float* __
 // records of undecided outputs into `undecided` ([M][ceil(N / 128)] records); D = 4: z = fma(scale, a 2^-s, bias) into Yv
 // (fp32 [M][N]), `undecided` unused.
 // planes [D][M][kpad], Bb [N][kpad], both 16-byte aligned, kpad % 64 == 0; meta: RowMeta (D = 3) or RowMeta4 (D = 4) [M].
-// X, Wp: the layer's own operands, for the fp32 sum in ascending k of outputs that do not fit a record (D = 3) or of
-// frames that could not be quantised (D = 4).  Grid: x = ceil(M / (64 WM)), y = ceil(N / (64 WN)); block = 256 threads;
+// X, Wp: the layer's own operands, for the fp32 sum in ascending k of frames that could not be quantised (D = 4).  Grid: x = ceil(M / (64 WM)), y = ceil(N / (64 WN)); block = 256 threads;
 // dynamic LDS i8_gemm_lds(D, WM, WN).
 template <int D, int WM, int WN>
 __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, WM * WN > 2 ? 1 : 2))) void realx_i8_gemm_kernel(
@@ -324,22 +323,21 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, W
         // A lane decides its 16 frames of a fragment on its own and keeps the answers as bit masks (bit v: frame v of
         // the fragment): no ballots, no scalar logic, no branch per sum.  The masks of all lanes go to LDS,
         // colmask[frame block of 32][g][output of the tile], and are turned into output words afterwards.
-        // LDS: column masks 2 WM x 2 x 64 WN x 2 bytes | the frames' quantisation records | per frame and 128 outputs: how many are
-        // undecided | their records (about one output in 250 is expected at K = 2048).
+        // LDS: column masks 2 WM x 2 x 64 WN x 2 bytes | the frames' quantisation records | per frame and 128 outputs the record
+        // of undecided ones (about one output in 250 is expected at K = 2048).
         uint16_t* colmask = reinterpret_cast<uint16_t*>(i8_lds);
         constexpr int kMaskBytes = 2 * WM * 2 * kTileN * 2, kRecs = kTileN / kUndecidedOutputs, kAllRecs = kTileM * kRecs;
         RowMeta* meta_s = reinterpret_cast<RowMeta*>(i8_lds + kMaskBytes);
-        unsigned int* und_count = reinterpret_cast<unsigned int*>(i8_lds + kMaskBytes + kTileM * sizeof(RowMeta));
-        unsigned char* und = reinterpret_cast<unsigned char*>(und_count + kAllRecs);   // [frame][kRecs][kUndecidedRecord]
-        static_assert((kMaskBytes + kTileM * sizeof(RowMeta)) % 16 == 0 &&
-                          kMaskBytes + kTileM * sizeof(RowMeta) + kAllRecs * (4 + kUndecidedRecord) <= i8_gemm_lds(3, WM, WN) &&
-                          kAllRecs <= kI8Threads && kAllRecs % 4 == 0,
+        u32x4* und = reinterpret_cast<u32x4*>(i8_lds + kMaskBytes + kTileM * sizeof(RowMeta));   // [frame][kRecs]
+        static_assert((kMaskBytes + kTileM * sizeof(RowMeta)) % 16 == 0 && sizeof(u32x4) == kUndecidedRecord &&
+                          kMaskBytes + kTileM * sizeof(RowMeta) + kAllRecs * kUndecidedRecord <= i8_gemm_lds(3, WM, WN) &&
+                          kAllRecs <= kI8Threads,
                       "epilogue LDS");
         if (tid < kTileM) {
             const int m = m_tile + tid;
             meta_s[tid] = meta[m < M ? m : M - 1];
         }
-        if (tid < kAllRecs) und_count[tid] = 0u;
+        if (tid < kAllRecs) und[tid] = u32x4{0u, 0u, 0u, 0u};
         __syncthreads();
         float sc[WN], bi[WN], asc[WN];
         bool nvalid[WN];
@@ -386,14 +384,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, W
                     const int v = __builtin_ctz(ub);
                     ub &= ub - 1u;
                     const int ml = fb * 32 + 8 * (v >> 2) + 4 * g + (v & 3);
-                    const int rec = ml * kRecs + nl / kUndecidedOutputs;
-                    const unsigned int slot = atomicAdd(&und_count[rec], 1u);
-                    if (slot < (unsigned int)kUndecidedMax) {
-                        und[rec * kUndecidedRecord + 1 + (int)slot] = (unsigned char)(nl % kUndecidedOutputs);
-                    } else {   // more than the frame's record holds: summed here
-                        const int m = m_tile + ml, n = n_tile + nl;
-                        if (sign_bit(affine(sc[fn], canonical_acc_global(X + (size_t)m * K, Wp + (size_t)n * w32, K), bi[fn]))) bt |= 1u << v;
-                    }
+                    atomicOr(reinterpret_cast<uint32_t*>(und) + ml * (kTileN / 32) + (nl >> 5), 1u << (nl & 31));
                 }
                 colmask[(fb * 2 + g) * kTileN + nl] = (uint16_t)bt;
             }
@@ -430,10 +421,7 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, W
         if (tid < kAllRecs) {
             const int m = m_tile + tid / kRecs, q = n_tile / kUndecidedOutputs + tid % kRecs;
             const int recs = (N + kUndecidedOutputs - 1) / kUndecidedOutputs;
-            u32x4 rec = *reinterpret_cast<const u32x4*>(und + tid * kUndecidedRecord);
-            const unsigned int cnt = und_count[tid] < (unsigned int)kUndecidedMax ? und_count[tid] : (unsigned int)kUndecidedMax;
-            rec.x = (rec.x & ~0xFFu) | cnt;
-            if (m < M && q < recs) *reinterpret_cast<u32x4*>(undecided + ((size_t)m * recs + q) * kUndecidedRecord) = rec;
+            if (m < M && q < recs) *reinterpret_cast<u32x4*>(undecided + ((size_t)m * recs + q) * kUndecidedRecord) = und[tid];
         }
     } else {
         const RowMeta4* meta = static_cast<const RowMeta4*>(meta_in);
@@ -508,8 +496,8 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, W
 // slabs of 256 k, twice buffered (the next slab is on its way from memory while this one is added up, one barrier per
 // slab); a lane reads its frame's values from there (lanes of one frame read the same address, the 16 frames lie in
 // different banks), forms the signs from its own weight words (eight per slab, read one slab ahead) and adds.
-// More than 256 outputs: further passes over the frames; more than kResolveCap: the lane that finds them sums them
-// from global memory.  The last slab of a frame is padded with +0 and added up to the end of the block of 32 in which the
+// More than 256 outputs: further passes over the frames; more than kResolveCap: further rounds, a thread keeping what its
+// records still hold.  The last slab of a frame is padded with +0 and added up to the end of the block of 32 in which the
 // frame ends.
 // VEC: K % 4 == 0 and X 16-byte aligned.  Grid: ceil(M / 16) workgroups of 256 threads.
 constexpr int kResolveFrames = 16;
@@ -599,85 +587,98 @@ __global__ __launch_bounds__(kResolveThreads) void realx_resolve_rows_kernel(con
     };
     Pieces P;
     request(P, 0);   // the frames' first slab is on its way while the records are read
-    if (tid == 0) total_s = 0u;
-    __syncthreads();
-    for (int t = tid; t < kResolveFrames * recs; t += kResolveThreads) {
-        const int r = t / recs, q = t - r * recs;
-        const int m = m0 + r;
-        if (m >= M) continue;
-        const u32x4 rec = *reinterpret_cast<const u32x4*>(undecided + ((size_t)m * recs + q) * kUndecidedRecord);
-        const int cnt = min((int)(rec.x & 0xFFu), kUndecidedMax);
-        if (cnt == 0) continue;
-        const unsigned int base = atomicAdd(&total_s, (unsigned int)cnt);
-        for (int i = 0; i < cnt; ++i) {
-            const int b = i + 1;   // byte of the record
-            const unsigned int word = b < 8 ? (b < 4 ? rec.x : rec.y) : (b < 12 ? rec.z : rec.w);
-            const int n = q * kUndecidedOutputs + (int)((word >> (8 * (b & 3))) & 0xFFu);
-            if (base + i < (unsigned int)kResolveCap) {
-                ent[base + i] = ((unsigned int)r << 28) | (unsigned int)n;
-            } else {
-                const float s1 = scale ? scale[n] : 1.0f, b1 = bias ? bias[n] : 0.0f;
-                if (sign_bit(affine(s1, canonical_acc_global(X + (size_t)m * K, Wp + (size_t)n * w32, K), b1)))
-                    atomicOr(&Y[(size_t)m * yw32 + (n >> 5)], 1u << (n & 31));
-            }
-        }
-    }
-    __syncthreads();
-    const int total = (int)min(total_s, (unsigned int)kResolveCap);   // workgroup-uniform
-    if (total == 0) return;
-    for (int first = 0; first < total; first += kResolveThreads) {   // workgroup-uniform
-        const bool active = first + tid < total;
-        const unsigned int e = ent[active ? first + tid : 0];
-        const int r = (int)(e >> 28), n = (int)(e & 0x0FFFFFFFu);
-        const uint32_t* wrow = Wp + (size_t)n * w32;
-        const int wlast = (K - 1) >> 5;
-        constexpr int kWords = kResolveSlab / 32;
-        static_assert(kWords == 8, "eight weight words per slab and lane");
-        float acc32 = 0.0f;
-        struct Words { u32x4 lo, hi; };
-        auto words = [&](Words& w, int sl) {
-            uint32_t v[kWords];
-#pragma unroll
-            for (int b = 0; b < kWords; ++b) v[b] = wrow[min(sl * kWords + b, wlast)];
-            w.lo = u32x4{v[0], v[1], v[2], v[3]};
-            w.hi = u32x4{v[4], v[5], v[6], v[7]};
-        };
-        // What comes from global memory (the frames' next slab, the lane's next eight weight words) is requested before
-        // the slab is added up and goes to LDS after it: nothing in between waits for memory.
-        Words W;
-        __syncthreads();   // the previous pass no longer reads the buffers
-        if (first > 0) request(P, 0);
-        words(W, 0);
-        deposit(P, 0);
-        ws[0][tid][0] = W.lo;
-        ws[0][tid][1] = W.hi;
+    int t = tid;                          // the thread's record: frame t / recs of the workgroup
+    u32x4 left{0u, 0u, 0u, 0u};           // its outputs that are still to be taken
+    bool loaded = false, again = false;   // again: not the first pass over the frames
+    for (;;) {
+        if (tid == 0) total_s = 0u;
         __syncthreads();
-        for (int sl = 0; sl < nsl; ++sl) {
-            if (sl + 1 < nsl) {   // workgroup-uniform
-                request(P, sl + 1);
-                words(W, sl + 1);
+        while (t < kResolveFrames * recs) {
+            const int r = t / recs, q = t - r * recs;
+            if (!loaded) {
+                if (m0 + r < M) left = *reinterpret_cast<const u32x4*>(undecided + ((size_t)(m0 + r) * recs + q) * kUndecidedRecord);
+                loaded = true;
+            }
+            const int cnt = __builtin_popcount(left.x) + __builtin_popcount(left.y) + __builtin_popcount(left.z) + __builtin_popcount(left.w);
+            if (cnt) {
+                // (places are given out without gaps, so a list that could not take everything is full)
+                const unsigned int base = atomicAdd(&total_s, (unsigned int)cnt);
+                const int room = base < (unsigned int)kResolveCap ? min(cnt, kResolveCap - (int)base) : 0;
+                for (int i = 0; i < room; ++i) {
+                    const int w = left.x ? 0 : left.y ? 1 : left.z ? 2 : 3;
+                    const uint32_t v = left.x ? left.x : left.y ? left.y : left.z ? left.z : left.w;
+                    const uint32_t rest = v & (v - 1u);
+                    ent[base + i] = ((unsigned int)r << 28) | (unsigned int)(q * kUndecidedOutputs + 32 * w + __builtin_ctz(v));
+                    if (w == 0) left.x = rest;
+                    else if (w == 1) left.y = rest;
+                    else if (w == 2) left.z = rest;
+                    else left.w = rest;
+                }
+                if (room < cnt) break;
+            }
+            t += kResolveThreads;
+            loaded = false;
+        }
+        __syncthreads();
+        const unsigned int found = total_s;                          // workgroup-uniform
+        const int total = (int)min(found, (unsigned int)kResolveCap);
+        for (int first = 0; first < total; first += kResolveThreads) {   // workgroup-uniform
+            const bool active = first + tid < total;
+            const unsigned int e = ent[active ? first + tid : 0];
+            const int r = (int)(e >> 28), n = (int)(e & 0x0FFFFFFFu);
+            const uint32_t* wrow = Wp + (size_t)n * w32;
+            const int wlast = (K - 1) >> 5;
+            constexpr int kWords = kResolveSlab / 32;
+            static_assert(kWords == 8, "eight weight words per slab and lane");
+            float acc32 = 0.0f;
+            struct Words { u32x4 lo, hi; };
+            auto words = [&](Words& w, int sl) {
+                uint32_t v[kWords];
+    #pragma unroll
+                for (int b = 0; b < kWords; ++b) v[b] = wrow[min(sl * kWords + b, wlast)];
+                w.lo = u32x4{v[0], v[1], v[2], v[3]};
+                w.hi = u32x4{v[4], v[5], v[6], v[7]};
+            };
+            // What comes from global memory (the frames' next slab, the lane's next eight weight words) is requested before
+            // the slab is added up and goes to LDS after it: nothing in between waits for memory.
+            Words W;
+            __syncthreads();   // the previous pass no longer reads the buffers
+            if (again) request(P, 0);
+            again = true;
+            words(W, 0);
+            deposit(P, 0);
+            ws[0][tid][0] = W.lo;
+            ws[0][tid][1] = W.hi;
+            __syncthreads();
+            for (int sl = 0; sl < nsl; ++sl) {
+                if (sl + 1 < nsl) {   // workgroup-uniform
+                    request(P, sl + 1);
+                    words(W, sl + 1);
+                }
+                if (active) {
+                    // The slab's 256 terms as one stream (the last slab of a frame is padded with +0).  A result is ready some
+                    // clocks after its instruction, and a wave has nothing else to issue meanwhile, so no instruction reads
+                    // what one of the two before it wrote: around the addition of term t stand the mask of term t + 4, the
+                    // shift of term t + 8 and, every fourth term, the LDS read of terms t + 16 .. t + 19.
+                    const u32x4 lo = ws[sl & 1][tid][0], hi = ws[sl & 1][tid][1];
+                    const uint32_t wc[kWords] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
+                    resolve_slab(K - sl * kResolveSlab, &xs[sl & 1][r][0], wc, acc32, std::make_integer_sequence<int, kResolveSlab + 16>{});
+                }
+                if (sl + 1 < nsl) {
+                    deposit(P, sl + 1);
+                    ws[(sl + 1) & 1][tid][0] = W.lo;
+                    ws[(sl + 1) & 1][tid][1] = W.hi;
+                }
+                __syncthreads();
             }
             if (active) {
-                // The slab's 256 terms as one stream (the last slab of a frame is padded with +0).  A result is ready some
-                // clocks after its instruction, and a wave has nothing else to issue meanwhile, so no instruction reads
-                // what one of the two before it wrote: around the addition of term t stand the mask of term t + 4, the
-                // shift of term t + 8 and, every fourth term, the LDS read of terms t + 16 .. t + 19.
-                const u32x4 lo = ws[sl & 1][tid][0], hi = ws[sl & 1][tid][1];
-                const uint32_t wc[kWords] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
-                resolve_slab(K - sl * kResolveSlab, &xs[sl & 1][r][0], wc, acc32, std::make_integer_sequence<int, kResolveSlab + 16>{});
+                const int m = m0 + r;
+                const float s1 = scale ? scale[n] : 1.0f, b1 = bias ? bias[n] : 0.0f;
+                if (sign_bit(affine(s1, acc32, b1))) atomicOr(&Y[(size_t)m * yw32 + (n >> 5)], 1u << (n & 31));
             }
-            if (sl + 1 < nsl) {
-                deposit(P, sl + 1);
-                ws[(sl + 1) & 1][tid][0] = W.lo;
-                ws[(sl + 1) & 1][tid][1] = W.hi;
-            }
-            __syncthreads();
         }
-        if (active) {
-            const int m = m0 + r;
-            const float s1 = scale ? scale[n] : 1.0f, b1 = bias ? bias[n] : 0.0f;
-            if (sign_bit(affine(s1, acc32, b1))) atomicOr(&Y[(size_t)m * yw32 + (n >> 5)], 1u << (n & 31));
-        }
+        if (found <= (unsigned int)kResolveCap) return;   // every record is empty
+        __syncthreads();                                  // (nobody clears total_s before all have read it)
     }
 }
 

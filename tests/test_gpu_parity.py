@@ -680,11 +680,30 @@ def test_slab_filter_sigmoid_inputs_and_near_ties(G, bnn, oracle):
     want = oracle.layer_binw_realx(X, Wp, K, scale, bias, "sign", wb)
     frac = np.unpackbits(want.view(np.uint8), bitorder="little").mean()
     assert 0.05 < frac < 0.95
-    # the tiled product records what it cannot decide per frame and 128 outputs (here about 55, far more than the 15 a record
-    # holds, and more than 1024 for 16 frames where the second kernel takes 1024: the rest is summed by the lane that finds
-    # it, in either kernel); the 16-frame kernel keeps its list in LDS
+    # the tiled product records what it cannot decide as one bit per output (here about 55 of 128), and the second kernel sums
+    # them in rounds of 1024 for 16 frames (about 8 rounds here); the 16-frame kernel keeps its list in LDS and sums what does
+    # not fit where it is found
     for arm in (1, 2):
         assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, arm), want), arm
+
+
+@pytest.mark.parametrize("N", [63, 64, 65, 128, 129])
+@pytest.mark.parametrize("K", [516, 769])
+def test_undecided_outputs_around_one_round_of_exact_sums(G, bnn, oracle, K, N):
+    """Every output of every frame within rounding of 0: 16 N exact sums per 16 frames, where a round takes 1024; the last
+    workgroup has 5 frames."""
+    M, wb = 133, 32
+    X, W, scale, bias = _rand_layer(K + N, M, K, N)
+    X[:] = X[0]
+    X[1::2] *= np.float32(1.0 + 2.0 ** -22)
+    Wp = oracle.pack_sign(W, wb)
+    acc32, _ = oracle.realx_acc(X[:1], oracle.unpack_pm1(Wp, K, wb))
+    bias = (-scale * acc32[0]).astype(np.float32)
+    bias[::3] = np.nextafter(bias[::3], np.float32(np.inf))
+    bias[1::3] = np.nextafter(bias[1::3], np.float32(-np.inf))
+    want = oracle.layer_binw_realx(X, Wp, K, scale, bias, "sign", wb)
+    assert 0.05 < np.unpackbits(want.view(np.uint8), bitorder="little").mean() < 0.95
+    assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, 1), want)
 
 
 @pytest.mark.parametrize("M", [70, 200])
