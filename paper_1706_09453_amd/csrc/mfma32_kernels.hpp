@@ -304,65 +304,44 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
             else if (part == 2) d[2] = (int)((w >> 2) & em.b0);   // 0.5 (the shift serves part 3 too)
             else d[3] = (int)((w >> 2) & em.b1);              // 1
         };
-        auto products = [&](const uint4 (&a)[WM], const uint4 (&b)[WN]) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                v8i bx[WN];
-#pragma unroll
-                for (int f = 0; f < WN; ++f) {
-                    clear_hi(bx[f]);
-#pragma unroll
-                    for (int part = 0; part < 4; ++part) weights_piece(bx[f], word_of(b[f], j), part);
-                    if constexpr (!X01) count(ones_b[f], word_of(b[f], j));
-                }
-#pragma unroll
-                for (int fm = 0; fm < WM; ++fm) {
-                    v8i ax;
-                    clear_hi(ax);
-#pragma unroll
-                    for (int part = 0; part < 4; ++part) frames_piece(ax, word_of(a[fm], j), part);
-                    count(ones_a[fm], word_of(a[fm], j));
-#pragma unroll
-                    for (int fn = 0; fn < WN; ++fn)
-                        acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ax, bx[fn], acc[fm][fn], 4, 4, 0, 0, 0, 0);
-                }
-            }
-        };
         if (nS > 2) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(2 * (AI + BI)) : "memory");
         else if (nS > 1) asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(AI + BI) : "memory");
         else asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
         uint4 a0[WM], b0[WN], a1[WM], b1[WN];
         fetch(a0, b0, 0, so0);
-        if constexpr (WM >= 4) {
-            // Issue order inside a half-step, written out and pinned slot by slot.  A wave issues in order, and an MFMA that
-            // finds the pipe busy (32 clocks per 32x32x64) blocks whatever follows it.  Here every MFMA is followed by four or
-            // five expansion instructions of operands needed two to eight MFMAs later, which issue in its shadow: the frames
-            // fragment fm+1 of this step while fm is multiplied, and the two weights fragments and frames fragment 0 of the
-            // NEXT step (taken from the next half-stage's words after the last step of a half-stage) spread over the slots.
-            static_assert(WM == 4 && WN == 2, "the slot plan below is written for 4 x 2 fragments");
-            v8i bx[2][WN];   // expanded weights: [parity of the step][fragment]
-            v8i ax[2];       // expanded frames: fragment fm lives in ax[fm & 1]
-            clear_hi(ax[0]); clear_hi(ax[1]);
+        // Issue order inside a half-step, written out and pinned slot by slot.  A wave issues in order, and an MFMA that
+        // finds the pipe busy (32 clocks per 32x32x64) blocks whatever follows it.  Here every MFMA is followed by four to
+        // seven expansion instructions of operands needed two to eight MFMAs later, which issue in its shadow: the frames
+        // fragment fm+1 of this step while fm is multiplied, and the two weights fragments and frames fragment 0 of the
+        // NEXT step (taken from the next half-stage's words after the last step of a half-stage) spread over the slots.
+        // (64-row tiles with the order left to the compiler, which starts every half-step with seventeen expansions in a row:
+        // 315 x 7680 x 4096 15.4 -> 13.6 us, 600 x 2048 x 2048 6.2 -> 5.8.)
+        static_assert((WM == 4 || WM == 2) && WN == 2, "the slot plans below are written for 4 x 2 and 2 x 2 fragments");
+        v8i bx[2][WN];   // expanded weights: [parity of the step][fragment]
+        v8i ax[2];       // expanded frames: fragment fm lives in ax[fm & 1]
+        clear_hi(ax[0]); clear_hi(ax[1]);
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int f = 0; f < WN; ++f) clear_hi(bx[t][f]);
-            auto half_step = [&](const uint4 (&a)[WM], const uint4 (&b)[WN], const uint4 (&an)[WM], const uint4 (&bn)[WN]) {
+            for (int f = 0; f < WN; ++f) clear_hi(bx[t][f]);
+        auto half_step = [&](const uint4 (&a)[WM], const uint4 (&b)[WN], const uint4 (&an)[WM], const uint4 (&bn)[WN]) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int pc = j & 1, pn = pc ^ 1;
-                    // words of the next step: the next word of this set, or the first word of the next set
-                    const uint32_t wb0 = j < 3 ? word_of(b[0], j + 1) : word_of(bn[0], 0);
-                    const uint32_t wb1 = j < 3 ? word_of(b[1], j + 1) : word_of(bn[1], 0);
-                    const uint32_t wa0 = j < 3 ? word_of(a[0], j + 1) : word_of(an[0], 0);
-                    const uint32_t wa1 = word_of(a[1], j), wa2 = word_of(a[2], j), wa3 = word_of(a[3], j);
-                    auto count_a = [&](int f) { count(ones_a[f], word_of(a[f], j)); };
-                    auto count_b = [&](int f) { if constexpr (!X01) count(ones_b[f], word_of(b[f], j)); };
-                    auto fp = [&](int f, uint32_t w, int p) { frames_piece(ax[f & 1], w, p); };
-                    auto wp = [&](int f, uint32_t w, int p) { weights_piece(bx[pn][f], w, p); };
+            for (int j = 0; j < 4; ++j) {
+                const int pc = j & 1, pn = pc ^ 1;
+                // words of the next step: the next word of this set, or the first word of the next set
+                const uint32_t wb0 = j < 3 ? word_of(b[0], j + 1) : word_of(bn[0], 0);
+                const uint32_t wb1 = j < 3 ? word_of(b[1], j + 1) : word_of(bn[1], 0);
+                const uint32_t wa0 = j < 3 ? word_of(a[0], j + 1) : word_of(an[0], 0);
+                const uint32_t wa1 = word_of(a[1], j);
+                auto count_a = [&](int f) { count(ones_a[f], word_of(a[f], j)); };
+                auto count_b = [&](int f) { if constexpr (!X01) count(ones_b[f], word_of(b[f], j)); };
+                auto fp = [&](int f, uint32_t w, int p) { frames_piece(ax[f & 1], w, p); };
+                auto wp = [&](int f, uint32_t w, int p) { weights_piece(bx[pn][f], w, p); };
 #define BNN_MFMA(fm, fn) acc[fm][fn] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ax[(fm) & 1], bx[pc][fn], acc[fm][fn], 4, 4, 0, 0, 0, 0)
 #define BNN_SLOT_END __builtin_amdgcn_sched_barrier(0)
+                if constexpr (WM == 4) {
+                    const uint32_t wa2 = word_of(a[2], j), wa3 = word_of(a[3], j);
                     BNN_MFMA(0, 0); fp(1, wa1, 0); fp(1, wa1, 1); fp(1, wa1, 2); count_a(0); BNN_SLOT_END;
                     BNN_MFMA(0, 1); fp(1, wa1, 3); wp(0, wb0, 0); wp(0, wb0, 1); BNN_SLOT_END;
                     BNN_MFMA(1, 0); fp(2, wa2, 0); fp(2, wa2, 1); fp(2, wa2, 2); count_a(1); BNN_SLOT_END;
@@ -372,50 +351,51 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
                     // frames fragment 0 of the next step overwrites ax[0], which MFMA (2, *) has finished reading
                     BNN_MFMA(3, 0); fp(0, wa0, 0); fp(0, wa0, 1); fp(0, wa0, 2); count_a(3); count_b(1); BNN_SLOT_END;
                     BNN_MFMA(3, 1); fp(0, wa0, 3); wp(1, wb1, 2); wp(1, wb1, 3); BNN_SLOT_END;
+                } else {
+                    BNN_MFMA(0, 0); fp(1, wa1, 0); fp(1, wa1, 1); fp(1, wa1, 2); count_a(0); wp(0, wb0, 1); wp(1, wb1, 1); BNN_SLOT_END;
+                    BNN_MFMA(0, 1); fp(1, wa1, 3); wp(0, wb0, 0); wp(0, wb0, 2); wp(0, wb0, 3); BNN_SLOT_END;
+                    // as above: ax[0], which MFMA (0, *) has finished reading
+                    BNN_MFMA(1, 0); fp(0, wa0, 0); fp(0, wa0, 1); fp(0, wa0, 2); count_a(1); count_b(0); wp(1, wb1, 0); BNN_SLOT_END;
+                    BNN_MFMA(1, 1); fp(0, wa0, 3); wp(1, wb1, 2); wp(1, wb1, 3); count_b(1); BNN_SLOT_END;
+                }
 #undef BNN_MFMA
 #undef BNN_SLOT_END
-                }
-            };
-            {   // operands of the very first step
-#pragma unroll
-                for (int part = 0; part < 4; ++part) {
-                    weights_piece(bx[0][0], word_of(b0[0], 0), part);
-                    weights_piece(bx[0][1], word_of(b0[1], 0), part);
-                    frames_piece(ax[0], word_of(a0[0], 0), part);
-                }
             }
-            int slot = 0, S = 0;
-            do {   // (K > 0: at least one stage)
-                const int nslot = next_slot(slot);
-                fetch(a1, b1, slot, so1);
-                __builtin_amdgcn_sched_barrier(0);
-                half_step(a0, b0, a1, b1);
-                __builtin_amdgcn_sched_barrier(0);
-                turn(S);
-                fetch(a0, b0, S + 1 < nS ? nslot : slot, so0);   // (behind the last stage: read again, unused)
-                if (S + 3 < nS) request(S + 3, slot);
-                __builtin_amdgcn_sched_barrier(0);
-                half_step(a1, b1, a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-                slot = nslot;
-            } while (++S < nS);
-        } else {
-            int slot = 0, S = 0;
-            do {   // (K > 0: at least one stage)
-                const int nslot = next_slot(slot);
-                fetch(a1, b1, slot, so1);
-                __builtin_amdgcn_sched_barrier(0);
-                products(a0, b0);
-                __builtin_amdgcn_sched_barrier(0);
-                turn(S);
-                fetch(a0, b0, S + 1 < nS ? nslot : slot, so0);
-                if (S + 3 < nS) request(S + 3, slot);
-                __builtin_amdgcn_sched_barrier(0);
-                products(a1, b1);
-                __builtin_amdgcn_sched_barrier(0);
-                slot = nslot;
-            } while (++S < nS);
+        };
+        auto pin_low = [](v8i& d) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                int v = d[i];
+                asm volatile("" : "+v"(v));
+                d[i] = v;
+            }
+        };
+        {   // operands of the very first step
+#pragma unroll
+            for (int part = 0; part < 4; ++part) {
+                weights_piece(bx[0][0], word_of(b0[0], 0), part);
+                weights_piece(bx[0][1], word_of(b0[1], 0), part);
+                frames_piece(ax[0], word_of(a0[0], 0), part);
+            }
         }
+        int slot = 0, S = 0;
+        do {   // (K > 0: at least one stage)
+            const int nslot = next_slot(slot);
+            fetch(a1, b1, slot, so1);
+            __builtin_amdgcn_sched_barrier(0);
+            half_step(a0, b0, a1, b1);
+            pin_low(ax[0]);   // expanded in front of the barrier, in the shadow of the last products, not behind it
+#pragma unroll
+            for (int f = 0; f < WN; ++f) pin_low(bx[0][f]);
+            __builtin_amdgcn_sched_barrier(0);
+            turn(S);
+            fetch(a0, b0, S + 1 < nS ? nslot : slot, so0);   // (behind the last stage: read again, unused)
+            if (S + 3 < nS) request(S + 3, slot);
+            __builtin_amdgcn_sched_barrier(0);
+            half_step(a1, b1, a0, b0);
+            __builtin_amdgcn_sched_barrier(0);
+            slot = nslot;
+        } while (++S < nS);
         // The counts join the sum (see "0/1 operands" above) as one more product per fragment, in bfloat16, eight bits of a count
         // per element of k: acc - popcount(frame) / 2 [- popcount(weights) / 2].
         {

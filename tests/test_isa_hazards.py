@@ -99,6 +99,26 @@ def test_no_lds_read_is_under_way_at_a_barrier_of_the_loads_that_write_lds(code)
     assert n > 0 and not bad, (n, len(bad), sorted(bad)[:4])
 
 
+def test_binary_product_loops_wait_for_no_more_lds_reads_than_they_need(code):
+    """The words of a stage's second half are requested in front of the products of its first half, and are not to be waited
+    for there: no block with products of the kernels that fetch through LDS has a wait for all LDS operations (the one at
+    the stage's barrier, which also counts memory, aside)."""
+    n, bad = 0, set()
+    for name, body in _kernels(code):
+        if "binx_mfma32_kernel" not in name or not any(_loads_lds(l) for l in body):
+            continue
+        products = waits = 0
+        for ins in body + ["end:"]:
+            if ins.endswith(":"):
+                n += products > 0
+                if products and waits:
+                    bad.add(name)
+                products = waits = 0
+            products += ins.startswith("v_mfma_f32_32x32x64_f8f6f4")
+            waits += ins == "s_waitcnt lgkmcnt(0)"
+    assert n > 0 and not bad, (n, len(bad), sorted(bad)[:4])
+
+
 def test_loads_that_write_lds_do_not_read_fresh_sgprs(code):
     n, bad = 0, []
     for name, body in _kernels(code):
