@@ -310,6 +310,14 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
         __builtin_amdgcn_sched_barrier(0);
         uint4 a0[WM], b0[WN], a1[WM], b1[WN];
         fetch(a0, b0, 0, so0);
+        // (scale and bias here, not in front of the epilogue, where a wave has nothing else to do meanwhile)
+        const float* affine_s = reinterpret_cast<const float*>(m32_mem + kM32Stages * kStage) + (wave & 1) * (32 * WN) + r;
+#pragma unroll
+        for (int f = 0; f < WN; ++f) {
+            const bool in = n_base + f * 32 + r < N;
+            sc[f] = in ? (scale ? affine_s[f * 32] : 1.0f) : 0.0f;
+            bi[f] = in ? (bias ? affine_s[64 * WN + f * 32] : 0.0f) : 0.0f;
+        }
         // Issue order inside a half-step, written out and pinned slot by slot.  A wave issues in order, and an MFMA that
         // finds the pipe busy (32 clocks per 32x32x64) blocks whatever follows it.  Here every MFMA is followed by four to
         // seven expansion instructions of operands needed two to eight MFMAs later, which issue in its shadow: the frames
@@ -397,14 +405,15 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
             slot = nslot;
         } while (++S < nS);
         // The counts join the sum (see "0/1 operands" above) as one more product per fragment, in bfloat16, eight bits of a count
-        // per element of k: acc - popcount(frame) / 2 [- popcount(weights) / 2].
+        // per element of k: acc - popcount(frame) / 2 [- popcount(weights) / 2].  Each of the two lanes of a row brings its own
+        // share of the count, and the product adds them up.
         {
             typedef __bf16 bf16x8m __attribute__((ext_vector_type(8)));
             typedef uint32_t u32x4m __attribute__((ext_vector_type(4)));
             auto hi = [](float v) { return __float_as_uint(v) >> 16; };   // (eight significant bits: exact)
             const uint32_t h0 = hi(-0.5f), h1 = hi(-128.0f), h2 = hi(-32768.0f);
             auto share = [&](int ones, uint32_t (&q)[3]) {
-                const uint32_t c = (uint32_t)(ones + __shfl_xor(ones, 32, kWave));
+                const uint32_t c = (uint32_t)ones;
                 q[0] = hi((float)(c & 255u));
                 q[1] = hi((float)((c >> 8) & 255u));
                 q[2] = hi((float)(c >> 16));
@@ -414,29 +423,22 @@ __global__ __launch_bounds__(256, 2) void binx_mfma32_kernel(const uint32_t* __r
             for (int f = 0; f < WN; ++f) {
                 uint32_t q[3] = {0u, 0u, 0u};
                 if constexpr (!X01) share(ones_b[f], q);
-                cb[f] = __builtin_bit_cast(bf16x8m, g == 0 ? u32x4m{h0 | (h1 << 16), h2 | (q[0] << 16), q[1] | (q[2] << 16), 0u} : u32x4m{0u, 0u, 0u, 0u});
+                cb[f] = __builtin_bit_cast(bf16x8m, u32x4m{h0 | (h1 << 16), h2 | (q[0] << 16), q[1] | (q[2] << 16), 0u});
             }
 #pragma unroll
             for (int f = 0; f < WM; ++f) {
                 uint32_t q[3];
                 share(ones_a[f], q);
-                const bf16x8m ca = __builtin_bit_cast(bf16x8m, g == 0 ? (X01 ? u32x4m{q[0] | (q[1] << 16), q[2], 0u, 0u}
-                                                                            : u32x4m{q[0] | (q[1] << 16), q[2] | (h0 << 16), h1 | (h2 << 16), 0u})
-                                                                     : u32x4m{0u, 0u, 0u, 0u});
+                const bf16x8m ca = __builtin_bit_cast(bf16x8m, X01 ? u32x4m{q[0] | (q[1] << 16), q[2], 0u, 0u}
+                                                                   : u32x4m{q[0] | (q[1] << 16), q[2] | (h0 << 16), h1 | (h2 << 16), 0u});
 #pragma unroll
                 for (int fn = 0; fn < WN; ++fn) acc[f][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ca, cb[fn], acc[f][fn], 0, 0, 0);
             }
         }
-        if constexpr (ACT != ACT_SIGN) __syncthreads();   // the epilogue takes the stages' place
+        // The epilogue takes the stages' place with no barrier of its own: behind the last stage's every wave has what it uses of
+        // them in registers and no load is under way (what is read again behind it is not used).
         if constexpr (ACT != ACT_LSM_COOP) {
             if (m_base >= M || n_base >= N) return;   // wave-uniform
-        }
-        const float* affine_s = reinterpret_cast<const float*>(m32_mem + kM32Stages * kStage) + (wave & 1) * (32 * WN) + r;
-#pragma unroll
-        for (int f = 0; f < WN; ++f) {
-            const bool in = n_base + f * 32 + r < N;
-            sc[f] = in ? (scale ? affine_s[f * 32] : 1.0f) : 0.0f;
-            bi[f] = in ? (bias ? affine_s[64 * WN + f * 32] : 0.0f) : 0.0f;
         }
     } else {
         const ExpandConsts ec = expand_consts();
