@@ -456,20 +456,24 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         const bool al = rows16 && (K % 512 == 0);
         if (i16) act = ACT_DOT_I16;
         const int64_t tiles_n4 = (N + 127) / 128, tiles4 = ((M + 255) / 256) * tiles_n4;
-        // 128-row wave tiles expand fewer operand words per MAC; 64-row ones give twice the workgroups, which
-        // matters more while the 128-row grid leaves CUs without a workgroup (measured on MI355X: 64-row tiles win
-        // up to 2048 frames x 2048 outputs, 128-row tiles from 4096 x 2048 on)
-        const int64_t blocks4 = ((M + 255) / 256) * ((N + 127) / 128);
-        const int wm32 = g_mfma32_wm.load();
-        const bool wm2 = wm32 == 2 || (wm32 == 0 && blocks4 < 200);
         // fetch through LDS, order pinned: 16384 x 4096 x 4096 95 us against 124 from memory to registers, 4096 x 2048 x 2048 9.3
-        // and 10.5, 600 x 2048 x 2048 6.5 and 9.2.  Buffer addressing needs operands below 2 GiB, exact sums of 0/1 products and
+        // and 10.5, 600 x 2048 x 2048 5.8 and 9.2.  Buffer addressing needs operands below 2 GiB, exact sums of 0/1 products and
         // counts in fp32 K < 2^22
         const bool pinned = g_mfma32_pipeline.load() != 2 && K < (1 << 22) && (size_t)M * w32 * 4 < 0x7fffffffu && (size_t)N * w32 * 4 < 0x7fffffffu;
+        const bool lsm = act == BNN_ACT_LOGSOFTMAX || act == ACT_DOT_I16, coop_asked = lsm && g_cooperative.load();
+        // 128-row wave tiles expand fewer operand words per MAC; 64-row ones give twice the workgroups, which
+        // matters more while the 128-row grid leaves CUs without a workgroup (measured on MI355X: 64-row tiles win
+        // up to 2048 frames x 2048 outputs, 128-row tiles from 4096 x 2048 on).  With a single stage of K a workgroup is mostly
+        // its start and its end, and more of them on a CU cover each other (128 and 64 rows, K = 512: 11789 x 4410 20.6 and 18.8 us,
+        // 9247 x 3808 16.9 and 15.1, 4998 x 4864 11.1 and 9.5, 16384 x 4000 with the log-Softmax 105 and 95; but K = 1024: 11789 x 4410
+        // 25.7 and 26.1, 8192 x 2048 9.0 and 9.2).
+        const int64_t blocks4 = ((M + 255) / 256) * ((N + 127) / 128);
+        const int wm32 = g_mfma32_wm.load();
+        const bool wm2 = wm32 == 2 || (wm32 == 0 && (blocks4 < 200 || (K == 512 && pinned && !coop_asked)));
         // Cooperative log-Softmax (opt-in): the product kernel finishes the rows itself.  Its workgroups wait for each
         // other, so all of them have to be resident at once.
         CoopLsm coop{};
-        if ((act == BNN_ACT_LOGSOFTMAX || act == ACT_DOT_I16) && g_cooperative.load() && al && pinned && !wm2 && tiles_n4 <= 64 &&
+        if (coop_asked && al && pinned && !wm2 && tiles_n4 <= 64 &&
             tiles4 <= kCoopMaxTiles) {
             int dev = -1;
             unsigned char* base = coop_base(&dev);
