@@ -706,8 +706,8 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     launch_split(X, M, Ki, kpad, xs, st);
     launch_split(W, N, Ki, kpad, ws, st);
     // 256 x 128 outputs per workgroup or 128 x 128?  One workgroup per CU either way, and a round of the small ones takes 0.55 to
-    // 0.6 of the time.  Whole layers, K = 2048, large -> small: 600 frames x 3400 outputs 145 -> 90 us, 4096 x 1000 155 -> 112, three
-    // rounds against two 306 -> 263 (2600 x 3400); but two against one 174 -> 183 (2048 x 3400), five against three 483 -> 498.
+    // 0.65 of the time.  Whole layers, K = 2048, large -> small: 600 frames x 3400 outputs 127 -> 82 us, 4096 x 1000 138 -> 111, three
+    // rounds against two 279 -> 246 (2600 x 3400); but two against one 162 -> 174 (2048 x 3400), five against three 456 -> 458 (6000 x 3400).
     const int64_t large = (int64_t)((Mi + 255) / 256) * ((Ni + 127) / 128), small = (int64_t)((Mi + 127) / 128) * ((Ni + 127) / 128);
     const bool small_tiles = 3 * ((small + 255) / 256) < 5 * ((large + 255) / 256);
     const int rc = small_tiles ? launch_split_product<2, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st)

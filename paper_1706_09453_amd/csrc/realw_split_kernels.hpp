@@ -105,7 +105,9 @@ __global__ __launch_bounds__(256) void split_bf16x3_kernel(const float* __restri
 // operand fragments out of LDS one block ahead of the MFMAs that use them, one memory instruction between two MFMAs.  In LDS
 // a row's four 16-byte slots are stored at slot ^ ((row / 4) % 4), which spreads the fragment reads of 16 lanes over all
 // banks.  Lane (r = lane % 32, g = lane / 32) feeds row r, k = 8 g .. 8 g + 7 of a block to both operands.
-// (With loads to registers and LDS stores a pass over 4096 frames of 6 x 2048 units and 3400 outputs took 563 us, now 545.)
+// Against loads to registers and LDS stores (256 x 128 tiles only), whole layers: 4096 x 2048 x 3400 312 -> 298 us, 4221 x 4096 x 1024
+// 283 -> 243, 600 x 2048 x 3400 128 -> 81.  What is slower: K above about 4800 with one round of large tiles and planes beyond the
+// 256 MB of the last-level cache, 738 x 7200 x 7159 580 -> 640, 4812 x 5792 x 769 369 -> 401.
 template <int WM, int WN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void realw_bf16x3_kernel(
     const uint16_t* __restrict__ Xs, const uint16_t* __restrict__ Ws, const float* __restrict__ bias, int M, int kpad, int N,
@@ -120,7 +122,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     const int r = lane & 31, g = lane >> 5;
-    const int m_tile = (int)blockIdx.x * kTileM, n_tile = (int)blockIdx.y * kTileN;
+    // Workgroups go round the eight XCDs.  An XCD takes consecutive tiles in an order that runs down two rows of tiles at a time, so
+    // that its L2 serves few frames and many weights, whatever the number of tile rows (4221 x 4096 x 1024, 17 x 8 tiles, 306 ->
+    // 248 us a layer; 16 tile rows: nothing changes).  Short sums are bound by the outputs, which the launch's own order stores
+    // faster (8206 x 16 x 898 47.6 and 51.4, 3828 x 50 x 2048 34.6 and 37.3; from 200 terms on no difference).
+    int tm = (int)blockIdx.x, tn = (int)blockIdx.y;
+    if (kpad >= 256) {
+        const int gx = (int)gridDim.x, gy = (int)gridDim.y, total = gx * gy, id = tm + gx * tn;
+        const int xcd = id & 7, t = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+        const int pair = t / (2 * gy), in = t - pair * (2 * gy);
+        const bool two = 2 * pair + 1 < gx;   // (an odd number of tile rows: the last one alone)
+        tm = 2 * pair + (two ? in & 1 : 0);
+        tn = two ? in >> 1 : in;
+    }
+    const int m_tile = tm * kTileM, n_tile = tn * kTileN;
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);
 
@@ -176,8 +191,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
 
     // One block of 16 k, written out MFMA by MFMA and pinned: the six piece products, smallest first; each accumulator is touched
-    // once per WM WN MFMAs.  Behind each of the first ones a fragment read of the next block, behind each of the last ones (REQ)
-    // a load of step `step` to `stage`.
+    // once per WM WN MFMAs.  Behind each of the first ones a fragment read of the next block; REQ: the loads of step `step` to `stage`
+    // spread evenly over the block.  (The four waves issue them together, 64 clocks in the one texture path: behind every one of the last
+    // MFMAs they held these back, 4096 x 2048 x 3400 315 us a layer, spread 300.)
     auto block = [&](const Frags& now, Frags& next, const unsigned char* rd, int rd_h, auto req, int step, uint32_t stage) {
         constexpr bool REQ = decltype(req)::value;
         constexpr int px[6] = {0, 1, 2, 0, 1, 0};
@@ -187,7 +203,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
             const int q = i / (WM * WN), fm = (i / WN) % WM, fn = i % WN;
             acc[fm][fn] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(now.a[px[q]][fm], now.b[pw[q]][fn], acc[fm][fn], 0, 0, 0);
             if (i < NR) lread_one(next, rd, rd_h, i);
-            if (REQ && i >= NM - NL) request_one(step, stage, i - (NM - NL));
+            if (REQ && i * NL / NM != (i + 1) * NL / NM) request_one(step, stage, i * NL / NM);
             __builtin_amdgcn_sched_barrier(0);
         }
     };

@@ -855,10 +855,10 @@ def test_softmax_layer_real_weights_bf16_pieces(G, bnn, oracle, M, K, N, kind):
 
 
 @pytest.mark.parametrize("M,N", [(129, 129), (2049, 3329)])   # 128 x 128 tiles; 256 x 128 tiles
-@pytest.mark.parametrize("K", [31, 64, 65, 97, 129])         # one to five steps of 32 k, two or three of them in LDS
+@pytest.mark.parametrize("K", [31, 64, 65, 97, 129, 225, 257])   # one to nine steps of 32 k, two or three of them in LDS
 def test_softmax_layer_bf16_piece_tiles(G, bnn, oracle, M, N, K):
     """Integers below 2^8 in magnitude: one piece each, every product and sum below 2^24 and exact, so the log-posteriors are
-    those of the exact sums, to the rounding of the log-Softmax."""
+    those of the exact sums, to the rounding of the log-Softmax.  (The last two K: tiles in the launch's order and in the XCDs'.)"""
     rng = np.random.default_rng(M + K)
     X = rng.integers(-16, 17, (M, K)).astype(np.float32)
     W = (rng.integers(-16, 17, (N, K)) / 64).astype(np.float32)
@@ -874,6 +874,23 @@ def test_softmax_layer_bf16_piece_tiles(G, bnn, oracle, M, N, K):
     z -= z.max(1, keepdims=True)
     want = z - np.log(np.exp(z).sum(1, keepdims=True))
     assert np.max(np.abs(out.cpu().numpy() - want)) <= 1e-6 * np.max(np.abs(want)) + 1e-6 * np.log(N)
+
+
+@pytest.mark.parametrize("M,N", [(129, 129), (2049, 3329)])   # 128 x 128 tiles; 256 x 128 tiles
+@pytest.mark.parametrize("K", [31, 97, 289])
+def test_softmax_layer_bf16_piece_tiles_use_every_piece(G, bnn, M, N, K):
+    """One product of two full fp32 numbers per output, three pieces each, so that nothing rounds but that product: six piece
+    products added in fp32 (2^-21 |z| allowed; what is left out is below 2^-25) and the log-Softmax (2^-22 of the largest).  A
+    third piece is up to 2^-18 of its number: taken from the wrong place, or left out, it shows."""
+    rng = np.random.default_rng(M + K)
+    X = (rng.choice([-1, 1], (M, K)) * rng.uniform(32, 64, (M, K))).astype(np.float32)
+    W = np.zeros((N, K), np.float32)
+    at = 7 * np.arange(N) % K
+    W[np.arange(N), at] = rng.choice([-1, 1], N) * rng.uniform(32, 64, N)
+    got = _one_layer_realw_logsoftmax(G, bnn, X, W, np.zeros(N, np.float32), K, N, 1).astype(np.float64)
+    z = X[:, at].astype(np.float64) * W[np.arange(N), at].astype(np.float64)
+    bound = 2.0 ** -21 * (np.abs(z) + np.abs(z[:, :1])) + 2.0 ** -22 * np.abs(z).max(1, keepdims=True)
+    assert np.all(np.abs((got - got[:, :1]) - (z - z[:, :1])) <= bound)
 
 
 def test_softmax_layer_bf16_pieces_sum_within_its_bound(G, bnn, oracle):
