@@ -688,13 +688,13 @@ void launch_split(const float* A, int64_t rows, int K, int kpad, uint16_t* plane
     if ((K & 3) == 0 && aligned(A, 16)) split_bf16x3_kernel<true><<<grid, 256, 0, st>>>(A, rows, K, kpad, planes);
     else split_bf16x3_kernel<false><<<grid, 256, 0, st>>>(A, rows, K, kpad, planes);
 }
-template <int WM, int WN>
+template <int WM, int WN, bool LONG = false>
 int launch_split_product(const uint16_t* xs, const uint16_t* ws, const float* bias, int M, int kpad, int N, float* Y, hipStream_t st) {
     constexpr unsigned lds = split_dynamic_lds(WM, WN);
     static std::atomic<uint64_t> allowed;
-    if (!allow_lds(&realw_bf16x3_kernel<WM, WN>, lds, allowed)) return BNN_EDEVICE;
+    if (!allow_lds(&realw_bf16x3_kernel<WM, WN, LONG>, lds, allowed)) return BNN_EDEVICE;
     const dim3 grid((unsigned)((M + 64 * WM - 1) / (64 * WM)), (unsigned)((N + 64 * WN - 1) / (64 * WN)));
-    realw_bf16x3_kernel<WM, WN><<<grid, 256, lds, st>>>(xs, ws, bias, M, kpad, N, Y);
+    realw_bf16x3_kernel<WM, WN, LONG><<<grid, 256, lds, st>>>(xs, ws, bias, M, kpad, N, Y);
     return BNN_OK;
 }
 int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, float* Y,
@@ -710,8 +710,10 @@ int run_realw_split_lsm(const float* X, const float* W, const float* bias, int64
     // rounds against two 279 -> 246 (2600 x 3400); but two against one 162 -> 174 (2048 x 3400), five against three 456 -> 458 (6000 x 3400).
     const int64_t large = (int64_t)((Mi + 255) / 256) * ((Ni + 127) / 128), small = (int64_t)((Mi + 127) / 128) * ((Ni + 127) / 128);
     const bool small_tiles = 3 * ((small + 255) / 256) < 5 * ((large + 255) / 256);
-    const int rc = small_tiles ? launch_split_product<2, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st)
-                               : launch_split_product<4, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st);
+    // (rows of 8 MiB and more: a device holds a few thousand of them, one tile is enough)
+    const int rc = kpad >= kSplitLongRow ? launch_split_product<2, 2, true>(xs, ws, bias, Mi, kpad, Ni, Y, st)
+                   : small_tiles         ? launch_split_product<2, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st)
+                                         : launch_split_product<4, 2>(xs, ws, bias, Mi, kpad, Ni, Y, st);
     if (rc != BNN_OK) return rc;
     launch_log_softmax(Y, Mi, Ni, st);
     return launch_status();

@@ -43,6 +43,10 @@ __device__ __forceinline__ void load_lds16(i32x4m rsrc, int voff, int soff, uint
 __device__ __forceinline__ void load_lds4(i32x4m rsrc, int voff, int soff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds" ::"s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
 }
+// 16 bytes per lane from an address per lane: lane i's go to lds + 16 i
+__device__ __forceinline__ void load_lds16_at(const void* p, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(p) : "memory");
+}
 __device__ __forceinline__ i32x4m raw_buffer(const void* p, unsigned int bytes) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);
     return i32x4m{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};

@@ -35,6 +35,8 @@ __host__ __device__ constexpr int split_stage(int wm, int wn) { return kSplitPie
 __host__ __device__ constexpr int split_stages(int wm, int wn) { return 3 * split_stage(wm, wn) <= 163840 ? 3 : 2; }
 __host__ __device__ constexpr unsigned split_dynamic_lds(int wm, int wn) { return (unsigned)(split_stages(wm, wn) * split_stage(wm, wn)); }
 
+constexpr int kSplitLongRow = 1 << 22;   // kpad from which the offsets of 256 rows do not fit 31 bits
+
 __host__ __device__ inline int split_kpad(int K) { return (K + kSplitKStep - 1) / kSplitKStep * kSplitKStep; }
 
 // bf16 nearest to v (ties to even) as its 16 bits; a finite v that would round to infinity is truncated instead, so that
@@ -108,7 +110,8 @@ __global__ __launch_bounds__(256) void split_bf16x3_kernel(const float* __restri
 // Against loads to registers and LDS stores (256 x 128 tiles only), whole layers: 4096 x 2048 x 3400 312 -> 298 us, 4221 x 4096 x 1024
 // 283 -> 243, 600 x 2048 x 3400 128 -> 81.  What is slower: K above about 4800 with one round of large tiles and planes beyond the
 // 256 MB of the last-level cache, 738 x 7200 x 7159 580 -> 640, 4812 x 5792 x 769 369 -> 401.
-template <int WM, int WN>
+// LONG: kpad >= kSplitLongRow; addresses of 64 bits per lane instead of a buffer and an offset of 32.
+template <int WM, int WN, bool LONG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void realw_bf16x3_kernel(
     const uint16_t* __restrict__ Xs, const uint16_t* __restrict__ Ws, const float* __restrict__ bias, int M, int kpad, int N,
     float* __restrict__ Y) {
@@ -143,27 +146,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     //      else weights rows 16 (WN wave + sub - WM) ..  One buffer per piece and operand, over the rows of the tile (rows past
     //      the end: the last one again).
     const int lrow = lane >> 2, lsrc = ((lane & 3) ^ ((lrow >> 2) & 3)) * 16;
-    const int rows_a = min(M - m_tile, kTileM), rows_b = min(N - n_tile, kTileN), row_bytes = 2 * kpad;
+    const int rows_a = min(M - m_tile, kTileM), rows_b = min(N - n_tile, kTileN), row_bytes = LONG ? 0 : 2 * kpad;
     i32x4m ars[kSplitPieces], brs[kSplitPieces];
-#pragma unroll
-    for (int p = 0; p < kSplitPieces; ++p) {
-        ars[p] = raw_buffer(Xs + ((size_t)p * M + m_tile) * kpad, (unsigned int)(rows_a * row_bytes));
-        brs[p] = raw_buffer(Ws + ((size_t)p * N + n_tile) * kpad, (unsigned int)(rows_b * row_bytes));
-    }
     int aofs[WM], bofs[WN];
+    const char *aptr[WM], *bptr[WN];
+    if constexpr (LONG) {
 #pragma unroll
-    for (int i = 0; i < WM; ++i) aofs[i] = min(16 * (WM * wave + i) + lrow, rows_a - 1) * row_bytes + lsrc;
+        for (int i = 0; i < WM; ++i)
+            aptr[i] = reinterpret_cast<const char*>(Xs + (size_t)(m_tile + min(16 * (WM * wave + i) + lrow, rows_a - 1)) * kpad) + lsrc;
 #pragma unroll
-    for (int i = 0; i < WN; ++i) bofs[i] = min(16 * (WN * wave + i) + lrow, rows_b - 1) * row_bytes + lsrc;
+        for (int i = 0; i < WN; ++i)
+            bptr[i] = reinterpret_cast<const char*>(Ws + (size_t)(n_tile + min(16 * (WN * wave + i) + lrow, rows_b - 1)) * kpad) + lsrc;
+    } else {
+#pragma unroll
+        for (int p = 0; p < kSplitPieces; ++p) {
+            ars[p] = raw_buffer(Xs + ((size_t)p * M + m_tile) * kpad, (unsigned int)(rows_a * row_bytes));
+            brs[p] = raw_buffer(Ws + ((size_t)p * N + n_tile) * kpad, (unsigned int)(rows_b * row_bytes));
+        }
+#pragma unroll
+        for (int i = 0; i < WM; ++i) aofs[i] = min(16 * (WM * wave + i) + lrow, rows_a - 1) * row_bytes + lsrc;
+#pragma unroll
+        for (int i = 0; i < WN; ++i) bofs[i] = min(16 * (WN * wave + i) + lrow, rows_b - 1) * row_bytes + lsrc;
+    }
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)split_lds;
     auto request_one = [&](int step, uint32_t stage, int i) {
-        const int p = i / (WM + WN), sub = i % (WM + WN);
-        if (sub < WM)
-            load_lds16(ars[p], aofs[sub < WM ? sub : 0], step * kSplitRowBytes,
-                       stage + (uint32_t)((p * kTileM + 16 * (WM * wave + sub)) * kSplitRowBytes));
-        else
-            load_lds16(brs[p], bofs[sub < WM ? 0 : sub - WM], step * kSplitRowBytes,
-                       stage + (uint32_t)(kStageA + (p * kTileN + 16 * (WN * wave + sub - WM)) * kSplitRowBytes));
+        const int p = i / (WM + WN), sub = i % (WM + WN), ia = sub < WM ? sub : 0, ib = sub < WM ? 0 : sub - WM;
+        const uint32_t to = stage + (uint32_t)(sub < WM ? (p * kTileM + 16 * (WM * wave + ia)) * kSplitRowBytes
+                                                        : kStageA + (p * kTileN + 16 * (WN * wave + ib)) * kSplitRowBytes);
+        if constexpr (LONG) {
+            const size_t at = (size_t)p * (sub < WM ? M : N) * kpad * 2 + (size_t)step * kSplitRowBytes;
+            load_lds16_at((sub < WM ? aptr[ia] : bptr[ib]) + at, to);
+        } else {
+            load_lds16(sub < WM ? ars[p] : brs[p], sub < WM ? aofs[ia] : bofs[ib], step * kSplitRowBytes, to);
+        }
     };
 
     // ---- the wave's operand fragments of block h (0 or 1) of a stage: NR reads, numbered like the loads

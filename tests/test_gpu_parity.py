@@ -893,6 +893,28 @@ def test_softmax_layer_bf16_piece_tiles_use_every_piece(G, bnn, M, N, K):
     assert np.all(np.abs((got - got[:, :1]) - (z - z[:, :1])) <= bound)
 
 
+def test_softmax_layer_real_weights_rows_beyond_32_bit_offsets(G, bnn):
+    """Rows of 2^24 + 36 numbers: 127 of them end beyond 2^32 bytes of a plane.  One product per output and row, as above, at the
+    row's start, around 2^23 and 2^24 and in its last elements."""
+    M, K, N = 130, (1 << 24) + 36, 12
+    at = torch.tensor([0, 31, 1 << 20, (1 << 22) + 5, (1 << 23) - 1, 1 << 23, (1 << 23) + 77, (1 << 24) - 32, (1 << 24) - 1, 1 << 24, K - 2, K - 1], device=G.DEV)
+    g = torch.Generator(device=G.DEV).manual_seed(3)
+    X = torch.rand(M, K, device=G.DEV, generator=g).add_(1.0).mul_(32.0)
+    W = torch.zeros(N, K, device=G.DEV)
+    w = (torch.rand(N, device=G.DEV, generator=g) + 1.0) * 32.0
+    W[torch.arange(N, device=G.DEV), at] = w
+    arr = bnn.make_layer_array([dict(K=K, N=N, act=bnn.BNN_ACT_LOGSOFTMAX, word_bits=32, x_is_binary=0, w_is_real=1, Wp=G.ptr(W),
+                                     scale=0, bias=0)])
+    nbytes = bnn.bnn_forward_workspace_bytes(arr, 1, M)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=G.DEV)
+    out = torch.empty(M, N, device=G.DEV)
+    bnn.bnn_forward(arr, 1, G.ptr(X), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
+    torch.cuda.synchronize()
+    got, z = out.double(), X[:, at].double() * w.double()
+    bound = 2.0 ** -21 * (z.abs() + z[:, :1].abs()) + 2.0 ** -22 * z.abs().amax(1, keepdim=True)
+    assert bool(((got - got[:, :1]) - (z - z[:, :1])).abs().le(bound).all())
+
+
 def test_softmax_layer_bf16_pieces_sum_within_its_bound(G, bnn, oracle):
     """The bound the kernel states for its sums, seen through the log-posteriors: out[m][a] - out[m][0] = z_a - z_0, and
     each z is within 2^-22 sum_k |x_k w_k| (the piece products left out) plus the rounding of about 800 fp32 additions

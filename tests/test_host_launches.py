@@ -229,6 +229,23 @@ for coop in (0, 1):
     assert not [w for _, w in got if w]
 
 
+def test_softmax_layer_with_real_weights_tiles_and_long_rows(host):
+    """Which tile of the bf16-piece product a layer takes, by rounds of workgroups; and rows whose offsets in a tile would not fit 32
+    bits take the instantiation with 64-bit addresses, on every size the entry point accepts."""
+    got = host(FORWARD + """
+result = []
+for M, K, N in ((128, 64, 1), (600, 2048, 3400), (2049, 289, 3329), (4096, 2048, 3400), (4096, 2048, 1000), (2600, 2048, 3400),
+                (1 << 12, (1 << 22) - 32, 1 << 13), (128, (1 << 22) - 31, 7), (4096, 1 << 22, 8192), (300, 1 << 23, 130), (128, 1 << 24, 7), (128, 1 << 30, 1)):
+    forward(M, (K, N), (bnn.BNN_ACT_LOGSOFTMAX,), real=(0,), out=0x700000000000)
+    l = [l for l in launches() if "realw_bf16x3_kernel" in l["kernel"]][0]
+    t = l["kernel"].split("realw_bf16x3_kernelI")[1].split("E")
+    result.append([t[0][2:] + "x" + t[1][2:] + ("" if t[2] == "Lb0" else " long"), l["grid"][:2], l["wrong"]])
+""")
+    assert [k for k, _, _ in got] == ["2x2", "2x2", "4x2", "4x2", "2x2", "2x2", "4x2", "2x2 long", "2x2 long", "2x2 long", "2x2 long", "2x2 long"]
+    assert got[1][1] == [5, 27] and got[2][1] == [9, 27] and got[9][1] == [3, 2]
+    assert not [w for _, _, w in got if w]
+
+
 def test_static_forward_is_not_charged_for_memory_no_kernel_uses(host):
     """A hidden layer with real weights: what bnn_forward only reserves for it does not keep the tiled products out of the
     fixed array.  The size a caller provides stays what it was."""
