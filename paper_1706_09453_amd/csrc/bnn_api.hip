@@ -464,12 +464,14 @@ int run_binx(const void* Xp, const void* Wp, const float* scale, const float* bi
         // 128-row wave tiles expand fewer operand words per MAC; 64-row ones give twice the workgroups, which
         // matters more while the 128-row grid leaves CUs without a workgroup (measured on MI355X: 64-row tiles win
         // up to 2048 frames x 2048 outputs, 128-row tiles from 4096 x 2048 on).  With a single stage of K a workgroup is mostly
-        // its start and its end, and more of them on a CU cover each other (128 and 64 rows, K = 512: 11789 x 4410 20.6 and 18.8 us,
-        // 9247 x 3808 16.9 and 15.1, 4998 x 4864 11.1 and 9.5, 16384 x 4000 with the log-Softmax 105 and 95; but K = 1024: 11789 x 4410
-        // 25.7 and 26.1, 8192 x 2048 9.0 and 9.2).
-        const int64_t blocks4 = ((M + 255) / 256) * ((N + 127) / 128);
+        // its start and its end, and three 64-row ones on a CU cover each other better than two 128-row ones, unless the 128-row
+        // ones are done in one round and the others are not (128 and 64 rows, K = 512: 9247 x 3808 16.9 and 15.1 us, 4998 x 4864 11.1
+        // and 9.5, 5000 x 2048 6.5 and 5.5, 16384 x 3000 17.2 and 16.8; but 1798 x 6816 6.8 and 8.0, 6373 x 2554 8.1 and 8.4; K = 1024:
+        // 11789 x 4410 25.7 and 26.1, 8192 x 2048 9.0 and 9.2).
+        const int64_t blocks4 = ((M + 255) / 256) * ((N + 127) / 128), blocks2 = ((M + 127) / 128) * ((N + 127) / 128);
         const int wm32 = g_mfma32_wm.load();
-        const bool wm2 = wm32 == 2 || (wm32 == 0 && (blocks4 < 200 || (K == 512 && pinned && !coop_asked)));
+        const bool one_stage = K == 512 && pinned && !coop_asked && (blocks4 > 512 || blocks2 <= 768);
+        const bool wm2 = wm32 == 2 || (wm32 == 0 && (blocks4 < 200 || one_stage));
         // Cooperative log-Softmax (opt-in): the product kernel finishes the rows itself.  Its workgroups wait for each
         // other, so all of them have to be resident at once.
         CoopLsm coop{};

@@ -213,19 +213,19 @@ for M, K, N, act in ((1024, 512, 1000, Z), (512, 512, 64, Z), (511, 512, 64, Z),
 
 
 def test_binary_layers_of_one_stage_take_64_row_tiles(host):
-    """K = 512 is one stage of the kernel that fetches through LDS: 64-row tiles however large the layer, unless the cooperative
-    log-Softmax, which has 128-row tiles only, is asked for."""
+    """K = 512 is one stage of the kernel that fetches through LDS: 64-row tiles, unless only the 128-row ones are done in one round
+    of workgroups, or the cooperative log-Softmax, which has 128-row tiles only, is asked for."""
     got = host("""
 Z, S = bnn.BNN_ACT_LOGSOFTMAX, bnn.BNN_ACT_SIGN
 result = []
 for coop in (0, 1):
     bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE, coop)
-    for M, K, N, act in ((16384, 512, 4096, S), (16384, 1024, 4096, S), (1500, 1024, 2048, S), (4096, 512, 2048, Z), (4096, 1024, 2048, Z)):
+    for M, K, N, act in ((16384, 512, 4096, S), (1798, 512, 6816, S), (16384, 1024, 4096, S), (1500, 1024, 2048, S), (4096, 512, 2048, Z), (4096, 1024, 2048, Z)):
         bnn.bnn_layer_binw_binx(A, B, C, C, M, K, N, act, 32, D)
         l = launches()[0]
         result.append([l["kernel"].split("binx_mfma32_kernelILi")[1][0], l["wrong"]])
 """)
-    assert [w for w, _ in got] == ["2", "4", "2", "2", "4", "2", "4", "2", "4", "4"]
+    assert [w for w, _ in got] == ["2", "4", "4", "2", "2", "4", "2", "4", "4", "2", "4", "4"]
     assert not [w for _, w in got if w]
 
 
