@@ -52,6 +52,18 @@ __device__ __forceinline__ i32x4m raw_buffer(const void* p, unsigned int bytes) 
     return i32x4m{(int)(uint32_t)a, (int)((uint32_t)(a >> 32) & 0xFFFFu), (int)bytes, 0x00020000};
 }
 
+// The tile of a workgroup in a grid of gridDim.x tile rows by gridDim.y tile columns.  Workgroups go round the eight XCDs: here an
+// XCD takes consecutive tiles in an order that runs down two tile rows at a time, so that its L2 serves few rows and many
+// columns whatever the number of tile rows.  (In the launch's own order it does so only where that is a multiple of eight.)
+__device__ __forceinline__ void xcd_tile(int& tm, int& tn) {
+    const int gx = (int)gridDim.x, gy = (int)gridDim.y, total = gx * gy, id = (int)blockIdx.x + gx * (int)blockIdx.y;
+    const int xcd = id & 7, t = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
+    const int pair = t / (2 * gy), in = t - pair * (2 * gy);
+    const bool two = 2 * pair + 1 < gx;   // (an odd number of tile rows: the last one alone)
+    tm = 2 * pair + (two ? in & 1 : 0);
+    tn = two ? in >> 1 : in;
+}
+
 // Eq. 3 of the paper: +1 exactly when v > 0 (0, -0 and NaN give -1, i.e. bit 0).
 __device__ __forceinline__ bool sign_bit(float v) { return v > 0.0f; }
 

@@ -125,19 +125,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     const int r = lane & 31, g = lane >> 5;
-    // Workgroups go round the eight XCDs.  An XCD takes consecutive tiles in an order that runs down two rows of tiles at a time, so
-    // that its L2 serves few frames and many weights, whatever the number of tile rows (4221 x 4096 x 1024, 17 x 8 tiles, 306 ->
-    // 248 us a layer; 16 tile rows: nothing changes).  Short sums are bound by the outputs, which the launch's own order stores
-    // faster (8206 x 16 x 898 47.6 and 51.4, 3828 x 50 x 2048 34.6 and 37.3; from 200 terms on no difference).
+    // 4221 x 4096 x 1024, 17 x 8 tiles: 306 -> 248 us a layer with the tiles in the XCDs' order; 16 tile rows: nothing changes.  Short
+    // sums are bound by the outputs, which the launch's own order stores faster (8206 x 16 x 898 47.6 and 51.4, 3828 x 50 x 2048
+    // 34.6 and 37.3; from 200 terms on no difference).
     int tm = (int)blockIdx.x, tn = (int)blockIdx.y;
-    if (kpad >= 256) {
-        const int gx = (int)gridDim.x, gy = (int)gridDim.y, total = gx * gy, id = tm + gx * tn;
-        const int xcd = id & 7, t = xcd * (total >> 3) + min(xcd, total & 7) + (id >> 3);
-        const int pair = t / (2 * gy), in = t - pair * (2 * gy);
-        const bool two = 2 * pair + 1 < gx;   // (an odd number of tile rows: the last one alone)
-        tm = 2 * pair + (two ? in & 1 : 0);
-        tn = two ? in >> 1 : in;
-    }
+    if (kpad >= 256) xcd_tile(tm, tn);
     const int m_tile = tm * kTileM, n_tile = tn * kTileN;
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);

@@ -213,7 +213,12 @@ __global__ __launch_bounds__(kI8Threads) __attribute__((amdgpu_waves_per_eu(1, W
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = lane_id();
     const int r = lane & 31, g = lane >> 5;
-    const int m_tile = (int)blockIdx.x * kTileM, n_tile = (int)blockIdx.y * kTileN;
+    int tm = (int)blockIdx.x, tn = (int)blockIdx.y;
+    // The XCDs' order from eight tile rows on (whole calls, launch's order -> XCDs': 4026 x 8124 x 1024 312 -> 218 us, 2048 x 4096 x 2048
+    // 93 -> 80, 512 x 4096 x 4096 57.7 -> 52.7, 900 x 1024 x 1000 24.2 -> 21.5; with fewer 256 x 4096 x 4096 47.9 -> 49.5, 200 x 2048 x 2048
+    // 28.0 -> 29.3).
+    if ((int)gridDim.x >= 8) xcd_tile(tm, tn);
+    const int m_tile = tm * kTileM, n_tile = tn * kTileN;
     const int m_base = m_tile + (wave >> 1) * (WM * 32);
     const int n_base = n_tile + (wave & 1) * (WN * 32);
 
