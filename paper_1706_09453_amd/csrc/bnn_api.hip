@@ -757,9 +757,9 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
     s.total = s.undecided + (act == BNN_ACT_SIGN ? round_up((size_t)M * pairs * 2 * kUndecidedRecord, 256) : 0);
     return s;
 }
-// Frames of up to 4096 elements in 16-byte pieces are held in registers, in as many groups of 256 as they need (a power of
-// two: what a frame does not fill costs loads of its first elements again).  Longer ones would take more registers than
-// leave two waves per SIMD, ragged ones a load per element.
+// Frames in 16-byte pieces are held in registers, in as many groups of 256 as they need (a power of two: what a frame does not
+// fill costs loads of its first elements again); 32 groups, the longest frames there are, take 214 to 216 registers, which leaves
+// two waves per SIMD (4096 x 6144 43 -> 33 us against reading the frame twice).  Ragged frames need a load per element and are read twice.
 template <int D>
 void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* planes, void* meta, hipStream_t st) {
     const dim3 grid((unsigned)((M + 3) / 4));
@@ -769,7 +769,8 @@ void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* 
     else if (kpad <= 1024) realx_quantize_nat_kernel<D, true, 4><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
     else if (kpad <= 2048) realx_quantize_nat_kernel<D, true, 8><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
     else if (kpad <= 4096) realx_quantize_nat_kernel<D, true, 16><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else realx_quantize_nat_kernel<D, true, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    else realx_quantize_nat_kernel<D, true, 32><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    static_assert(kSlabMaxK <= 32 * 256, "a frame fits the registers");
 }
 // Tiles of 128 frames x 256 outputs (one workgroup per CU) or of 64 x 128 (two per CU)?  A round of the small ones, 512
 // workgroups, is half the outputs of a round of 256 large ones and takes 0.55 to 0.67 of its time (a weight byte in LDS serves

@@ -77,8 +77,8 @@ __device__ __forceinline__ uint32_t negate_digits(uint32_t d) { return (0x808080
 
 // One wave per frame: scale, digits (odd digits negated), RowMeta (D = 3) or RowMeta4 (D = 4).  planes: [D][M][kpad].
 // Four consecutive elements per lane and group of 256.  VEC: K % 4 == 0 and X 16-byte aligned.
-// NG > 0 (VEC only): the frame has at most NG groups and is requested whole, NG loads of a lane in flight, and kept in
-// registers; NG == 0: it is read twice (largest element, then digits), one load after the other.
+// NG > 0 (with VEC): the frame has at most NG groups and is requested whole, NG loads of a lane in flight, and kept in
+// registers; NG == 0 (without): it is read twice (largest element, then digits), one load after the other.
 // Bound by memory: a number in, D bytes out.  Against one load after the other, twice:
 // 4096 frames of 2048 15.5 -> 12.2 us, 2048 of 4096 26.2 -> 13.0 (5.2 TB/s).
 // Grid: ceil(M / 4) workgroups of 256 threads.
@@ -86,20 +86,16 @@ template <int D, bool VEC, int NG>
 __global__ __launch_bounds__(256) void realx_quantize_nat_kernel(const float* __restrict__ X, int M, int K, int kpad, int qbits,
                                                                  int8_t* __restrict__ planes, void* __restrict__ meta_out) {
     static_assert(D == 3 || D == 4, "three digits for Sign layers, four in front of the log-Softmax");
-    static_assert(NG == 0 || VEC, "whole frames are requested in pieces of 16 bytes");
+    static_assert((NG > 0) == VEC, "whole frames are requested in pieces of 16 bytes");
     const int m = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
     if (m >= M) return;   // wave-uniform
     const int lane = lane_id();
     const float* x = X + (size_t)m * K;
     auto load4 = [&](int k) -> f32x4g {
-        if constexpr (VEC) {   // K % 4 == 0: the four are inside or outside together
-            return k < K ? *reinterpret_cast<const f32x4g*>(x + k) : f32x4g{0.0f, 0.0f, 0.0f, 0.0f};
-        } else {
-            f32x4g v;
+        f32x4g v;
 #pragma unroll
-            for (int t = 0; t < 4; ++t) v[t] = (k + t < K) ? x[k + t] : 0.0f;
-            return v;
-        }
+        for (int t = 0; t < 4; ++t) v[t] = (k + t < K) ? x[k + t] : 0.0f;
+        return v;
     };
     unsigned int mx = 0;   // largest |x| of the row as a bit pattern (NaN/Inf have the largest patterns)
     auto largest = [&](const f32x4g& v) {

@@ -201,7 +201,7 @@ def test_layer_binw_realx_on_the_int8_matrix_cores(G, bnn, oracle, M, K, N, wb):
     assert np.all(np.abs(got.astype(np.float64) - want) <= tol)
 
 
-@pytest.mark.parametrize("K", [4, 508, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 513])
+@pytest.mark.parametrize("K", [4, 508, 512, 516, 1024, 1028, 2048, 2052, 4096, 4100, 8188, 8192, 513])
 @pytest.mark.parametrize("M", [1, 5])
 def test_layer_binw_realx_int8_row_lengths(G, bnn, oracle, M, K):
     """Both sides of every length at which the quantisation takes another number of registers, and a ragged length: the
