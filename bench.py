@@ -592,8 +592,8 @@ def main() -> int:
         bound, peak = "alu", PEAK_XOR_POPC_TOPS
     # HBM bytes per launch of each kernel group from rocprofv3 FETCH_SIZE / WRITE_SIZE, scaled by a plain copy
     # (profiles/forward_c3_hbm_traffic.txt); measured for this workload with the matrix-core arm only
-    measured_traffic = {"realx": (8.19 + 1.00) * 2 ** 20, "binx hidden": (5.35 + 1.00) * 2 ** 20,
-                        "binx output": (8.09 + 26.81 + 27.27 + 53.13) * 2 ** 20}   # (output layer: the two-kernel path)
+    measured_traffic = {"realx": (8.19 + 1.00) * 2 ** 20, "binx hidden": (5.26 + 1.00) * 2 ** 20,
+                        "binx output": (8.02 + 26.75 + 27.26 + 53.13) * 2 ** 20}   # (output layer: the two-kernel path)
     traffic = None
     if args.arm == "mfma" and not args.opt:
         traffic = next(int(v) for k, v in measured_traffic.items() if dominant.startswith(k))
@@ -617,7 +617,7 @@ def main() -> int:
         "metric": "frames/sec, 6x2048 binarized DNN (binary weights and activations), batch 4096, 1xMI355X",
         "value": round(frames_per_s, 1), "unit": "frames/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
         "ms_per_step": round(ms_per_step, 5), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": {"mfma": "b1 (+-1 as fp4-e2m1 MFMA operands, exact fp32 accumulate) + f32",
+        "dtype": {"mfma": "b1 (0/1 as fp4-e2m1 MFMA operands, exact fp32 accumulate) + f32",
                   "mfma_i8": "b1 (+-1 as int8 MFMA operands, int32 accumulate) + f32",
                   "valu": "b1 (xor+popcount u32) + f32"}[args.arm],
         "data": "synthetic",

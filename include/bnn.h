@@ -87,9 +87,9 @@ typedef enum bnn_option {
                                    binary-activation network; the layer behind a Sigmoid layer in the paper's Table 2
                                    topology): 1 = matrix-core filter with exact sums for the outputs it cannot decide
                                    (default; K <= 8192, scratch from the forward workspace for K > 512 or layers other
-                                   than the first: for 128 frames or more a tiled product, 128 frames x 256 outputs per
-                                   workgroup, followed by a kernel that sums the undecided outputs; workgroups of 16
-                                   frames otherwise), 2 = the same with workgroups of 16 frames for every batch size,
+                                   than the first: for 128 frames or more a tiled product, 128 frames x 256 or 64 x 128
+                                   outputs per workgroup, followed by a kernel that sums the undecided outputs;
+                                   workgroups of 16 frames otherwise), 2 = the same with workgroups of 16 frames for every batch size,
                                    0 = the ascending-k sums of BNN_OPT_REALX_TM; same bits in all three            */
     BNN_OPT_FUSED_LOGSOFTMAX = 6, /* binary-input LOGSOFTMAX layer on the matrix-core arm: 1 = product and
                                    log-Softmax in one kernel (needs K % 256 == 0 and N <= 4096),

@@ -1,15 +1,16 @@
 // Matrix-core arm of the binary x binary product (paper Sec. 2.3), large-batch version:
-// V_MFMA_F32_32X32X64_F8F6F4 with both operands in the 4-bit float format (+-1.0 exactly, see
-// mfma_kernels.hpp for the encoding and for why the result is the exact integer dot product).
+// V_MFMA_F32_32X32X64_F8F6F4 with both operands in the 4-bit float format, whose products and fp32 sums are the exact integers
+// (see mfma_kernels.hpp).  On 16-byte rows with K % 512 == 0 the operands go through LDS and are multiplied as 0 and 1 (the
+// pinned variants, below); other rows, and operands of 2 GiB and more, from memory to registers as +-1.
 //
-// Why this shape: every operand word a lane holds (32 elements of one row) has to be expanded from bits to
-// nibbles by the vector ALU (7 instructions), and the SIMD issues either a VALU instruction or an MFMA per
-// 4 clocks.  What counts is therefore expansions per multiply-accumulate: a wave that owns a 128 x 64 tile of
-// [M][N] as 4 x 2 accumulator fragments of 32 x 32 expands 6 words for 8 MFMAs of 65536 MACs each, about
-// half the expansion work per MAC of the 16 x 16 x 128 kernel with 64 x 64 wave tiles.
+// Why this shape: every operand word a lane holds (32 elements of one row) has to be expanded from bits to nibbles by the
+// vector ALU (five to seven instructions), and the SIMD issues either a VALU instruction or an MFMA per 4 clocks.  What counts is
+// therefore expansions per multiply-accumulate: a wave that owns a 128 x 64 tile of [M][N] as 4 x 2 accumulator fragments of
+// 32 x 32 expands 6 words for 8 MFMAs of 65536 MACs each, about half the expansion work per MAC of the 16 x 16 x 128 kernel with
+// 64 x 64 wave tiles.
 //
-// K advances in super-steps of 512 bits: lane (r = lane%32, g = lane/32) takes eight words of row r of every fragment;
-// word j feeds MFMA step j.  Inside a fragment the order of k is therefore permuted, identically for both operands.
+// K advances in super-steps of 512 bits; lane (r = lane%32, g = lane/32) takes eight words of row r of every fragment, one per
+// MFMA step.  Inside a fragment the order of k is therefore permuted, identically for both operands.
 // A workgroup is 2 x 2 waves: a (64 WM) x (64 WN) tile; at M = 4096, N = 2048 with WM = 4, WN = 2 that is
 // 256 workgroups, one wave per SIMD of the chip.
 #pragma once
@@ -28,9 +29,9 @@ typedef float v16f __attribute__((ext_vector_type(16)));
 //     frames                   w & 1..: 0.5   w & 2..: 1   w & 4..: 2   (w >> 2) & 2..: 1
 //     weights             (w << 2) & 4..: 2   w & 2..: 1   (w >> 2) & 1..: 0.5   (w >> 2) & 2..: 1
 // Five and six instructions per word, and one for its popcount, where +-1 takes seven; and three quarters of the products are
-// 0.  What bounds a large product here is the energy of an MFMA and of what stands around it: with +-1 operands the clock falls
-// to 1.5 GHz in the pinned loop, at 32.4 clocks per MFMA (16384 x 4096 x 4096; register to register, with five vector
-// instructions per MFMA: +-1 18.3 ns per MFMA at 1.96 GHz, 0/1 16.1 ns at 2.2).
+// 0, which cost the matrix cores less energy: what bounds a large product here is the clock that the chip holds under them.
+// 16384 x 4096 x 4096: 42.5 clocks per MFMA and SIMD at 1.86 GHz, matrix cores busy 75 % of them, 5.9 vector instructions per MFMA
+// with the epilogue (profiles/forward_c3_c4_counters.txt).
 struct ExpandMasks { uint32_t b0, b1, b2; };
 __device__ __forceinline__ ExpandMasks expand_masks() {
     ExpandMasks m{0x11111111u, 0x22222222u, 0x44444444u};
@@ -135,9 +136,8 @@ __device__ __forceinline__ uint32_t word_of(const Raw8& v, int j) {
 // fragment load touches 32 rows, 64 different pieces of 16 bytes, and the texture path takes those one after the other: at
 // 16384 x 4096 x 4096 a wave then issued an MFMA every 29 ns, where the matrix core needs 13.6 and the expansion fits
 // beside it (V independent vector instructions per MFMA, one or two waves per SIMD: V = 5 14.9 ns, V = 6 15.6 to 16.8).
-// Measured, with the 0/1 operands below: Sign layers 16384 x 4096 x 4096 124 -> 95 us (of which the stages alone 100, with
-// +-1 operands), 65536 x 4096 x 4096 465 -> 328, 4096 x 8192 x 2048 29.1 -> 23.8, 4096 x 2048 x 2048 10.5 -> 9.3; a wave of the
-// last takes 1.3 us to its first operands, 6.3 for its 256 MFMAs and 1.4 behind them.
+// Measured against that, with the 0/1 operands above: Sign layers 16384 x 4096 x 4096 124 -> 95 us, 65536 x 4096 x 4096 465 -> 328,
+// 4096 x 8192 x 2048 29.1 -> 23.8, 4096 x 2048 x 2048 10.5 -> 9.2.
 // In LDS a row of a stage is 64 bytes, its four 16-byte slots at slot ^ (row / 4 % 4), so that the 16 lanes that are served
 // together read 16 different slots of the 64 banks.
 constexpr int kM32Stages = 3;
