@@ -731,11 +731,11 @@ bool realw_reserved_applies(const bnn_layer_desc& d, int64_t M) {
 size_t realw_reserved_bytes(int64_t K, int64_t N) {
     return round_up((size_t)((K + 63) / 64 * 64) * (size_t)N * 4, 256);
 }
-// Real-input layers with binary weights on the int8 matrix cores as a tiled product (128 frames x 256 outputs per
-// workgroup), inside bnn_forward for batches of 128 frames or more: Sign layers (three digit planes, exact bits: the
+// Real-input layers with binary weights on the int8 matrix cores as a tiled product (128 frames x 256 or 64 x 128 outputs
+// per workgroup), inside bnn_forward for batches of 128 frames or more: Sign layers (three digit planes, exact bits: the
 // outputs the filter cannot decide are listed and resolved by a second kernel) and the layer in front of the
-// log-Softmax (four digit planes).  Scratch, all 256-byte aligned: digit planes, weight bytes, one record per frame,
-// the list's counter, the list.
+// log-Softmax (four digit planes).  Scratch, all 256-byte aligned: digit planes, weight bytes, one quantisation record per
+// frame, the undecided outputs as bits.
 bool realx_i8_gemm_applies(const bnn_layer_desc& d, int64_t M) {
     return !d.x_is_binary && !d.w_is_real && d.K <= kSlabMaxK && M >= 128 &&
            (d.act == BNN_ACT_SIGN || d.act == BNN_ACT_LOGSOFTMAX);
@@ -773,11 +773,12 @@ void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* 
     static_assert(kSlabMaxK <= 32 * 256, "a frame fits the registers");
 }
 // Tiles of 128 frames x 256 outputs (one workgroup per CU) or of 64 x 128 (two per CU)?  A round of the small ones, 512
-// workgroups, is half the outputs of a round of 256 large ones and takes 0.55 to 0.67 of its time (a weight byte in LDS serves
-// half as many frames); what decides is how many rounds there are, and at most 512 small workgroups always win.  Whole calls,
-// large -> small, K = 2048: 600 frames x 2048 outputs 66 -> 32 us, 2048 x 2048 69 -> 51, 600 x 3400 66 -> 44; two rounds of small
-// tiles against one of large ones 74 -> 80 (2600 x 2048) and 78 -> 91 (3400 x 2048), three against two 139 -> 146 (6000 x 2048).
-// Sign layers with what resolves their undecided outputs: 600 x 2048 81 -> 59, 2048 x 2048 83 -> 71, 4096 x 2048 89 -> 97.
+// workgroups, is half the outputs of a round of 256 large ones and takes 0.5 to 0.7 of its time (a weight byte in LDS serves
+// half as many frames).  Whole calls, large -> small, K = 2048: 600 frames x 2048 outputs 65 -> 33 us, 2048 x 2048 68 -> 50, 600 x 3400
+// 66 -> 45; two full rounds of small tiles against one of large ones 75 -> 79 (4096 x 2048), two against a nearly full one 72 -> 78
+// (3400 x 2048).  Sign layers with what resolves their undecided outputs: 600 x 2048 71 -> 50, 2048 x 2048 72 -> 62, 4096 x 2048 77 -> 85.
+// The rule counts whole rounds of both and is on the careful side: with the last round of small tiles less than half full they
+// would win, too (2600 x 2048 70 -> 64, 6000 x 2048 128 -> 112), though not with the longest sums (5475 x 8000 x 1000 279 -> 293).
 bool i8_small_tiles(int M, int N) {
     const int64_t large = (int64_t)((M + 127) / 128) * ((N + 255) / 256), small = (int64_t)((M + 63) / 64) * ((N + 127) / 128);
     return 2 * ((small + 511) / 512) < 3 * ((large + 255) / 256);
