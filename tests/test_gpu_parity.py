@@ -625,7 +625,8 @@ def test_first_layer_mfma_filter_bit_exact(G, bnn, oracle, M, K, N, wb):
         assert np.array_equal(_first_layer_bits(G, bnn, X, Wp, scale, bias, K, N, wb, arm), want), arm
 
 
-@pytest.mark.parametrize("M,N", [(65, 129), (2049, 2049)])   # 64 x 128 tiles; 128 x 256 tiles; ragged on both sides
+# 64 x 128 tiles, in the launch's order and (17 tile rows) in the XCDs'; 128 x 256 tiles; ragged on both sides
+@pytest.mark.parametrize("M,N", [(65, 129), (1030, 200), (2049, 2049)])
 @pytest.mark.parametrize("K", [576, 640, 641])
 def test_int8_product_tiles_sign_layers(G, bnn, oracle, M, N, K):
     """Both tiles of the int8 product at their edges, undecided outputs among them (biases at the sums of frame 0): the bits

@@ -216,7 +216,8 @@ def test_layer_binw_realx_int8_row_lengths(G, bnn, oracle, M, K):
     assert np.all(np.abs(got.astype(np.float64) - acc64) <= K * 2.0 ** -27 * 7.5 + 2.0 ** -23 * np.abs(acc64))
 
 
-@pytest.mark.parametrize("M,N", [(1, 1), (65, 129), (2049, 2049)])   # 64 x 128 tiles, 128 x 256 tiles, ragged
+# 64 x 128 tiles, in the launch's order and (17 tile rows) in the XCDs'; 128 x 256 tiles; ragged
+@pytest.mark.parametrize("M,N", [(1, 1), (65, 129), (1030, 200), (2049, 2049)])
 @pytest.mark.parametrize("K", [3, 64, 65, 129, 193, 257, 320])       # one to five steps of 64 k, three of them in LDS
 def test_layer_binw_realx_int8_tiles(G, bnn, oracle, M, N, K):
     """Integers of at most 2^14 as inputs: quantised without rounding, and the sums are below 2^24, so the result is exact."""
