@@ -118,7 +118,8 @@ typedef enum bnn_option {
                                        on the vector ALU; 16 on the fp32 matrix cores for real weights, and for real inputs
                                        from 17 frames on), so that a layer is spread over the whole chip and takes one pass
                                        over its weight rows (binary layers that would need more workgroups than the chip
-                                       holds stay on the matrix cores); 0 = never.  Default 64.  Same results either way. */
+                                       holds stay on the matrix cores).  In bnn_forward, binary layers of up to 2048 inputs that follow each
+                                       other share one launch.  0 = never.  Default 64.  Same results either way. */
     BNN_OPT_MFMA32_SPLITK = 14,     /* 0 or 1, without effect: Sign layers once had a variant with K split between the halves of
                                        a workgroup of 8 waves.  Same bits.                                               */
     BNN_OPT_REALX_I8_LOGSOFTMAX = 16, /* bnn_forward, LOGSOFTMAX layer with binary weights and real inputs, 128 frames or more,
@@ -142,7 +143,9 @@ typedef enum bnn_option {
     BNN_OPT_COOPERATIVE_SPIN = 15,  /* polls of the other workgroups' flags before a workgroup of a cooperative kernel gives
                                        up (>= 1; default 2^20, about a second).  A small value makes the bounded wait run
                                        out on purpose: the kernel still ends, its rows are wrong and
-                                       bnn_cooperative_timeouts counts the workgroups that gave up (for tests of that path) */
+                                       bnn_cooperative_timeouts counts the workgroups that gave up (for tests of that path).
+                                       The runs of binary layers of a streaming batch poll at most this often too (and never
+                                       more than 48 times) before a wave works out itself what it waits for: same results.  */
     BNN_OPT_COOPERATIVE = 13        /* 1 = kernels whose workgroups wait for each other may be used: a binary-input
                                        LOGSOFTMAX layer on the matrix-core arm then finishes its rows inside the product
                                        kernel (the tiles of a row exchange their maxima and sums of exponentials through
@@ -294,8 +297,9 @@ size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, i
  *   workspace DEVICE scratch of at least bnn_forward_workspace_bytes() bytes, 256-byte aligned
  *             (may be NULL when that is 0)
  * A layer with w_is_real = 1 runs as bnn_layer_realw (after bnn_unpack_activations if its input is binary).
- * Enqueues one kernel per layer (two for a LOGSOFTMAX layer or a real-input Sign layer on the slab filter) on `stream`,
- * no host synchronisation.
+ * Enqueues one kernel per layer (two for a LOGSOFTMAX layer or a real-input Sign layer on the slab filter; one for a run of
+ * binary layers of a streaming batch) on `stream`, no host synchronisation.  A workspace smaller than
+ * bnn_forward_workspace_bytes() by no more than the scratch of such runs is accepted too: they then take a launch per layer.
  */
 int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,
                 void* workspace, size_t workspace_bytes, void* stream);

@@ -10,6 +10,7 @@
 #include "../../include/bnn.h"
 #include "mfma32_kernels.hpp"
 #include "mfma_i8_kernels.hpp"
+#include "few_chain_kernel.hpp"
 #include "launch.hpp"
 #include "realx_mfma_kernels.hpp"
 #include "realw_kernels.hpp"
@@ -144,20 +145,20 @@ void launch_f32_sums(const ChainArgs& a, int act, bool few) {
 
 template <int TM, bool BCAST>
 void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                       int w32, int act, void* Y, int yw32, hipStream_t st) {
+                       int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear) {
     const dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
     switch (act) {
         case BNN_ACT_SIGN:
-            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
             break;
         case BNN_ACT_HARDTANH:
-            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
             break;
         case BNN_ACT_SIGMOID:
-            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
             break;
         default:
-            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
+            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
             break;
     }
 }
@@ -165,9 +166,9 @@ void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, c
 // the row-broadcast variant reads 16 bytes of a frame per lane: rows 16-byte aligned
 template <int TM>
 void launch_realx_tm(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                     int w32, int act, void* Y, int yw32, hipStream_t st) {
-    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st);
-    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st);
+                     int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear) {
+    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear);
+    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear);
 }
 
 void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
@@ -181,7 +182,7 @@ void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
 }
 
 int run_realx(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N,
-              int act, int wb, void* Y, hipStream_t st) {
+              int act, int wb, void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
     if (M == 0) return BNN_OK;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
@@ -202,17 +203,17 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
         g_realx_f32_mfma.load() != 1)
         tm = ((M + 7) / 8) * ((N + 255) / 256) >= 2048 ? 8 : 4;
     if (tm == 0) {
-        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st}, act, few);
+        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st, clear}, act, few);
         if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
         return launch_status();
     }
     switch (tm) {
-        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
-        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
-        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
-        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
-        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
-        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st); break;
+        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();
@@ -220,7 +221,7 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
 
 // A layer with real-valued weights.
 int run_realw(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, int act, int wb,
-              void* Y, hipStream_t st) {
+              void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
     if (M == 0) return BNN_OK;
     const int yw32 = (int)row_w32(N, wb);
     const int f32_mfma = g_realx_f32_mfma.load();
@@ -232,7 +233,7 @@ int run_realw(const float* X, const float* W, const float* bias, int64_t M, int6
         if (M <= 4) realw_gemv_kernel<4><<<dim3(nb, (unsigned)((M + 3) / 4)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
         else realw_gemv_kernel<8><<<dim3(nb, (unsigned)((M + 7) / 8)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
     } else {
-        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st}, act, M <= g_stream_max_frames.load());
+        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st, clear}, act, M <= g_stream_max_frames.load());
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();
@@ -1244,17 +1245,119 @@ BNN_EXPORT int bnn_semi_stochastic_binarize(float* w, const float* u, int64_t co
     return launch_status();
 }
 
+// Runs of binary layers of a streaming batch in one launch (few_chain_kernel.hpp), inside bnn_forward: the layers from l on, as many
+// as bits pass between, behind a layer with real inputs or weights (whose launch clears the marks).  0: none.
+// Whole passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 1 frame 24.9 -> 13.2 us (512
+// units), 27.2 -> 13.5 (1024), 26.0 -> 17.1 (2048); 16 frames 26.1 -> 15.5 and 27.6 -> 19.7 (1024, 2048); 64 frames 29.0 -> 18.8
+// and 37.8 -> 29.2.  Rows that are no multiple of 16 bytes gain more, having no split of K over lanes otherwise (51 frames of 1344 units
+// 64.6 -> 33.8).  Wider layers stay apart: every XCD reads all weights here, and 4096 units are 2 MB a layer (6 layers, 32 frames
+// 48.9 -> 45.5 us, but 1 frame 27.0 -> 28.0, 64 frames 56.7 -> 68.6), in registers that leave no room for a second launch beside
+// this one.  Two hidden layers alone gain nothing where their rows are whole pieces (1 frame, 3584 units 52.2 -> 54.2).
+static int few_chain_layers(const bnn_layer_desc* layers, int n_layers, int l, int64_t M) {
+    if (l < 1 || l >= n_layers || M > kFewMaxFrames) return 0;
+    auto binary = [](const bnn_layer_desc& d) { return d.x_is_binary && !d.w_is_real; };
+    if (binary(layers[l - 1])) return 0;
+    int n = 0;
+    bool whole = true;   // rows of whole 16-byte pieces
+    for (; l + n < n_layers && n < kFewMaxLayers && binary(layers[l + n]); ++n) {
+        const bnn_layer_desc& d = layers[l + n];
+        const int64_t w32 = row_w32(d.K, d.word_bits);
+        if (w32 > kFewMaxInputWords || d.N > kFewMaxClasses) break;
+        whole = whole && w32 % 4 == 0 && aligned(d.Wp, 16);
+    }
+    const bool lsm = n > 0 && layers[l + n - 1].act == BNN_ACT_LOGSOFTMAX;
+    return n >= (whole && !lsm ? 3 : 2) ? n : 0;
+}
+static int few_chain_pieces(const bnn_layer_desc* layers, int l, int n) {   // 16-byte pieces of a row of bits per lane
+    int nr = 1;
+    for (int j = l; j < l + n; ++j)
+        while (row_w32(layers[j].K, layers[j].word_bits) > 16 * nr) nr *= 2;
+    return nr;
+}
+struct FewScratch {
+    size_t words, z, total;   // the layers' marked words, one behind the other; the last layer's pre-activations; both
+};
+static FewScratch few_chain_scratch(const bnn_layer_desc* layers, int l, int n, int64_t M) {
+    FewScratch s{};
+    const bnn_layer_desc& last = layers[l + n - 1];
+    const bool lsm = last.act == BNN_ACT_LOGSOFTMAX;
+    s.words = round_up((size_t)M * 8 * ((size_t)(n - 1) * 16 * few_chain_pieces(layers, l, n) + (lsm ? kFewMaxWords : 0)), 256);
+    s.z = lsm ? round_up((size_t)M * round_up((size_t)last.N, 2) * 4, 256) : 0;
+    s.total = s.words + s.z;
+    return s;
+}
+// In this call?  Y: where the last of the n layers writes.  (Written at other times than by one launch per layer: it must not lie
+// over what the run still reads.)
+static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M, const void* Y) {
+    if (n == 0 || M > g_stream_max_frames.load() || g_default_arm.load() != BNN_ARM_MFMA) return false;
+    const bnn_layer_desc& last = layers[l + n - 1];
+    if (last.act == BNN_ACT_LOGSOFTMAX && !aligned(Y, 16)) return false;
+    const size_t yb = out_bytes(M, last.N, last.act, last.word_bits);
+    for (int j = l; j < l + n; ++j) {
+        const bnn_layer_desc& d = layers[j];
+        if (overlap(Y, yb, d.Wp, (size_t)d.N * row_w32(d.K, d.word_bits) * 4) || overlap(Y, yb, d.scale, d.scale ? (size_t)d.N * 4 : 0) ||
+            overlap(Y, yb, d.bias, d.bias ? (size_t)d.N * 4 : 0))
+            return false;
+    }
+    return true;
+}
+static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st) {
+    const FewScratch s = few_chain_scratch(layers, l, n, M);
+    const int nr = few_chain_pieces(layers, l, n);
+    FewArgs a{};
+    a.F = ((int)M + kFewGroups - 1) / kFewGroups;
+    bool vec = true;
+    uint64_t* words = reinterpret_cast<uint64_t*>(scratch_mem);
+    for (int j = 0; j < n; ++j) {
+        const bnn_layer_desc& d = layers[l + j];
+        FewLayer& f = a.layer[j];
+        f = {static_cast<const uint32_t*>(d.Wp), d.scale, d.bias, words, (int)d.K, (int)d.N, (int)row_w32(d.K, d.word_bits), d.x_is_binary == 2, 0, 0, 0};
+        f.blocks = (f.N + 31) / 32;
+        f.per_block = (65536 + f.blocks - 1) / f.blocks;   // (exact for the 128 waves of a group)
+        const int parts = max(1, min(a.F, kFewWaves * kFewSlots / f.blocks));
+        f.f = (a.F + parts - 1) / parts;
+        words += (size_t)M * (j < n - 1 ? 16 * nr : kFewMaxWords);
+        vec = vec && f.w32 % 4 == 0 && aligned(d.Wp, 16);
+    }
+    const bnn_layer_desc& last = layers[l + n - 1];
+    a.X = static_cast<const uint32_t*>(X);
+    a.Y = Y;
+    a.z = reinterpret_cast<float*>(scratch_mem + s.words);
+    a.layers = n;
+    a.M = (int)M;
+    a.act = last.act;
+    a.yw32 = (int)row_w32(last.N, last.word_bits);
+    a.z_ld = (int)round_up((size_t)last.N, 2);
+    a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
+    auto go = [&](auto nrc) {
+        constexpr int NR = decltype(nrc)::value;
+        if (vec) few_chain_kernel<NR, true><<<kFewGroups * kFewSlots, kFewThreads, 0, st>>>(a);
+        else few_chain_kernel<NR, false><<<kFewGroups * kFewSlots, kFewThreads, 0, st>>>(a);
+    };
+    if (nr == 1) go(std::integral_constant<int, 1>{});
+    else if (nr == 2) go(std::integral_constant<int, 2>{});
+    else go(std::integral_constant<int, 4>{});
+    return launch_status();
+}
+
 // Workspace layout of bnn_forward: two ping-pong buffers of `half` bytes, then `unpacked` bytes for the fp32 copy of
 // the bits that a real-weight layer reads, or for the digit planes of a real-input Sign layer (whichever is larger).
+// and, beyond what a call has to have, `few` bytes for runs of binary layers of a streaming batch (used if they are there).
 struct ForwardWorkspace {
-    size_t half, unpacked;
+    size_t half, unpacked, few;
+    size_t needed() const { return 2 * half + unpacked; }
+    size_t total() const { return needed() + few; }
 };
 // `roomy`: with the scratch of the tiled matrix-core products (the weight bytes and the list of realx_i8_gemm, the bf16
 // planes of a Softmax layer with real weights); without it those layers run on the kernels that need less or none
 // `callers`: a workspace of the caller's, with what is only reserved (realw_reserved_bytes)
 static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_layers, int64_t M, bool callers, bool roomy = true) {
-    size_t biggest = 0, unpacked = 0;
+    size_t biggest = 0, unpacked = 0, few = 0;
     for (int l = 0; l < n_layers; ++l) {
+        if (const int n = few_chain_layers(layers, n_layers, l, M)) {
+            const size_t b = few_chain_scratch(layers, l, n, M).total;
+            if (b > few) few = b;
+        }
         if (l + 1 < n_layers) {
             const size_t b = out_bytes(M, layers[l].N, layers[l].act, layers[l].word_bits);
             if (b > biggest) biggest = b;
@@ -1280,13 +1383,12 @@ static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_la
             if (b > unpacked) unpacked = b;
         }
     }
-    return {round_up(biggest, 256), round_up(unpacked, 256)};
+    return {round_up(biggest, 256), round_up(unpacked, 256), few};
 }
 
 BNN_EXPORT size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, int64_t M) {
     if (check_chain(layers, n_layers, M) != BNN_OK) return 0;
-    const ForwardWorkspace ws = forward_workspace(layers, n_layers, M, true);
-    return 2 * ws.half + ws.unpacked;
+    return forward_workspace(layers, n_layers, M, true).total();
 }
 
 // Scratch of bnn_forward_static: a fixed array in the library's device image (every GPU the library runs on holds its
@@ -1330,12 +1432,12 @@ BNN_EXPORT int bnn_forward_static(const bnn_layer_desc* layers, int n_layers, co
     // bnn_forward uses with these products switched off.
     bool roomy = true;
     ForwardWorkspace ws = forward_workspace(layers, n_layers, M, false);
-    if (2 * ws.half + ws.unpacked > kStaticScratchBytes) {
+    if (ws.needed() > kStaticScratchBytes) {
         roomy = false;
         ws = forward_workspace(layers, n_layers, M, false, false);
     }
-    const size_t need = 2 * ws.half + ws.unpacked;
-    if (need > kStaticScratchBytes) return BNN_EWORKSPACE;
+    if (ws.needed() > kStaticScratchBytes) return BNN_EWORKSPACE;
+    const size_t need = ws.total() > kStaticScratchBytes ? ws.needed() : ws.total();
     void* mem = nullptr;
     if (need) {
         mem = static_scratch();
@@ -1356,18 +1458,30 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
     if (M == 0) return BNN_OK;
     if (!X || !out) return BNN_EINVAL;
     const ForwardWorkspace ws = forward_workspace(layers, n_layers, M, callers, roomy);
-    const size_t need = 2 * ws.half + ws.unpacked;
+    const size_t need = ws.needed();
     if (need && (!workspace || workspace_bytes < need)) return BNN_EWORKSPACE;
     if (need && !aligned(workspace, 256)) return BNN_EALIGN;
     // Check every layer's arguments before anything is enqueued.
     char* buf[2] = {static_cast<char*>(workspace), static_cast<char*>(workspace) + ws.half};
     float* unpacked = reinterpret_cast<float*>(static_cast<char*>(workspace) + 2 * ws.half);
+    char* few = ws.few && workspace_bytes >= ws.total() ? static_cast<char*>(workspace) + need : nullptr;
     hipStream_t st = static_cast<hipStream_t>(stream);
     for (int pass = 0; pass < 2; ++pass) {
         const void* in = X;
         for (int l = 0; l < n_layers; ++l) {
             const bnn_layer_desc& d = layers[l];
-            void* o = (l == n_layers - 1) ? out : static_cast<void*>(buf[l & 1]);
+            auto output = [&](const void* input, int layer) -> void* { return layer == n_layers - 1 ? out : input == buf[0] ? buf[1] : buf[0]; };
+            void* o = output(in, l);
+            // a run of binary layers behind this one that takes a single launch: its marks are cleared by this layer's
+            int run = 0;
+            Clear clear{nullptr, 0};
+            void* run_out = nullptr;
+            if (pass == 1 && few) {
+                run = few_chain_layers(layers, n_layers, l + 1, M);
+                run_out = output(o, l + run);
+                if (run && few_chain_runs(layers, l + 1, run, M, run_out)) clear = {reinterpret_cast<uint4*>(few), (int)(few_chain_scratch(layers, l + 1, run, M).words / 16)};
+                else run = 0;
+            }
             if (pass == 0) {
                 if (d.w_is_real && d.x_is_binary) {
                     if (!aligned(in, d.word_bits / 8)) return BNN_EALIGN;
@@ -1389,7 +1503,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                     rc = run_realw_split_lsm(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N,
                                              static_cast<float*>(o), planes, st);
                 else
-                    rc = run_realw(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o, st);
+                    rc = run_realw(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o, st, clear);
             } else if (d.x_is_binary) {
                 rc = run_binx(in, d.Wp, d.scale, d.bias, M, d.K, d.N, d.act, d.word_bits, o, BNN_ARM_AUTO, st,
                               d.x_is_binary == 2);
@@ -1410,10 +1524,16 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                                          unpacked, st);
             } else {
                 rc = run_realx(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.act, d.word_bits, o,
-                               st);
+                               st, clear);
             }
             if (rc != BNN_OK) return rc;
             in = o;
+            if (run) {
+                rc = run_few_chain(layers, l + 1, run, in, M, run_out, few, st);
+                if (rc != BNN_OK) return rc;
+                in = run_out;
+                l += run;
+            }
         }
     }
     return BNN_OK;

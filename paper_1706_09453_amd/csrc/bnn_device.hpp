@@ -64,6 +64,16 @@ __device__ __forceinline__ void xcd_tile(int& tm, int& tn) {
     tn = two ? in >> 1 : in;
 }
 
+// 16-byte pieces that a launch sets to 0 for the launch behind it (few_chain_kernel.hpp)
+struct Clear {
+    uint4* at;
+    int pieces;
+};
+__device__ __forceinline__ void clear_pieces(const Clear& c) {
+    const int threads = (int)(blockDim.x * gridDim.x * gridDim.y);
+    for (int i = (int)((blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x); i < c.pieces; i += threads) c.at[i] = make_uint4(0u, 0u, 0u, 0u);
+}
+
 // Eq. 3 of the paper: +1 exactly when v > 0 (0, -0 and NaN give -1, i.e. bit 0).
 __device__ __forceinline__ bool sign_bit(float v) { return v > 0.0f; }
 

@@ -6,6 +6,8 @@
 #include <atomic>
 #include <cstdint>
 
+#include "bnn_device.hpp"
+
 namespace bnn {
 
 inline bool aligned(const void* p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
@@ -35,6 +37,7 @@ struct ChainArgs {
     void* Y;
     int yw32;
     hipStream_t st;
+    Clear clear = {nullptr, 0};   // Sign layers: memory that the launch sets to 0
 };
 void launch_chain_bits(const ChainArgs& a, int act);   // W packed bits
 void launch_chain_real(const ChainArgs& a, int act);   // W fp32

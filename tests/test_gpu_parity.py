@@ -246,6 +246,48 @@ def test_streaming_forward(G, bnn, oracle, cfg_id, M):
         _net_parity(G, bnn, oracle, workloads.CONFIGS[cfg_id], M)
 
 
+@pytest.mark.parametrize("spins", [1 << 20, 1])   # 1: every wave gives up waiting and works out what it needs itself
+@pytest.mark.parametrize("M,dims,last,zero_one,wb", [
+    (1, (40, 2048, 2048, 2048, 3400), "logsoftmax", False, 32), (7, (40, 512, 512, 512, 1003), "logsoftmax", True, 64),
+    (64, (40, 1000, 1000, 4096), "logsoftmax", False, 64), (64, (143, 2048, 2048, 2048, 2048), "sigmoid", False, 32),
+    (9, (40, 33, 1984, 70, 97), "sign", False, 64), (33, (40, 1, 31, 32, 5), "linear", True, 32),
+    (16, (40, 4096, 2048, 4096, 130), "logsoftmax", False, 32), (50, (40, 2047, 1003, 513, 2049, 77), "logsoftmax", True, 32),
+    (23, (40,) + (96,) * 18 + (50,), "hardtanh", False, 32)])
+def test_streaming_run_of_binary_layers(G, bnn, M, dims, last, zero_one, wb, spins):
+    """The binary layers of a streaming batch in one launch: the bits of the same layers called one by one, for one batch after
+    another on the same workspace (whose marks the first layer's launch clears), whether waves wait for each other or not."""
+    g = torch.Generator().manual_seed(M + len(dims) + dims[-1])
+    n = len(dims) - 1
+    descs, keep = [], []
+    for l, (K, N) in enumerate(zip(dims, dims[1:])):
+        Wp, _ = G.pack_weights(torch.randn(N, K, generator=g).cuda(), wb)
+        scale, bias = (torch.rand(N, generator=g) / K ** 0.5).cuda(), torch.randn(N, generator=g).cuda() * 0.1
+        keep += [Wp, scale, bias]
+        descs.append(dict(K=K, N=N, act=bnn.ACT_BY_NAME["sign" if l < n - 1 else last], word_bits=wb,
+                          x_is_binary=0 if l == 0 else 2 if zero_one else 1, Wp=G.ptr(Wp), scale=G.ptr(scale), bias=G.ptr(bias)))
+    layers = bnn.make_layer_array(descs)
+
+    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = G.out_tensor(M, dims[-1], descs[-1]["act"], wb)
+    bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, spins)
+    try:
+        with _streaming(bnn):
+            for _ in range(3):
+                X = torch.randn(M, dims[0], generator=g).cuda()
+                bnn.bnn_forward(layers, n, G.ptr(X), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
+                h = X
+                for d in descs:
+                    Y = G.out_tensor(M, d["N"], d["act"], wb)
+                    fn = (bnn.bnn_layer_binw_realx, bnn.bnn_layer_binw_binx, bnn.bnn_layer_binw_binx01)[d["x_is_binary"]]
+                    fn(G.ptr(h), d["Wp"], d["scale"], d["bias"], M, d["K"], d["N"], d["act"], wb, G.ptr(Y), G.stream())
+                    h = Y
+                torch.cuda.synchronize()
+                assert torch.equal(out, h)
+    finally:
+        bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
+
+
 def test_streaming_forward_equals_large_batch_forward(G, bnn, oracle):
     """The same 48 frames through the streaming kernels (16 at a time) and through the large-batch kernels: the
     log-posteriors agree within the tolerance of the two log-Softmax kernels, their arg max exactly."""
