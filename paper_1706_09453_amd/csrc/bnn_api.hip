@@ -11,6 +11,7 @@
 #include "mfma32_kernels.hpp"
 #include "mfma_i8_kernels.hpp"
 #include "few_chain_kernel.hpp"
+#include "hidden_run_kernel.hpp"
 #include "launch.hpp"
 #include "realx_mfma_kernels.hpp"
 #include "realw_kernels.hpp"
@@ -572,7 +573,7 @@ bool realx_sign_mfma_applies(const bnn_layer_desc& d) {
 }
 
 int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K,
-                        int64_t N, int wb, void* Y, hipStream_t st) {
+                        int64_t N, int wb, void* Y, hipStream_t st, const Clear& clear) {
     const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const int kpad = (Ki + 63) / 64 * 64;
@@ -600,10 +601,10 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     if (!allow_lds(vec16 ? &realx_sign_fused_kernel<true> : &realx_sign_fused_kernel<false>, most, allowed[vec16])) return BNN_EDEVICE;
     if (vec16)
         realx_sign_fused_kernel<true><<<grid, block, lds, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, kpad,
-                                                               Ni, nb, w32, static_cast<uint32_t*>(Y), yw32);
+                                                               Ni, nb, w32, static_cast<uint32_t*>(Y), yw32, clear);
     else
         realx_sign_fused_kernel<false><<<grid, block, lds, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, kpad,
-                                                                Ni, nb, w32, static_cast<uint32_t*>(Y), yw32);
+                                                                Ni, nb, w32, static_cast<uint32_t*>(Y), yw32, clear);
     return launch_status();
 }
 
@@ -797,7 +798,7 @@ int launch_i8_product(const int8_t* planes, const int8_t* bytes, const void* met
 }
 template <int D>
 int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int Mi, int Ki, int Ni, int w32,
-                         void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st) {
+                         void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
     const int kpad = i8_kpad(Ki);
     int8_t* planes = reinterpret_cast<int8_t*>(mem + sc.planes);
     int8_t* bytes = reinterpret_cast<int8_t*>(mem + sc.bytes);
@@ -816,20 +817,20 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
         const unsigned int rg = (unsigned int)((Mi + kResolveFrames - 1) / kResolveFrames);
         if ((Ki & 3) == 0 && aligned(X, 16))
             realx_resolve_rows_kernel<true><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
-                                                                          undecided, recs, static_cast<uint32_t*>(Y), yw32);
+                                                                          undecided, recs, static_cast<uint32_t*>(Y), yw32, clear);
         else
             realx_resolve_rows_kernel<false><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
-                                                                           undecided, recs, static_cast<uint32_t*>(Y), yw32);
+                                                                           undecided, recs, static_cast<uint32_t*>(Y), yw32, clear);
     }
     return BNN_OK;
 }
 int run_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N, int wb,
-                      int act, void* Y, void* scratch_mem, hipStream_t st) {
+                      int act, void* Y, void* scratch_mem, hipStream_t st, const Clear& clear) {
     const I8GemmScratch sc = i8_gemm_scratch(M, K, N, act);
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     int rc;
     if (act == BNN_ACT_SIGN) {
-        rc = launch_realx_i8_gemm<3>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, static_cast<char*>(scratch_mem), sc, st);
+        rc = launch_realx_i8_gemm<3>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, static_cast<char*>(scratch_mem), sc, st, clear);
     } else {
         rc = launch_realx_i8_gemm<4>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, 0, static_cast<char*>(scratch_mem), sc, st);
         if (rc == BNN_OK) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
@@ -1286,12 +1287,10 @@ static FewScratch few_chain_scratch(const bnn_layer_desc* layers, int l, int n, 
     s.total = s.words + s.z;
     return s;
 }
-// In this call?  Y: where the last of the n layers writes.  (Written at other times than by one launch per layer: it must not lie
-// over what the run still reads.)
-static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M, const void* Y) {
-    if (n == 0 || M > g_stream_max_frames.load() || g_default_arm.load() != BNN_ARM_MFMA) return false;
+// The output of a run is written while its earlier layers are still read, which one launch per layer never does: it must not lie over
+// their weights.
+static bool apart(const bnn_layer_desc* layers, int l, int n, int64_t M, const void* Y) {
     const bnn_layer_desc& last = layers[l + n - 1];
-    if (last.act == BNN_ACT_LOGSOFTMAX && !aligned(Y, 16)) return false;
     const size_t yb = out_bytes(M, last.N, last.act, last.word_bits);
     for (int j = l; j < l + n; ++j) {
         const bnn_layer_desc& d = layers[j];
@@ -1300,6 +1299,13 @@ static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M
             return false;
     }
     return true;
+}
+// In this call?  Y: where the last of the n layers writes.
+static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M, const void* Y) {
+    if (n == 0 || M > g_stream_max_frames.load() || g_default_arm.load() != BNN_ARM_MFMA) return false;
+    const bnn_layer_desc& last = layers[l + n - 1];
+    if (last.act == BNN_ACT_LOGSOFTMAX && !aligned(Y, 16)) return false;
+    return apart(layers, l, n, M, Y);
 }
 static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st) {
     const FewScratch s = few_chain_scratch(layers, l, n, M);
@@ -1340,9 +1346,82 @@ static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void*
     return launch_status();
 }
 
+// Runs of equal Sign layers of a mid-size batch in one launch (hidden_run_kernel.hpp), inside bnn_forward: the layers from l on,
+// behind a real-input Sign layer whose last launch clears the flags.  0: none.
+// Whole passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 333 frames 42.2 -> 32.4 us (512
+// units), 47.0 -> 35.0 (1024), 49.8 -> 38.5 (1536), 54.9 -> 46.9 (2048); 1000 frames 44.6 -> 36.8 and 49.7 -> 41.6 (512, 1024).
+// Up to 1024 units to 2^21 outputs of a layer, where the tiles of one launch per layer make up for it: 3000 frames of 1024 units 71.1
+// and 70.2, 8192 of 512 93.8 and 99.8, but 2048 of 1024 62.1 and 55.6.  Wider layers while a wave's share is one fragment, 2048 units to
+// 384 frames: their registers leave little room for other launches beside this one, and with four batches in flight on four
+// streams each waits for workgroups that find no place (333 frames of 2048 units 35.6 -> 40.6 us a pass, 400 of 1536 35.1 -> 24.3, but
+// 500 of 2048 34.7 -> 55.7, alone 55.0 -> 49.7).
+static int hidden_run_layers(const bnn_layer_desc* layers, int n_layers, int l, int64_t M) {
+    if (l < 1 || l >= n_layers || M <= kFewMaxFrames) return 0;
+    const bnn_layer_desc& before = layers[l - 1];
+    if (before.x_is_binary || before.w_is_real || !(l == 1 && realx_sign_mfma_applies(before) ? true : realx_i8_gemm_applies(before, M))) return 0;
+    const int64_t N = layers[l].N;
+    if (N % 512 != 0 || N > 2048 || (N <= 1024 ? M * N > ((int64_t)1 << 21) : M > (N <= 1536 ? 512 : 384))) return 0;
+    int n = 0;
+    while (l + n < n_layers && n < kRunMaxLayers && layers[l + n].x_is_binary && !layers[l + n].w_is_real && layers[l + n].act == BNN_ACT_SIGN &&
+           layers[l + n].K == N && layers[l + n].N == N && aligned(layers[l + n].Wp, 16))
+        ++n;
+    return n >= 2 ? n : 0;
+}
+struct RunScratch {
+    size_t flags, rows, total;   // all layers' flags; one layer's words (each but the last has its own); everything
+};
+static RunScratch hidden_run_scratch(int64_t N, int n, int64_t M) {
+    RunScratch s{};
+    s.flags = (size_t)n * kRunFlags * 4;
+    s.rows = round_up((size_t)M * (size_t)(N / 8), 256);
+    s.total = s.flags + (size_t)(n - 1) * s.rows;
+    return s;
+}
+static bool hidden_run_runs(const bnn_layer_desc* layers, int l, int n, int64_t M, const void* Y) {
+    if (n == 0 || M <= g_stream_max_frames.load() || g_default_arm.load() != BNN_ARM_MFMA || g_realx_sign_mfma.load() != 1 ||
+        g_mfma_shape.load() != 0 || g_mfma32_wm.load() != 0 || g_mfma32_pipeline.load() == 2 || !aligned(Y, 16))
+        return false;
+    return apart(layers, l, n, M, Y);
+}
+static int run_hidden_run(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st) {
+    const int64_t N = layers[l].N;
+    const RunScratch s = hidden_run_scratch(N, n, M);
+    RunArgs a{};
+    for (int j = 0; j < n; ++j) {
+        const bnn_layer_desc& d = layers[l + j];
+        a.layer[j] = {static_cast<const uint32_t*>(d.Wp), d.scale, d.bias,
+                      static_cast<uint32_t*>(j == n - 1 ? Y : static_cast<void*>(scratch_mem + s.flags + (size_t)j * s.rows)), d.x_is_binary == 2};
+    }
+    a.X = static_cast<const uint32_t*>(X);
+    a.flags = reinterpret_cast<uint32_t*>(scratch_mem);
+    a.layers = n;
+    a.M = (int)M;
+    a.F = 16 * (((int)M + 16 * kFewGroups - 1) / (16 * kFewGroups));
+    a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
+    const int per_wave = (a.F / 16 + kRunCrews - 1) / kRunCrews, passes = (per_wave + 3) / 4, fm = (per_wave + passes - 1) / passes;
+    auto go = [&](auto nfc, auto fmc) {
+        hidden_run_kernel<decltype(nfc)::value, decltype(fmc)::value><<<kFewGroups * kFewSlots, kRunThreads, 0, st>>>(a);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    using I4 = std::integral_constant<int, 4>;
+    auto with_fm = [&](auto nfc) {
+        if (fm == 1) go(nfc, I1{});
+        else if (fm == 2) go(nfc, I2{});
+        else if (fm == 3) go(nfc, I3{});
+        else go(nfc, I4{});
+    };
+    if (N == 512) with_fm(I1{});
+    else if (N == 1024) with_fm(I2{});
+    else if (N == 1536) go(I3{}, I1{});
+    else go(I4{}, I1{});
+    return launch_status();
+}
+
 // Workspace layout of bnn_forward: two ping-pong buffers of `half` bytes, then `unpacked` bytes for the fp32 copy of
 // the bits that a real-weight layer reads, or for the digit planes of a real-input Sign layer (whichever is larger).
-// and, beyond what a call has to have, `few` bytes for runs of binary layers of a streaming batch (used if they are there).
+// and, beyond what a call has to have, `few` bytes for runs of binary layers (used if they are there).
 struct ForwardWorkspace {
     size_t half, unpacked, few;
     size_t needed() const { return 2 * half + unpacked; }
@@ -1356,6 +1435,10 @@ static ForwardWorkspace forward_workspace(const bnn_layer_desc* layers, int n_la
     for (int l = 0; l < n_layers; ++l) {
         if (const int n = few_chain_layers(layers, n_layers, l, M)) {
             const size_t b = few_chain_scratch(layers, l, n, M).total;
+            if (b > few) few = b;
+        }
+        if (const int n = hidden_run_layers(layers, n_layers, l, M)) {
+            const size_t b = hidden_run_scratch(layers[l].N, n, M).total;
             if (b > few) few = b;
         }
         if (l + 1 < n_layers) {
@@ -1477,10 +1560,14 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
             Clear clear{nullptr, 0};
             void* run_out = nullptr;
             if (pass == 1 && few) {
-                run = few_chain_layers(layers, n_layers, l + 1, M);
+                const bool streaming = M <= kFewMaxFrames;
+                run = streaming ? few_chain_layers(layers, n_layers, l + 1, M) : hidden_run_layers(layers, n_layers, l + 1, M);
+                if (!streaming && !roomy && !(l == 0 && realx_sign_mfma_applies(d))) run = 0;   // (the layer in front runs on other kernels)
                 run_out = output(o, l + run);
-                if (run && few_chain_runs(layers, l + 1, run, M, run_out)) clear = {reinterpret_cast<uint4*>(few), (int)(few_chain_scratch(layers, l + 1, run, M).words / 16)};
-                else run = 0;
+                if (run && (streaming ? few_chain_runs : hidden_run_runs)(layers, l + 1, run, M, run_out))
+                    clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16)};
+                else
+                    run = 0;
             }
             if (pass == 0) {
                 if (d.w_is_real && d.x_is_binary) {
@@ -1509,12 +1596,12 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                               d.x_is_binary == 2);
             } else if (l == 0 && realx_sign_mfma_applies(d) && g_realx_sign_mfma.load() && M > g_stream_max_frames.load()) {
                 rc = run_realx_sign_mfma(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits,
-                                         o, st);
+                                         o, st, clear);
             } else if (roomy && realx_i8_gemm_applies(d, M) && M > g_stream_max_frames.load() &&
                        (d.act == BNN_ACT_SIGN ? g_realx_sign_mfma.load() == 1
                                               : (g_realx_i8_lsm.load() == 1 && g_realx_f32_mfma.load() != 2))) {
                 rc = run_realx_i8_gemm(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits, d.act, o,
-                                       unpacked, st);
+                                       unpacked, st, clear);
             } else if (realx_i8_lsm_applies(d, M) && g_realx_i8_lsm.load() && g_realx_f32_mfma.load() != 2 &&
                        M > g_stream_max_frames.load()) {
                 rc = run_realx_i8_lsm(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits,
@@ -1529,7 +1616,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
             if (rc != BNN_OK) return rc;
             in = o;
             if (run) {
-                rc = run_few_chain(layers, l + 1, run, in, M, run_out, few, st);
+                rc = (M <= kFewMaxFrames ? run_few_chain : run_hidden_run)(layers, l + 1, run, in, M, run_out, few, st);
                 if (rc != BNN_OK) return rc;
                 in = run_out;
                 l += run;

@@ -308,6 +308,18 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
     few_join();
 }
 
+// A wave's share of pulling `bytes` into the XCD's L2, a load per 128 bytes.
+__device__ __forceinline__ void few_pull(const void* from, uint32_t bytes, int slot, int lane) {
+    constexpr uint32_t step = kFewSlots * kWave * 128;
+    const uint32_t last = bytes - 4u;
+    for (uint32_t at = (uint32_t)(slot * kWave + lane) * 128u; at <= last; at += 8 * step) {
+        uint32_t t = 0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t ^= *global_at<const uint32_t>(from, min(at + i * step, last & ~127u));
+        asm volatile("" ::"v"(t));
+    }
+}
+
 // Grid: kFewGroups * kFewSlots, kFewThreads threads, no dynamic LDS.
 template <int NR, bool VEC>
 __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel(FewArgs a) {
@@ -321,16 +333,7 @@ __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel
     if (frames <= 0) return;
 
     if (wave == kFewWaves) {   // the later layers' weights into this XCD's L2, a load per 128 bytes
-        for (int j = 1; j < a.layers; ++j) {
-            const FewLayer& L = a.layer[j];
-            const uint32_t last = (uint32_t)L.N * (uint32_t)L.w32 * 4u - 4u, step = kFewSlots * kWave * 128;
-            for (uint32_t at = (uint32_t)(slot * kWave + lane) * 128u; at <= last; at += 8 * step) {
-                uint32_t t = 0;
-#pragma unroll
-                for (int i = 0; i < 8; ++i) t ^= *global_at<const uint32_t>(L.W, min(at + i * step, last & ~127u));
-                asm volatile("" ::"v"(t));
-            }
-        }
+        for (int j = 1; j < a.layers; ++j) few_pull(a.layer[j].W, (uint32_t)a.layer[j].N * (uint32_t)a.layer[j].w32 * 4u, slot, lane);
         return;
     }
     uint32_t *x = bits[wave][0], *y = bits[wave][1];

@@ -546,7 +546,8 @@ template <bool VEC>
 __global__ __launch_bounds__(kResolveThreads) void realx_resolve_rows_kernel(const float* __restrict__ X, const uint32_t* __restrict__ Wp,
                                                                            const float* __restrict__ scale, const float* __restrict__ bias,
                                                                            int M, int K, int w32, const unsigned char* __restrict__ undecided,
-                                                                           int recs, uint32_t* __restrict__ Y, int yw32) {
+                                                                           int recs, uint32_t* __restrict__ Y, int yw32, Clear clear) {
+    clear_pieces(clear);
     __shared__ __attribute__((aligned(16))) float xs[2][kResolveFrames][kResolveLd];
     __shared__ u32x4 ws[2][kResolveThreads][2];   // a lane's eight weight words of a slab
     __shared__ unsigned int ent[kResolveCap];   // (frame of the workgroup) << 28 | output

@@ -252,9 +252,15 @@ def test_streaming_forward(G, bnn, oracle, cfg_id, M):
     (64, (40, 1000, 1000, 4096), "logsoftmax", False, 64), (64, (143, 2048, 2048, 2048, 2048), "sigmoid", False, 32),
     (9, (40, 33, 1984, 70, 97), "sign", False, 64), (33, (40, 1, 31, 32, 5), "linear", True, 32),
     (16, (40, 4096, 2048, 4096, 130), "logsoftmax", False, 32), (50, (40, 2047, 1003, 513, 2049, 77), "logsoftmax", True, 32),
-    (23, (40,) + (96,) * 18 + (50,), "hardtanh", False, 32)])
-def test_streaming_run_of_binary_layers(G, bnn, M, dims, last, zero_one, wb, spins):
-    """The binary layers of a streaming batch in one launch: the bits of the same layers called one by one, for one batch after
+    (23, (40,) + (96,) * 18 + (50,), "hardtanh", False, 32),
+    # more frames: equal layers of up to 2048 units, every number of fragments per wave and of units, ragged last fragments
+    (65, (40, 512, 512, 512, 1003), "logsoftmax", False, 32), (128, (40, 1024, 1024, 1024, 70), "linear", True, 64),
+    (333, (440, 1024, 1024, 1024, 1024), "sign", False, 32), (384, (40, 2048, 2048, 2048, 300), "logsoftmax", False, 32),
+    (99, (143, 2048, 2048, 2048, 64), "sigmoid", True, 64), (501, (40, 1536, 1536, 1536, 200), "logsoftmax", False, 64),
+    (700, (40, 1024, 1024, 1024, 33), "logsoftmax", True, 32), (1500, (143, 1024, 1024, 1024, 65), "linear", False, 64),
+    (2048, (40, 1024, 1024, 1024, 96), "hardtanh", False, 32), (4096, (600, 512, 512, 512, 512, 40), "linear", True, 32)])
+def test_run_of_binary_layers_in_one_launch(G, bnn, M, dims, last, zero_one, wb, spins):
+    """The binary layers of a batch in one launch: the bits of the same layers called one by one, for one batch after
     another on the same workspace (whose marks the first layer's launch clears), whether waves wait for each other or not."""
     g = torch.Generator().manual_seed(M + len(dims) + dims[-1])
     n = len(dims) - 1
