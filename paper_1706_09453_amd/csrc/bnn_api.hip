@@ -228,11 +228,15 @@ int run_realw(const float* X, const float* W, const float* bias, int64_t M, int6
     const int f32_mfma = g_realx_f32_mfma.load();
     if (act == BNN_ACT_LOGSOFTMAX && f32_mfma != 2 && M <= 64 && M <= g_stream_max_frames.load() && (K & 3) == 0 &&
         aligned(X, 16) && aligned(W, 16)) {
-        // a few frames in front of the log-Softmax: K split over the lanes, so that N / 4 waves pull the weights
+        // a few frames in front of the log-Softmax: K split over the lanes, so that N / 4 waves pull the weights, or from 5 frames on
+        // over the waves of a workgroup and the matrix cores (512 x 1000: 4 frames 6.9 and 7.7 us, 5 frames 8.8 and 8.4; 2048 x 3400: 4
+        // frames 13.8 and 14.0, 5 frames 16.2 and 14.3)
         float* Yf = static_cast<float*>(Y);
-        const unsigned nb = (unsigned)((N + 15) / 16);
-        if (M <= 4) realw_gemv_kernel<4><<<dim3(nb, (unsigned)((M + 3) / 4)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
-        else realw_gemv_kernel<8><<<dim3(nb, (unsigned)((M + 7) / 8)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
+        if (M <= 4) {
+            realw_gemv_kernel<<<dim3((unsigned)((N + 15) / 16)), 256, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
+        } else {
+            realw_frames16_kernel<<<dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16)), kFrames16Threads, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
+        }
     } else {
         launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st, clear}, act, M <= g_stream_max_frames.load());
     }

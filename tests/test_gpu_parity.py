@@ -421,6 +421,22 @@ def test_streaming_real_weight_layer(G, bnn, oracle, M, K, N, act):
         assert np.array_equal(Y.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("M", [1, 4, 5, 16, 17, 64])
+@pytest.mark.parametrize("K,N", [(4, 1), (60, 15), (512, 17), (516, 16), (1028, 130), (2048, 3400)])
+def test_streaming_softmax_layer_with_real_weights(G, bnn, M, K, N):
+    """Up to 64 frames in front of the log-Softmax: K split over lanes or waves, partial turns of either.  Every output is the sum of
+    at most 64 chains of ceil(K / 64) + 4 terms, added pairwise, so a pre-activation is within (K / 64 + 16) 2^-24 of sum |x w| of its
+    exact value, and a log-posterior within twice that and the rounding of the log-Softmax."""
+    X, W, bias = _rand_realw(M + 7 * K + N, M, K, N)
+    with _streaming(bnn):
+        Y = G.layer_realw(G.to_dev(X), G.to_dev(W), G.to_dev(bias), K, N, bnn.BNN_ACT_LOGSOFTMAX, 32)
+        torch.cuda.synchronize()
+    x, w = torch.from_numpy(X).double(), torch.from_numpy(W).double()
+    want = torch.log_softmax(x @ w.t() + torch.from_numpy(bias).double(), 1)
+    bound = 2 * (K / 64 + 16) * 2.0 ** -24 * float((x.abs() @ w.abs().t()).max()) + 2.0 ** -19 * max(1.0, float(want.abs().max()))
+    assert float((Y.cpu().double() - want).abs().max()) <= bound
+
+
 def _one_layer_realw_forward(G, bnn, X, W, bias, K, N, act, wb=32):
     """A one-layer network with real weights through bnn_forward."""
     keep = [G.to_dev(W), G.to_dev(bias)]
