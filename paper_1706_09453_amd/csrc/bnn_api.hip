@@ -767,15 +767,16 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
 // fill costs loads of its first elements again); 32 groups, the longest frames there are, take 214 to 216 registers, which leaves
 // two waves per SIMD (4096 x 6144 43 -> 33 us against reading the frame twice).  Ragged frames need a load per element and are read twice.
 template <int D>
-void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* planes, void* meta, hipStream_t st) {
-    const dim3 grid((unsigned)((M + 3) / 4));
+void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* planes, void* meta, const ByteRows& weights, hipStream_t st) {
+    const int64_t byte_blocks = (weights.N * (kpad / 16) + 255) / 256;
+    const dim3 grid((unsigned)(((int64_t)M + 3) / 4 + (byte_blocks < 16384 ? byte_blocks : 16384)));
     const bool vec = (K & 3) == 0 && aligned(X, 16);
-    if (!vec) realx_quantize_nat_kernel<D, false, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else if (kpad <= 512) realx_quantize_nat_kernel<D, true, 2><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else if (kpad <= 1024) realx_quantize_nat_kernel<D, true, 4><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else if (kpad <= 2048) realx_quantize_nat_kernel<D, true, 8><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else if (kpad <= 4096) realx_quantize_nat_kernel<D, true, 16><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
-    else realx_quantize_nat_kernel<D, true, 32><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta);
+    if (!vec) realx_quantize_nat_kernel<D, false, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
+    else if (kpad <= 512) realx_quantize_nat_kernel<D, true, 2><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
+    else if (kpad <= 1024) realx_quantize_nat_kernel<D, true, 4><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
+    else if (kpad <= 2048) realx_quantize_nat_kernel<D, true, 8><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
+    else if (kpad <= 4096) realx_quantize_nat_kernel<D, true, 16><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
+    else realx_quantize_nat_kernel<D, true, 32><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
     static_assert(kSlabMaxK <= 32 * 256, "a frame fits the registers");
 }
 // Tiles of 128 frames x 256 outputs (one workgroup per CU) or of 64 x 128 (two per CU)?  A round of the small ones, 512
@@ -809,9 +810,7 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     void* meta = mem + sc.meta;
     unsigned char* undecided = reinterpret_cast<unsigned char*>(mem + sc.undecided);
     const int qbits = D == 3 ? slab_quant_bits(Ki) : kQuantBits4;
-    launch_quantize<D>(X, Mi, Ki, kpad, qbits, planes, meta, st);
-    const int64_t eb = ((int64_t)Ni * (kpad / 16) + 255) / 256;
-    bits_to_bytes_kernel<<<(unsigned)(eb < 16384 ? eb : 16384), 256, 0, st>>>(static_cast<const uint32_t*>(Wp), Ni, Ki, w32, kpad, bytes);
+    launch_quantize<D>(X, Mi, Ki, kpad, qbits, planes, meta, {static_cast<const uint32_t*>(Wp), bytes, Ni, w32}, st);
     const int rc = i8_small_tiles(Mi, Ni)
         ? launch_i8_product<D, 1, 2>(planes, bytes, meta, X, Wp, scale, bias, Mi, Ki, kpad, Ni, w32, Y, yw32, undecided, st)
         : launch_i8_product<D, 2, 4>(planes, bytes, meta, X, Wp, scale, bias, Mi, Ki, kpad, Ni, w32, Y, yw32, undecided, st);

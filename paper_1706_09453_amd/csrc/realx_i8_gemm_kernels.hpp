@@ -51,16 +51,21 @@ __host__ __device__ inline int i8_kpad(int K) { return (K + kI8KStep - 1) / kI8K
 constexpr int kUndecidedOutputs = 128;
 constexpr int kUndecidedRecord = kUndecidedOutputs / 8;
 
-// B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k.  Grid: any number of blocks of 256.
-__global__ __launch_bounds__(256) void bits_to_bytes_kernel(const uint32_t* __restrict__ Wp, int64_t N, int K, int w32, int kpad,
-                                                            int8_t* __restrict__ B) {
+// B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k; block `block` of `blocks` of 256 threads.
+struct ByteRows {
+    const uint32_t* Wp;
+    int8_t* B;
+    int64_t N;
+    int w32;
+};
+__device__ __forceinline__ void expand_bytes(const ByteRows& b, int K, int kpad, int block, int blocks) {
     const int per_row = kpad >> 4;
-    const int64_t total = N * per_row;
-    for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-        const int64_t n = i / per_row;
+    const int64_t total = b.N * per_row;
+    for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < total; i += (int64_t)blocks * 256) {
+        const int64_t n = total < ((int64_t)1 << 31) ? (int64_t)((uint32_t)i / (uint32_t)per_row) : i / per_row;
         const int k0 = (int)(i - n * per_row) * 16;
         uint32_t bits = 0;
-        if (k0 < K) bits = (Wp[(size_t)n * w32 + (k0 >> 5)] >> (k0 & 31)) & 0xFFFFu;
+        if (k0 < K) bits = (b.Wp[(size_t)n * b.w32 + (k0 >> 5)] >> (k0 & 31)) & 0xFFFFu;
         if (K - k0 < 16 && K > k0) bits &= (1u << (K - k0)) - 1u;
         uint32_t w[4];
 #pragma unroll
@@ -68,7 +73,7 @@ __global__ __launch_bounds__(256) void bits_to_bytes_kernel(const uint32_t* __re
             const uint32_t nib = (bits >> (4 * j)) & 0xFu;
             w[j] = (nib & 1u) | ((nib & 2u) << 7) | ((nib & 4u) << 14) | ((nib & 8u) << 21);
         }
-        *reinterpret_cast<uint4*>(B + (size_t)n * kpad + k0) = make_uint4(w[0], w[1], w[2], w[3]);
+        *reinterpret_cast<uint4*>(b.B + (size_t)n * kpad + k0) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
 
@@ -81,10 +86,17 @@ __device__ __forceinline__ uint32_t negate_digits(uint32_t d) { return (0x808080
 // registers; NG == 0 (without): it is read twice (largest element, then digits), one load after the other.
 // Bound by memory: a number in, D bytes out.  Against one load after the other, twice:
 // 4096 frames of 2048 15.5 -> 12.2 us, 2048 of 4096 26.2 -> 13.0 (5.2 TB/s).
-// Grid: ceil(M / 4) workgroups of 256 threads.
+// The weights' bytes are made in the same launch, by the workgroups behind those of the frames: neither waits for the other, and a launch
+// of their own cost 2 to 3 us (600 frames through the mixed network, two such calls 141.7 -> 139.3 us; a training step, eleven, 1971 -> 1941).
+// Grid: ceil(M / 4) workgroups of 256 threads, then those of expand_bytes.
 template <int D, bool VEC, int NG>
 __global__ __launch_bounds__(256) void realx_quantize_nat_kernel(const float* __restrict__ X, int M, int K, int kpad, int qbits,
-                                                                 int8_t* __restrict__ planes, void* __restrict__ meta_out) {
+                                                                 int8_t* __restrict__ planes, void* __restrict__ meta_out, ByteRows weights) {
+    const int frame_blocks = (int)(((int64_t)M + 3) >> 2);
+    if ((int)blockIdx.x >= frame_blocks) {
+        expand_bytes(weights, K, kpad, (int)blockIdx.x - frame_blocks, (int)gridDim.x - frame_blocks);
+        return;
+    }
     static_assert(D == 3 || D == 4, "three digits for Sign layers, four in front of the log-Softmax");
     static_assert((NG > 0) == VEC, "whole frames are requested in pieces of 16 bytes");
     const int m = (int)blockIdx.x * 4 + (int)(threadIdx.x >> 6);
