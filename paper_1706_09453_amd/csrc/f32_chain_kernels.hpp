@@ -17,7 +17,7 @@
 // t: one LDS instruction brings the operands of two steps, and with rows KC + 4 numbers apart its 64 lanes (16 rows, four
 // neighbours each) read 64 different banks.
 // Measured at 4096 x 2048 x 2048: binary weights 261 us = 132 TFLOP/s, real weights 272 us (vector-ALU kernels: 331 us,
-// and 290 with real weights); at 256 x 2048 x 2048 27 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.
+// and 290 with real weights); at 256 x 2048 x 2048 21.6 us against 72; real weights at 16 x 2048 x 2048 13.9 us against 50.
 // What is left to 153 TFLOP/s (register-only loop of the same MFMA): the sign-building and LDS instructions of the staging,
 // and the first and last chunk of a workgroup.
 // Columns past K are stored as +0 in the frames and as -0 in real weights: fma(-0, 0, acc) adds -0, which returns every acc,

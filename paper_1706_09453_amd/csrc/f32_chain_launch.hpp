@@ -23,6 +23,9 @@ void launch_chain_tile(const ChainArgs& a) {
 // Workgroup tile: the one whose fullest CU has the least to multiply, counting what a tile of that size loses to its
 // memory instructions (rates measured at 4096 x 2048 x 2048: 132 TFLOP/s with 256 x 128 tiles, 129 with 128 x 128, 124
 // with 64 x 64, 86 with 32 x 64; at 256 x 2048 x 2048, where the large tiles leave most CUs idle, 8, 15, 58 and 80).
+// Tiles of 32 x 64 take chunks of 64: with 128, half as many barriers but a first chunk that takes twice as long to arrive and a workgroup
+// that shares its CU with no other, 256 x 2048 x 2048 took 25.0 us, 21.6 now (real weights 26.9 and 23.6), 256 x 440 x 2048 9.0 and
+// 7.5, 256 x 3400 x 2048 40.0 and 34.2; the rate in the model is the one its lines were drawn with.
 template <int ACT, bool WREAL>
 void launch_chain_act(const ChainArgs& a) {
     // 32-bit byte offsets inside a workgroup's rows: 256 rows of at most 2^22 - 1 numbers
@@ -78,7 +81,7 @@ void launch_chain_act(const ChainArgs& a) {
     if (best == 0) launch_chain_tile<8, 4, 2, 32, ACT, WREAL, true>(a);
     else if (best == 1) launch_chain_tile<4, 4, 2, 32, ACT, WREAL, true>(a);
     else if (best == 2) launch_chain_tile<2, 2, 2, 64, ACT, WREAL, true>(a);
-    else if (best == 3) launch_chain_tile<1, 2, 2, 128, ACT, WREAL, true>(a);
+    else if (best == 3) launch_chain_tile<1, 2, 2, 64, ACT, WREAL, true>(a);
     else few(yes);
 }
 template <bool WREAL>
