@@ -146,20 +146,25 @@ void launch_f32_sums(const ChainArgs& a, int act, bool few) {
 
 template <int TM, bool BCAST>
 void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                       int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear) {
-    const dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
+                       int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear, const Pull* ahead) {
+    dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
+    Pull pull = ahead ? *ahead : Pull{};
+    if (pull.layers > 0) {
+        pull.from = (int)(grid.x * grid.y);
+        grid.y += (8 * kPullGroups + grid.x - 1) / grid.x;
+    }
     switch (act) {
         case BNN_ACT_SIGN:
-            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
+            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
             break;
         case BNN_ACT_HARDTANH:
-            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
+            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
             break;
         case BNN_ACT_SIGMOID:
-            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
+            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
             break;
         default:
-            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear);
+            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
             break;
     }
 }
@@ -167,9 +172,9 @@ void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, c
 // the row-broadcast variant reads 16 bytes of a frame per lane: rows 16-byte aligned
 template <int TM>
 void launch_realx_tm(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                     int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear) {
-    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear);
-    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear);
+                     int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear, const Pull* ahead) {
+    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear, ahead);
+    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear, ahead);
 }
 
 void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
@@ -183,7 +188,7 @@ void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
 }
 
 int run_realx(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N,
-              int act, int wb, void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
+              int act, int wb, void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}, const Pull* ahead = nullptr) {
     if (M == 0) return BNN_OK;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
@@ -209,12 +214,12 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
         return launch_status();
     }
     switch (tm) {
-        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
-        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
-        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
-        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
-        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
-        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear); break;
+        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();
@@ -1278,6 +1283,7 @@ static int few_chain_pieces(const bnn_layer_desc* layers, int l, int n) {   // 1
         while (row_w32(layers[j].K, layers[j].word_bits) > 16 * nr) nr *= 2;
     return nr;
 }
+static_assert(kFewMaxLayers <= kPullLayers && kFewSlots == kPullGroups, "as many layers and workgroups");
 struct FewScratch {
     size_t words, z, total;   // the layers' marked words, one behind the other; the last layer's pre-activations; both
 };
@@ -1347,6 +1353,17 @@ static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void*
     else if (nr == 2) go(std::integral_constant<int, 2>{});
     else go(std::integral_constant<int, 4>{});
     return launch_status();
+}
+
+// The weights of a run, for the launch in front of it to pull into the L2s.
+static Pull few_chain_pull(const bnn_layer_desc* layers, int l, int n, int64_t M) {
+    Pull p{};
+    for (int j = l; j < l + n; ++j) {
+        p.at[p.layers] = static_cast<const char*>(layers[j].Wp);
+        p.bytes[p.layers++] = (uint32_t)(layers[j].N * row_w32(layers[j].K, layers[j].word_bits) * 4);
+    }
+    p.xcds = (int)(M < kFewGroups ? M : kFewGroups);
+    return p;
 }
 
 // Runs of equal Sign layers of a mid-size batch in one launch (hidden_run_kernel.hpp), inside bnn_forward: the layers from l on,
@@ -1561,6 +1578,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
             // a run of binary layers behind this one that takes a single launch: its marks are cleared by this layer's
             int run = 0;
             Clear clear{nullptr, 0};
+            Pull ahead{};
             void* run_out = nullptr;
             if (pass == 1 && few) {
                 const bool streaming = M <= kFewMaxFrames;
@@ -1571,6 +1589,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                     clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16)};
                 else
                     run = 0;
+                if (run && streaming) ahead = few_chain_pull(layers, l + 1, run, M);
             }
             if (pass == 0) {
                 if (d.w_is_real && d.x_is_binary) {
@@ -1614,7 +1633,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                                          unpacked, st);
             } else {
                 rc = run_realx(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.act, d.word_bits, o,
-                               st, clear);
+                               st, clear, run && M <= kFewMaxFrames ? &ahead : nullptr);
             }
             if (rc != BNN_OK) return rc;
             in = o;

@@ -92,8 +92,12 @@ __device__ __forceinline__ void fmac_row_bcast(float& acc, float x, float w) {
 template <int TM, int ACT, bool BCAST>
 __global__ __launch_bounds__(256) void realx_valu_kernel(const float* __restrict__ X, const uint32_t* __restrict__ Wp,
                                                          const float* __restrict__ scale, const float* __restrict__ bias,
-                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32, Clear clear) {
-    if constexpr (ACT == ACT_SIGN) clear_pieces(clear);
+                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32, Clear clear, Pull pull) {
+    if constexpr (ACT == ACT_SIGN) {
+        const int block = (int)(blockIdx.y * gridDim.x + blockIdx.x);
+        if (pull.layers > 0 && block >= pull.from) return pull_memory(pull, block, (int)threadIdx.x);
+        clear_pieces(clear, pull.layers > 0 ? pull.from : (int)(gridDim.x * gridDim.y));
+    }
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
     const int n0 = ((int)blockIdx.y * 4 + wave) * kWave;
