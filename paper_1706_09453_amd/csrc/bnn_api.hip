@@ -144,11 +144,26 @@ void launch_f32_sums(const ChainArgs& a, int act, bool few) {
     }
 }
 
+// What the launch in front of a run of binary layers does for it (few_chain_kernel.hpp, hidden_run_kernel.hpp): memory that it sets to
+// 0, and memory that it pulls into the L2s if it can.  Whoever launches a kernel that clears sets `cleared`; without it there is no run,
+// whichever kernel the options of the moment have chosen.
+struct Front {
+    Clear clear{nullptr, 0};
+    Pull pull{};
+    bool cleared = false;
+};
+Clear clear_for(Front* front, int act) {
+    if (!front || act != BNN_ACT_SIGN) return {nullptr, 0};   // (only their Sign instances clear)
+    front->cleared = true;
+    return front->clear;
+}
+
 template <int TM, bool BCAST>
 void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                       int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear, const Pull* ahead) {
+                       int w32, int act, void* Y, int yw32, hipStream_t st, Front* front) {
     dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
-    Pull pull = ahead ? *ahead : Pull{};
+    Pull pull = front ? front->pull : Pull{};
+    const Clear clear = clear_for(front, act);
     if (pull.layers > 0) {
         pull.from = (int)(grid.x * grid.y);
         grid.y += (8 * kPullGroups + grid.x - 1) / grid.x;
@@ -172,9 +187,9 @@ void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, c
 // the row-broadcast variant reads 16 bytes of a frame per lane: rows 16-byte aligned
 template <int TM>
 void launch_realx_tm(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
-                     int w32, int act, void* Y, int yw32, hipStream_t st, const Clear& clear, const Pull* ahead) {
-    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear, ahead);
-    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, clear, ahead);
+                     int w32, int act, void* Y, int yw32, hipStream_t st, Front* front) {
+    if ((K & 3) == 0 && aligned(X, 16)) launch_realx_tm_b<TM, true>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, front);
+    else launch_realx_tm_b<TM, false>(X, Wp, scale, bias, M, K, N, w32, act, Y, yw32, st, front);
 }
 
 void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
@@ -188,7 +203,7 @@ void launch_log_softmax(float* Z, int M, int N, hipStream_t st) {
 }
 
 int run_realx(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N,
-              int act, int wb, void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}, const Pull* ahead = nullptr) {
+              int act, int wb, void* Y, hipStream_t st, Front* front = nullptr) {
     if (M == 0) return BNN_OK;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const uint32_t* W = static_cast<const uint32_t*>(Wp);
@@ -209,17 +224,17 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
         g_realx_f32_mfma.load() != 1)
         tm = ((M + 7) / 8) * ((N + 255) / 256) >= 2048 ? 8 : 4;
     if (tm == 0) {
-        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st, clear}, act, few);
+        launch_f32_sums<false>({X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, st, clear_for(front, act)}, act, few);
         if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
         return launch_status();
     }
     switch (tm) {
-        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
-        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
-        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
-        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
-        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
-        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, clear, ahead); break;
+        case 1: launch_realx_tm<1>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
+        case 2: launch_realx_tm<2>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
+        case 4: launch_realx_tm<4>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
+        case 8: launch_realx_tm<8>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
+        case 32: launch_realx_tm<32>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
+        default: launch_realx_tm<16>(X, W, scale, bias, (int)M, (int)K, (int)N, w32, act, Y, yw32, st, front); break;
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();
@@ -227,7 +242,7 @@ int run_realx(const float* X, const void* Wp, const float* scale, const float* b
 
 // A layer with real-valued weights.
 int run_realw(const float* X, const float* W, const float* bias, int64_t M, int64_t K, int64_t N, int act, int wb,
-              void* Y, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
+              void* Y, hipStream_t st, Front* front = nullptr) {
     if (M == 0) return BNN_OK;
     const int yw32 = (int)row_w32(N, wb);
     const int f32_mfma = g_realx_f32_mfma.load();
@@ -243,7 +258,7 @@ int run_realw(const float* X, const float* W, const float* bias, int64_t M, int6
             realw_frames16_kernel<<<dim3((unsigned)((N + 15) / 16), (unsigned)((M + 15) / 16)), kFrames16Threads, 0, st>>>(X, W, bias, (int)M, (int)K, (int)N, Yf);
         }
     } else {
-        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st, clear}, act, M <= g_stream_max_frames.load());
+        launch_f32_sums<true>({X, W, nullptr, bias, (int)M, (int)K, (int)N, 0, Y, yw32, st, clear_for(front, act)}, act, M <= g_stream_max_frames.load());
     }
     if (act == BNN_ACT_LOGSOFTMAX) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
     return launch_status();
@@ -582,7 +597,7 @@ bool realx_sign_mfma_applies(const bnn_layer_desc& d) {
 }
 
 int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K,
-                        int64_t N, int wb, void* Y, hipStream_t st, const Clear& clear) {
+                        int64_t N, int wb, void* Y, hipStream_t st, Front* front) {
     const int Mi = (int)M, Ki = (int)K, Ni = (int)N;
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     const int kpad = (Ki + 63) / 64 * 64;
@@ -608,6 +623,7 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     constexpr unsigned most = (unsigned)realx_dynamic_lds(kRealxMfmaMaxK, (kRealxMfmaMaxK + 63) / 64 * 64, (kRealxMfmaMaxK + 63) / 64 * 2, kRealxMaxNB);
     const bool vec16 = aligned(Wp, 16);   // chunks start at multiples of 512 rows: 16-byte aligned whenever the matrix is
     if (!allow_lds(vec16 ? &realx_sign_fused_kernel<true> : &realx_sign_fused_kernel<false>, most, allowed[vec16])) return BNN_EDEVICE;
+    const Clear clear = clear_for(front, BNN_ACT_SIGN);
     if (vec16)
         realx_sign_fused_kernel<true><<<grid, block, lds, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, kpad,
                                                                Ni, nb, w32, static_cast<uint32_t*>(Y), yw32, clear);
@@ -808,7 +824,7 @@ int launch_i8_product(const int8_t* planes, const int8_t* bytes, const void* met
 }
 template <int D>
 int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int Mi, int Ki, int Ni, int w32,
-                         void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st, const Clear& clear = Clear{nullptr, 0}) {
+                         void* Y, int yw32, char* mem, const I8GemmScratch& sc, hipStream_t st, Front* front = nullptr) {
     const int kpad = i8_kpad(Ki);
     int8_t* planes = reinterpret_cast<int8_t*>(mem + sc.planes);
     int8_t* bytes = reinterpret_cast<int8_t*>(mem + sc.bytes);
@@ -822,6 +838,7 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     if (rc != BNN_OK) return rc;
     const int recs = (Ni + kUndecidedOutputs - 1) / kUndecidedOutputs;
     if (D == 3) {
+        const Clear clear = clear_for(front, BNN_ACT_SIGN);
         const unsigned int rg = (unsigned int)((Mi + kResolveFrames - 1) / kResolveFrames);
         if ((Ki & 3) == 0 && aligned(X, 16))
             realx_resolve_rows_kernel<true><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
@@ -833,12 +850,12 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     return BNN_OK;
 }
 int run_realx_i8_gemm(const float* X, const void* Wp, const float* scale, const float* bias, int64_t M, int64_t K, int64_t N, int wb,
-                      int act, void* Y, void* scratch_mem, hipStream_t st, const Clear& clear) {
+                      int act, void* Y, void* scratch_mem, hipStream_t st, Front* front) {
     const I8GemmScratch sc = i8_gemm_scratch(M, K, N, act);
     const int w32 = (int)row_w32(K, wb), yw32 = (int)row_w32(N, wb);
     int rc;
     if (act == BNN_ACT_SIGN) {
-        rc = launch_realx_i8_gemm<3>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, static_cast<char*>(scratch_mem), sc, st, clear);
+        rc = launch_realx_i8_gemm<3>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, yw32, static_cast<char*>(scratch_mem), sc, st, front);
     } else {
         rc = launch_realx_i8_gemm<4>(X, Wp, scale, bias, (int)M, (int)K, (int)N, w32, Y, 0, static_cast<char*>(scratch_mem), sc, st);
         if (rc == BNN_OK) launch_log_softmax(static_cast<float*>(Y), (int)M, (int)N, st);
@@ -1577,8 +1594,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
             void* o = output(in, l);
             // a run of binary layers behind this one that takes a single launch: its marks are cleared by this layer's
             int run = 0;
-            Clear clear{nullptr, 0};
-            Pull ahead{};
+            Front front;
             void* run_out = nullptr;
             if (pass == 1 && few) {
                 const bool streaming = M <= kFewMaxFrames;
@@ -1586,11 +1602,12 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                 if (!streaming && !roomy && !(l == 0 && realx_sign_mfma_applies(d))) run = 0;   // (the layer in front runs on other kernels)
                 run_out = output(o, l + run);
                 if (run && (streaming ? few_chain_runs : hidden_run_runs)(layers, l + 1, run, M, run_out))
-                    clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16)};
+                    front.clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16)};
                 else
                     run = 0;
-                if (run && streaming) ahead = few_chain_pull(layers, l + 1, run, M);
+                if (run && streaming) front.pull = few_chain_pull(layers, l + 1, run, M);
             }
+            Front* const f = run ? &front : nullptr;
             if (pass == 0) {
                 if (d.w_is_real && d.x_is_binary) {
                     if (!aligned(in, d.word_bits / 8)) return BNN_EALIGN;
@@ -1612,18 +1629,18 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                     rc = run_realw_split_lsm(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N,
                                              static_cast<float*>(o), planes, st);
                 else
-                    rc = run_realw(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o, st, clear);
+                    rc = run_realw(xin, static_cast<const float*>(d.Wp), d.bias, M, d.K, d.N, d.act, d.word_bits, o, st, f);
             } else if (d.x_is_binary) {
                 rc = run_binx(in, d.Wp, d.scale, d.bias, M, d.K, d.N, d.act, d.word_bits, o, BNN_ARM_AUTO, st,
                               d.x_is_binary == 2);
             } else if (l == 0 && realx_sign_mfma_applies(d) && g_realx_sign_mfma.load() && M > g_stream_max_frames.load()) {
                 rc = run_realx_sign_mfma(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits,
-                                         o, st, clear);
+                                         o, st, f);
             } else if (roomy && realx_i8_gemm_applies(d, M) && M > g_stream_max_frames.load() &&
                        (d.act == BNN_ACT_SIGN ? g_realx_sign_mfma.load() == 1
                                               : (g_realx_i8_lsm.load() == 1 && g_realx_f32_mfma.load() != 2))) {
                 rc = run_realx_i8_gemm(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits, d.act, o,
-                                       unpacked, st, clear);
+                                       unpacked, st, f);
             } else if (realx_i8_lsm_applies(d, M) && g_realx_i8_lsm.load() && g_realx_f32_mfma.load() != 2 &&
                        M > g_stream_max_frames.load()) {
                 rc = run_realx_i8_lsm(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.word_bits,
@@ -1633,11 +1650,11 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                                          unpacked, st);
             } else {
                 rc = run_realx(static_cast<const float*>(in), d.Wp, d.scale, d.bias, M, d.K, d.N, d.act, d.word_bits, o,
-                               st, clear, run && M <= kFewMaxFrames ? &ahead : nullptr);
+                               st, f);
             }
             if (rc != BNN_OK) return rc;
             in = o;
-            if (run) {
+            if (front.cleared) {
                 rc = (M <= kFewMaxFrames ? run_few_chain : run_hidden_run)(layers, l + 1, run, in, M, run_out, few, st);
                 if (rc != BNN_OK) return rc;
                 in = run_out;

@@ -1,6 +1,7 @@
 // Stands in for the HIP runtime so that the library's host side runs without a GPU: every launch is recorded (kernel,
 // grid, block, dynamic LDS) and checked against what the runtime would accept, nothing is executed.  Loaded with
 // RTLD_GLOBAL in front of the library, its symbols are the ones the library binds to.
+#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <cstdint>
@@ -8,6 +9,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <utility>
 
 struct Dim3 { uint32_t x, y, z; };
@@ -24,6 +26,8 @@ thread_local Call call;
 bool hold_next_grant = false;
 int launches = 0;
 thread_local int last_error = 0;
+std::thread turner;
+std::atomic<bool> turning;
 }  // namespace
 
 extern "C" {
@@ -32,6 +36,15 @@ void stub_set_device(int d) { device = d; }
 void stub_hold_next_grant() { std::lock_guard<std::mutex> g(mu); hold_next_grant = true; }
 const char* stub_records() { return records.c_str(); }
 void stub_clear() { std::lock_guard<std::mutex> g(mu); records.clear(); }
+
+// another thread gives an option one value and the other in turn, as fast as it can, until stub_turn_end
+void stub_turn(int (*set_option)(int, int), int option, int one, int other) {
+    turning = true;
+    turner = std::thread([=] {
+        while (turning) { set_option(option, one); set_option(option, other); }
+    });
+}
+void stub_turn_end() { turning = false; turner.join(); }
 
 void** __hipRegisterFatBinary(const void*) { static void* handle[1]; return handle; }
 void __hipUnregisterFatBinary(void**) {}

@@ -280,3 +280,33 @@ for M, N in ((1, 1), (600, 3400), (2048, 2048), (2600, 2048), (4096, 2048), (204
     assert small == [True, True, True, False, False, False, False, True]
     assert got[1][1][:2] == [10, 27] and got[4][1][:2] == [32, 8]
     assert not [w for _, _, w in got if w]
+
+
+def test_a_run_of_binary_layers_follows_a_launch_that_clears_its_marks(host):
+    """Whatever another thread does to the options while a forward pass chooses its kernels: a run in one launch comes only behind a
+    kernel that clears what the run trusts (such kernels take a Clear), never behind the slab kernel, which does not."""
+    runs, uncleared = host("""
+G, S = bnn.BNN_ACT_SIGMOID, bnn.BNN_ACT_SIGN
+def network(N):
+    dims, acts = (440, 600) + (N,) * 6, (G,) + (S,) * 6
+    return bnn.make_layer_array([dict(K=dims[l], N=dims[l + 1], act=acts[l], word_bits=32, x_is_binary=int(l > 1), w_is_real=0,
+                                      Wp=B + l * 0x10000000, scale=C, bias=C) for l in range(7)])
+stub.stub_turn.argtypes = [ctypes.c_void_p] + [ctypes.c_int] * 3
+set_option = ctypes.cast(bnn.binding._lib.bnn_set_option, ctypes.c_void_p)
+runs = uncleared = 0
+for M, N in ((64, 64), (200, 512)):
+    for option, one, other in ((bnn.BNN_OPT_REALX_SIGN_MFMA, 2, 1), (bnn.BNN_OPT_STREAM_MAX_FRAMES, 0, 64)):
+        arr = network(N)
+        size = bnn.bnn_forward_workspace_bytes(arr, 7, M)
+        stub.stub_turn(set_option, option, one, other)
+        for _ in range(1000):
+            bnn.bnn_forward(arr, 7, A, M, D, E, size, 0)
+            kernels = [l["kernel"] for l in launches()]
+            for before, k in zip(kernels, kernels[1:]):
+                if "few_chain_kernel" in k or "hidden_run_kernel" in k:
+                    runs += 1
+                    uncleared += "Clear" not in before
+        stub.stub_turn_end()
+result = [runs, uncleared]
+""")
+    assert runs > 100 and uncleared == 0
