@@ -30,6 +30,10 @@ struct CoopLsm {
     int spin_limit;           // polls of the flags before a workgroup gives up
 };
 
+// The XCD that the wave runs on (bits 0..3 of hardware register 20, HW_REG_XCC_ID) and 1: what a workgroup marks data with that lies in
+// its XCD's L2, so that whoever runs on another one does not take the mark for its own.  Never 0.
+__device__ __forceinline__ uint32_t xcd_mark() { return (uint32_t)__builtin_amdgcn_s_getreg(20 | 3 << 11) + 1u; }
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
 typedef int i32x4m __attribute__((ext_vector_type(4)));

@@ -14,7 +14,11 @@
 //     layers' weights into the L2.
 // No wave depends on another one being on the chip: a wave that has polled in vain `spins` times works out what is missing by itself, from
 // the first layer on if need be, and every word has one possible value, so it makes no difference who publishes
-// it.  That also covers workgroups of one group on different XCDs, which would not see each other's words.
+// it.  That also covers workgroups of one group on different XCDs, which would not see each other's words, or later.  A word carries
+// its mark, so it is complete wherever it is seen.  The last layer's pre-activations are stored apart from their marks, and of two lines
+// in another XCD's L2 the mark's may be the first to reach memory: such a mark is the number of the writer's XCD (xcd_mark) and counts
+// on that XCD only, whose L2 has the pre-activations since the store was acknowledged.  (On others: worked out again, the same numbers.)
+// Only the speed rests on the order in which workgroups go round the XCDs.
 // The marks have to be clear when the launch starts: the launch before it, which the first layer reads from, clears them.
 //
 // Measured: at few_chain_layers in bnn_api.hip.
@@ -36,7 +40,8 @@ constexpr int kFewMaxWords = 128, kFewMaxClasses = 32 * kFewMaxWords;   // ... a
 struct FewLayer {
     const uint32_t* W;          // [N][w32]
     const float *scale, *bias;  // nullptr: 1 and 0
-    uint64_t* words;            // [M][LD], the last layer's [M][kFewMaxWords]: bits 31..0 a word of output bits, bit 32 the mark
+    uint64_t* words;            // [M][LD], the last layer's [M][kFewMaxWords]: bits 31..0 a word of output bits
+                                // (last layer: xcd_mark), bit 32 the mark
     int K, N, w32;
     int zero_one;               // input bits read as 0/1 instead of -1/+1
     // ceil(N / 32) blocks of 32 outputs; a wave takes one of them for f of the group's frames, so that every wave of the group has
@@ -113,6 +118,8 @@ __device__ __forceinline__ uint64_t few_published(const uint64_t* words, uint32_
 __device__ __forceinline__ void few_publish(uint64_t* words, uint32_t at, uint32_t word) {
     __hip_atomic_store(global_at<uint64_t>(words, 8u * at), kFewMark | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+// Is this word published?  closing: of the last layer, on this XCD.
+__device__ __forceinline__ bool few_there(uint64_t v, bool closing) { return closing ? v == (kFewMark | xcd_mark()) : (v & kFewMark) != 0; }
 // A wave's lanes that parted meet again here, not at the next turn of a loop: there the compiler would take what a wave has one of
 // (layer, pointers) for values per lane.
 __device__ __forceinline__ void few_join() { __builtin_amdgcn_wave_barrier(); }
@@ -230,7 +237,7 @@ __device__ __forceinline__ void few_finish(FewWeights<NR, VEC>& r, const FewArgs
         }
     } else if (lsm) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // in the L2 before the mark is
-        if (lane < nf) few_publish(L.words, (uint32_t)((m0 + lane) * kFewMaxWords + b), 0u);
+        if (lane < nf) few_publish(L.words, (uint32_t)((m0 + lane) * kFewMaxWords + b), xcd_mark());
     }
     few_join();
 }
@@ -257,15 +264,17 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
     uint64_t missing_lo = 0, missing_hi = 0;   // blocks of the layer that are not there
     auto look = [&](int layer, uint32_t* to) {
         const FewLayer& L = a.layer[layer];
-        const int ld = layer == a.layers - 1 ? kFewMaxWords : LD, total = nf * ld;
+        const bool closing = layer == a.layers - 1;
+        const int ld = closing ? kFewMaxWords : LD, total = nf * ld;
         missing_lo = missing_hi = 0;
         for (int base = 0; base < total; base += kWave) {
             const int e = base + lane, c = e & (ld - 1);
-            uint64_t v = kFewMark;
-            if (e < total && c < L.blocks) v = few_published(L.words, (uint32_t)(m0 * ld + e));
+            const bool wanted = e < total && c < L.blocks;
+            uint64_t v = 0;
+            if (wanted) v = few_published(L.words, (uint32_t)(m0 * ld + e));
             if (e < total) to[e] = (uint32_t)v;
             few_join();
-            uint64_t not_there = __ballot(!(v & kFewMark));
+            uint64_t not_there = __ballot(wanted && !few_there(v, closing));
             if (ld <= 32) not_there |= not_there >> 32;   // several frames in a ballot
             if (ld <= 16) not_there |= not_there >> 16;
             if (ld < 64) not_there &= ((uint64_t)1 << ld) - 1;
@@ -285,9 +294,9 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
         for (int i = 0; i < L.blocks; ++i) {
             const int b = first + i < L.blocks ? first + i : first + i - L.blocks;
             if (!((b < 64 ? missing_lo >> b : missing_hi >> (b - 64)) & 1)) continue;
-            uint64_t v = kFewMark;
+            uint64_t v = 0;
             if (lane < nf) v = few_published(L.words, (uint32_t)((m0 + lane) * (closing ? kFewMaxWords : LD) + b));
-            if (!__all((v & kFewMark) != 0)) {
+            if (!__all(lane >= nf || few_there(v, closing))) {
                 FewWeights<NR, VEC> r;
                 r.request(L, 32 * b, lane);
                 if (closing) {
@@ -441,10 +450,11 @@ __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel
         const int m = first + row;
         bool there = false;
         for (int spin = 0; !there && spin <= (in_time ? a.spins : 8); ++spin) {
-            uint64_t v0 = kFewMark, v1 = kFewMark;
+            const uint64_t mark = kFewMark | xcd_mark();
+            uint64_t v0 = mark, v1 = mark;
             if (lane3 < last.blocks) v0 = few_published(last.words, (uint32_t)(m * kFewMaxWords + lane3));
             if (lane3 + kWave < last.blocks) v1 = few_published(last.words, (uint32_t)(m * kFewMaxWords + lane3 + kWave));
-            there = __all((v0 & v1 & kFewMark) != 0);
+            there = __all(v0 == mark && v1 == mark);
         }
         if (!there) few_catch_up<NR, VEC>(a, a.layers, m, 1, u, lane3, x, y);
         few_log_softmax_row(a.z + (size_t)m * a.z_ld, static_cast<float*>(a.Y) + (size_t)m * last.N, last.N, red, wave);

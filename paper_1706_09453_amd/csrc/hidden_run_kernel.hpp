@@ -11,7 +11,10 @@
 // mfma_kernels.hpp; 0/1 inputs are multiplied as -1/+1 and put right by the weights' popcounts, sum hw = (sum aw + sum w) / 2.
 // Nobody depends on a workgroup that is not on the chip: a wave whose wait runs out works out the missing blocks of its crew's frames
 // itself, from the last complete layer on; a word has one possible value, so it does not matter who writes it.  Every layer has
-// memory of its own, so a late writer disturbs no one.  The flags are cleared by the launch before.
+// memory of its own, so a late writer disturbs no one.  The flags are cleared by the launch before.  Words and flag lie on different
+// lines: in the XCD of the workgroup that wrote them the words are in the L2 before the flag is, in another one a flag may come first.
+// So a flag is the number of the writer's XCD (xcd_mark) and counts on that XCD only; on another the block is worked out again, to the
+// same words.  Only the speed rests on the order in which workgroups go round the XCDs.
 // What bounds it where there are many frames: one wave per SIMD, which expands 16 NF rows of weights once per layer and crew, 450
 // vector instructions at 2048 units, beside 64 MFMAs per fragment of frames.  Eight crews, two waves per SIMD, pull the weights twice as
 // often through the L1: 2048 units, 1000 frames 57.6 -> 64.3 us a pass (1024 units, 3000 frames 70.2 -> 65.9, which the tiled kernels
@@ -35,7 +38,7 @@ struct RunLayer {
 struct RunArgs {
     RunLayer layer[kRunMaxLayers];
     const uint32_t* X;   // [M][N / 32]
-    uint32_t* flags;     // [layers][kFewGroups][kRunCrews][kFewSlots]
+    uint32_t* flags;     // [layers][kFewGroups][kRunCrews][kFewSlots]: 0, or the xcd_mark of who has done it
     int layers, M, F, spins;   // F: frames of a group, a multiple of 16
 };
 
@@ -158,12 +161,12 @@ __global__ __launch_bounds__(kRunThreads, NF == 4 ? 3 : 4) void hidden_run_kerne
     const int n0 = slot * 16 * NF;
     uint32_t* const flags = a.flags + (group * kRunCrews + crew) * kFewSlots;   // + layer * kRunFlags
     auto done = [&](int layer, int who) {   // (one lane) this crew's frames through block `who` of a layer; its words are in the L2 before
-        __hip_atomic_store(global_at<uint32_t>(flags, 4u * (uint32_t)(layer * kRunFlags + who)), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_store(global_at<uint32_t>(flags, 4u * (uint32_t)(layer * kRunFlags + who)), xcd_mark(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     };
-    auto blocks_done = [&](int layer, int lane) -> uint32_t {   // a bit per block; past the L1
+    auto blocks_done = [&](int layer, int lane) -> uint32_t {   // a bit per block that is done on this XCD; past the L1
         uint32_t f = 0;
         if (lane < kFewSlots) f = __hip_atomic_load(global_at<const uint32_t>(flags, 4u * (uint32_t)(layer * kRunFlags + lane)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return (uint32_t)__ballot(f != 0);
+        return (uint32_t)__ballot(f == xcd_mark());
     };
     RunLayer L = a.layer[0], next = L;
     const uint32_t* X = a.X;

@@ -294,6 +294,61 @@ def test_run_of_binary_layers_in_one_launch(G, bnn, M, dims, last, zero_one, wb,
         bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
 
 
+def _sign_net(G, bnn, M, dims, last="logsoftmax", wb=32, zero_one=False, seed=0):
+    """A network of Sign layers (the last one with act `last`) on the GPU: its descriptors and what they point to."""
+    g = torch.Generator().manual_seed(seed + M + len(dims) + dims[-1])
+    n = len(dims) - 1
+    descs, keep = [], []
+    for l, (K, N) in enumerate(zip(dims, dims[1:])):
+        Wp, _ = G.pack_weights(torch.randn(N, K, generator=g).cuda(), wb)
+        scale, bias = (torch.rand(N, generator=g) / K ** 0.5).cuda(), torch.randn(N, generator=g).cuda() * 0.1
+        keep += [Wp, scale, bias]
+        descs.append(dict(K=K, N=N, act=bnn.ACT_BY_NAME["sign" if l < n - 1 else last], word_bits=wb,
+                          x_is_binary=0 if l == 0 else 2 if zero_one else 1, Wp=G.ptr(Wp), scale=G.ptr(scale), bias=G.ptr(bias)))
+    return descs, keep
+
+
+def _run_scratch_bytes(bnn, descs, first, n, M):
+    """Scratch of a run of n binary layers from `first` on: the bytes of its marks, and all of it."""
+    up = lambda v: (v + 255) // 256 * 256
+    if M > 64:
+        marks = n * 4096
+        return marks, marks + (n - 1) * up(M * descs[first]["N"] // 8)
+    words, last = 16, descs[first + n - 1]
+    while any(bnn.bnn_packed_words(d["K"], d["word_bits"]) * d["word_bits"] // 32 > words for d in descs[first:first + n]):
+        words *= 2
+    lsm = last["act"] == bnn.BNN_ACT_LOGSOFTMAX
+    marks = up(8 * M * ((n - 1) * words + 128 * lsm))
+    return marks, marks + up(M * (last["N"] + last["N"] % 2) * 4) * lsm
+
+
+@pytest.mark.parametrize("M,dims", [(64, (40, 512, 512, 1003)), (64, (40, 512, 512, 512, 4096)), (512, (40, 512, 512, 512, 70)), (333, (40, 2048, 2048, 2048, 70))])
+def test_marks_of_a_run_name_the_xcd_of_their_writer(G, bnn, M, dims):
+    """What lies apart from its mark (pre-activations, rows of bits) is safe to read only on the XCD that wrote both: every mark is
+    that XCD's number and 1, and the groups of frames, one to an XCD, have different ones."""
+    descs, keep = _sign_net(G, bnn, M, dims)
+    layers, n = bnn.make_layer_array(descs), len(descs)
+    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    out, X = G.out_tensor(M, dims[-1], descs[-1]["act"], 32), torch.randn(M, dims[0]).cuda()
+    with _streaming(bnn):
+        bnn.bnn_forward(layers, n, G.ptr(X), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
+    run = n - 1 if M <= 64 else n - 2
+    marks, total = _run_scratch_bytes(bnn, descs, 1, run, M)
+    got = ws[nbytes - total:nbytes - total + marks].cpu().view(torch.int32).numpy()
+    if M <= 64:
+        words = got[:2 * M * ((run - 1) * 16 + 128)][2 * M * (run - 1) * 16:].reshape(M, 128, 2)[:, :(dims[-1] + 31) // 32]
+        assert (words[:, :, 1] == 1).all()
+        xcds = words[:, :, 0]
+    else:
+        flags = got.reshape(run, 8, 4, 32)
+        per_group = (M + 127) // 128 * 16
+        has = np.array([[16 * crew < min(per_group, M - group * per_group) for crew in range(4)] for group in range(8)])
+        assert (flags[:, ~has] == 0).all()
+        xcds = flags[:, has]
+    assert xcds.min() >= 1 and xcds.max() <= 16 and len(np.unique(xcds)) > 1
+
+
 def test_streaming_forward_equals_large_batch_forward(G, bnn, oracle):
     """The same 48 frames through the streaming kernels (16 at a time) and through the large-batch kernels: the
     log-posteriors agree within the tolerance of the two log-Softmax kernels, their arg max exactly."""
