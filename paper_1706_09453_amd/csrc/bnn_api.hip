@@ -148,12 +148,12 @@ void launch_f32_sums(const ChainArgs& a, int act, bool few) {
 // 0, and memory that it pulls into the L2s if it can.  Whoever launches a kernel that clears sets `cleared`; without it there is no run,
 // whichever kernel the options of the moment have chosen.
 struct Front {
-    Clear clear{nullptr, 0};
+    Clear clear{};
     Pull pull{};
     bool cleared = false;
 };
 Clear clear_for(Front* front, int act) {
-    if (!front || act != BNN_ACT_SIGN) return {nullptr, 0};   // (only their Sign instances clear)
+    if (!front || act != BNN_ACT_SIGN) return {};   // (only their Sign instances clear)
     front->cleared = true;
     return front->clear;
 }
@@ -162,24 +162,26 @@ template <int TM, bool BCAST>
 void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, const float* bias, int M, int K, int N,
                        int w32, int act, void* Y, int yw32, hipStream_t st, Front* front) {
     dim3 grid((M + TM - 1) / TM, (N + 255) / 256), block(256);
-    Pull pull = front ? front->pull : Pull{};
-    const Clear clear = clear_for(front, act);
-    if (pull.layers > 0) {
-        pull.from = (int)(grid.x * grid.y);
-        grid.y += (8 * kPullGroups + grid.x - 1) / grid.x;
+    if constexpr (TM == 1) {   // (what batches of a few frames take)
+        if (front && act == BNN_ACT_SIGN) {
+            const Clear clear = cleared_by(clear_for(front, act), grid);
+            if (front->pull.layers > 0) grid.y += (8 * kPullGroups + grid.x - 1) / grid.x;
+            realx_valu_kernel<TM, ACT_SIGN, BCAST, Clear, Pull><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, front->pull);
+            return;
+        }
     }
     switch (act) {
         case BNN_ACT_SIGN:
-            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
+            realx_valu_kernel<TM, ACT_SIGN, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         case BNN_ACT_HARDTANH:
-            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
+            realx_valu_kernel<TM, ACT_HARDTANH, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         case BNN_ACT_SIGMOID:
-            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
+            realx_valu_kernel<TM, ACT_SIGMOID, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
         default:
-            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, pull);
+            realx_valu_kernel<TM, ACT_LINEAR, BCAST><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32);
             break;
     }
 }
@@ -623,7 +625,7 @@ int run_realx_sign_mfma(const float* X, const void* Wp, const float* scale, cons
     constexpr unsigned most = (unsigned)realx_dynamic_lds(kRealxMfmaMaxK, (kRealxMfmaMaxK + 63) / 64 * 64, (kRealxMfmaMaxK + 63) / 64 * 2, kRealxMaxNB);
     const bool vec16 = aligned(Wp, 16);   // chunks start at multiples of 512 rows: 16-byte aligned whenever the matrix is
     if (!allow_lds(vec16 ? &realx_sign_fused_kernel<true> : &realx_sign_fused_kernel<false>, most, allowed[vec16])) return BNN_EDEVICE;
-    const Clear clear = clear_for(front, BNN_ACT_SIGN);
+    const Clear clear = cleared_by(clear_for(front, BNN_ACT_SIGN), grid);
     if (vec16)
         realx_sign_fused_kernel<true><<<grid, block, lds, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, kpad,
                                                                Ni, nb, w32, static_cast<uint32_t*>(Y), yw32, clear);
@@ -789,8 +791,7 @@ I8GemmScratch i8_gemm_scratch(int64_t M, int64_t K, int64_t N, int act) {
 // two waves per SIMD (4096 x 6144 43 -> 33 us against reading the frame twice).  Ragged frames need a load per element and are read twice.
 template <int D>
 void launch_quantize(const float* X, int M, int K, int kpad, int qbits, int8_t* planes, void* meta, const ByteRows& weights, hipStream_t st) {
-    const int64_t byte_blocks = (weights.N * (kpad / 16) + 255) / 256;
-    const dim3 grid((unsigned)(((int64_t)M + 3) / 4 + (byte_blocks < 16384 ? byte_blocks : 16384)));
+    const dim3 grid((unsigned)(((int64_t)M + 3) / 4 + byte_blocks(weights.N, kpad)));
     const bool vec = (K & 3) == 0 && aligned(X, 16);
     if (!vec) realx_quantize_nat_kernel<D, false, 0><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
     else if (kpad <= 512) realx_quantize_nat_kernel<D, true, 2><<<grid, 256, 0, st>>>(X, M, K, kpad, qbits, planes, meta, weights);
@@ -838,8 +839,8 @@ int launch_realx_i8_gemm(const float* X, const void* Wp, const float* scale, con
     if (rc != BNN_OK) return rc;
     const int recs = (Ni + kUndecidedOutputs - 1) / kUndecidedOutputs;
     if (D == 3) {
-        const Clear clear = clear_for(front, BNN_ACT_SIGN);
         const unsigned int rg = (unsigned int)((Mi + kResolveFrames - 1) / kResolveFrames);
+        const Clear clear = cleared_by(clear_for(front, BNN_ACT_SIGN), dim3(rg));
         if ((Ki & 3) == 0 && aligned(X, 16))
             realx_resolve_rows_kernel<true><<<rg, kResolveThreads, 0, st>>>(X, static_cast<const uint32_t*>(Wp), scale, bias, Mi, Ki, w32,
                                                                           undecided, recs, static_cast<uint32_t*>(Y), yw32, clear);
@@ -1602,7 +1603,7 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
                 if (!streaming && !roomy && !(l == 0 && realx_sign_mfma_applies(d))) run = 0;   // (the layer in front runs on other kernels)
                 run_out = output(o, l + run);
                 if (run && (streaming ? few_chain_runs : hidden_run_runs)(layers, l + 1, run, M, run_out))
-                    front.clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16)};
+                    front.clear = {reinterpret_cast<uint4*>(few), (int)((streaming ? few_chain_scratch(layers, l + 1, run, M).words : hidden_run_scratch(d.N, run, M).flags) / 16), 0, 0};
                 else
                     run = 0;
                 if (run && streaming) front.pull = few_chain_pull(layers, l + 1, run, M);

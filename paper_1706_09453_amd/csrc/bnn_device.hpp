@@ -68,33 +68,47 @@ __device__ __forceinline__ void xcd_tile(int& tm, int& tn) {
     tn = two ? in >> 1 : in;
 }
 
-// 16-byte pieces that a launch sets to 0 for the launch behind it (few_chain_kernel.hpp)
+// 16-byte pieces that a launch sets to 0 for the launch behind it (few_chain_kernel.hpp): by its first `blocks` workgroups, `gx` of them
+// in x.  (Both are here and not read from the grid: with more than 112 bytes of arguments, what the runtime adds for the grid's size
+// among them, a launch takes the host 3.5 us instead of 2.9.)
 struct Clear {
     uint4* at;
-    int pieces;
+    int pieces, gx, blocks;
 };
-__device__ __forceinline__ void clear_pieces(const Clear& c, int blocks) {   // by the launch's first `blocks` workgroups
-    for (int i = (int)((blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x); i < c.pieces; i += blocks * (int)blockDim.x) c.at[i] = make_uint4(0u, 0u, 0u, 0u);
+template <int THREADS>
+__device__ __forceinline__ void clear_pieces(const Clear& c) {
+    const uint32_t block = blockIdx.y * (uint32_t)c.gx + blockIdx.x;
+    for (uint32_t i = block * (uint32_t)THREADS + threadIdx.x; i < (uint32_t)c.pieces; i += (uint32_t)c.blocks * (uint32_t)THREADS) c.at[i] = make_uint4(0u, 0u, 0u, 0u);
 }
-__device__ __forceinline__ void clear_pieces(const Clear& c) { clear_pieces(c, (int)(gridDim.x * gridDim.y)); }
 
-// Memory that a launch's workgroups from number `from` on pull into the L2s of the first `xcds` XCDs, for the launch behind it
+// Memory that a launch's workgroups behind those of Clear pull into the L2s of the first `xcds` XCDs, for the launch behind it
 // (few_chain_kernel.hpp): 32 of them on each XCD, workgroups going round the XCDs.  A first layer of few frames leaves most of the chip idle for
 // 5 to 15 us: one frame through six layers of 2048 units 20.2 -> 19.3 us a pass, 16 frames of the mixed network 45.4 -> 44.3.
 constexpr int kPullLayers = 16, kPullGroups = 32;
 struct Pull {
     const char* at[kPullLayers];
     uint32_t bytes[kPullLayers];
-    int layers, xcds, from;
+    int layers, xcds;
 };
-__device__ __forceinline__ void pull_memory(const Pull& p, int block, int thread) {
+__device__ __forceinline__ void pull_memory(const Pull& p, int block, int from, int thread) {
     if ((block & 7) >= p.xcds) return;
-    const uint32_t first = (uint32_t)((block - p.from) >> 3) * 256u + (uint32_t)thread;
+    const uint32_t first = (uint32_t)((block - from) >> 3) * 256u + (uint32_t)thread;
     for (int j = 0; j < p.layers; ++j)
         for (uint32_t at = first * 128u; at < p.bytes[j]; at += kPullGroups * 256u * 128u) {
             const uint32_t t = *reinterpret_cast<const uint32_t*>(p.at[j] + at);
             asm volatile("" ::"v"(t));
         }
+}
+
+// Both, in front of a kernel of 256 threads.  false: this workgroup has pulled, there is nothing else for it to do.
+__device__ __forceinline__ bool front_of_run(const Clear& c, const Pull& p) {
+    const int block = (int)(blockIdx.y * (uint32_t)c.gx + blockIdx.x);
+    if (block >= c.blocks) {
+        pull_memory(p, block, c.blocks, (int)threadIdx.x);
+        return false;
+    }
+    clear_pieces<256>(c);
+    return true;
 }
 
 // Eq. 3 of the paper: +1 exactly when v > 0 (0, -0 and NaN give -1, i.e. bit 0).

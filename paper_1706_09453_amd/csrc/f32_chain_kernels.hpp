@@ -45,7 +45,7 @@ template <int FM, int FN, int WR, int KC, int ACT, bool WREAL, bool VEC, bool SK
 __global__ __launch_bounds__(256) void f32_chain_kernel(const float* __restrict__ X, const void* __restrict__ Wv,
                                                         const float* __restrict__ scale, const float* __restrict__ bias, int M, int K,
                                                         int N, int w32, void* __restrict__ Y, int yw32, Clear clear) {
-    if constexpr (ACT == ACT_SIGN) clear_pieces(clear);
+    if constexpr (ACT == ACT_SIGN) clear_pieces<256>(clear);
     constexpr int WC = 4 / WR, TM = 16 * FM * WR, TN = 16 * FN * WC, LD = KC + 4;
     constexpr int XPR = KC / 4, WPR = WREAL ? KC / 4 : KC / 16;   // pieces per row and chunk: 4 numbers, or 16 weight bits
     constexpr int NPX = TM * XPR / 256, NPW = TN * WPR / 256;      // pieces per thread

@@ -18,7 +18,7 @@ void launch_chain_tile(const ChainArgs& a) {
     }
     const int cols = ACT == ACT_SIGN ? a.yw32 * 32 : a.N;   // Sign: every word of a row of Y is written
     const dim3 grid((unsigned)((a.M + TM - 1) / TM), (unsigned)((cols + TN - 1) / TN));
-    f32_chain_kernel<FM, FN, WR, KC, ACT, WREAL, VEC, SKIP><<<grid, 256, lds, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, a.Y, a.yw32, a.clear);
+    f32_chain_kernel<FM, FN, WR, KC, ACT, WREAL, VEC, SKIP><<<grid, 256, lds, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, a.Y, a.yw32, cleared_by(a.clear, grid));
 }
 // Workgroup tile: the one whose fullest CU has the least to multiply, counting what a tile of that size loses to its
 // memory instructions (rates measured at 4096 x 2048 x 2048: 132 TFLOP/s with 256 x 128 tiles, 129 with 128 x 128, 124

@@ -28,6 +28,13 @@ bool allow_lds(Kernel kernel, unsigned bytes, std::atomic<uint64_t>& allowed) {
     return true;
 }
 
+// A launch of this grid clears.
+inline Clear cleared_by(Clear c, dim3 grid) {
+    c.gx = (int)grid.x;
+    c.blocks = (int)(grid.x * grid.y);
+    return c;
+}
+
 // Ascending-k fp32 sums on the matrix cores (f32_chain_launch.hpp); arguments already checked.
 struct ChainArgs {
     const float* X;
@@ -37,7 +44,7 @@ struct ChainArgs {
     void* Y;
     int yw32;
     hipStream_t st;
-    Clear clear = {nullptr, 0};   // Sign layers: memory that the launch sets to 0
+    Clear clear{};   // Sign layers: memory that the launch sets to 0
 };
 void launch_chain_bits(const ChainArgs& a, int act);   // W packed bits
 void launch_chain_real(const ChainArgs& a, int act);   // W fp32

@@ -94,7 +94,7 @@ __global__ __launch_bounds__(kRealxThreads) void realx_sign_fused_kernel(const f
                                                                const float* __restrict__ scale, const float* __restrict__ bias,
                                                                int M, int K, int kpad, int N, int NB, int w32,
                                                                uint32_t* __restrict__ Y, int yw32, Clear clear) {
-    clear_pieces(clear);
+    clear_pieces<kRealxThreads>(clear);
     constexpr int WN = 4;   // 16-output fragments per wave and chunk
     extern __shared__ __attribute__((aligned(16))) int8_t lds_raw[];
     __shared__ RowMeta meta[kRealxBM];

@@ -51,14 +51,19 @@ __host__ __device__ inline int i8_kpad(int K) { return (K + kI8KStep - 1) / kI8K
 constexpr int kUndecidedOutputs = 128;
 constexpr int kUndecidedRecord = kUndecidedOutputs / 8;
 
-// B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k; block `block` of `blocks` of 256 threads.
+// B[n][k] = bit k of weight row n as a byte (0 past K).  One thread per 16 k; block `block` of byte_blocks() of 256 threads.
 struct ByteRows {
     const uint32_t* Wp;
     int8_t* B;
     int64_t N;
     int w32;
 };
-__device__ __forceinline__ void expand_bytes(const ByteRows& b, int K, int kpad, int block, int blocks) {
+__host__ __device__ inline int byte_blocks(int64_t N, int kpad) {
+    const int64_t blocks = (N * (kpad / 16) + 255) / 256;
+    return (int)(blocks < 16384 ? blocks : 16384);
+}
+__device__ __forceinline__ void expand_bytes(const ByteRows& b, int K, int kpad, int block) {
+    const int blocks = byte_blocks(b.N, kpad);
     const int per_row = kpad >> 4;
     const int64_t total = b.N * per_row;
     for (int64_t i = (int64_t)block * 256 + threadIdx.x; i < total; i += (int64_t)blocks * 256) {
@@ -88,13 +93,13 @@ __device__ __forceinline__ uint32_t negate_digits(uint32_t d) { return (0x808080
 // 4096 frames of 2048 15.5 -> 12.2 us, 2048 of 4096 26.2 -> 13.0 (5.2 TB/s).
 // The weights' bytes are made in the same launch, by the workgroups behind those of the frames: neither waits for the other, and a launch
 // of their own cost 2 to 3 us (600 frames through the mixed network, two such calls 141.7 -> 139.3 us; a training step, eleven, 1971 -> 1941).
-// Grid: ceil(M / 4) workgroups of 256 threads, then those of expand_bytes.
+// Grid: ceil(M / 4) workgroups of 256 threads, then byte_blocks().
 template <int D, bool VEC, int NG>
 __global__ __launch_bounds__(256) void realx_quantize_nat_kernel(const float* __restrict__ X, int M, int K, int kpad, int qbits,
                                                                  int8_t* __restrict__ planes, void* __restrict__ meta_out, ByteRows weights) {
     const int frame_blocks = (int)(((int64_t)M + 3) >> 2);
     if ((int)blockIdx.x >= frame_blocks) {
-        expand_bytes(weights, K, kpad, (int)blockIdx.x - frame_blocks, (int)gridDim.x - frame_blocks);
+        expand_bytes(weights, K, kpad, (int)blockIdx.x - frame_blocks);
         return;
     }
     static_assert(D == 3 || D == 4, "three digits for Sign layers, four in front of the log-Softmax");
@@ -559,7 +564,7 @@ __global__ __launch_bounds__(kResolveThreads) void realx_resolve_rows_kernel(con
                                                                            const float* __restrict__ scale, const float* __restrict__ bias,
                                                                            int M, int K, int w32, const unsigned char* __restrict__ undecided,
                                                                            int recs, uint32_t* __restrict__ Y, int yw32, Clear clear) {
-    clear_pieces(clear);
+    clear_pieces<kResolveThreads>(clear);
     __shared__ __attribute__((aligned(16))) float xs[2][kResolveFrames][kResolveLd];
     __shared__ u32x4 ws[2][kResolveThreads][2];   // a lane's eight weight words of a slab
     __shared__ unsigned int ent[kResolveCap];   // (frame of the workgroup) << 28 | output

@@ -89,14 +89,14 @@ __device__ __forceinline__ void fmac_row_bcast(float& acc, float x, float w) {
 //   !BCAST x[m][k] is a wave-uniform load and arrives through the scalar cache as an SGPR operand (61 % of the
 //          4-cycle VALU issue rate measured; BCAST reaches 73 % with TM = 16, where 16 of 18 instructions are fmas).
 // Grid: x = ceil(M / TM), y = ceil(N / 256) (4 waves x 64 outputs).
-template <int TM, int ACT, bool BCAST>
+// Front: nothing, or the Clear and the Pull of a launch in front of a run of binary layers, which the others' argument lists do not carry
+// (see Clear).
+template <int TM, int ACT, bool BCAST, class... Front>
 __global__ __launch_bounds__(256) void realx_valu_kernel(const float* __restrict__ X, const uint32_t* __restrict__ Wp,
                                                          const float* __restrict__ scale, const float* __restrict__ bias,
-                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32, Clear clear, Pull pull) {
-    if constexpr (ACT == ACT_SIGN) {
-        const int block = (int)(blockIdx.y * gridDim.x + blockIdx.x);
-        if (pull.layers > 0 && block >= pull.from) return pull_memory(pull, block, (int)threadIdx.x);
-        clear_pieces(clear, pull.layers > 0 ? pull.from : (int)(gridDim.x * gridDim.y));
+                                                         int M, int K, int N, int w32, void* __restrict__ Y, int yw32, Front... front) {
+    if constexpr (sizeof...(Front) > 0) {
+        if (!front_of_run(front...)) return;
     }
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = lane_id();
