@@ -150,7 +150,7 @@ void launch_f32_sums(const ChainArgs& a, int act, bool few) {
 struct Front {
     Clear clear{};
     Pull pull{};
-    bool cleared = false;
+    bool cleared = false, pulled = false;
 };
 Clear clear_for(Front* front, int act) {
     if (!front || act != BNN_ACT_SIGN) return {};   // (only their Sign instances clear)
@@ -166,6 +166,7 @@ void launch_realx_tm_b(const float* X, const uint32_t* Wp, const float* scale, c
         if (front && act == BNN_ACT_SIGN) {
             const Clear clear = cleared_by(clear_for(front, act), grid);
             if (front->pull.layers > 0) grid.y += (8 * kPullGroups + grid.x - 1) / grid.x;
+            front->pulled = true;
             realx_valu_kernel<TM, ACT_SIGN, BCAST, Clear, Pull><<<grid, block, 0, st>>>(X, Wp, scale, bias, M, K, N, w32, Y, yw32, clear, front->pull);
             return;
         }
@@ -1274,10 +1275,10 @@ BNN_EXPORT int bnn_semi_stochastic_binarize(float* w, const float* u, int64_t co
 
 // Runs of binary layers of a streaming batch in one launch (few_chain_kernel.hpp), inside bnn_forward: the layers from l on, as many
 // as bits pass between, behind a layer with real inputs or weights (whose launch clears the marks).  0: none.
-// Whole passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 1 frame 24.9 -> 13.2 us (512
-// units), 27.2 -> 13.5 (1024), 26.0 -> 17.1 (2048); 16 frames 26.1 -> 15.5 and 27.6 -> 19.7 (1024, 2048); 64 frames 29.0 -> 18.8
-// and 37.8 -> 29.2.  Rows that are no multiple of 16 bytes gain more, having no split of K over lanes otherwise (51 frames of 1344 units
-// 64.6 -> 33.8).  Wider layers stay apart: every XCD reads all weights here, and 4096 units are 2 MB a layer (6 layers, 32 frames
+// Whole passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 1 frame 25.5 -> 12.9 us (512
+// units), 25.4 -> 13.4 (1024), 27.1 -> 15.3 (2048); 16 frames 27.8 -> 15.5 and 27.3 -> 17.8 (1024, 2048); 64 frames 28.9 -> 18.3
+// and 37.3 -> 27.3.  Rows that are no multiple of 16 bytes gain more, having no split of K over lanes otherwise (51 frames of 1344 units
+// 64.5 -> 31.0).  Four streams at once: 16 frames 9.3 -> 5.8 and 13.0 -> 9.7, 64 frames 12.8 -> 7.5 and 20.4 -> 12.3.  Wider layers stay apart: every XCD reads all weights here, and 4096 units are 2 MB a layer (6 layers, 32 frames
 // 48.9 -> 45.5 us, but 1 frame 27.0 -> 28.0, 64 frames 56.7 -> 68.6), in registers that leave no room for a second launch beside
 // this one.  Two hidden layers alone gain nothing where their rows are whole pieces (1 frame, 3584 units 52.2 -> 54.2).
 static int few_chain_layers(const bnn_layer_desc* layers, int n_layers, int l, int64_t M) {
@@ -1334,7 +1335,9 @@ static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M
     if (last.act == BNN_ACT_LOGSOFTMAX && !aligned(Y, 16)) return false;
     return apart(layers, l, n, M, Y);
 }
-static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st) {
+// pulled: the launch in front has pulled the weights into the L2s.  Otherwise the run does, by workgroups of its own behind the others (64 frames
+// of 6 x 512 and 6 x 1024 units 17.5 -> 16.7 us and 20.4 -> 18.3 a pass), up to 1024 inputs (2048: 32 frames 22.2 without, 23.0 with).
+static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st, bool pulled) {
     const FewScratch s = few_chain_scratch(layers, l, n, M);
     const int nr = few_chain_pieces(layers, l, n);
     FewArgs a{};
@@ -1364,8 +1367,9 @@ static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void*
     a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
     auto go = [&](auto nrc) {
         constexpr int NR = decltype(nrc)::value;
-        if (vec) few_chain_kernel<NR, true><<<kFewGroups * kFewSlots, kFewThreads, 0, st>>>(a);
-        else few_chain_kernel<NR, false><<<kFewGroups * kFewSlots, kFewThreads, 0, st>>>(a);
+        const int grid = (NR < 4 && !pulled ? 2 : 1) * kFewGroups * kFewSlots;
+        if (vec) few_chain_kernel<NR, true><<<grid, kFewThreads, 0, st>>>(a);
+        else few_chain_kernel<NR, false><<<grid, kFewThreads, 0, st>>>(a);
     };
     if (nr == 1) go(std::integral_constant<int, 1>{});
     else if (nr == 2) go(std::integral_constant<int, 2>{});
@@ -1386,19 +1390,20 @@ static Pull few_chain_pull(const bnn_layer_desc* layers, int l, int n, int64_t M
 
 // Runs of equal Sign layers of a mid-size batch in one launch (hidden_run_kernel.hpp), inside bnn_forward: the layers from l on,
 // behind a real-input Sign layer whose last launch clears the flags.  0: none.
-// Whole passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 333 frames 42.2 -> 32.4 us (512
-// units), 47.0 -> 35.0 (1024), 49.8 -> 38.5 (1536), 54.9 -> 46.9 (2048); 1000 frames 44.6 -> 36.8 and 49.7 -> 41.6 (512, 1024).
-// Up to 1024 units to 2^21 outputs of a layer, where the tiles of one launch per layer make up for it: 3000 frames of 1024 units 71.1
-// and 70.2, 8192 of 512 93.8 and 99.8, but 2048 of 1024 62.1 and 55.6.  Wider layers while a wave's share is one fragment, 2048 units to
-// 384 frames: their registers leave little room for other launches beside this one, and with four batches in flight on four
-// streams each waits for workgroups that find no place (333 frames of 2048 units 35.6 -> 40.6 us a pass, 400 of 1536 35.1 -> 24.3, but
-// 500 of 2048 34.7 -> 55.7, alone 55.0 -> 49.7).
+// Passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 320 frames 42.0 -> 32.2 us (512
+// units), 47.1 -> 34.4 (1024), 49.8 -> 38.4 (1536); 128 of 2048 51.4 -> 39.3; 1000 frames 45.1 -> 36.9 and 50.2 -> 41.1 (512, 1024).
+// How many frames: alone, a run is faster far beyond these lines, but with as many batches in flight as the device has queues the chip is
+// full, and the more fragments a wave takes the more the tiles of one launch per layer win.  Alone, and a pass of four streams at once:
+// 1024 units, 1024 frames 49.6 -> 41.2 and 21.6 -> 20.0, 1152 55.2 -> 45.3 but 21.6 -> 26.2; 512 units, 2048 frames 53.0 -> 46.5 and
+// 22.7 -> 21.7, 3200 62.2 -> 56.0 but 32.6 -> 33.0 (eight layers, 100 outputs 22.5 -> 27.6); 1536 units, 320 frames 48.8 -> 37.7 and 17.2
+// -> 16.0, 384 48.6 -> 38.1 but 17.3 -> 18.2; 2048 units, 128 frames 50.6 -> 39.4 and 19.4 -> 16.4, 160 52.2 -> 42.5 but 20.5 -> 21.9, 333
+// 54.9 -> 47.0 but 21.5 -> 30.5.
 static int hidden_run_layers(const bnn_layer_desc* layers, int n_layers, int l, int64_t M) {
     if (l < 1 || l >= n_layers || M <= kFewMaxFrames) return 0;
     const bnn_layer_desc& before = layers[l - 1];
     if (before.x_is_binary || before.w_is_real || !(l == 1 && realx_sign_mfma_applies(before) ? true : realx_i8_gemm_applies(before, M))) return 0;
     const int64_t N = layers[l].N;
-    if (N % 512 != 0 || N > 2048 || (N <= 1024 ? M * N > ((int64_t)1 << 21) : M > (N <= 1536 ? 512 : 384))) return 0;
+    if (N % 512 != 0 || N > 2048 || (N <= 1024 ? M * N > ((int64_t)1 << 20) : M > (N <= 1536 ? 320 : 128))) return 0;
     int n = 0;
     while (l + n < n_layers && n < kRunMaxLayers && layers[l + n].x_is_binary && !layers[l + n].w_is_real && layers[l + n].act == BNN_ACT_SIGN &&
            layers[l + n].K == N && layers[l + n].N == N && aligned(layers[l + n].Wp, 16))
@@ -1436,7 +1441,7 @@ static int run_hidden_run(const bnn_layer_desc* layers, int l, int n, const void
     a.M = (int)M;
     a.F = 16 * (((int)M + 16 * kFewGroups - 1) / (16 * kFewGroups));
     a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
-    const int per_wave = (a.F / 16 + kRunCrews - 1) / kRunCrews, passes = (per_wave + 3) / 4, fm = (per_wave + passes - 1) / passes;
+    const int fm = (a.F / 16 + kRunCrews - 1) / kRunCrews;   // fragments per wave: 1 to 4 with 512 units, 1 or 2 with 1024, else 1
     auto go = [&](auto nfc, auto fmc) {
         hidden_run_kernel<decltype(nfc)::value, decltype(fmc)::value><<<kFewGroups * kFewSlots, kRunThreads, 0, st>>>(a);
     };
@@ -1444,14 +1449,12 @@ static int run_hidden_run(const bnn_layer_desc* layers, int l, int n, const void
     using I2 = std::integral_constant<int, 2>;
     using I3 = std::integral_constant<int, 3>;
     using I4 = std::integral_constant<int, 4>;
-    auto with_fm = [&](auto nfc) {
-        if (fm == 1) go(nfc, I1{});
-        else if (fm == 2) go(nfc, I2{});
-        else if (fm == 3) go(nfc, I3{});
-        else go(nfc, I4{});
-    };
-    if (N == 512) with_fm(I1{});
-    else if (N == 1024) with_fm(I2{});
+    if (N == 512 && fm == 1) go(I1{}, I1{});
+    else if (N == 512 && fm == 2) go(I1{}, I2{});
+    else if (N == 512 && fm == 3) go(I1{}, I3{});
+    else if (N == 512) go(I1{}, I4{});
+    else if (N == 1024 && fm == 1) go(I2{}, I1{});
+    else if (N == 1024) go(I2{}, I2{});
     else if (N == 1536) go(I3{}, I1{});
     else go(I4{}, I1{});
     return launch_status();
@@ -1656,7 +1659,8 @@ static int forward_run(const bnn_layer_desc* layers, int n_layers, const void* X
             if (rc != BNN_OK) return rc;
             in = o;
             if (front.cleared) {
-                rc = (M <= kFewMaxFrames ? run_few_chain : run_hidden_run)(layers, l + 1, run, in, M, run_out, few, st);
+                rc = M <= kFewMaxFrames ? run_few_chain(layers, l + 1, run, in, M, run_out, few, st, front.pulled)
+                                        : run_hidden_run(layers, l + 1, run, in, M, run_out, few, st);
                 if (rc != BNN_OK) return rc;
                 in = run_out;
                 l += run;

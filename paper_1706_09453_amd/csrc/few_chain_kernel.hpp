@@ -10,8 +10,7 @@
 //   * a word of 32 output bits leaves as one 64-bit store with a mark in its upper half, and whoever needs it polls the word itself:
 //     one way through the L2 and one back, no flag, no fence;
 //   * a wave is on its own: it takes 32 outputs x the frames of its group, no barrier inside a layer; weights do not depend on the
-//     layer before, so they are requested in front of the wait, and a wave of every workgroup that does nothing else pulls the later
-//     layers' weights into the L2.
+//     layer before, so they are requested in front of the wait.
 // No wave depends on another one being on the chip: a wave that has polled in vain `spins` times works out what is missing by itself, from
 // the first layer on if need be, and every word has one possible value, so it makes no difference who publishes
 // it.  That also covers workgroups of one group on different XCDs, which would not see each other's words, or later.  A word carries
@@ -19,6 +18,11 @@
 // in another XCD's L2 the mark's may be the first to reach memory: such a mark is the number of the writer's XCD (xcd_mark) and counts
 // on that XCD only, whose L2 has the pre-activations since the store was acknowledged.  (On others: worked out again, the same numbers.)
 // Only the speed rests on the order in which workgroups go round the XCDs.
+// Workgroups of four waves with at most 128 registers and 16 KB of LDS, so that four launches fit on every CU, as many as the device's
+// queues run at once.  Where fewer fit, runs on several streams each get a part of their workgroups, and all of them wait for the rest
+// until they give up: with a fifth wave and 168 registers, two to a CU, 16 frames of 6 x 1536 units on four streams at once took 33 us a
+// pass, 8.0 now (one launch per layer 10.0), 62 of 8 x 1088 in whole words of 32 73 and 15.1 (45).  (few_fresh keeps the
+// registers down; the code for waits that run out had most of them.)  Alone, the two 18.9 -> 16.5 us and 36.5 -> 34.8.
 // The marks have to be clear when the launch starts: the launch before it, which the first layer reads from, clears them.
 //
 // Measured: at few_chain_layers in bnn_api.hip.
@@ -33,7 +37,7 @@ namespace bnn {
 
 constexpr int kFewMaxLayers = 16, kFewMaxFrames = 64, kFewGroups = 8, kFewSlots = 32;   // (a group: 32 workgroups, one per CU of an XCD)
 constexpr int kFewGroupFrames = kFewMaxFrames / kFewGroups;
-constexpr int kFewWaves = 4, kFewThreads = (kFewWaves + 1) * kWave;
+constexpr int kFewWaves = 4, kFewThreads = kFewWaves * kWave;
 constexpr int kFewMaxInputWords = 64;   // layers of up to 2048 inputs ...
 constexpr int kFewMaxWords = 128, kFewMaxClasses = 32 * kFewMaxWords;   // ... and 4096 outputs
 
@@ -122,6 +126,11 @@ __device__ __forceinline__ void few_publish(uint64_t* words, uint32_t at, uint32
 __device__ __forceinline__ bool few_there(uint64_t v, bool closing) { return closing ? v == (kFewMark | xcd_mark()) : (v & kFewMark) != 0; }
 // A wave's lanes that parted meet again here, not at the next turn of a loop: there the compiler would take what a wave has one of
 // (layer, pointers) for values per lane.
+// The lane number, another one to the compiler each time: what follows from it is worked out where it is needed and not kept in registers.
+__device__ __forceinline__ int few_fresh(int lane) {
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
 __device__ __forceinline__ void few_join() { __builtin_amdgcn_wave_barrier(); }
 
 // The weights of a block of 32 outputs: this lane's pieces of outputs n0 + 2 o and n0 + 2 o + 1 (past N: the last one again).
@@ -258,12 +267,13 @@ __device__ __forceinline__ void few_fill(const FewArgs& a, uint32_t* x, int m0, 
 // published, every wave beginning at another one, so that the waves of a group share what workgroups that are not on the chip leave
 // undone.  Result in x.
 template <int NR, bool VEC>
-__device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m0, int nf, int wave_id, int lane, uint32_t* x, uint32_t* y) {
+__device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m0, int nf, int wave_id, int lane_in, uint32_t* x, uint32_t* y) {
     constexpr int LD = 16 * NR;
     uint32_t *in = x, *out = y;
     uint64_t missing_lo = 0, missing_hi = 0;   // blocks of the layer that are not there
     auto look = [&](int layer, uint32_t* to) {
         const FewLayer& L = a.layer[layer];
+        const int lane = few_fresh(lane_in);
         const bool closing = layer == a.layers - 1;
         const int ld = closing ? kFewMaxWords : LD, total = nf * ld;
         missing_lo = missing_hi = 0;
@@ -285,14 +295,14 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
     };
     int k = target - 1;
     while (k > 0 && !look(k - 1, in)) --k;
-    if (k == 0) few_fill<LD>(a, in, m0, nf, lane);
+    if (k == 0) few_fill<LD>(a, in, m0, nf, few_fresh(lane_in));
     for (; k < target; ++k) {
         const FewLayer& L = a.layer[k];
         const bool closing = k == a.layers - 1;
         look(k, out);
         const int first = wave_id % L.blocks;
         for (int i = 0; i < L.blocks; ++i) {
-            const int b = first + i < L.blocks ? first + i : first + i - L.blocks;
+            const int b = first + i < L.blocks ? first + i : first + i - L.blocks, lane = few_fresh(lane_in);
             if (!((b < 64 ? missing_lo >> b : missing_hi >> (b - 64)) & 1)) continue;
             uint64_t v = 0;
             if (lane < nf) v = few_published(L.words, (uint32_t)((m0 + lane) * (closing ? kFewMaxWords : LD) + b));
@@ -313,38 +323,35 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
         in = out, out = t;
     }
     if (in != x)
-        for (int e = lane; e < nf * LD; e += kWave) x[e] = in[e];
+        for (int e = few_fresh(lane_in); e < nf * LD; e += kWave) x[e] = in[e];
     few_join();
 }
 
-// A wave's share of pulling `bytes` into the XCD's L2, a load per 128 bytes.
-__device__ __forceinline__ void few_pull(const void* from, uint32_t bytes, int slot, int lane) {
-    constexpr uint32_t step = kFewSlots * kWave * 128;
-    const uint32_t last = bytes - 4u;
-    for (uint32_t at = (uint32_t)(slot * kWave + lane) * 128u; at <= last; at += 8 * step) {
-        uint32_t t = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t ^= *global_at<const uint32_t>(from, min(at + i * step, last & ~127u));
-        asm volatile("" ::"v"(t));
+// The later layers' weights into an XCD's L2, by kFewSlots workgroups, a load per 128 bytes.
+__device__ __forceinline__ void few_pull(const FewArgs& a, int slot) {
+    constexpr uint32_t step = kFewSlots * kFewThreads * 128u;
+    for (int j = 1; j < a.layers; ++j) {
+        const uint32_t bytes = (uint32_t)a.layer[j].N * (uint32_t)a.layer[j].w32 * 4u;
+        for (uint32_t at = ((uint32_t)slot * kFewThreads + threadIdx.x) * 128u; at < bytes; at += step) {
+            const uint32_t t = *global_at<const uint32_t>(a.layer[j].W, at);
+            asm volatile("" ::"v"(t));
+        }
     }
 }
 
-// Grid: kFewGroups * kFewSlots, kFewThreads threads, no dynamic LDS.
+// Grid: kFewGroups * kFewSlots, or twice that, where the second half pulls; kFewThreads threads, no dynamic LDS.
 template <int NR, bool VEC>
-__global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel(FewArgs a) {
+__global__ __launch_bounds__(kFewThreads, 4) void few_chain_kernel(FewArgs a) {
     constexpr int LD = 16 * NR;
     __shared__ __attribute__((aligned(16))) uint32_t bits[kFewWaves][2][kFewGroupFrames * LD];   // (the second: for few_catch_up)
     __shared__ float red[kFewWaves];
     const int group = (int)blockIdx.x & (kFewGroups - 1), slot = (int)blockIdx.x / kFewGroups;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = lane_id();
+    const int lane0 = lane_id();
     const int first = group * a.F, frames = min(a.F, a.M - first);
     if (frames <= 0) return;
 
-    if (wave == kFewWaves) {   // the later layers' weights into this XCD's L2, a load per 128 bytes
-        for (int j = 1; j < a.layers; ++j) few_pull(a.layer[j].W, (uint32_t)a.layer[j].N * (uint32_t)a.layer[j].w32 * 4u, slot, lane);
-        return;
-    }
+    if (slot >= kFewSlots) return few_pull(a, slot - kFewSlots);
     uint32_t *x = bits[wave][0], *y = bits[wave][1];
     const int u = wave * kFewSlots + slot;
 
@@ -393,7 +400,7 @@ __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel
     const uint64_t* before = nullptr;   // of the layer before: its words and how many a row has
     int before_blocks = 0, j = 0;
     for (; j < a.layers - 1; ++j) {
-        const int part = (u * L.per_block) >> 16, b = u - part * L.blocks, nf = min(L.f, frames - part * L.f), m0 = first + part * L.f;
+        const int part = (u * L.per_block) >> 16, b = u - part * L.blocks, nf = min(L.f, frames - part * L.f), m0 = first + part * L.f, lane = few_fresh(lane0);
         FewWeights<NR, VEC> r;
         if (nf > 0) r.request(L, 32 * b, lane);
         next = a.layer[j + 1];
@@ -410,10 +417,7 @@ __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel
         before = L.words, before_blocks = L.blocks;
         L = next;
     }
-    // (from here on the lane number is another one to the compiler, which would work out ahead of the loop above what follows from it
-    // and run out of registers there)
-    int lane2 = lane;
-    asm volatile("" : "+v"(lane2));
+    const int lane2 = few_fresh(lane0);
     if (j == a.layers - 1) {
         const int part = (u * L.per_block) >> 16, b = u - part * L.blocks, nf = min(L.f, frames - part * L.f), m0 = first + part * L.f;
         bool there = true;
@@ -427,13 +431,13 @@ __global__ __launch_bounds__(kFewThreads, NR == 4 ? 3 : 4) void few_chain_kernel
     }
     // A wave that has waited in vain once waits no more.  (A loop of its own: its state would crowd the registers of the one above.)
     const bool in_time = j == a.layers;
-    int lane3 = lane2;
-    asm volatile("" : "+v"(lane3));
+    int lane3 = few_fresh(lane0);
     for (; j < a.layers; ++j) {
         const FewLayer& S = a.layer[j];
         const int part = (u * S.per_block) >> 16, b = u - part * S.blocks, nf = min(S.f, frames - part * S.f), m0 = first + part * S.f;
         if (nf <= 0) continue;
         few_catch_up<NR, VEC>(a, j, m0, nf, u, lane3, x, y);
+        lane3 = few_fresh(lane3);
         FewWeights<NR, VEC> r;
         r.request(S, 32 * b, lane3);
         if (j < a.layers - 1) {

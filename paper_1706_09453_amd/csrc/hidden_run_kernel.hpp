@@ -16,9 +16,9 @@
 // So a flag is the number of the writer's XCD (xcd_mark) and counts on that XCD only; on another the block is worked out again, to the
 // same words.  Only the speed rests on the order in which workgroups go round the XCDs.
 // What bounds it where there are many frames: one wave per SIMD, which expands 16 NF rows of weights once per layer and crew, 450
-// vector instructions at 2048 units, beside 64 MFMAs per fragment of frames.  Eight crews, two waves per SIMD, pull the weights twice as
-// often through the L1: 2048 units, 1000 frames 57.6 -> 64.3 us a pass (1024 units, 3000 frames 70.2 -> 65.9, which the tiled kernels
-// do in 71).
+// vector instructions at 2048 units, beside 64 MFMAs per fragment of frames.
+// Workgroups of four waves, four of them to a CU (three at 2048 units, whose 128 frames at most leave one wave of each), for the reason in
+// few_chain_kernel.hpp: with a fifth wave 256 frames of 6 x 1536 units on four streams took 19.0 us a pass, now 14.6 (one launch per layer 16.2).
 #pragma once
 
 #include "few_chain_kernel.hpp"
@@ -26,7 +26,7 @@
 
 namespace bnn {
 
-constexpr int kRunMaxLayers = 16, kRunCrews = 4, kRunThreads = (kRunCrews + 1) * kWave;
+constexpr int kRunMaxLayers = 16, kRunCrews = 4, kRunThreads = kRunCrews * kWave;
 constexpr int kRunFlags = kFewGroups * kRunCrews * kFewSlots;   // of one layer
 
 struct RunLayer {
@@ -59,7 +59,9 @@ struct RunWeights {
     }
 };
 
-// Outputs n0 .. n0 + 16 NF - 1 of a crew's frames: fragments crew, crew + 4, ... of the `frames` frames from `first`, FM at a time.
+// Outputs n0 .. n0 + 16 NF - 1 of a crew's frames: fragments crew, crew + 4, ... of the `frames` frames from `first`, FM at a time.  (The
+// launch makes FM as many as there are, one turn of the loop.  As a loop it takes 92 registers with NF = FM = 2 and not 114, which
+// with four launches on the chip is 20.4 us a pass and not 22.6, 1000 frames of 6 x 1024 units.)
 template <int NF, int FM>
 __device__ __forceinline__ void run_block(RunWeights<NF>& w, const RunLayer& L, const uint32_t* X, int n0, int first, int frames, int crew, int lane) {
     const int r = lane & 15, g = lane >> 4;
@@ -153,10 +155,6 @@ __global__ __launch_bounds__(kRunThreads, NF == 4 ? 3 : 4) void hidden_run_kerne
     int lane = lane_id();
     const int first = group * a.F, frames = min(a.F, a.M - first);
     if (frames <= 0) return;
-    if (crew == kRunCrews) {   // the later layers' weights into this XCD's L2
-        for (int j = 1; j < a.layers; ++j) few_pull(a.layer[j].W, 32768u * NF * NF, slot, lane);
-        return;
-    }
     if (16 * crew >= frames) return;
     const int n0 = slot * 16 * NF;
     uint32_t* const flags = a.flags + (group * kRunCrews + crew) * kFewSlots;   // + layer * kRunFlags

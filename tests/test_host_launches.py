@@ -310,3 +310,26 @@ for M, N in ((64, 64), (200, 512)):
 result = [runs, uncleared]
 """)
     assert runs > 100 and uncleared == 0
+
+
+def test_which_binary_layers_share_a_launch(host):
+    """Runs of a few frames and of mid-size batches, on both sides of each line."""
+    got = host(FORWARD + """
+S, Z = bnn.BNN_ACT_SIGN, bnn.BNN_ACT_LOGSOFTMAX
+result = []
+for M, widths in ((1, (512, 512)), (1, (512, 512, 512)), (1, (520, 512)), (64, (2048, 2048, 2048)), (64, (2049, 2049, 2049)), (17, (4096, 2048, 2048)),
+                  (2048, (512, 512)), (2049, (512, 512)), (1024, (1024, 1024)), (1025, (1024, 1024)), (320, (1536, 1536)), (321, (1536, 1536)),
+                  (128, (2048, 2048)), (129, (2048, 2048)), (65, (1000, 1000)), (65, (512, 1024)),
+                  (17, (1024, 1024, 1024)), (17, (1025, 1025, 1025))):
+    for last in (None, 100):
+        dims = (40, widths[0]) + widths + ((last,) if last else ())
+        forward(M, dims, (S,) * (len(dims) - 1 - bool(last)) + ((Z,) if last else ()))
+        k = [l for l in launches() if "few_chain" in l["kernel"] or "hidden_run" in l["kernel"]]
+        result.append([("few" if "few_chain" in l["kernel"] else "mid") + str(l["grid"][0]) for l in k])
+""")
+    few, pulling, mid = ["few256"], ["few512"], ["mid256"]
+    # (without, with an output layer): two binary layers of whole pieces are a run only with the log-Softmax behind them; 512 workgroups: half of them pull
+    want = [[], few, few, few, few, few, few, few, [], [], [], [],
+            mid, mid, [], [], mid, mid, [], [], mid, mid, [], [], mid, mid, [], [], [], [], [], [],
+            pulling, pulling, few, few]
+    assert got == want, [(i, g, w) for i, (g, w) in enumerate(zip(got, want)) if g != w]

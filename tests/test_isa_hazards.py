@@ -48,6 +48,15 @@ def code(assembly):
     return [l for l in lines if l and not l.startswith("//") and (l.endswith(":") or not l.startswith("."))]
 
 
+def _metadata(assembly):
+    """The figures the compiler gives for every kernel: name, registers, LDS, size of the arguments and so on."""
+    for text in assembly.values():
+        for k in re.split(r"\n  - ", text[text.index("amdhsa.kernels"):])[1:]:
+            fields = dict(re.findall(r"\.(\w+):\s+(\S+)", k.split(".args:")[0] + k[k.rfind(".group_segment_fixed_size"):]))
+            if "name" in fields:
+                yield fields
+
+
 def _kernels(code):
     """(name, instructions) of every function."""
     name, body = None, []
@@ -182,15 +191,17 @@ def test_first_layers_take_few_launch_arguments(assembly):
     """A launch with more than 112 bytes of arguments (the 256 that hold the grid's size among them) takes the host 3.5 us instead of
     2.9: the kernels that may stand in front of a run of binary layers keep below that wherever they stand, but for the two that also
     pull the run's weights."""
-    n, bad = 0, []
-    for text in assembly.values():
-        meta = text[text.index("amdhsa.kernels"):]
-        for k in re.split(r"\n  - ", meta)[1:]:
-            name = re.search(r"\.name:\s+(\S+)", k)
-            size = re.search(r"\.kernarg_segment_size: (\d+)", k)
-            if not name or not re.search(r"realx_valu_kernel|realx_sign_fused_kernel|realx_resolve_rows|realx_quantize_nat|f32_chain_kernel", name.group(1)):
-                continue
-            n += 1
-            if int(size.group(1)) > 112 and "4Pull" not in name.group(1):
-                bad.append((name.group(1), int(size.group(1))))
-    assert n > 80 and not bad, (n, len(bad), bad[:4])
+    first = r"realx_valu_kernel|realx_sign_fused_kernel|realx_resolve_rows|realx_quantize_nat|f32_chain_kernel"
+    sizes = {k["name"]: int(k["kernarg_segment_size"]) for k in _metadata(assembly) if re.search(first, k["name"]) and "4Pull" not in k["name"]}
+    assert len(sizes) > 80 and max(sizes.values()) <= 112, [k for k in sizes.items() if k[1] > 112][:4]
+
+
+def test_four_launches_of_a_run_of_binary_layers_fit_on_a_cu(assembly):
+    """Their workgroups, one to a CU, wait for each other: where the runs of four streams (as many queues as the device runs at once) do
+    not all fit, each of them gets a part of its workgroups and all wait until they give up.  512 registers and a wave of each
+    workgroup per SIMD, 160 KB of LDS.  (2048 units have at most 128 frames, of which one wave per workgroup takes care.)"""
+    runs = [k for k in _metadata(assembly) if re.search(r"few_chain_kernel|hidden_run_kernel", k["name"])]
+    assert len(runs) >= 14
+    for k in runs:
+        most = 168 if "hidden_run_kernelILi4ELi1E" in k["name"] else 128
+        assert int(k["max_flat_workgroup_size"]) <= 256 and int(k["vgpr_count"]) <= most and 4 * int(k["group_segment_fixed_size"]) <= 160 * 1024, k
