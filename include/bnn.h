@@ -52,7 +52,7 @@ typedef enum bnn_status {
     BNN_EINVAL = -1,     /* null pointer, unknown act / arm, act not allowed for this call, overlapping buffers */
     BNN_ESHAPE = -2,     /* M < 0, K <= 0, N <= 0, word_bits not in {32, 64}, inconsistent layer chain */
     BNN_EALIGN = -3,     /* a packed or fp32 pointer is not aligned as required */
-    BNN_EWORKSPACE = -4, /* workspace missing or smaller than bnn_forward_workspace_bytes() */
+    BNN_EWORKSPACE = -4, /* workspace missing or smaller than the call needs: bnn_forward_workspace_bytes(), see bnn_forward */
     BNN_EDEVICE = -5     /* a HIP call failed (launch error) */
 } bnn_status;
 
@@ -119,7 +119,7 @@ typedef enum bnn_option {
                                        from 17 frames on), so that a layer is spread over the whole chip and takes one pass
                                        over its weight rows (binary layers that would need more workgroups than the chip
                                        holds stay on the matrix cores).  In bnn_forward, binary layers of up to 2048 inputs that follow each
-                                       other share one launch.  0 = never.  Default 64.  Same results either way. */
+                                       other share one launch (see there).  0 = never.  Default 64.  Same results either way. */
     BNN_OPT_MFMA32_SPLITK = 14,     /* 0 or 1, without effect: Sign layers once had a variant with K split between the halves of
                                        a workgroup of 8 waves.  Same bits.                                               */
     BNN_OPT_REALX_I8_LOGSOFTMAX = 16, /* bnn_forward, LOGSOFTMAX layer with binary weights and real inputs, 128 frames or more,
@@ -144,9 +144,11 @@ typedef enum bnn_option {
                                        up (>= 1; default 2^20, about a second).  A small value makes the bounded wait run
                                        out on purpose: the kernel still ends, its rows are wrong and
                                        bnn_cooperative_timeouts counts the workgroups that gave up (for tests of that path).
-                                       The runs of binary layers of a streaming batch poll at most this often too (and never
-                                       more than 48 times) before a wave works out itself what it waits for: same results.  */
-    BNN_OPT_COOPERATIVE = 13        /* 1 = kernels whose workgroups wait for each other may be used: a binary-input
+                                       The runs of binary layers that share a launch in bnn_forward, whatever
+                                       BNN_OPT_COOPERATIVE says, poll at most this often too (and never more than 48 times)
+                                       before a wave works out itself what it waits for: same results.  */
+    BNN_OPT_COOPERATIVE = 13        /* 1 = kernels may be used whose rows are right only if all their workgroups are resident at
+                                       once: a binary-input
                                        LOGSOFTMAX layer on the matrix-core arm then finishes its rows inside the product
                                        kernel (the tiles of a row exchange their maxima and sums of exponentials through
                                        memory) instead of running a second kernel over the rows.  Such a kernel needs all its
@@ -155,7 +157,10 @@ typedef enum bnn_option {
                                        streams the caller serialises).  The waits are bounded: a launch that could not
                                        get its workgroups resident ends anyway, with wrong rows, and is counted
                                        (bnn_cooperative_timeouts).  0 = never (default).  Results within the same
-                                       tolerance as the two-kernel path (sums of exponentials taken in another order).   */
+                                       tolerance as the two-kernel path (sums of exponentials taken in another order).
+                                       (The runs of binary layers of bnn_forward wait for each other too, but need no such
+                                       promise: a wave that has waited in vain does the missing work itself.  This option
+                                       does not concern them.)                                                           */
 } bnn_option;
 
 /* One layer of a network for bnn_forward.  HOST struct; the three pointers are DEVICE pointers. */
@@ -279,6 +284,11 @@ int bnn_layer_binw_binx_arm(const void* Xp, const void* Wp, const float* scale, 
  * weight (K padded to 64) and, for Sign units, a record of 32 bytes per frame and 256 outputs; a real-weight layer adds
  * the bf16 pieces of both operands (LOGSOFTMAX, 128 frames or more: 6 bytes per element, K padded to 32) or reserves
  * 4 bytes per weight that no kernel uses (other activations, 512 frames or more, K a multiple of 4 and padded to 64).
+ * Behind these, for the runs of binary layers that share a launch (see bnn_forward; the largest of them counts): for a run of
+ * n layers on a streaming batch 8 bytes per frame for each of (n - 1) * 16, 32 or 64 words (widest input up to 512, 1024
+ * or 2048), and if it closes with LOGSOFTMAX for 128 words more, together a multiple of 256, and 4 bytes per frame and output (an
+ * even number of outputs), a multiple of 256; on a mid-size batch n * 4096 bytes and n - 1 times the packed output of a layer,
+ * a multiple of 256 each.
  * 0 on invalid arguments, and for a one-layer network without such a layer.
  * HOST helper; layers is a HOST array.
  */
@@ -297,9 +307,18 @@ size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, i
  *   workspace DEVICE scratch of at least bnn_forward_workspace_bytes() bytes, 256-byte aligned
  *             (may be NULL when that is 0)
  * A layer with w_is_real = 1 runs as bnn_layer_realw (after bnn_unpack_activations if its input is binary).
- * Enqueues one kernel per layer (two for a LOGSOFTMAX layer or a real-input Sign layer on the slab filter; one for a run of
- * binary layers of a streaming batch) on `stream`, no host synchronisation.  A workspace smaller than
- * bnn_forward_workspace_bytes() by no more than the scratch of such runs is accepted too: they then take a launch per layer.
+ * Enqueues one kernel per layer (two for a LOGSOFTMAX layer or a real-input Sign layer on the slab filter) on `stream`, no host
+ * synchronisation.  Layers with binary weights and inputs that follow each other behind a layer with real inputs or weights
+ * share one kernel, with the same results, in two cases:
+ *   - streaming batches (BNN_OPT_STREAM_MAX_FRAMES, at most 64 frames): up to 16 layers of at most 2048 inputs and 4096 outputs,
+ *     three or more, or two if they close with LOGSOFTMAX or have rows that are no multiple of 16 bytes;
+ *   - mid-size batches: two to 16 Sign layers of 512, 1024, 1536 or 2048 inputs and as many outputs, for up to 2048, 1024, 320 and
+ *     128 frames, behind a real-input Sign layer with binary weights (the first layer with at most 512 inputs, or any from 128
+ *     frames on).
+ * The workgroups of such a kernel wait for each other, so it is at its best where all of them, one per CU, are on the chip; four
+ * such kernels (the hardware queues of a process) fit side by side.  A program that shares the device with more of them can
+ * have a launch per layer instead: bnn_forward accepts a workspace without the scratch of these runs (the last part of what
+ * bnn_forward_workspace_bytes() counts), and then takes none.
  */
 int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,
                 void* workspace, size_t workspace_bytes, void* stream);
@@ -316,7 +335,8 @@ int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64
  *     that layer there: 2048 inputs fit up to about 2600 frames).  The extra scratch of the tiled matrix-core products
  *     (a byte per weight of a real-input layer with binary weights, six bytes per weight of a Softmax layer with real
  *     weights) is left out when it does not fit: those layers then run on the kernels with 16-frame workgroups and on
- *     the fp32 matrix cores, with the results those give in bnn_forward (same bits for Sign layers);
+ *     the fp32 matrix cores, with the results those give in bnn_forward (same bits for Sign layers); so is the scratch of the
+ *     runs of binary layers, which then take a launch per layer (same results);
  *   - BNN_EDEVICE if the array's address cannot be obtained on the current device.
  * Every call on a GPU shares that GPU's one array: calls that overlap in time on one GPU (different streams or threads)
  * race on it; calls on one stream are ordered and safe.  Nothing in the array has to be cleared between calls: every

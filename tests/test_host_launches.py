@@ -333,3 +333,29 @@ for M, widths in ((1, (512, 512)), (1, (512, 512, 512)), (1, (520, 512)), (64, (
             mid, mid, [], [], mid, mid, [], [], mid, mid, [], [], mid, mid, [], [], [], [], [], [],
             pulling, pulling, few, few]
     assert got == want, [(i, g, w) for i, (g, w) in enumerate(zip(got, want)) if g != w]
+
+
+def test_workspace_without_the_scratch_of_runs(host):
+    """The size of that scratch is what bnn.h says; without it a launch per layer, with less BNN_EWORKSPACE."""
+    got = host("""
+S, Z = bnn.BNN_ACT_SIGN, bnn.BNN_ACT_LOGSOFTMAX
+up = lambda v: (v + 255) // 256 * 256
+result = []
+for M, dims, last, scratch in ((1, (40, 512, 512, 1001), Z, up(8 * (16 + 128)) + up(1002 * 4)), (50, (40, 1000, 90, 1024, 70), S, up(8 * 50 * 2 * 32)),
+                               (33, (40, 2048, 2048, 7, 4096), Z, up(8 * 33 * (2 * 64 + 128)) + up(33 * 4096 * 4)),
+                               (333, (40, 1024, 1024, 1024, 70), Z, 2 * 4096 + up(333 * 128)), (130, (600, 512, 512, 512, 512), S, 3 * 4096 + 2 * up(130 * 64))):
+    n = len(dims) - 1
+    arr = bnn.make_layer_array([dict(K=dims[l], N=dims[l + 1], act=S if l < n - 1 else last, word_bits=32, x_is_binary=int(l > 0), w_is_real=0,
+                                     Wp=B + l * 0x10000000, scale=C, bias=C) for l in range(n)])
+    total = bnn.bnn_forward_workspace_bytes(arr, n, M)
+    row = []
+    for size in (total, total - 1, total - scratch, total - scratch - 1):
+        try:
+            bnn.bnn_forward(arr, n, A, M, D, E, size, 0)
+            row.append(sum("few_chain" in l["kernel"] or "hidden_run" in l["kernel"] for l in launches()))
+        except bnn.BnnError as e:
+            row.append(str(e))
+    result.append(row)
+""")
+    for row in got:
+        assert row[:3] == [1, 0, 0] and "workspace" in str(row[3]).lower(), row
