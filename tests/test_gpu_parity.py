@@ -246,66 +246,57 @@ def test_streaming_forward(G, bnn, oracle, cfg_id, M):
         _net_parity(G, bnn, oracle, workloads.CONFIGS[cfg_id], M)
 
 
-@pytest.mark.parametrize("spins", [1 << 20, 1])   # 1: every wave gives up waiting and works out what it needs itself
-@pytest.mark.parametrize("M,dims,last,zero_one,wb", [
-    (1, (40, 2048, 2048, 2048, 3400), "logsoftmax", False, 32), (7, (40, 512, 512, 512, 1003), "logsoftmax", True, 64),
-    (64, (40, 1000, 1000, 4096), "logsoftmax", False, 64), (64, (143, 2048, 2048, 2048, 2048), "sigmoid", False, 32),
-    (9, (40, 33, 1984, 70, 97), "sign", False, 64), (33, (40, 1, 31, 32, 5), "linear", True, 32),
-    (16, (40, 4096, 2048, 4096, 130), "logsoftmax", False, 32), (50, (40, 2047, 1003, 513, 2049, 77), "logsoftmax", True, 32),
-    (23, (40,) + (96,) * 18 + (50,), "hardtanh", False, 32),
-    # more frames: equal layers of up to 2048 units, every number of fragments per wave and of units, ragged last fragments
-    (65, (40, 512, 512, 512, 1003), "logsoftmax", False, 32), (128, (40, 1024, 1024, 1024, 70), "linear", True, 64),
-    (333, (440, 1024, 1024, 1024, 1024), "sign", False, 32), (384, (40, 2048, 2048, 2048, 300), "logsoftmax", False, 32),
-    (99, (143, 2048, 2048, 2048, 64), "sigmoid", True, 64), (501, (40, 1536, 1536, 1536, 200), "logsoftmax", False, 64),
-    (700, (40, 1024, 1024, 1024, 33), "logsoftmax", True, 32), (1500, (143, 1024, 1024, 1024, 65), "linear", False, 64),
-    (2048, (40, 1024, 1024, 1024, 96), "hardtanh", False, 32), (4096, (600, 512, 512, 512, 512, 40), "linear", True, 32)])
-def test_run_of_binary_layers_in_one_launch(G, bnn, M, dims, last, zero_one, wb, spins):
-    """The binary layers of a batch in one launch: the bits of the same layers called one by one, for one batch after
-    another on the same workspace (whose marks the first layer's launch clears), whether waves wait for each other or not."""
+def _net(G, bnn, M, dims, acts, wb=32, zero_one=False, real=()):
+    """A network on the GPU, layer l with act acts[l], those in `real` with real weights: its descriptors and what they point to."""
     g = torch.Generator().manual_seed(M + len(dims) + dims[-1])
-    n = len(dims) - 1
-    descs, keep = [], []
+    descs, keep, binary = [], [], 0
     for l, (K, N) in enumerate(zip(dims, dims[1:])):
-        Wp, _ = G.pack_weights(torch.randn(N, K, generator=g).cuda(), wb)
+        W = torch.randn(N, K, generator=g).cuda()
         scale, bias = (torch.rand(N, generator=g) / K ** 0.5).cuda(), torch.randn(N, generator=g).cuda() * 0.1
+        Wp = W if l in real else G.pack_weights(W, wb)[0]
         keep += [Wp, scale, bias]
-        descs.append(dict(K=K, N=N, act=bnn.ACT_BY_NAME["sign" if l < n - 1 else last], word_bits=wb,
-                          x_is_binary=0 if l == 0 else 2 if zero_one else 1, Wp=G.ptr(Wp), scale=G.ptr(scale), bias=G.ptr(bias)))
-    layers = bnn.make_layer_array(descs)
-
-    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
-    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
-    out = G.out_tensor(M, dims[-1], descs[-1]["act"], wb)
-    bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, spins)
-    try:
-        with _streaming(bnn):
-            for _ in range(3):
-                X = torch.randn(M, dims[0], generator=g).cuda()
-                bnn.bnn_forward(layers, n, G.ptr(X), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
-                h = X
-                for d in descs:
-                    Y = G.out_tensor(M, d["N"], d["act"], wb)
-                    fn = (bnn.bnn_layer_binw_realx, bnn.bnn_layer_binw_binx, bnn.bnn_layer_binw_binx01)[d["x_is_binary"]]
-                    fn(G.ptr(h), d["Wp"], d["scale"], d["bias"], M, d["K"], d["N"], d["act"], wb, G.ptr(Y), G.stream())
-                    h = Y
-                torch.cuda.synchronize()
-                assert torch.equal(out, h)
-    finally:
-        bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
-
-
-def _sign_net(G, bnn, M, dims, last="logsoftmax", wb=32, zero_one=False, seed=0):
-    """A network of Sign layers (the last one with act `last`) on the GPU: its descriptors and what they point to."""
-    g = torch.Generator().manual_seed(seed + M + len(dims) + dims[-1])
-    n = len(dims) - 1
-    descs, keep = [], []
-    for l, (K, N) in enumerate(zip(dims, dims[1:])):
-        Wp, _ = G.pack_weights(torch.randn(N, K, generator=g).cuda(), wb)
-        scale, bias = (torch.rand(N, generator=g) / K ** 0.5).cuda(), torch.randn(N, generator=g).cuda() * 0.1
-        keep += [Wp, scale, bias]
-        descs.append(dict(K=K, N=N, act=bnn.ACT_BY_NAME["sign" if l < n - 1 else last], word_bits=wb,
-                          x_is_binary=0 if l == 0 else 2 if zero_one else 1, Wp=G.ptr(Wp), scale=G.ptr(scale), bias=G.ptr(bias)))
+        descs.append(dict(K=K, N=N, act=bnn.ACT_BY_NAME[acts[l]], word_bits=wb, x_is_binary=binary, w_is_real=int(l in real), Wp=G.ptr(Wp),
+                          scale=0 if l in real else G.ptr(scale), bias=G.ptr(bias)))
+        binary = (2 if zero_one else 1) if acts[l] == "sign" else 0
     return descs, keep
+
+
+def _layer_by_layer(G, bnn, descs, X):
+    h, M = X, X.shape[0]
+    for d in descs:
+        Y = G.out_tensor(M, d["N"], d["act"], d["word_bits"])
+        if d["w_is_real"]:
+            bnn.bnn_layer_realw(G.ptr(h), d["Wp"], d["bias"], M, d["K"], d["N"], d["act"], d["word_bits"], G.ptr(Y), G.stream())
+        else:
+            fn = (bnn.bnn_layer_binw_realx, bnn.bnn_layer_binw_binx, bnn.bnn_layer_binw_binx01)[d["x_is_binary"]]
+            fn(G.ptr(h), d["Wp"], d["scale"], d["bias"], M, d["K"], d["N"], d["act"], d["word_bits"], G.ptr(Y), G.stream())
+        h = Y
+    return h
+
+
+def _runs(bnn, descs, M):
+    """The runs of binary layers that share a launch, as bnn.h states them: (first layer, how many)."""
+    runs, l = [], 1
+    binary = lambda d: d["x_is_binary"] and not d["w_is_real"]
+    while l < len(descs):
+        front, n = descs[l - 1], 0
+        if not binary(front):
+            if M <= 64:
+                while l + n < len(descs) and n < 16 and binary(descs[l + n]) and descs[l + n]["K"] <= 2048 and descs[l + n]["N"] <= 4096:
+                    n += 1
+                pieces = all(bnn.bnn_packed_words(d["K"], d["word_bits"]) * d["word_bits"] % 128 == 0 for d in descs[l:l + n])
+                if n < 2 or (n < 3 and pieces and descs[l + n - 1]["act"] != bnn.BNN_ACT_LOGSOFTMAX):
+                    n = 0
+            elif not front["x_is_binary"] and not front["w_is_real"] and (M >= 128 or (l == 1 and front["K"] <= 512)):
+                N = descs[l]["N"]
+                while l + n < len(descs) and n < 16 and binary(descs[l + n]) and descs[l + n]["act"] == bnn.BNN_ACT_SIGN and descs[l + n]["K"] == descs[l + n]["N"] == N:
+                    n += 1
+                if n < 2 or M > {512: 2048, 1024: 1024, 1536: 320, 2048: 128}.get(N, 0):
+                    n = 0
+        if n:
+            runs.append((l, n))
+        l += max(n, 1)
+    return runs
 
 
 def _run_scratch_bytes(bnn, descs, first, n, M):
@@ -322,11 +313,78 @@ def _run_scratch_bytes(bnn, descs, first, n, M):
     return marks, marks + up(M * (last["N"] + last["N"] % 2) * 4) * lsm
 
 
+def _check_marks(bnn, ws, descs, M, runs):
+    """After a call on a workspace that was full of 0xFF: its scratch of runs holds the marks of the last one."""
+    if not runs:
+        return
+    scratch = [_run_scratch_bytes(bnn, descs, first, n, M) for first, n in runs]
+    start, (first, n) = ws.numel() - max(total for _, total in scratch), runs[-1]
+    got = ws[start:start + scratch[-1][0]].cpu().view(torch.int32).numpy()
+    if M > 64:
+        flags = got.reshape(n, 8, 4, 32)
+        per_group = (M + 127) // 128 * 16
+        has = np.array([[16 * crew < min(per_group, M - group * per_group) for crew in range(4)] for group in range(8)])
+        assert (flags[:, ~has] == 0).all() and flags[:, has].min() >= 1 and flags[:, has].max() <= 16
+        return
+    ld, at = 16, 0
+    while any(bnn.bnn_packed_words(d["K"], d["word_bits"]) * d["word_bits"] // 32 > ld for d in descs[first:first + n]):
+        ld *= 2
+    for d in descs[first:first + n]:
+        closing = d is descs[first + n - 1]
+        if closing and d["act"] != bnn.BNN_ACT_LOGSOFTMAX:
+            break
+        words = got[at:at + 2 * M * (128 if closing else ld)].reshape(M, -1, 2)[:, :(d["N"] + 31) // 32]
+        assert (words[:, :, 1] == 1).all() and (not closing or (words[:, :, 0].min() >= 1 and words[:, :, 0].max() <= 16))
+        at += 2 * M * ld
+
+
+@pytest.mark.parametrize("spins", [1 << 20, 1])   # 1: every wave gives up waiting and works out what it needs itself
+@pytest.mark.parametrize("M,dims,last,zero_one,wb", [
+    (1, (40, 2048, 2048, 2048, 3400), "logsoftmax", False, 32), (7, (40, 512, 512, 512, 1003), "logsoftmax", True, 64),
+    (64, (40, 1000, 1000, 4096), "logsoftmax", False, 64), (64, (143, 2048, 2048, 2048, 2048), "sigmoid", False, 32),
+    (9, (40, 33, 1984, 70, 97), "sign", False, 64), (33, (40, 1, 31, 32, 5), "linear", True, 32),
+    (16, (40, 4096, 2048, 4096, 130), "logsoftmax", False, 32), (50, (40, 2047, 1003, 513, 2049, 77), "logsoftmax", True, 32),
+    (23, (40,) + (96,) * 18 + (50,), "hardtanh", False, 32),
+    # more frames: equal layers of up to 2048 units, every number of fragments per wave and of units, ragged last fragments
+    (65, (40, 512, 512, 512, 1003), "logsoftmax", False, 32), (128, (40, 1024, 1024, 1024, 70), "linear", True, 64),
+    (333, (440, 1024, 1024, 1024, 1024), "sign", False, 32), (384, (40, 2048, 2048, 2048, 300), "logsoftmax", False, 32),
+    (99, (143, 2048, 2048, 2048, 64), "sigmoid", True, 64), (501, (40, 1536, 1536, 1536, 200), "logsoftmax", False, 64),
+    (700, (40, 1024, 1024, 1024, 33), "logsoftmax", True, 32), (1500, (143, 1024, 1024, 1024, 65), "linear", False, 64),
+    (2048, (40, 1024, 1024, 1024, 96), "hardtanh", False, 32), (4096, (600, 512, 512, 512, 512, 40), "linear", True, 32),
+    (641, (440, 512, 512, 512, 70), "linear", True, 64), (1025, (40, 512, 512, 512, 512), "sign", False, 32), (2048, (143, 512, 512, 512, 70), "linear", False, 32),
+    (1024, (440, 1024, 1024, 1024, 70), "linear", True, 32), (320, (440, 1536, 1536, 1536, 70), "linear", True, 32),
+    (128, (440, 2048, 2048, 2048, 2048), "sign", True, 64), (2049, (440, 512, 512, 512, 70), "linear", False, 32)])
+def test_run_of_binary_layers_in_one_launch(G, bnn, M, dims, last, zero_one, wb, spins):
+    """The binary layers of a batch in one launch: the bits of the same layers called one by one, for one batch after
+    another on the same workspace (whose marks the first layer's launch clears), whether waves wait for each other or not."""
+    g = torch.Generator().manual_seed(M)
+    n = len(dims) - 1
+    descs, keep = _net(G, bnn, M, dims, ["sign"] * (n - 1) + [last], wb, zero_one)
+    runs = _runs(bnn, descs, M)
+    layers = bnn.make_layer_array(descs)
+
+    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
+    ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
+    out = G.out_tensor(M, dims[-1], descs[-1]["act"], wb)
+    bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, spins)
+    try:
+        with _streaming(bnn):
+            for _ in range(3):
+                X = torch.randn(M, dims[0], generator=g).cuda()
+                bnn.bnn_forward(layers, n, G.ptr(X), M, G.ptr(out), G.ptr(ws), nbytes, G.stream())
+                h = _layer_by_layer(G, bnn, descs, X)
+                torch.cuda.synchronize()
+                assert torch.equal(out, h)
+                _check_marks(bnn, ws, descs, M, runs)
+    finally:
+        bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
+
+
 @pytest.mark.parametrize("M,dims", [(64, (40, 512, 512, 1003)), (64, (40, 512, 512, 512, 4096)), (512, (40, 512, 512, 512, 70)), (128, (40, 2048, 2048, 2048, 70))])
 def test_marks_of_a_run_name_the_xcd_of_their_writer(G, bnn, M, dims):
     """What lies apart from its mark (pre-activations, rows of bits) is safe to read only on the XCD that wrote both: every mark is
     that XCD's number and 1, and the groups of frames, one to an XCD, have different ones."""
-    descs, keep = _sign_net(G, bnn, M, dims)
+    descs, keep = _net(G, bnn, M, dims, ["sign"] * (len(dims) - 2) + ["logsoftmax"])
     layers, n = bnn.make_layer_array(descs), len(descs)
     nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
     ws = torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda")
@@ -347,6 +405,90 @@ def test_marks_of_a_run_name_the_xcd_of_their_writer(G, bnn, M, dims):
         assert (flags[:, ~has] == 0).all()
         xcds = flags[:, has]
     assert xcds.min() >= 1 and xcds.max() <= 16 and len(np.unique(xcds)) > 1
+
+
+@pytest.mark.parametrize("spins", [1 << 20, 1])
+@pytest.mark.parametrize("M,dims,acts,real,runs", [
+    (33, (440, 512, 512, 512, 70), ("sign", "sign", "sign", "logsoftmax"), (0,), 1),                                  # real weights in front
+    (200, (440, 300, 1024, 1024, 1024, 70), ("sigmoid", "sign", "sign", "sign", "linear"), (), 1),                    # behind a Sigmoid layer
+    (20, (440, 512, 512, 512, 300, 512, 512, 512, 70), ("sign",) * 3 + ("sigmoid",) + ("sign",) * 3 + ("logsoftmax",), (), 2),   # two of them
+    (9, (440, 512, 512, 90, 2048, 2048, 2048, 33), ("sign",) * 2 + ("sigmoid",) + ("sign",) * 3 + ("sign",), (3,), 1),
+    (200, (440, 512, 512, 512, 300, 1024, 1024, 1024, 70), ("sign",) * 3 + ("sigmoid",) + ("sign",) * 3 + ("linear",), (), 2)])
+def test_runs_inside_networks(G, bnn, M, dims, acts, real, runs, spins):
+    """Runs behind every kind of layer that may stand in front, two in a network on the same scratch, and the same network on a
+    workspace without it: the bits of the layers called one by one."""
+    descs, keep = _net(G, bnn, M, dims, acts, real=real)
+    layers, n = bnn.make_layer_array(descs), len(descs)
+    found = _runs(bnn, descs, M)
+    assert len(found) == runs
+    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
+    scratch = max(_run_scratch_bytes(bnn, descs, first, count, M)[1] for first, count in found)
+    g = torch.Generator().manual_seed(M)
+    bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, spins)
+    try:
+        with _streaming(bnn):
+            for size in (nbytes, nbytes - scratch):
+                ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+                for _ in range(2):
+                    X = torch.randn(M, dims[0], generator=g).cuda()
+                    out = G.out_tensor(M, dims[-1], descs[-1]["act"], 32)
+                    bnn.bnn_forward(layers, n, G.ptr(X), M, G.ptr(out), G.ptr(ws), size, G.stream())
+                    want = _layer_by_layer(G, bnn, descs, X)
+                    torch.cuda.synchronize()
+                    assert torch.equal(out, want)
+                    if size == nbytes:
+                        _check_marks(bnn, ws, descs, M, found)
+    finally:
+        bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
+
+
+@pytest.mark.parametrize("spins", [1 << 20, 4])   # 4: some waves give up, some do not
+@pytest.mark.parametrize("M,dims", [(16, (440,) + (2048,) * 6 + (3400,)), (64, (40,) + (1344,) * 5 + (1003,)), (333, (440,) + (1024,) * 6 + (70,)),
+                                    (128, (440,) + (2048,) * 4 + (70,))])
+def test_runs_on_several_streams_and_in_graphs(G, bnn, M, dims, spins):
+    """Six streams at once, more than the device has queues, each with frames, outputs and a workspace of its own: every output as
+    on one stream alone.  Then the same passes as a graph, replayed with other work between and new frames each time."""
+    acts = ["sign"] * (len(dims) - 2) + ["logsoftmax"]
+    descs, keep = _net(G, bnn, M, dims, acts)
+    layers, n, S = bnn.make_layer_array(descs), len(descs), 6
+    assert len(_runs(bnn, descs, M)) == 1
+    nbytes = bnn.bnn_forward_workspace_bytes(layers, n, M)
+    g = torch.Generator().manual_seed(M)
+    Xs = [torch.randn(M, dims[0], generator=g).cuda() for _ in range(S)]
+    outs = [G.out_tensor(M, dims[-1], descs[-1]["act"], 32) for _ in range(S)]
+    wss = [torch.full((nbytes,), 0xFF, dtype=torch.uint8, device="cuda") for _ in range(S)]
+    streams = [torch.cuda.Stream() for _ in range(S)]
+    forward = lambda j, st: bnn.bnn_forward(layers, n, G.ptr(Xs[j]), M, G.ptr(outs[j]), G.ptr(wss[j]), nbytes, st)
+    with _streaming(bnn):
+        alone = []
+        for j in range(S):
+            forward(j, G.stream())
+            torch.cuda.synchronize()
+            alone.append(outs[j].clone())
+        bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, spins)
+        try:
+            for _ in range(5):
+                for o in outs:
+                    o.fill_(float("nan"))
+                torch.cuda.synchronize()
+                for _ in range(4):
+                    for j in range(S):
+                        forward(j, streams[j].cuda_stream)
+                torch.cuda.synchronize()
+                for j in range(S):
+                    assert torch.equal(outs[j], alone[j]), f"stream {j}"
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=streams[0]):
+                forward(0, streams[0].cuda_stream)
+        finally:
+            bnn.bnn_set_option(bnn.BNN_OPT_COOPERATIVE_SPIN, 1 << 20)
+        for j in (3, 1, 2, 4):
+            Xs[0].copy_(Xs[j])
+            outs[0].fill_(float("nan"))
+            graph.replay()
+            forward(5, G.stream())
+            torch.cuda.synchronize()
+            assert torch.equal(outs[0], alone[j])
 
 
 def test_streaming_forward_equals_large_batch_forward(G, bnn, oracle):

@@ -359,3 +359,16 @@ for M, dims, last, scratch in ((1, (40, 512, 512, 1001), Z, up(8 * (16 + 128)) +
 """)
     for row in got:
         assert row[:3] == [1, 0, 0] and "workspace" in str(row[3]).lower(), row
+
+
+def test_no_run_writes_over_weights_it_still_reads(host):
+    """The output may lie where a layer before the last one keeps its weights: then every layer takes a launch of its own."""
+    got = host(FORWARD + """
+S, Z = bnn.BNN_ACT_SIGN, bnn.BNN_ACT_LOGSOFTMAX
+result = []
+for M, dims, acts in ((8, (40, 512, 512, 512, 70), (S, S, S, Z)), (200, (40, 512, 512, 512, 512), (S, S, S, S))):
+    for out in (D, B + 0x10000000 + 512 * 64 - 16, B + 0x10000000 + 512 * 64):   # (the first layer of the run: 32 KB of weights)
+        forward(M, dims, acts, out=out)
+        result.append(sum("few_chain" in l["kernel"] or "hidden_run" in l["kernel"] for l in launches()))
+""")
+    assert got == [1, 0, 1, 1, 0, 1]
