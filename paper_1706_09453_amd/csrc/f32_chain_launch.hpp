@@ -21,11 +21,14 @@ void launch_chain_tile(const ChainArgs& a) {
     f32_chain_kernel<FM, FN, WR, KC, ACT, WREAL, VEC, SKIP><<<grid, 256, lds, a.st>>>(a.X, a.W, a.scale, a.bias, a.M, a.K, a.N, a.w32, a.Y, a.yw32, cleared_by(a.clear, grid));
 }
 // Workgroup tile: the one whose fullest CU has the least to multiply, counting what a tile of that size loses to its
-// memory instructions (rates measured at 4096 x 2048 x 2048: 132 TFLOP/s with 256 x 128 tiles, 129 with 128 x 128, 124
-// with 64 x 64, 86 with 32 x 64; at 256 x 2048 x 2048, where the large tiles leave most CUs idle, 8, 15, 58 and 80).
+// memory instructions (TFLOP/s: 132 with 256 x 128 tiles, 129 with 128 x 128 and 124 with 64 x 64, measured at 4096 x 2048 x 2048; 112
+// with 32 x 64, 90 with 16 x 64, 70 with real weights, such that over 35000 sizes of 17 to 9000 frames, 68 to 4096 inputs and 200 to
+// 4096 outputs, timed in every tile, the choice costs least: 1.1 % more than the best tile with weight bits, 0.4 % with real weights.  The
+// rates these tiles had before their chunks of 64, 86 and 71, or 76, cost 2.7 and 2.0 %: 588 x 256 x 4096 with real weights 22.8 us in 64 x
+// 64 tiles, 18.0 in 32 x 64; no size got slower by more than 2 %).
 // Tiles of 32 x 64 take chunks of 64: with 128, half as many barriers but a first chunk that takes twice as long to arrive and a workgroup
 // that shares its CU with no other, 256 x 2048 x 2048 took 25.0 us, 21.6 now (real weights 26.9 and 23.6), 256 x 440 x 2048 9.0 and
-// 7.5, 256 x 3400 x 2048 40.0 and 34.2; the rate in the model is the one its lines were drawn with.
+// 7.5, 256 x 3400 x 2048 40.0 and 34.2.
 template <int ACT, bool WREAL>
 void launch_chain_act(const ChainArgs& a) {
     // 32-bit byte offsets inside a workgroup's rows: 256 rows of at most 2^22 - 1 numbers
@@ -33,13 +36,13 @@ void launch_chain_act(const ChainArgs& a) {
     const bool wide = a.N > 65535 * 64 - 64;   // tiles of 64 outputs would not fit the second grid dimension
     auto tiles = [&](int tm, int tn) { return (int64_t)((a.M + tm - 1) / tm) * ((a.N + tn - 1) / tn); };
     // Tiles of 16 frames x 64 outputs, one fragment per wave: the time is the chain itself (K / 4 dependent MFMAs), the same
-    // for 1 frame and for 64 as long as the grid fits the chip, 15 us for K = 2048 where 32 x 64 tiles take 25 (which is what
+    // for 1 frame and for 64 as long as the grid fits the chip, 15 us for K = 2048 where 32 x 64 tiles take 21 (which is what
     // its rate in the model stands for).  Against the vector-ALU kernels: real weights 16 x 440 x 2048 12.1 -> 5.8 us,
     // 16 x 2048 x 2048 50 -> 14, 16 x 2047 x 2048 547 -> 16; weight bits 64 x 4096 x 4096 69 -> 33, 65 x 440 x 512
     // 6.2 -> 5.2, 256 x 2047 x 512 26 -> 15 (8.6 and 37 with the larger tiles).  Chunks of 64 for the weight bits (17.7 us
     // with 128 at K = 2048), of 128 for real weights, whose staging is spread over the chunk (13.9 us, 14.5 with 64).
     constexpr int kFewKC = WREAL ? 128 : 64;
-    const double few_rate = WREAL ? (vec ? 76 : 60) : 71;   // (84 KiB of LDS with real weights: one workgroup per CU)
+    const double few_rate = WREAL ? (vec ? 70 : 60) : (vec ? 90 : 71);   // (84 KiB of LDS with real weights: one workgroup per CU)
     auto few = [&](auto v) { launch_chain_tile<1, 1, 1, kFewKC, ACT, WREAL, decltype(v)::value, true>(a); };
     const std::true_type yes;
     const std::false_type no;
@@ -68,7 +71,7 @@ void launch_chain_act(const ChainArgs& a) {
         }
     }
     auto cost = [&](int tm, int tn, double rate) { return (double)((tiles(tm, tn) + 255) / 256) * tm * tn / rate; };
-    const double c[5] = {cost(256, 128, 132), cost(128, 128, 129), cost(64, 64, 124), cost(32, 64, 86), cost(16, 64, few_rate)};
+    const double c[5] = {cost(256, 128, 132), cost(128, 128, 129), cost(64, 64, 124), cost(32, 64, 112), cost(16, 64, few_rate)};
     if (!vec) {
         if (wide) launch_chain_tile<4, 4, 2, 32, ACT, WREAL, false>(a);
         else if (c[4] < c[2]) few(no);
