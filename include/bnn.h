@@ -312,12 +312,12 @@ size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, i
  * share one kernel, with the same results, in two cases:
  *   - streaming batches (BNN_OPT_STREAM_MAX_FRAMES, at most 64 frames): up to 16 layers of at most 2048 inputs and 4096 outputs,
  *     three or more, or two if they close with LOGSOFTMAX or have rows that are no multiple of 16 bytes;
- *   - mid-size batches: two to 16 Sign layers of 512, 1024, 1536 or 2048 inputs and as many outputs, for up to 2048, 1024, 320 and
+ *   - mid-size batches: two to 16 Sign layers of 512, 1024, 1536 or 2048 inputs and as many outputs, for up to 4096, 1024, 512 and
  *     128 frames, behind a real-input Sign layer with binary weights (the first layer with at most 512 inputs, or any from 128
  *     frames on).
  * The workgroups of such a kernel wait for each other, so it is at its best where all of them, one per CU, are on the chip; four
- * such kernels (the hardware queues of a process) fit side by side.  A program that shares the device with more of them can
- * have a launch per layer instead: bnn_forward accepts a workspace without the scratch of these runs (the last part of what
+ * such kernels (the hardware queues of a process) fit side by side.  A program that shares the device with more of them, or
+ * that keeps it full with mid-size batches from graphs or several threads, can have a launch per layer instead: bnn_forward accepts a workspace without the scratch of these runs (the last part of what
  * bnn_forward_workspace_bytes() counts), and then takes none.
  */
 int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,

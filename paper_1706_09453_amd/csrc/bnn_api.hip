@@ -1392,18 +1392,18 @@ static Pull few_chain_pull(const bnn_layer_desc* layers, int l, int n, int64_t M
 // behind a real-input Sign layer whose last launch clears the flags.  0: none.
 // Passes back to back, 440 inputs, six hidden layers, 3400 outputs, one launch per layer -> this: 320 frames 42.0 -> 32.2 us (512
 // units), 47.1 -> 34.4 (1024), 49.8 -> 38.4 (1536); 128 of 2048 51.4 -> 39.3; 1000 frames 45.1 -> 36.9 and 50.2 -> 41.1 (512, 1024).
-// How many frames: alone, a run is faster far beyond these lines, but with as many batches in flight as the device has queues the chip is
-// full, and the more fragments a wave takes the more the tiles of one launch per layer win.  Alone, and a pass of four streams at once:
-// 1024 units, 1024 frames 49.6 -> 41.2 and 21.6 -> 20.0, 1152 55.2 -> 45.3 but 21.6 -> 26.2; 512 units, 2048 frames 53.0 -> 46.5 and
-// 22.7 -> 21.7, 3200 62.2 -> 56.0 but 32.6 -> 33.0 (eight layers, 100 outputs 22.5 -> 27.6); 1536 units, 320 frames 48.8 -> 37.7 and 17.2
-// -> 16.0, 384 48.6 -> 38.1 but 17.3 -> 18.2; 2048 units, 128 frames 50.6 -> 39.4 and 19.4 -> 16.4, 160 52.2 -> 42.5 but 20.5 -> 21.9, 333
-// 54.9 -> 47.0 but 21.5 -> 30.5.
+// How many frames: alone, a run is faster far beyond these lines, and with four batches in flight that one thread launches one by one,
+// too.  But where graphs or threads keep as many batches on the chip as the device has queues, the tiles of one launch per layer win with every
+// fragment that a wave takes.  The lines are where that costs up to 8 %.  Alone, and a pass of four graphs at once: 512 units, 2048 frames
+// 53.0 -> 46.5 and 22.7 -> 21.7, 3200 62.2 -> 56.0 and 32.6 -> 33.0 (at worst, eight layers and 100 outputs, 53.0 -> 41.9 and 22.5 -> 27.6); 1024 units,
+// 1024 frames 49.6 -> 41.2 and 21.6 -> 20.0, but 1152 55.2 -> 45.3 and 21.6 -> 26.2; 1536 units, 320 frames 48.8 -> 37.7 and 17.2 -> 16.0, 512 47.2 ->
+// 39.6 and 18.4 -> 19.6; 2048 units, 128 frames 50.6 -> 39.4 and 19.4 -> 16.4, but 200 53.3 -> 43.5 and 21.3 -> 23.3, 333 54.9 -> 47.0 and 21.5 -> 30.5.
 static int hidden_run_layers(const bnn_layer_desc* layers, int n_layers, int l, int64_t M) {
     if (l < 1 || l >= n_layers || M <= kFewMaxFrames) return 0;
     const bnn_layer_desc& before = layers[l - 1];
     if (before.x_is_binary || before.w_is_real || !(l == 1 && realx_sign_mfma_applies(before) ? true : realx_i8_gemm_applies(before, M))) return 0;
     const int64_t N = layers[l].N;
-    if (N % 512 != 0 || N > 2048 || (N <= 1024 ? M * N > ((int64_t)1 << 20) : M > (N <= 1536 ? 320 : 128))) return 0;
+    if (N % 512 != 0 || N > 2048 || M > (N == 512 ? 4096 : N == 1024 ? 1024 : N == 1536 ? 512 : 128)) return 0;
     int n = 0;
     while (l + n < n_layers && n < kRunMaxLayers && layers[l + n].x_is_binary && !layers[l + n].w_is_real && layers[l + n].act == BNN_ACT_SIGN &&
            layers[l + n].K == N && layers[l + n].N == N && aligned(layers[l + n].Wp, 16))
@@ -1441,7 +1441,8 @@ static int run_hidden_run(const bnn_layer_desc* layers, int l, int n, const void
     a.M = (int)M;
     a.F = 16 * (((int)M + 16 * kFewGroups - 1) / (16 * kFewGroups));
     a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
-    const int fm = (a.F / 16 + kRunCrews - 1) / kRunCrews;   // fragments per wave: 1 to 4 with 512 units, 1 or 2 with 1024, else 1
+    // fragments of a wave: up to 8 with 512 units, up to 2 with 1024, else 1; FM of them at a time
+    const int per_wave = (a.F / 16 + kRunCrews - 1) / kRunCrews, passes = (per_wave + 3) / 4, fm = (per_wave + passes - 1) / passes;
     auto go = [&](auto nfc, auto fmc) {
         hidden_run_kernel<decltype(nfc)::value, decltype(fmc)::value><<<kFewGroups * kFewSlots, kRunThreads, 0, st>>>(a);
     };

@@ -59,9 +59,9 @@ struct RunWeights {
     }
 };
 
-// Outputs n0 .. n0 + 16 NF - 1 of a crew's frames: fragments crew, crew + 4, ... of the `frames` frames from `first`, FM at a time.  (The
-// launch makes FM as many as there are, one turn of the loop.  As a loop it takes 92 registers with NF = FM = 2 and not 114, which
-// with four launches on the chip is 20.4 us a pass and not 22.6, 1000 frames of 6 x 1024 units.)
+// Outputs n0 .. n0 + 16 NF - 1 of a crew's frames: fragments crew, crew + 4, ... of the `frames` frames from `first`, FM at a time.
+// (More than one turn with 512 units only.  But without the loop it takes 114 registers with NF = FM = 2, not 92, and with four
+// launches on the chip 1000 frames of 6 x 1024 units 22.6 us a pass, not 20.4.)
 template <int NF, int FM>
 __device__ __forceinline__ void run_block(RunWeights<NF>& w, const RunLayer& L, const uint32_t* X, int n0, int first, int frames, int crew, int lane) {
     const int r = lane & 15, g = lane >> 4;

@@ -291,7 +291,7 @@ def _runs(bnn, descs, M):
                 N = descs[l]["N"]
                 while l + n < len(descs) and n < 16 and binary(descs[l + n]) and descs[l + n]["act"] == bnn.BNN_ACT_SIGN and descs[l + n]["K"] == descs[l + n]["N"] == N:
                     n += 1
-                if n < 2 or M > {512: 2048, 1024: 1024, 1536: 320, 2048: 128}.get(N, 0):
+                if n < 2 or M > {512: 4096, 1024: 1024, 1536: 512, 2048: 128}.get(N, 0):
                     n = 0
         if n:
             runs.append((l, n))
@@ -353,7 +353,7 @@ def _check_marks(bnn, ws, descs, M, runs):
     (2048, (40, 1024, 1024, 1024, 96), "hardtanh", False, 32), (4096, (600, 512, 512, 512, 512, 40), "linear", True, 32),
     (641, (440, 512, 512, 512, 70), "linear", True, 64), (1025, (40, 512, 512, 512, 512), "sign", False, 32), (2048, (143, 512, 512, 512, 70), "linear", False, 32),
     (1024, (440, 1024, 1024, 1024, 70), "linear", True, 32), (320, (440, 1536, 1536, 1536, 70), "linear", True, 32),
-    (128, (440, 2048, 2048, 2048, 2048), "sign", True, 64), (2049, (440, 512, 512, 512, 70), "linear", False, 32)])
+    (128, (440, 2048, 2048, 2048, 2048), "sign", True, 64), (2100, (440, 512, 512, 512, 70), "linear", False, 32), (4097, (440, 512, 512, 512, 70), "linear", False, 32)])
 def test_run_of_binary_layers_in_one_launch(G, bnn, M, dims, last, zero_one, wb, spins):
     """The binary layers of a batch in one launch: the bits of the same layers called one by one, for one batch after
     another on the same workspace (whose marks the first layer's launch clears), whether waves wait for each other or not."""

@@ -318,7 +318,7 @@ def test_which_binary_layers_share_a_launch(host):
 S, Z = bnn.BNN_ACT_SIGN, bnn.BNN_ACT_LOGSOFTMAX
 result = []
 for M, widths in ((1, (512, 512)), (1, (512, 512, 512)), (1, (520, 512)), (64, (2048, 2048, 2048)), (64, (2049, 2049, 2049)), (17, (4096, 2048, 2048)),
-                  (2048, (512, 512)), (2049, (512, 512)), (1024, (1024, 1024)), (1025, (1024, 1024)), (320, (1536, 1536)), (321, (1536, 1536)),
+                  (4096, (512, 512)), (4097, (512, 512)), (1024, (1024, 1024)), (1025, (1024, 1024)), (512, (1536, 1536)), (513, (1536, 1536)),
                   (128, (2048, 2048)), (129, (2048, 2048)), (65, (1000, 1000)), (65, (512, 1024)),
                   (17, (1024, 1024, 1024)), (17, (1025, 1025, 1025))):
     for last in (None, 100):
