@@ -1336,7 +1336,7 @@ static bool few_chain_runs(const bnn_layer_desc* layers, int l, int n, int64_t M
     return apart(layers, l, n, M, Y);
 }
 // pulled: the launch in front has pulled the weights into the L2s.  Otherwise the run does, by workgroups of its own behind the others (64 frames
-// of 6 x 512 and 6 x 1024 units 17.5 -> 16.7 us and 20.4 -> 18.3 a pass), up to 1024 inputs (2048: 32 frames 22.2 without, 23.0 with).
+// of 6 x 512 and 6 x 1024 units 17.5 -> 16.7 us and 20.4 -> 18.3 a pass), where few_pulls says so.
 static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void* X, int64_t M, void* Y, char* scratch_mem, hipStream_t st, bool pulled) {
     const FewScratch s = few_chain_scratch(layers, l, n, M);
     const int nr = few_chain_pieces(layers, l, n);
@@ -1367,7 +1367,7 @@ static int run_few_chain(const bnn_layer_desc* layers, int l, int n, const void*
     a.spins = min(g_coop_spin.load(), 48);   // 15 to 20 us
     auto go = [&](auto nrc) {
         constexpr int NR = decltype(nrc)::value;
-        const int grid = (NR < 4 && !pulled ? 2 : 1) * kFewGroups * kFewSlots;
+        const int grid = (few_pulls(NR) && !pulled ? 2 : 1) * kFewGroups * kFewSlots;
         if (vec) few_chain_kernel<NR, true><<<grid, kFewThreads, 0, st>>>(a);
         else few_chain_kernel<NR, false><<<grid, kFewThreads, 0, st>>>(a);
     };

@@ -327,7 +327,9 @@ __device__ __forceinline__ void few_catch_up(const FewArgs& a, int target, int m
     few_join();
 }
 
-// The later layers' weights into an XCD's L2, by kFewSlots workgroups, a load per 128 bytes.
+// The later layers' weights into an XCD's L2, by kFewSlots workgroups, a load per 128 bytes.  Up to 1024 inputs: with 2048 the run takes
+// longer with it (32 frames 22.2 -> 23.0 us a pass), and even the branch costs half a microsecond.
+constexpr bool few_pulls(int NR) { return NR < 4; }
 __device__ __forceinline__ void few_pull(const FewArgs& a, int slot) {
     constexpr uint32_t step = kFewSlots * kFewThreads * 128u;
     for (int j = 1; j < a.layers; ++j) {
@@ -351,7 +353,9 @@ __global__ __launch_bounds__(kFewThreads, 4) void few_chain_kernel(FewArgs a) {
     const int first = group * a.F, frames = min(a.F, a.M - first);
     if (frames <= 0) return;
 
-    if (slot >= kFewSlots) return few_pull(a, slot - kFewSlots);
+    if constexpr (few_pulls(NR)) {
+        if (slot >= kFewSlots) return few_pull(a, slot - kFewSlots);
+    }
     uint32_t *x = bits[wave][0], *y = bits[wave][1];
     const int u = wave * kFewSlots + slot;
 
