@@ -164,7 +164,6 @@ def streaming(args, bnn, workloads, G, torch) -> int:
             torch.cuda.synchronize()
             us = (time.perf_counter() - t0) * 1e6 / steps
             # the same pass waited for every time (what one caller sees from call to result), and as one captured graph
-            # (its launches become one: the host's share of a pass drops from about 27 us to a few)
             t0 = time.perf_counter()
             for _ in range(200):
                 model.forward(X, out)
@@ -202,8 +201,7 @@ def streaming(args, bnn, workloads, G, torch) -> int:
                               "latency_us": round(us, 1), "frames_per_s": round(M / (us * 1e-6), 1),
                               "latency_us_waited_for": round(us_sync, 1),
                               "latency_us_graph_replay": None if us_graph is None else round(us_graph, 1),
-                              "latency_us_graph_replay_waited_for": None if us_graph_sync is None else round(us_graph_sync, 1),
-                              "kernel_launches": model.n_layers + 1}), flush=True)
+                              "latency_us_graph_replay_waited_for": None if us_graph_sync is None else round(us_graph_sync, 1)}), flush=True)
         del model, Ws, bs
         torch.cuda.empty_cache()
     return 0
