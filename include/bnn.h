@@ -317,8 +317,9 @@ size_t bnn_forward_workspace_bytes(const bnn_layer_desc* layers, int n_layers, i
  *     frames on).
  * The workgroups of such a kernel wait for each other, so it is at its best where all of them, one per CU, are on the chip; four
  * such kernels (the hardware queues of a process) fit side by side.  A program that shares the device with more of them, or
- * that keeps it full with mid-size batches from graphs or several threads, can have a launch per layer instead: bnn_forward accepts a workspace without the scratch of these runs (the last part of what
- * bnn_forward_workspace_bytes() counts), and then takes none.
+ * that keeps it full with mid-size batches from graphs or several threads, can have a launch per layer instead: bnn_forward
+ * accepts a workspace without the scratch of these runs (the last part of what bnn_forward_workspace_bytes() counts), and then
+ * takes none.
  */
 int bnn_forward(const bnn_layer_desc* layers, int n_layers, const void* X, int64_t M, void* out,
                 void* workspace, size_t workspace_bytes, void* stream);

@@ -21,7 +21,7 @@
 // Workgroups of four waves with at most 128 registers and 16 KB of LDS, so that four launches fit on every CU, as many as the device's
 // queues run at once.  Where fewer fit, runs on several streams each get a part of their workgroups, and all of them wait for the rest
 // until they give up: with a fifth wave and 168 registers, two to a CU, 16 frames of 6 x 1536 units on four streams at once took 33 us a
-// pass, 8.0 now (one launch per layer 10.0), 62 of 8 x 1088 in whole words of 32 73 and 15.1 (45).  (few_fresh keeps the
+// pass, 8.0 now (one launch per layer 10.0), 62 of 8 x 1088 73 and 15.3 (46).  (few_fresh keeps the
 // registers down; the code for waits that run out had most of them.)  Alone, the two 18.9 -> 16.5 us and 36.5 -> 34.8.
 // The marks have to be clear when the launch starts: the launch before it, which the first layer reads from, clears them.
 //
